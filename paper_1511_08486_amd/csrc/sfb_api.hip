@@ -62,9 +62,9 @@ struct sfb_ctx {
     hipStream_t stream;
     FwdPlan fwd_all, fwd_worker;   // scores of all N rows / of one worker's B rows
     FwdPlan fwd_bf16;              // all N rows on the bf16 matrix cores (bf16 contexts)
-    FwdPlan fwd_split;             // all N rows, fp32 operands split into bf16 terms (64 x 128 tiles)
-    bool split_scores;             // use it where the shape allows
-    bool split_recon;              // reconstruction with split-bf16 products where the shape allows
+    FwdPlan fwd_split, fwd_split_worker;   // the same on the bf16 matrix cores, fp32 operands split exactly into bf16 terms
+    bool split_scores;             // use them where the shape allows
+    int split_recon;               // reconstruction with split-bf16 products: 1 where the shape allows, 0 never, -1 where it is the cheaper one
     ReconPlan recon;
     ReconPlan recon_padded;        // the plan of the padded shape (ragged fp32 contexts: see padded_factors)
     bool padded_factors;           // fp32 and J, D or P*B not what the LDS-DMA reconstructions take as they are
@@ -86,16 +86,13 @@ inline int64_t round_up4(int64_t x) { return (x + 3) / 4 * 4; }
 // Bytes of split-K partial scores (the first region of the workspace), rounded to 256.
 size_t scores_need(const sfb_ctx* c) {
     const int64_t ldz = round_up4(c->J);
-    size_t need = (size_t)c->fwd_all.split_k * (size_t)c->P * c->B * ldz * sizeof(float);
-    const size_t one = (size_t)c->fwd_worker.split_k * (size_t)c->B * ldz * sizeof(float);
+    const bool split = c->split_scores && c->D >= 4;
+    size_t need = (size_t)(split ? c->fwd_split : c->fwd_all).split_k * (size_t)c->P * c->B * ldz * sizeof(float);
+    const size_t one = (size_t)(split ? c->fwd_split_worker : c->fwd_worker).split_k * (size_t)c->B * ldz * sizeof(float);
     if (one > need) need = one;
     if (c->dtype == SFB_BF16) {
         const size_t bf = (size_t)c->fwd_bf16.split_k * (size_t)c->P * c->B * ldz * sizeof(float);
         if (bf > need) need = bf;
-    }
-    if (c->split_scores) {
-        const size_t sp = (size_t)c->fwd_split.split_k * (size_t)c->P * c->B * ldz * sizeof(float);
-        if (sp > need) need = sp;
     }
     if (c->fused_ok) {
         const size_t fu = (size_t)c->fused.slices * (size_t)c->P * c->B * ldz * sizeof(float);
@@ -249,9 +246,18 @@ sfb_status factors_rows(sfb_ctx* c, const FwdPlan& plan, const float* W, int64_t
     }
     // bf16 features, full batch, aligned: the bf16 matrix-core kernel with its own plan
     const bool on_bf16_cores = bf16 && n_rows == c->P * c->B && n_rows >= 128 && forward_bf16_ok(f);
-    // fp32 features, full batch, aligned, and the caller opted in: split-bf16 products
-    const bool on_split = !sparse_scores && !bf16 && c->split_scores && n_rows == c->P * c->B && forward_split_ok(f);
-    const FwdPlan& used = on_bf16_cores ? c->fwd_bf16 : on_split ? c->fwd_split : plan;
+    // fp32 features: split-bf16 products, unless the caller chose the fp32 matrix instruction (sfb_set_plan).  Leading
+    // dimensions beyond its 32-bit offsets take the fp32 kernels, whose plan may cut D into more slices than there is room for
+    const bool all_rows = n_rows == c->P * c->B;
+    const bool on_split = !sparse_scores && !bf16 && c->split_scores && forward_split_ok(f);
+    FwdPlan used = on_bf16_cores ? c->fwd_bf16 : on_split ? (all_rows ? c->fwd_split : c->fwd_split_worker) : plan;
+    if (!sparse_scores && !on_split && !on_bf16_cores) {
+        const int64_t fit = (int64_t)(scores_need(c) / ((size_t)n_rows * ldz * sizeof(float)));
+        if (used.split_k > fit) {
+            used.split_k = (int)fit;
+            finish_forward_plan(&used, n_rows, c->J, c->D);
+        }
+    }
     if (!sparse_scores) {
         Timed t(c, 0);
         hipError_t e = on_bf16_cores ? launch_forward_bf16(f, used, c->stream)
@@ -303,8 +309,14 @@ sfb_status recon_launch(sfb_ctx* c, float* W, int64_t ldw, const float* U, int64
     if (r.bf16) {
         if (c->ws == nullptr || c->ws_bytes < workspace_need(c)) return SFB_EWORKSPACE;
         e = launch_reconstruct_bf16(r, (char*)c->ws + scores_need(c), c->stream);
-    } else if (c->split_recon && reconstruct_split_ok(r)) {
-        e = launch_reconstruct_split(r, c->stream);
+        if (e != hipSuccess) return hip_fail(c, e);
+        return SFB_OK;
+    }
+    int bm = 128, bn = 128;
+    const bool whole = reconstruct_takes_dma(r, c->recon);
+    if (c->split_recon != 0 && reconstruct_split_ok(r) &&
+        (reconstruct_split_plan(c->J, c->D, r.N, !whole, &bm, &bn) || c->split_recon == 1)) {
+        e = launch_reconstruct_split(r, bm, bn, c->stream);
     } else {
         // calls that would end in the register-staged kernel first try a copy of the factors that the LDS-DMA
         // kernels accept: padded ones for ragged shapes, U with a dead worker's rows zeroed for a masked call
@@ -312,7 +324,7 @@ sfb_status recon_launch(sfb_ctx* c, float* W, int64_t ldw, const float* U, int64
         e = hipErrorNotSupported;
         const bool have_ws = c->ws != nullptr && c->ws_bytes >= workspace_need(c);
         const int64_t n_all = (int64_t)c->P * c->B;
-        if (have_ws && !reconstruct_takes_dma(r, c->recon)) {
+        if (have_ws && !whole) {
             if (c->padded_factors && conformed_variant_ok(c->recon_padded.variant)) {
                 if (c->recon_padded.n_split > 1) r.partial = (float*)((char*)c->ws + conform_workspace(c->J, c->D, n_all));
                 e = launch_reconstruct_conformed(r, c->recon_padded, c->ws, c->stream);
@@ -354,27 +366,22 @@ sfb_status sfb_create(sfb_ctx** out, sfb_model m, int64_t J, int64_t D, int32_t 
     c->fwd_all = plan_forward((int64_t)P * B, J, D);
     c->fwd_worker = plan_forward(B, J, D);
     c->fwd_bf16 = plan_forward_bf16((int64_t)P * B, J, D);
-    {
-        // 64 x 128 tiles; as many slices of D as bring the grid to about two workgroups per compute unit
-        FwdPlan sp{};
-        sp.bm = 64; sp.bn = 128; sp.dma = false;
-        const int64_t tiles = (((int64_t)P * B + 63) / 64) * ((J + 127) / 128);
-        // (two workgroups fit a compute unit and overlap each other's splitting and multiplying)
-        int64_t s = (512 + tiles / 2) / tiles;
-        if (s < 1) s = 1;
-        if (s > 8) s = 8;
-        sp.split_k = (int)s;
-        finish_forward_plan(&sp, (int64_t)P * B, J, D);
-        c->fwd_split = sp;
-    }
-    c->split_scores = false;
-    c->split_recon = false;
+    c->split_scores = input_dtype == SFB_F32;
+    c->split_recon = -1;
     c->recon = plan_reconstruct(J, D, (int64_t)P * B);
     {
         const int64_t N = (int64_t)P * B;
         c->padded_factors = input_dtype == SFB_F32 &&
                             !((J % 4) == 0 && J >= 4 && (D % 128) == 0 && (N % 32) == 0 && N >= 32);
         c->recon_padded = plan_reconstruct_padded(J, D, N, -1);
+        // the partial scores may take what ragged contexts reserve for their padded factor copies, else the 16 MiB that
+        // sfb_step_noalloc has, or what the fp32 matrix instruction's plan would take where that is more
+        size_t most = SFB_NOALLOC_SCRATCH_BYTES;
+        const size_t f32_need = (size_t)c->fwd_all.split_k * (size_t)N * (size_t)round_up4(J) * sizeof(float);
+        if (f32_need > most) most = f32_need;
+        if (c->padded_factors && conform_workspace(J, D, N) < most) most = conform_workspace(J, D, N);
+        c->fwd_split = plan_forward_split(N, J, D, most);
+        c->fwd_split_worker = plan_forward_split(B, J, D, (size_t)c->fwd_split.split_k * (size_t)N * (size_t)round_up4(J) * sizeof(float));
     }
     c->fused_ok = input_dtype == SFB_BF16 && m == SFB_MLR && fused_shape_ok(J, D, (int64_t)P * B);
     c->use_fused = true;
@@ -681,7 +688,7 @@ int sfb_last_hip_error(const sfb_ctx* c) { return c ? c->last_hip : 0; }
 
 sfb_status sfb_plan_info(const sfb_ctx* c, int32_t* fwd_split_k, int32_t* fwd_grid, int32_t* recon_grid) {
     if (!c) return SFB_EINVAL;
-    const FwdPlan& f = c->dtype == SFB_BF16 ? c->fwd_bf16 : c->fwd_all;
+    const FwdPlan& f = c->dtype == SFB_BF16 ? c->fwd_bf16 : c->split_scores && c->D >= 4 ? c->fwd_split : c->fwd_all;
     if (fwd_split_k) *fwd_split_k = f.split_k;
     if (fwd_grid) *fwd_grid = f.grid;
     if (recon_grid) {
@@ -706,8 +713,11 @@ sfb_status sfb_set_plan(sfb_ctx* c, int32_t fwd_bm, int32_t fwd_bn, int32_t fwd_
     if (fwd_dma >= 0) p.dma = (fwd_dma & 1) != 0;
     if (fwd_dma >= 0) c->sparse_forward = (fwd_dma & 2) == 0;   // bit 1 set: dense scores for CSR input
     if (fwd_dma >= 0) c->sparse_always = (fwd_dma & 32) != 0;   // bit 5 set: from the entries whenever the kernel can take them
-    if (fwd_dma >= 0) c->split_scores = (fwd_dma & 4) != 0;     // bit 2 set: fp32 scores as split-bf16 products
+    // bit 2 set: fp32 scores as split-bf16 products; a tile or slice count of its own means the fp32 instruction's kernels
+    if (fwd_dma >= 0) c->split_scores = (fwd_dma & 4) != 0 && c->dtype == SFB_F32;
+    else if (fwd_bm > 0 || fwd_bn > 0 || fwd_split_k > 0) c->split_scores = false;
     if (fwd_dma >= 0) c->split_recon = (fwd_dma & 8) != 0;      // bit 3 set: the reconstruction likewise
+    else if (recon_variant >= 0) c->split_recon = 0;
     if (fwd_dma >= 0) c->use_fused = (fwd_dma & 16) == 0;       // bit 4 set: sfb_step_pipelined runs two separate passes
     finish_forward_plan(&p, (int64_t)c->P * c->B, c->J, c->D);
     c->fwd_all = p;

@@ -1,62 +1,28 @@
-// Scores (Section 2, z = W a) for fp32 features, computed on the bf16 matrix cores at fp32
-// accuracy.
+// Scores (Section 2, z = W a) for fp32 features on the bf16 matrix cores at fp32 accuracy: Z[n][j] = sum_d A[n][d] *
+// W[j][d] with every operand split exactly into three bf16 terms (sfb_split.h: the arithmetic, its error, and how the
+// two groups of wavefronts take turns).
 //
-// gfx950 multiplies bf16 sixteen times faster than fp32 on its matrix cores.  Every fp32
-// operand is split exactly into three bf16 terms, x = h + m + l (h = bf16(x), m = bf16(x - h),
-// l = bf16(x - h - m): 3 x 8 significand bits cover fp32's 24, and both differences are exact
-// in fp32), and a product a * b is taken as the six term products whose weight is at least
-// 2^-16 of the leading one:
-//     a_h b_h  +  (a_h b_m + a_m b_h)  +  (a_h b_l + a_l b_h + a_m b_m).
-// What is dropped (a_m b_l, a_l b_m, a_l b_l) is below 2^-24 of |a b|: the same size as one
-// fp32 rounding.  Each term product is exact in the fp32 accumulator's input (8 x 8 bits), the
-// leading products and the corrections are accumulated separately and added once at the end.
-// Six bf16 MFMAs replace one fp32 MFMA of the same shape at 1/16 of the time each.
-//
-// Both operands are contiguous along k.  A lane keeps PF chunks of raw fp32 words in flight
-// in registers (the prefetch), splits a chunk once on its way into LDS (three bf16 planes per
-// operand, swizzled rows of 64 bytes), and two LDS stages alternate with one barrier per chunk.
-// 64 samples x 128 classes per workgroup, 2 x 2 wavefronts, D cut into slices (partial sums
-// go to the workspace as in the fp32 kernels).  DIFF: the operand is x_i - y_i (metric learning).
-#include "sfb_device.h"
+// Both operands are contiguous along the contraction.  A lane loads 16 bytes (four k) of a row of A or W, eight lanes to
+// a 128-byte line, splits them and writes 8 bytes per plane, so W is never copied and A passes through
+// once more only to be stored as V.  Rows beyond the matrix repeat the last row (their scores are not stored); in the
+// last, partial chunk of D the words beyond D are replaced by zero in both operands.  Accesses are 16 bytes wide at
+// 4-byte alignment: any leading dimension is taken.  DIFF: the operand is x_i - y_i (metric learning).
 #include "sfb_kernels.h"
+#include "sfb_split.h"
 
 namespace sfb {
 
-typedef __bf16 sbf16x8 __attribute__((ext_vector_type(8)));
-typedef uint32_t su32x4 __attribute__((ext_vector_type(4)));
-
-constexpr int kSsThreads = 256, kSsBM = 64, kSsBN = 128, kSsBK = 32;
-constexpr int kSsRowB = kSsBK * 2;                                   // bytes per row of one bf16 plane
-constexpr int kSsPlaneA = kSsBM * kSsRowB, kSsPlaneB = kSsBN * kSsRowB;
-constexpr int kSsStageBytes = 3 * (kSsPlaneA + kSsPlaneB);
-
-__device__ __forceinline__ int ss_swz(int r) { return (r >> 2) & 3; }   // 16-byte item c of row r sits at c ^ ss_swz(r)
-
-__device__ __forceinline__ void ss_barrier() {
-    // LDS writes of this wavefront visible, then the workgroup barrier; the prefetch loads stay in flight
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-}
-
-// four consecutive k of one row -> 8 bytes per plane
-__device__ __forceinline__ void split3_x4(f32x4 x, uint2& h, uint2& m, uint2& l) {
-    split3_pair(x[0], x[1], h.x, m.x, l.x);
-    split3_pair(x[2], x[3], h.y, m.y, l.y);
-}
-
-template <bool DIFF>
-__global__ __launch_bounds__(kSsThreads) void scores_split_kernel(
+template <int MT, int NT, bool DIFF>
+__global__ __launch_bounds__(kSplitThreads, 2) void scores_split_kernel(
     const float* __restrict__ A, const float* __restrict__ A2, int64_t lda, const float* __restrict__ W, int64_t ldw,
     float* __restrict__ Z, int64_t ldz, int64_t zstride, float* __restrict__ Vout, int64_t ldv, int M, int N, int K,
     int k_slice, int n_mb, int n_nb, int total) {
-    constexpr int BM = kSsBM, BN = kSsBN, BK = kSsBK, ROWB = kSsRowB;
-    constexpr int WGN = 2, WM = 32, WN = 64, NT = 2;
-    constexpr int A_LD = BM * 8 / kSsThreads, W_LD = BN * 8 / kSsThreads;   // 16-byte pieces (4 fp32) per lane
-    constexpr int ROW_STEP = kSsThreads / 8;                                 // rows between a lane's pieces
+    using Tile = SplitTile<MT, NT, 64, true>;
+    constexpr int BM = Tile::BM, BN = Tile::BN;
+    constexpr int A_IT = BM / 64, IT = (BM + BN) / 64;                   // 16-byte items per lane and chunk: of A, of A and W
     extern __shared__ __attribute__((aligned(16))) unsigned char ss_lds[];
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave / WGN, wn = wave % WGN;
-    const int l32 = lane & 31, half = lane >> 5;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
     // consecutive ids share the class block (its W rows then sit in one die's L2)
     int id = xcd_contiguous_id(blockIdx.x, total);
@@ -64,185 +30,172 @@ __global__ __launch_bounds__(kSsThreads) void scores_split_kernel(
     id /= n_mb;
     const int nb = id % n_nb, ks = id / n_nb;
     const int m0 = mb * BM, n0 = nb * BN;
-    const int k_begin = ks * k_slice;
-    const int n_chunks = (min(K, k_begin + k_slice) - k_begin) / BK;   // host: K % BK == 0
+    const int k_begin = ks * k_slice, k_end = min(K, k_begin + k_slice);
+    const int n_chunks = (k_end - k_begin + kSpChunk - 1) / kSpChunk;
+    const bool ragged = (K & 31) != 0 && k_end == K;                     // the last chunk is partial
 
-    // eight lanes per row: one wavefront instruction reads eight whole 128-byte lines.
-    // Addresses = uniform base + 32-bit lane offset, rows clamped into the matrix.
-    const unsigned char* a_base = reinterpret_cast<const unsigned char*>(A + (int64_t)m0 * lda + k_begin);
-    const unsigned char* a2_base = DIFF ? reinterpret_cast<const unsigned char*>(A2 + (int64_t)m0 * lda + k_begin) : nullptr;
-    const unsigned char* w_base = reinterpret_cast<const unsigned char*>(W + (int64_t)n0 * ldw + k_begin);
+    // item i of a lane: row r0 + 64 i of the A rows followed by the W rows, k 4 c0 .. 4 c0 + 3 of the chunk
     const int r0 = tid >> 3, c0 = tid & 7;
-    uint32_t a_off[A_LD], w_off[W_LD];
+    const unsigned char* const a_base = reinterpret_cast<const unsigned char*>(A + (int64_t)m0 * lda);
+    const unsigned char* const a2_base = DIFF ? reinterpret_cast<const unsigned char*>(A2 + (int64_t)m0 * lda) : nullptr;
+    const unsigned char* const w_base = reinterpret_cast<const unsigned char*>(W + (int64_t)n0 * ldw);
+    uint32_t off[IT];
 #pragma unroll
-    for (int i = 0; i < A_LD; ++i)
-        a_off[i] = (uint32_t)min(r0 + i * ROW_STEP, M - 1 - m0) * (uint32_t)lda * 4u + 16u * c0;
+    for (int i = 0; i < IT; ++i)
+        off[i] = i < A_IT ? (uint32_t)min(r0 + 64 * i, M - 1 - m0) * (uint32_t)lda * 4u
+                          : (uint32_t)min(r0 + 64 * i - BM, N - 1 - n0) * (uint32_t)ldw * 4u;
+    // rows r0 + 64 i share the swizzle
+    const int lds_item = r0 * 64 + 16 * ((c0 >> 1) ^ Tile::swz(r0)) + 8 * (c0 & 1);
+
+    struct Raw { f32x4 x[IT], y[DIFF ? A_IT : 1]; };
+    auto ld = [](const unsigned char* p) -> f32x4 { return *reinterpret_cast<const sp_f32x4u*>(p); };
+    auto fetch = [&](Raw& raw, int c) {
+        // in a partial chunk the words are read from the last four of the row and moved into place by prep (host: K >= 4)
+        const uint32_t o = (uint32_t)min(k_begin + min(c, n_chunks - 1) * kSpChunk + 4 * c0, K - 4) * 4u;
 #pragma unroll
-    for (int i = 0; i < W_LD; ++i)
-        w_off[i] = (uint32_t)min(r0 + i * ROW_STEP, N - 1 - n0) * (uint32_t)ldw * 4u + 16u * c0;
-    // where a lane's four values land inside a plane (piece i: ROW_STEP rows further down, same swizzle)
-    const int lds_piece = r0 * ROWB + 16 * ((c0 >> 1) ^ ss_swz(r0)) + 8 * (c0 & 1);
-    // the class blocks share the copy: block nb takes the chunks c with c % n_nb == nb
+        for (int i = 0; i < IT; ++i) {
+            raw.x[i] = ld((i < A_IT ? a_base : w_base) + (off[i] + o));
+            if (DIFF && i < A_IT) raw.y[i] = ld(a2_base + (off[i] + o));
+        }
+    };
+    // the class blocks share the copy of A (or X - Y) into V: block nb takes the chunks c with c % n_nb == nb
     const bool write_v = Vout != nullptr;
-
-    struct Chunk { f32x4 a[A_LD]; f32x4 a2[DIFF ? A_LD : 1]; f32x4 w[W_LD]; };
-    auto fetch = [&](Chunk& r, int chunk) {
-        const int cc = min(chunk, n_chunks - 1);       // past the end: a harmless repeat, never staged
-        const int64_t kb = (int64_t)cc * (BK * 4);
+    auto prep = [&](Raw& raw, int c) {
+        const int k0 = k_begin + c * kSpChunk + 4 * c0;
+        const bool last = ragged && c == n_chunks - 1;
+        if (DIFF) {
 #pragma unroll
-        for (int i = 0; i < A_LD; ++i) {
-            r.a[i] = *reinterpret_cast<const f32x4*>(a_base + kb + a_off[i]);
-            if (DIFF) r.a2[i] = *reinterpret_cast<const f32x4*>(a2_base + kb + a_off[i]);
+            for (int i = 0; i < A_IT; ++i) raw.x[i] -= raw.y[i];
         }
+        if (last) {                                                      // words read early move up, zeros beyond D
+            const int sh = max(0, k0 - (K - 4));
 #pragma unroll
-        for (int i = 0; i < W_LD; ++i) r.w[i] = *reinterpret_cast<const f32x4*>(w_base + kb + w_off[i]);
-    };
-    auto stage = [&](const Chunk& r, int st, int chunk) {
-        unsigned char* sa = ss_lds + st * kSsStageBytes + lds_piece;
-        unsigned char* sb = sa + 3 * kSsPlaneA;
-#pragma unroll
-        for (int i = 0; i < A_LD; ++i) {
-            f32x4 x = r.a[i];
-            if (DIFF) x -= r.a2[i];
-            uint2 h, m, l;
-            split3_x4(x, h, m, l);
-            *reinterpret_cast<uint2*>(sa + i * ROW_STEP * ROWB) = h;
-            *reinterpret_cast<uint2*>(sa + kSsPlaneA + i * ROW_STEP * ROWB) = m;
-            *reinterpret_cast<uint2*>(sa + 2 * kSsPlaneA + i * ROW_STEP * ROWB) = l;
-            if (write_v && (chunk % n_nb) == nb) {        // v_i = a_i (or x_i - y_i)
-                const int row = m0 + r0 + i * ROW_STEP;
-                if (row < M)
-                    *reinterpret_cast<f32x4*>(Vout + (int64_t)row * ldv + k_begin + chunk * BK + 4 * c0) = x;
+            for (int i = 0; i < IT; ++i) {
+                f32x4& x = raw.x[i];
+                if (sh & 1) x = f32x4{x[1], x[2], x[3], 0.f};
+                if (sh & 2) x = f32x4{x[2], x[3], 0.f, 0.f};
+                if (sh >= 4) x = f32x4{0.f, 0.f, 0.f, 0.f};
             }
         }
+        if (write_v && (c % n_nb) == nb && c < n_chunks) {               // v_i = a_i (or x_i - y_i)
 #pragma unroll
-        for (int i = 0; i < W_LD; ++i) {
-            uint2 h, m, l;
-            split3_x4(r.w[i], h, m, l);
-            *reinterpret_cast<uint2*>(sb + i * ROW_STEP * ROWB) = h;
-            *reinterpret_cast<uint2*>(sb + kSsPlaneB + i * ROW_STEP * ROWB) = m;
-            *reinterpret_cast<uint2*>(sb + 2 * kSsPlaneB + i * ROW_STEP * ROWB) = l;
-        }
-    };
-
-    f32x16 lead[NT], corr[NT];      // leading products and corrections, added once at the end
+            for (int i = 0; i < A_IT; ++i) {
+                if (m0 + r0 + 64 * i >= M) continue;
+                float* out = Vout + (int64_t)(m0 + r0 + 64 * i) * ldv + k0;
+                if (!last || k0 + 4 <= K) {
+                    *reinterpret_cast<sp_f32x4u*>(out) = raw.x[i];
+                } else {
 #pragma unroll
-    for (int j = 0; j < NT; ++j)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-            lead[j][e] = 0.f;
-            corr[j][e] = 0.f;
-        }
-
-    // every row a lane reads is congruent to l32 modulo 32: the swizzle is a lane constant
-    const int frag_row = l32 * ROWB;
-    const int frag_item[2] = {16 * ((0 + half) ^ ss_swz(l32)), 16 * ((2 + half) ^ ss_swz(l32))};
-    auto mfma = [](su32x4 a, su32x4 b, f32x16 c) {
-        return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(sbf16x8, a), __builtin_bit_cast(sbf16x8, b), c,
-                                                       0, 0, 0);
-    };
-    auto compute = [&](int st) {
-        const unsigned char* as = ss_lds + st * kSsStageBytes + wm * WM * ROWB + frag_row;
-        const unsigned char* bs = ss_lds + st * kSsStageBytes + 3 * kSsPlaneA + wn * WN * ROWB + frag_row;
-#pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            su32x4 fa[3], fb[3][NT];
-#pragma unroll
-            for (int p = 0; p < 3; ++p) {
-                fa[p] = *reinterpret_cast<const su32x4*>(as + p * kSsPlaneA + frag_item[s]);
-#pragma unroll
-                for (int j = 0; j < NT; ++j)
-                    fb[p][j] = *reinterpret_cast<const su32x4*>(bs + p * kSsPlaneB + j * 32 * ROWB + frag_item[s]);
-            }
-#pragma unroll
-            for (int j = 0; j < NT; ++j) {
-                lead[j] = mfma(fa[0], fb[0][j], lead[j]);            // h h
-                corr[j] = mfma(fa[0], fb[2][j], corr[j]);            // h l
-                corr[j] = mfma(fa[2], fb[0][j], corr[j]);            // l h
-                corr[j] = mfma(fa[1], fb[1][j], corr[j]);            // m m
-                corr[j] = mfma(fa[0], fb[1][j], corr[j]);            // h m
-                corr[j] = mfma(fa[1], fb[0][j], corr[j]);            // m h
+                    for (int e = 0; e < 3; ++e)
+                        if (k0 + e < K) out[e] = raw.x[i][e];
+                }
             }
         }
     };
-
-    // Chunk c waits in register slot c % 3 until it is staged, one step before it is
-    // multiplied; the slot is then reloaded with chunk c + 3.  Straight-line groups of three
-    // steps keep the slot indices static and every load three chunks ahead of its use.
-    Chunk q0, q1, q2;
-    fetch(q0, 0);
-    fetch(q1, 1);
-    fetch(q2, 2);
-    stage(q0, 0, 0);
-    ss_barrier();
-    int c = 0;
-    for (; c + 3 <= n_chunks; c += 3) {
-        fetch(q0, c + 3);
-        __builtin_amdgcn_sched_barrier(0);   // the loads go out before anything waits on older ones
-        compute(c & 1);
-        stage(q1, (c + 1) & 1, c + 1);
-        ss_barrier();
-        fetch(q1, c + 4);
-        __builtin_amdgcn_sched_barrier(0);
-        compute((c + 1) & 1);
-        stage(q2, (c + 2) & 1, c + 2);
-        ss_barrier();
-        fetch(q2, c + 5);
-        __builtin_amdgcn_sched_barrier(0);
-        compute((c + 2) & 1);
-        if (c + 3 < n_chunks) stage(q0, (c + 3) & 1, c + 3);
-        ss_barrier();
-    }
-    // at most two chunks left; chunk c is staged, c + 1 sits in q1
-    if (c < n_chunks) {
-        compute(c & 1);
-        if (c + 1 < n_chunks) {
-            stage(q1, (c + 1) & 1, c + 1);
-            ss_barrier();
-            compute((c + 1) & 1);
+    struct State { SplitQuad s; };
+    auto park = [&](auto part, const Raw& raw, State& st, unsigned char* buf) {
+        constexpr int p = decltype(part)::value, i = p / 4;                          // item
+        st.s.template part<p % 4>(raw.x[i][0], raw.x[i][1], raw.x[i][2], raw.x[i][3]);
+        if constexpr (p % 4 == 3) {
+            unsigned char* o = buf + lds_item + i * 64 * 64;
+            *reinterpret_cast<uint2*>(o) = make_uint2(st.s.ha, st.s.hb);
+            *reinterpret_cast<uint2*>(o + Tile::PLANE) = make_uint2(st.s.ma, st.s.mb);
+            *reinterpret_cast<uint2*>(o + 2 * Tile::PLANE) = make_uint2(st.s.la, st.s.lb);
         }
-    }
+    };
 
+    Tile t;
+    t.init(wave, lane);
+    t.template run<Raw, State, 4 * IT, true, (IT <= 3 && !DIFF) || IT == 2 ? 4 : 2>(n_chunks, ss_lds, fetch, prep, park);
+
+    float sum[MT][NT][8];
+    t.exchange(wave, lane, ss_lds, sum);
     float* zout = Z + (int64_t)ks * zstride;
+    const int wm = (wave & 3) >> 1, wn = wave & 1;
 #pragma unroll
     for (int j = 0; j < NT; ++j) {
-        const int col = n0 + wn * WN + j * 32 + l32;
+        const int col = n0 + (wn * NT + j) * 32 + (lane & 31);
 #pragma unroll
-        for (int e = 0; e < 16; ++e) {
-            const int row = m0 + wm * WM + 8 * (e / 4) + 4 * half + (e % 4);
-            if (row < M && col < N) zout[(int64_t)row * ldz + col] = lead[j][e] + corr[j][e];
-        }
+        for (int i = 0; i < MT; ++i)
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                const int row = m0 + (wm * MT + i) * 32 + Tile::entry_row(wave >> 2, q, lane);
+                if (row < M && col < N) zout[(int64_t)row * ldz + col] = sum[i][j][q];
+            }
     }
 }
 
 bool forward_split_ok(const FwdArgs& a) {
-    auto al = [](const void* ptr, int64_t ld) { return ((uintptr_t)ptr % 16) == 0 && (ld % 4) == 0; };
-    return !a.bf16 && al(a.a, a.lda) && (!a.diff || al(a.a2, a.lda)) && al(a.w, a.ldw) &&
-           (a.v == nullptr || al(a.v, a.ldv)) && (a.D % kSsBK) == 0 && a.D >= kSsBK && a.lda < (1 << 23) &&
-           a.ldw < (1 << 22);   // lane offsets (up to 64 rows of A, 128 of W, 4 bytes each) stay below 2^32
+    // lane offsets (up to 128 rows of 4-byte words) stay below 2^32
+    return !a.bf16 && a.D >= 4 && a.lda < (1 << 22) && a.ldw < (1 << 22);
 }
 
-template <bool DIFF>
+template <int MT, int NT, bool DIFF>
 static hipError_t launch_split(const FwdArgs& a, const FwdPlan& p, hipStream_t s) {
-    constexpr size_t lds_bytes = 2 * (size_t)kSsStageBytes;
+    using Tile = SplitTile<MT, NT, 64, true>;
+    constexpr size_t lds_bytes = Tile::LDS;
     static std::atomic<bool> raised{false};
     if (!raised) {
-        hipError_t e = hipFuncSetAttribute((const void*)scores_split_kernel<DIFF>,
+        hipError_t e = hipFuncSetAttribute((const void*)scores_split_kernel<MT, NT, DIFF>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
         if (e != hipSuccess) return e;
         raised = true;
     }
-    const int n_mb = (a.n_rows + kSsBM - 1) / kSsBM, n_nb = (a.J + kSsBN - 1) / kSsBN;
+    const int n_mb = (a.n_rows + Tile::BM - 1) / Tile::BM, n_nb = (a.J + Tile::BN - 1) / Tile::BN;
     const int total = n_mb * n_nb * p.split_k;
-    SFB_LAUNCH((scores_split_kernel<DIFF>), dim3(total), dim3(kSsThreads), lds_bytes, s, (const float*)a.a,
+    SFB_LAUNCH((scores_split_kernel<MT, NT, DIFF>), dim3(total), dim3(kSplitThreads), lds_bytes, s, (const float*)a.a,
                (const float*)a.a2, a.lda, a.w, a.ldw, a.zp, a.ldz, a.zstride, (float*)a.v, a.ldv, a.n_rows, a.J, a.D,
                p.k_slice, n_mb, n_nb, total);
     return hipGetLastError();
 }
 
-// The plan must have been made for 64 x 128 tiles (p.bm, p.bn) with k_slice a multiple of 32.
+template <bool DIFF>
+static hipError_t launch_split_tile(const FwdArgs& a, const FwdPlan& p, hipStream_t s) {
+    if (p.bm == 128 && p.bn == 128) return launch_split<2, 2, DIFF>(a, p, s);
+    if (p.bm == 128 && p.bn == 64) return launch_split<2, 1, DIFF>(a, p, s);
+    if (p.bm == 64 && p.bn == 128) return launch_split<1, 2, DIFF>(a, p, s);
+    if (p.bm == 64 && p.bn == 64) return launch_split<1, 1, DIFF>(a, p, s);
+    return hipErrorInvalidValue;
+}
+
+// Tile and slices of D, by a cost in microseconds fitted to 202 shapes (J = 32 to 2000, D = 256 to 8192, N = 64 to 4096,
+// four tiles, up to three slice counts each, one MI355X; the choice is within 2 % of the best measured one on average):
+// a chunk of 32 columns costs a compute unit 1.10 / 0.72 / 0.40 us with 256 / 192 / 128 rows staged (the small tiles
+// pay more LDS traffic per product), three 64 x 64 workgroups share a unit, every further round of 256 workgroups
+// restarts for 1.7 us, and a slice's partial scores are written and read back at about 2.2 TB/s together.
+// `most` bounds the bytes of partial scores (the caller's room for them); one slice is always allowed.
+FwdPlan plan_forward_split(int64_t n_rows, int64_t J, int64_t D, size_t most) {
+    static const struct { int bm, bn, resident; double chunk_us, lone_us; } tiles[4] = {
+        {128, 128, 1, 1.10, 1.10}, {64, 128, 1, 0.72, 0.72}, {128, 64, 1, 0.72, 0.72}, {64, 64, 3, 0.40, 0.44}};
+    FwdPlan p{};
+    p.dma = false;
+    double best = 1e300;
+    const int64_t chunks = (D + kSpChunk - 1) / kSpChunk;
+    const double plane = (double)n_rows * (double)((J + 3) / 4 * 4) * 4.0;
+    for (const auto& t : tiles) {
+        const int64_t n = ((n_rows + t.bm - 1) / t.bm) * ((J + t.bn - 1) / t.bn);
+        for (int64_t s = 1; s <= 32; ++s) {
+            if (s > 1 && (s * 2 > chunks || (double)s * plane > (double)most)) break;
+            const int64_t per = (chunks + s - 1) / s, slices = (chunks + per - 1) / per;
+            if (slices != s) continue;
+            const double rounds = (double)((n * s + 255) / 256);
+            const double deep = (double)((n * s + 256 * t.resident - 1) / (256 * t.resident));
+            const double a = t.lone_us * deep, b = t.chunk_us * rounds;
+            const double us = (double)per * (a > b ? a : b) + (t.resident == 1 ? 1.7 * (rounds - 1.0) : 0.0) + (double)s * plane / 2.2e6;
+            if (us < best * (1.0 - 1e-9)) {
+                best = us;
+                p.bm = t.bm; p.bn = t.bn; p.split_k = (int)s;
+                p.k_slice = (int)(per * kSpChunk);
+                p.grid = (int)(n * s);
+            }
+        }
+    }
+    return p;
+}
+
+// k_slice of the plan is a multiple of 32.
 hipError_t launch_forward_split(const FwdArgs& a, const FwdPlan& p, hipStream_t s) {
-    return a.diff ? launch_split<true>(a, p, s) : launch_split<false>(a, p, s);
+    return a.diff ? launch_split_tile<true>(a, p, s) : launch_split_tile<false>(a, p, s);
 }
 
 }  // namespace sfb

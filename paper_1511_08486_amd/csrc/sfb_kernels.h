@@ -61,8 +61,9 @@ struct FwdArgs {
     bool bf16, diff;
 };
 hipError_t launch_forward(const FwdArgs& a, const FwdPlan& p, hipStream_t s);
-// fp32 scores as six bf16 term products per product (sfb_forward_split.hip); 64 x 128 tiles
+// fp32 scores on the bf16 matrix cores, every operand split exactly into three bf16 terms (sfb_forward_split.hip)
 bool forward_split_ok(const FwdArgs& a);
+FwdPlan plan_forward_split(int64_t n_rows, int64_t J, int64_t D, size_t most);
 hipError_t launch_forward_split(const FwdArgs& a, const FwdPlan& p, hipStream_t s);
 
 // Dual side of SDCA (Section 2.1): with `dual` set, the MLR factor kernel turns its
@@ -204,9 +205,11 @@ hipError_t launch_reconstruct_ksplit(const ReconArgs& a, hipStream_t s);
 // 128 x 128 tiles with eight wavefronts in two groups that take the stages in turn (sfb_reconstruct_pair.hip)
 bool reconstruct_pair_ok(const ReconArgs& a);
 hipError_t launch_reconstruct_pair(const ReconArgs& a, hipStream_t s);
-// fp32 reconstruction as six bf16 term products per product (sfb_reconstruct_split.hip); 128 x 128 tiles
+// fp32 reconstruction on the bf16 matrix cores, every operand split exactly into three bf16 terms
+// (sfb_reconstruct_split.hip); takes ragged, misaligned and masked factors as they are
 bool reconstruct_split_ok(const ReconArgs& a);
-hipError_t launch_reconstruct_split(const ReconArgs& a, hipStream_t s);
+bool reconstruct_split_plan(int64_t J, int64_t D, int64_t N, bool copies, int* bm, int* bn);
+hipError_t launch_reconstruct_split(const ReconArgs& a, int bm, int bn, hipStream_t s);
 
 // bf16-feature path on the bf16 matrix cores (sfb_bf16.hip)
 bool forward_bf16_ok(const FwdArgs& a);                       // alignment / shape the DMA kernel needs

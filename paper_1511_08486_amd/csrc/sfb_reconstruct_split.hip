@@ -1,199 +1,216 @@
-// Reconstruction + update (Section 3, Section 2.1) for fp32 factors on the bf16 matrix cores at
-// fp32 accuracy:  W += alpha * U^T V  with every fp32 operand split exactly into three bf16
-// terms and every product taken as its six leading term products (see sfb_forward_split.hip
-// for the arithmetic and its error).
+// Reconstruction + update (Section 3, Section 2.1) for fp32 factors on the bf16 matrix cores at fp32 accuracy:
+//     W[j][d] <- W[j][d] + alpha * sum_n U[n][j] * V[n][d]
+// with every operand split exactly into three bf16 terms (sfb_split.h: the arithmetic, its error, and how the two
+// groups of wavefronts take turns).
 //
-// The contraction runs over the factor pairs (the rows of U and V), which is the slow index of
-// both operands in memory, while the bf16 MFMA wants eight consecutive k per lane.  The
-// transposition happens in registers on the way into LDS: a lane loads a 4 (pairs) x 4
-// (columns) block with four 16-byte loads, splits its 16 values, and writes, per plane, four
-// 8-byte items "one column, four consecutive pairs".  Planes are [row = column of U or V][k]
-// with rows padded to 80 bytes: the 8-byte writes of a wavefront then fall two per bank group
-// (the minimum for 512 bytes) and the 16-byte fragment reads of 16 consecutive rows hit 16
-// different bank groups.
-// 128 x 128 tile of W, 8 wavefronts (4 x 2, two per SIMD: one splits while the other
-// multiplies), three chunks of raw words prefetched in registers, two LDS stages, one barrier
-// per 32 pairs.  The W tile is requested first and consumed in the epilogue.
-#include "sfb_device.h"
+// The contraction runs over the factor pairs (the rows of U and V), the slow index of both operands in memory, while
+// the matrix instruction wants eight consecutive k per lane.  A lane therefore loads a block of 4 pairs x 4 columns
+// (four 16-byte loads, eight lanes to a 128-byte line), and writes per plane four 8-byte items "one column, four
+// consecutive pairs".  Two LDS layouts keep the writes of sixteen consecutive lanes and the fragment reads of eight
+// off each other's banks: rows of 80 bytes, one per column in order; and, where a wavefront owns two column blocks,
+// rows of 64 bytes with a swizzle, column 4 b + e of every 64 in row 16 e + b.  In the second a lane's two blocks
+// hold columns two apart and the lane sixteen further the ones between: one v_permlane16_swap per pair of sums and
+// a lane has two neighbouring columns of W, 32 lanes 256 contiguous bytes.
+// Columns beyond J or D repeat the last four (they feed entries of W that are not stored); pairs beyond N and pairs
+// of dead workers are replaced by zero on the way into LDS.  Accesses are 16 (W: 8 or 4) bytes wide at 4-byte
+// alignment: any leading dimension is taken.
 #include "sfb_kernels.h"
+#include "sfb_split.h"
 
 namespace sfb {
 
-typedef __bf16 rbf16x8 __attribute__((ext_vector_type(8)));
-typedef uint32_t ru32x4 __attribute__((ext_vector_type(4)));
+typedef float rs_f32x2u __attribute__((ext_vector_type(2), aligned(4)));
 
-constexpr int kRsThreads = 512, kRsBM = 128, kRsBN = 128, kRsBK = 32;
-constexpr int kRsRowB = kRsBK * 2 + 16;                              // padded bytes per plane row
-constexpr int kRsPlane = (kRsBM + kRsBN) * kRsRowB;                  // rows 0..127: U columns, 128..255: V columns
-constexpr int kRsStageBytes = 3 * kRsPlane;
+template <int MT, int NT>
+using ReconTile = SplitTile<MT, NT, NT == 2 ? 64 : 80, NT == 2>;
 
-__device__ __forceinline__ void rs_barrier() {
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+// column of the tile's A or B part that LDS row r holds
+template <int NT>
+__device__ __forceinline__ int rs_column(int r) {
+    return NT == 2 ? (r & ~63) + 4 * (r & 15) + ((r >> 4) & 3) : r;
 }
 
-__global__ __launch_bounds__(kRsThreads, 2) void reconstruct_split_kernel(
+template <int MT, int NT>
+__global__ __launch_bounds__(kSplitThreads, 2) void reconstruct_split_kernel(
     float* __restrict__ W, int64_t ldw, const float* __restrict__ U, int64_t ldu, const float* __restrict__ V,
-    int64_t ldv, int J, int D, int N, float alpha, int n_jb, int total, int prox_kind, float prox_a) {
-    constexpr int BM = kRsBM, BN = kRsBN, BK = kRsBK, ROWB = kRsRowB;
-    constexpr int WGN = 2, WM = 32, WN = 64, NT = 2;
+    int64_t ldv, int J, int D, int N, float alpha, int n_jb, int total, int prox_kind, float prox_a, uint64_t live_mask,
+    uint32_t inv_b) {
+    using Tile = ReconTile<MT, NT>;
+    constexpr int BM = Tile::BM, BN = Tile::BN;
+    constexpr bool PAIRS = NT == 2;                                      // the permuted layout: two columns of W per lane
     extern __shared__ __attribute__((aligned(16))) unsigned char rs_lds[];
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave / WGN, wn = wave % WGN;
-    const int l32 = lane & 31, half = lane >> 5;
-    int id = xcd_contiguous_id(blockIdx.x, total);
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int id = xcd_contiguous_id(blockIdx.x, total);
     const int jb = id % n_jb, db = id / n_jb;
     const int j0 = jb * BM, d0 = db * BN;
+    const int n_chunks = (N + kSpChunk - 1) / kSpChunk;
 
-    // W tile first (clamped addresses, no branches); the loads are ordinary ones, the compiler
-    // tracks them, and they have the whole contraction to arrive
-    float wreg[NT][16];
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-        const int col = min(d0 + wn * WN + t * 32 + l32, D - 1);
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-            const int row = j0 + wm * WM + 8 * (e / 4) + 4 * half + (e % 4);
-            wreg[t][e] = W[(int64_t)min(row, J - 1) * ldw + col];
-        }
-    }
-
-    // lanes 0..255 stage U, 256..511 stage V: a 4 x 4 block (pairs 4kb.., columns 4rb..) each
-    const bool is_v = tid >= 256;
-    const int t8 = tid & 255, kb = t8 & 7, rb = t8 >> 3;
+    // lane block: pairs 4 kb .. 4 kb + 3, columns 4 rb .. 4 rb + 3 of the BM columns of U and BN of V side by side
+    const int kb = tid & 7, rb = tid >> 3;
+    const bool stages = (BM + BN) * 2 == kSplitThreads || __builtin_amdgcn_readfirstlane(rb) < (BM + BN) / 4;   // by wavefronts
+    const bool is_v = __builtin_amdgcn_readfirstlane(rb) >= BM / 4;      // the same for a whole wavefront
     const int ncols = is_v ? D : J;
-    const int col0 = min((is_v ? d0 : j0) + 4 * rb, ncols - 4);       // host: J, D multiples of 4 and >= 4
+    const int col = is_v ? d0 + 4 * rb - BM : j0 + 4 * rb;
+    const int col_ok = min(col, ncols - 4);                              // host: J, D >= 4
+    const int shift = col - col_ok;                                      // 1..3: the words move down by that many columns
+    const bool edge = ((J & 3) != 0 && j0 + BM > J) || ((D & 3) != 0 && d0 + BN > D);   // uniform
     const int64_t ld = is_v ? ldv : ldu;
-    const float* src = (is_v ? V : U) + col0 + (int64_t)(4 * kb) * ld;
-    // first of the four rows this lane writes in a plane, at its 8-byte item
-    const int lds_block = ((is_v ? BM : 0) + 4 * rb) * ROWB + 8 * kb;
-    const int n_chunks = N / BK;                                       // host: N % BK == 0, N >= BK
+    const unsigned char* src = reinterpret_cast<const unsigned char*>(is_v ? V : U);     // uniform base + 32-bit lane offset
+    const uint32_t pitch = (uint32_t)ld * 4u;                            // host: N rows of it stay below 2^32 bytes
+    const uint32_t off = (uint32_t)(4 * kb) * pitch + (uint32_t)col_ok * 4u;
+    const uint32_t off_last = (uint32_t)(N - 1) * pitch + (uint32_t)col_ok * 4u;
+    const int row0 = PAIRS ? (rb >> 4) * 64 + (rb & 15) : 4 * rb;        // LDS row of the first column; the others follow every ROW_STEP
+    constexpr int ROW_STEP = PAIRS ? 16 * 64 : 80;
+    const int lds_block = PAIRS ? row0 * 64 + 16 * ((kb >> 1) ^ Tile::swz(row0)) + 8 * (kb & 1) : row0 * 80 + 8 * kb;
 
-    struct Chunk { f32x4 x[4]; };
-    auto fetch = [&](Chunk& r, int chunk) {
-        const float* p = src + (int64_t)min(chunk, n_chunks - 1) * BK * ld;   // past the end: a harmless repeat
+    struct Raw { f32x4 x[4]; };
+    auto fetch = [&](Raw& raw, int c) {
+        const uint32_t o = (uint32_t)min(c, n_chunks - 1) * (32u * pitch) + off;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) r.x[i] = *reinterpret_cast<const f32x4*>(p + (int64_t)i * ld);
+        for (int i = 0; i < 4; ++i)                                      // pairs beyond N repeat the last one
+            raw.x[i] = *reinterpret_cast<const sp_f32x4u*>(src + min(o + i * pitch, off_last));
     };
-    auto stage = [&](const Chunk& r, int st) {
-        unsigned char* base = rs_lds + st * kRsStageBytes + lds_block;
-        // per column e: the four pairs' terms as two packed words (pairs 0-1, 2-3), 8 bytes per plane
+    auto prep = [&](Raw& raw, int c) {
+        const int n0 = c * kSpChunk + 4 * kb;
+        if (inv_b != 0) {                                                // some workers are dead (uniform)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            uint2 h, m, l;
-            split3_pair(r.x[0][e], r.x[1][e], h.x, m.x, l.x);
-            split3_pair(r.x[2][e], r.x[3][e], h.y, m.y, l.y);
-            *reinterpret_cast<uint2*>(base + e * ROWB) = h;
-            *reinterpret_cast<uint2*>(base + kRsPlane + e * ROWB) = m;
-            *reinterpret_cast<uint2*>(base + 2 * kRsPlane + e * ROWB) = l;
-        }
-    };
-
-    f32x16 lead[NT], corr[NT];
-#pragma unroll
-    for (int t = 0; t < NT; ++t)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-            lead[t][e] = 0.f;
-            corr[t][e] = 0.f;
-        }
-    auto mfma = [](ru32x4 a, ru32x4 b, f32x16 c) {
-        return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(rbf16x8, a), __builtin_bit_cast(rbf16x8, b), c,
-                                                       0, 0, 0);
-    };
-    const int a_row = (wm * WM + l32) * ROWB, b_row = (BM + wn * WN + l32) * ROWB;
-    auto compute = [&](int st) {
-        const unsigned char* sp = rs_lds + st * kRsStageBytes;
-#pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            const int item = 16 * (2 * s + half);
-            ru32x4 fa[3], fb[3][NT];
-#pragma unroll
-            for (int p = 0; p < 3; ++p) {
-                fa[p] = *reinterpret_cast<const ru32x4*>(sp + p * kRsPlane + a_row + item);
-#pragma unroll
-                for (int t = 0; t < NT; ++t)
-                    fb[p][t] = *reinterpret_cast<const ru32x4*>(sp + p * kRsPlane + b_row + t * 32 * ROWB + item);
+            for (int i = 0; i < 4; ++i) {
+                const uint32_t p = __umulhi((uint32_t)min(n0 + i, N - 1), inv_b);
+                if (!((live_mask >> p) & 1ull)) raw.x[i] = f32x4{0.f, 0.f, 0.f, 0.f};
             }
+        }
+        if (c * kSpChunk + kSpChunk > N) {
 #pragma unroll
-            for (int t = 0; t < NT; ++t) {
-                lead[t] = mfma(fa[0], fb[0][t], lead[t]);            // h h
-                corr[t] = mfma(fa[0], fb[2][t], corr[t]);            // h l
-                corr[t] = mfma(fa[2], fb[0][t], corr[t]);            // l h
-                corr[t] = mfma(fa[1], fb[1][t], corr[t]);            // m m
-                corr[t] = mfma(fa[0], fb[1][t], corr[t]);            // h m
-                corr[t] = mfma(fa[1], fb[0][t], corr[t]);            // m h
+            for (int i = 0; i < 4; ++i)
+                if (n0 + i >= N) raw.x[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+        if (edge) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                f32x4& x = raw.x[i];
+                if (shift & 1) x = f32x4{x[1], x[2], x[3], x[3]};
+                if (shift & 2) x = f32x4{x[2], x[3], x[3], x[3]};
             }
         }
     };
-
-    // Chunk c waits in register slot c % 3 until it is staged, one step before it is multiplied
-    Chunk q0, q1, q2;
-    fetch(q0, 0);
-    fetch(q1, 1);
-    fetch(q2, 2);
-    stage(q0, 0);
-    rs_barrier();
-    int c = 0;
-    for (; c + 3 <= n_chunks; c += 3) {
-        fetch(q0, c + 3);
-        __builtin_amdgcn_sched_barrier(0);   // the loads go out before anything waits on older ones
-        compute(c & 1);
-        stage(q1, (c + 1) & 1);
-        rs_barrier();
-        fetch(q1, c + 4);
-        __builtin_amdgcn_sched_barrier(0);
-        compute((c + 1) & 1);
-        stage(q2, (c + 2) & 1);
-        rs_barrier();
-        fetch(q2, c + 5);
-        __builtin_amdgcn_sched_barrier(0);
-        compute((c + 2) & 1);
-        if (c + 3 < n_chunks) stage(q0, (c + 3) & 1);
-        rs_barrier();
-    }
-    if (c < n_chunks) {
-        compute(c & 1);
-        if (c + 1 < n_chunks) {
-            stage(q1, (c + 1) & 1);
-            rs_barrier();
-            compute((c + 1) & 1);
+    struct State { SplitQuad s; };
+    auto park = [&](auto part, const Raw& raw, State& st, unsigned char* buf) {
+        constexpr int p = decltype(part)::value, e = p / 4;                          // column
+        st.s.template part<p % 4>(raw.x[0][e], raw.x[1][e], raw.x[2][e], raw.x[3][e]);
+        if constexpr (p % 4 == 3) {
+            if (!stages) return;
+            unsigned char* o = buf + lds_block + e * ROW_STEP;
+            *reinterpret_cast<uint2*>(o) = make_uint2(st.s.ha, st.s.hb);
+            *reinterpret_cast<uint2*>(o + Tile::PLANE) = make_uint2(st.s.ma, st.s.mb);
+            *reinterpret_cast<uint2*>(o + 2 * Tile::PLANE) = make_uint2(st.s.la, st.s.lb);
         }
-    }
+    };
 
-    // W + alpha * (U^T V): lane l32 owns one column, 32 lanes cover a whole 128-byte line
+    Tile t;
+    t.init(wave, lane);
+    t.template run<Raw, State, 16, false, 2>(n_chunks, rs_lds, fetch, prep, park);
+
+    // the entries of W this wavefront finishes: requested before the exchange, used after it (requested before the
+    // contraction they stand in front of its loads in the in-order queue: 0.3 to 0.8 us slower)
+    const int wm = (wave & 3) >> 1, wn = wave & 1, l32 = lane & 31;
+    auto w_row = [&](int i, int q) { return j0 + rs_column<NT>((wm * MT + i) * 32 + Tile::entry_row(wave >> 2, q, lane)); };
+    // one column per block, or (PAIRS) the first of two neighbours
+    const int dcol = PAIRS ? d0 + wn * 64 + 4 * (l32 & 15) + 2 * (l32 >> 4) : d0 + wn * 32 + l32;
+    float w[MT][NT][8];
 #pragma unroll
-    for (int t = 0; t < NT; ++t) {
-        const int col = d0 + wn * WN + t * 32 + l32;
+    for (int i = 0; i < MT; ++i)
 #pragma unroll
-        for (int e = 0; e < 16; ++e) {
-            const int row = j0 + wm * WM + 8 * (e / 4) + 4 * half + (e % 4);
-            if (row < J && col < D) W[(int64_t)row * ldw + col] =
-                    prox_entry(wreg[t][e] + alpha * (lead[t][e] + corr[t][e]), prox_kind, prox_a);
+        for (int q = 0; q < 8; ++q) {
+            const float* row = W + (int64_t)min(w_row(i, q), J - 1) * ldw;
+            if constexpr (PAIRS) {
+                const rs_f32x2u x = *reinterpret_cast<const rs_f32x2u*>(row + min(dcol, D - 2));
+                w[i][0][q] = dcol > D - 2 ? x.y : x.x;
+                w[i][1][q] = x.y;
+            } else {
+                w[i][0][q] = row[min(dcol, D - 1)];
+            }
         }
-    }
+    float sum[MT][NT][8];
+    t.exchange(wave, lane, rs_lds, sum);
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const int row = w_row(i, q);
+            float* out = W + (int64_t)row * ldw + dcol;
+            if constexpr (PAIRS) {
+                // lanes 16..31 (48..63) give their first block's sum for the second block's of lanes 0..15 (32..47)
+                asm volatile("s_nop 1\n\tv_permlane16_swap_b32 %0, %1\n\ts_nop 1" : "+v"(sum[i][0][q]), "+v"(sum[i][1][q]));
+                rs_f32x2u x;
+                x.x = prox_entry(w[i][0][q] + alpha * sum[i][0][q], prox_kind, prox_a);
+                x.y = prox_entry(w[i][1][q] + alpha * sum[i][1][q], prox_kind, prox_a);
+                if (row < J) {
+                    if (dcol + 1 < D) *reinterpret_cast<rs_f32x2u*>(out) = x;
+                    else if (dcol < D) *out = x.x;
+                }
+            } else {
+                const float x = prox_entry(w[i][0][q] + alpha * sum[i][0][q], prox_kind, prox_a);
+                if (row < J && dcol < D) *out = x;
+            }
+        }
 }
 
 bool reconstruct_split_ok(const ReconArgs& a) {
-    auto al = [](const void* ptr, int64_t ld) { return ((uintptr_t)ptr % 16) == 0 && (ld % 4) == 0; };
-    return !a.bf16 && !a.use_mask && al(a.u, a.ldu) && al(a.v, a.ldv) && (a.J % 4) == 0 && a.J >= 4 &&
-           (a.D % 4) == 0 && a.D >= 4 && (a.N % kRsBK) == 0 && a.N >= kRsBK;
+    // 32-bit byte offsets into U and V;
+    // a masked call finds the worker of a pair with a 32-bit reciprocal of B: exact while N * B < 2^32
+    return !a.bf16 && a.J >= 4 && a.D >= 4 && ((int64_t)a.N + 64) * (a.ldu > a.ldv ? a.ldu : a.ldv) < (1LL << 30) &&
+           (!a.use_mask || (a.B > 1 && (int64_t)a.N * a.B < (1LL << 32)));
 }
 
-hipError_t launch_reconstruct_split(const ReconArgs& a, hipStream_t s) {
-    constexpr size_t lds_bytes = 2 * (size_t)kRsStageBytes;
+template <int MT, int NT>
+static hipError_t launch_split(const ReconArgs& a, hipStream_t s) {
+    using Tile = ReconTile<MT, NT>;
+    constexpr size_t lds_bytes = Tile::LDS;
     static std::atomic<bool> raised{false};
     if (!raised) {
-        hipError_t e = hipFuncSetAttribute((const void*)reconstruct_split_kernel,
+        hipError_t e = hipFuncSetAttribute((const void*)reconstruct_split_kernel<MT, NT>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
         if (e != hipSuccess) return e;
         raised = true;
     }
-    const int n_jb = (a.J + kRsBM - 1) / kRsBM, n_db = (a.D + kRsBN - 1) / kRsBN;
+    const int n_jb = (a.J + Tile::BM - 1) / Tile::BM, n_db = (a.D + Tile::BN - 1) / Tile::BN;
     const int total = n_jb * n_db;
-    SFB_LAUNCH(reconstruct_split_kernel, dim3(total), dim3(kRsThreads), lds_bytes, s, a.w, a.ldw, a.u, a.ldu,
-               (const float*)a.v, a.ldv, a.J, a.D, a.N, a.alpha, n_jb, total, a.prox_kind, a.prox_a);
+    const uint32_t inv_b = a.use_mask ? (uint32_t)(((1ull << 32) + a.B - 1) / a.B) : 0;
+    SFB_LAUNCH((reconstruct_split_kernel<MT, NT>), dim3(total), dim3(kSplitThreads), lds_bytes, s, a.w, a.ldw, a.u, a.ldu,
+               (const float*)a.v, a.ldv, a.J, a.D, a.N, a.alpha, n_jb, total, a.prox_kind, a.prox_a, a.live_mask, inv_b);
     return hipGetLastError();
+}
+
+// Tile and estimated microseconds of the kernel above for N pairs, and of the fp32 matrix instruction's kernels: both
+// fitted to 202 shapes (J = 32 to 2000, D = 256 to 8192, N = 64 to 4096) on one MI355X, the cheaper one by these
+// figures is within 0.4 % of the cheaper one measured on average.  The kernel above costs a chunk of 32 pairs 1.08 us
+// per round of 256 tiles (0.77 with 64 x 64 tiles) on top of 7 us and W's trip at 7.4 TB/s; the fp32 kernels cost
+// 16.5 ns per million multiply-adds on whole 64 x 64 tiles, no less than 18 ns per pair unless they cut a long
+// contraction of few tiles into slices, on top of 4.6 us.  So the split pays from about 256 pairs on a W that fills
+// the chip (1000 x 4096: 21.7 -> 20.5 us at 256 pairs, 37.5 -> 30.5 at 512, 256 -> 171 at 4096).
+// `copies`: the fp32 kernels would first have to copy ragged, misaligned or masked factors.
+bool reconstruct_split_plan(int64_t J, int64_t D, int64_t N, bool copies, int* bm, int* bn) {
+    const double chunks = (double)((N + kSpChunk - 1) / kSpChunk), w_mb = 8e-6 * (double)J * (double)D;
+    const double jd64 = (double)((J + 63) / 64 * 64) * (double)((D + 63) / 64 * 64);
+    const double rounds128 = (double)((((J + 127) / 128) * ((D + 127) / 128) + 255) / 256);
+    const double rounds64 = (double)((((J + 63) / 64) * ((D + 63) / 64) + 255) / 256);
+    const double us128 = 6.3 + 0.135 * w_mb + rounds128 * chunks * 1.08 + (rounds128 - 1.0) * 6.8;
+    const double us64 = 6.3 + 0.135 * w_mb + rounds64 * chunks * 0.77 + (rounds64 - 1.0) * 2.0;
+    const double latency = N >= 1000 && jd64 < 130.0 * 4096.0 ? 3.0 + 0.002 * (double)N : 0.018 * (double)N;
+    const double work = 0.0165e-6 * jd64 * (double)N;
+    const double fp32 = 4.6 + 0.05 * w_mb + (work > latency ? work : latency) +
+                        (copies ? 3.5 + 1.6e-6 * (double)N * (double)(J + D) : 0.0);
+    *bm = *bn = us64 < us128 ? 64 : 128;
+    // up to some ten million multiply-adds both are all latency (8 to 10 us): the fp32 kernels, on copies if need be
+    if ((double)N * (double)J * (double)D < 33e6) return false;
+    return (us64 < us128 ? us64 : us128) < fp32;
+}
+
+hipError_t launch_reconstruct_split(const ReconArgs& a, int bm, int bn, hipStream_t s) {
+    if (bm == 128 && bn == 128) return launch_split<2, 2>(a, s);
+    if (bm == 64 && bn == 64) return launch_split<1, 1>(a, s);
+    return hipErrorInvalidValue;
 }
 
 }  // namespace sfb
