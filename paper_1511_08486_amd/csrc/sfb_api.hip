@@ -313,9 +313,19 @@ sfb_status recon_launch(sfb_ctx* c, float* W, int64_t ldw, const float* U, int64
         return SFB_OK;
     }
     int bm = 128, bn = 128;
+    bool on_split = false;
     const bool whole = reconstruct_takes_dma(r, c->recon);
-    if (c->split_recon != 0 && reconstruct_split_ok(r) &&
-        (reconstruct_split_plan(c->J, c->D, r.N, !whole, &bm, &bn) || c->split_recon == 1)) {
+    if (c->split_recon != 0 && reconstruct_split_ok(r)) {
+        // what the fp32 kernels would take, copies of ragged, misaligned or masked factors included
+        const double macs = (double)r.N * (double)c->J * (double)c->D;
+        double fp32_us = reconstruct_fp32_us(c->padded_factors ? c->recon_padded : c->recon, c->J, c->D, r.N);
+        if (!whole) fp32_us += 3.5 + 1.6e-6 * (double)r.N * (double)(c->J + c->D);
+        on_split = reconstruct_split_plan(c->J, c->D, r.N, fp32_us, &bm, &bn);
+        // (up to some ten million multiply-adds copy and kernel together are all latency, about the same either way)
+        if (!whole && macs < 33e6) on_split = false;
+        if (c->split_recon == 1) on_split = true;
+    }
+    if (on_split) {
         e = launch_reconstruct_split(r, bm, bn, c->stream);
     } else {
         // calls that would end in the register-staged kernel first try a copy of the factors that the LDS-DMA
@@ -374,12 +384,15 @@ sfb_status sfb_create(sfb_ctx** out, sfb_model m, int64_t J, int64_t D, int32_t 
         c->padded_factors = input_dtype == SFB_F32 &&
                             !((J % 4) == 0 && J >= 4 && (D % 128) == 0 && (N % 32) == 0 && N >= 32);
         c->recon_padded = plan_reconstruct_padded(J, D, N, -1);
-        // the partial scores may take what ragged contexts reserve for their padded factor copies, else the 16 MiB that
-        // sfb_step_noalloc has, or what the fp32 matrix instruction's plan would take where that is more
+        // room for the partial scores: what ragged contexts reserve for their padded factor copies anyway, or a few MiB; the
+        // others the 16 MiB that sfb_step_noalloc has; or what the fp32 instruction's plan would take, where that is more
         size_t most = SFB_NOALLOC_SCRATCH_BYTES;
+        if (c->padded_factors) {
+            most = conform_workspace(J, D, N);
+            if (most < ((size_t)4 << 20)) most = (size_t)4 << 20;
+        }
         const size_t f32_need = (size_t)c->fwd_all.split_k * (size_t)N * (size_t)round_up4(J) * sizeof(float);
         if (f32_need > most) most = f32_need;
-        if (c->padded_factors && conform_workspace(J, D, N) < most) most = conform_workspace(J, D, N);
         c->fwd_split = plan_forward_split(N, J, D, most);
         c->fwd_split_worker = plan_forward_split(B, J, D, (size_t)c->fwd_split.split_k * (size_t)N * (size_t)round_up4(J) * sizeof(float));
     }

@@ -167,6 +167,8 @@ struct ReconArgs {
     int tile_cols() const { return Dp > 0 ? Dp : D; }
 };
 hipError_t launch_reconstruct(const ReconArgs& a, const ReconPlan& p, hipStream_t s);
+// estimated microseconds of the plan's kernel for n_rows pairs (fitted to one MI355X)
+double reconstruct_fp32_us(const ReconPlan& p, int64_t J, int64_t D, int64_t n_rows);
 // Ragged or misaligned fp32 factors through the LDS-DMA kernels: the factors are first copied
 // into `workspace` (conform_workspace(J, D, N) bytes, 256-byte aligned) with every row padded to
 // what those kernels assume, then the plan's kernel runs on the copies and updates W entry by
@@ -208,7 +210,7 @@ hipError_t launch_reconstruct_pair(const ReconArgs& a, hipStream_t s);
 // fp32 reconstruction on the bf16 matrix cores, every operand split exactly into three bf16 terms
 // (sfb_reconstruct_split.hip); takes ragged, misaligned and masked factors as they are
 bool reconstruct_split_ok(const ReconArgs& a);
-bool reconstruct_split_plan(int64_t J, int64_t D, int64_t N, bool copies, int* bm, int* bn);
+bool reconstruct_split_plan(int64_t J, int64_t D, int64_t N, double fp32_us, int* bm, int* bn);
 hipError_t launch_reconstruct_split(const ReconArgs& a, int bm, int bn, hipStream_t s);
 
 // bf16-feature path on the bf16 matrix cores (sfb_bf16.hip)

@@ -47,7 +47,9 @@ __global__ __launch_bounds__(kSplitThreads, 2) void reconstruct_split_kernel(
     const int n_chunks = (N + kSpChunk - 1) / kSpChunk;
 
     // lane block: pairs 4 kb .. 4 kb + 3, columns 4 rb .. 4 rb + 3 of the BM columns of U and BN of V side by side
-    const int kb = tid & 7, rb = tid >> 3;
+    // (four consecutive lanes read 64 contiguous bytes: with lanes of different rows side by side, rows a multiple of 32
+    // bytes apart took the loads of a 64 x 64 tile from 24.5 to 33 us at 1024 pairs)
+    const int kb = (tid >> 2) & 7, rb = (tid >> 6) * 8 + ((tid >> 5) & 1) * 4 + (tid & 3);
     const bool stages = (BM + BN) * 2 == kSplitThreads || __builtin_amdgcn_readfirstlane(rb) < (BM + BN) / 4;   // by wavefronts
     const bool is_v = __builtin_amdgcn_readfirstlane(rb) >= BM / 4;      // the same for a whole wavefront
     const int ncols = is_v ? D : J;
@@ -182,33 +184,31 @@ static hipError_t launch_split(const ReconArgs& a, hipStream_t s) {
     return hipGetLastError();
 }
 
-// Tile and estimated microseconds of the kernel above for N pairs, and of the fp32 matrix instruction's kernels: both
-// fitted to 202 shapes (J = 32 to 2000, D = 256 to 8192, N = 64 to 4096) on one MI355X, the cheaper one by these
-// figures is within 0.4 % of the cheaper one measured on average.  The kernel above costs a chunk of 32 pairs 1.08 us
-// per round of 256 tiles (0.77 with 64 x 64 tiles) on top of 7 us and W's trip at 7.4 TB/s; the fp32 kernels cost
-// 16.5 ns per million multiply-adds on whole 64 x 64 tiles, no less than 18 ns per pair unless they cut a long
-// contraction of few tiles into slices, on top of 4.6 us.  So the split pays from about 256 pairs on a W that fills
-// the chip (1000 x 4096: 21.7 -> 20.5 us at 256 pairs, 37.5 -> 30.5 at 512, 256 -> 171 at 4096).
-// `copies`: the fp32 kernels would first have to copy ragged, misaligned or masked factors.
-bool reconstruct_split_plan(int64_t J, int64_t D, int64_t N, bool copies, int* bm, int* bn) {
+// Tile, and whether this kernel beats the fp32 matrix instruction's: estimates in microseconds, fitted to 202 shapes
+// (J = 32 to 2000, D = 256 to 8192, N = 64 to 4096) on one MI355X.  A chunk of 32 pairs costs 1.04 / 0.63 us per round
+// of 256 tiles of 128 x 128 / 64 x 128 and 0.42 us with 64 x 64 tiles (three share a compute unit), on top of 5.6 us,
+// W's trip at 7 TB/s and 2.8 us per further round.  1000 x 4096: 21.7 -> 18.5 us at 256 pairs, 37.5 -> 28.9 at 512,
+// 256 -> 165 at 4096; 600 x 784 with 1024: 26 -> 20.5.
+// `fp32_us`: the estimate for the other kernels (reconstruct_fp32_us), copies of ragged or masked factors included.
+bool reconstruct_split_plan(int64_t J, int64_t D, int64_t N, double fp32_us, int* bm, int* bn) {
+    static const struct { int bm, bn, resident; double chunk_us, lone_us; } tiles[3] = {
+        {128, 128, 1, 1.04, 1.04}, {64, 128, 1, 0.63, 0.63}, {64, 64, 3, 0.42, 0.38}};
     const double chunks = (double)((N + kSpChunk - 1) / kSpChunk), w_mb = 8e-6 * (double)J * (double)D;
-    const double jd64 = (double)((J + 63) / 64 * 64) * (double)((D + 63) / 64 * 64);
-    const double rounds128 = (double)((((J + 127) / 128) * ((D + 127) / 128) + 255) / 256);
-    const double rounds64 = (double)((((J + 63) / 64) * ((D + 63) / 64) + 255) / 256);
-    const double us128 = 6.3 + 0.135 * w_mb + rounds128 * chunks * 1.08 + (rounds128 - 1.0) * 6.8;
-    const double us64 = 6.3 + 0.135 * w_mb + rounds64 * chunks * 0.77 + (rounds64 - 1.0) * 2.0;
-    const double latency = N >= 1000 && jd64 < 130.0 * 4096.0 ? 3.0 + 0.002 * (double)N : 0.018 * (double)N;
-    const double work = 0.0165e-6 * jd64 * (double)N;
-    const double fp32 = 4.6 + 0.05 * w_mb + (work > latency ? work : latency) +
-                        (copies ? 3.5 + 1.6e-6 * (double)N * (double)(J + D) : 0.0);
-    *bm = *bn = us64 < us128 ? 64 : 128;
-    // up to some ten million multiply-adds both are all latency (8 to 10 us): the fp32 kernels, on copies if need be
-    if ((double)N * (double)J * (double)D < 33e6) return false;
-    return (us64 < us128 ? us64 : us128) < fp32;
+    double best = 1e300;
+    for (const auto& t : tiles) {
+        const int64_t n = ((J + t.bm - 1) / t.bm) * ((D + t.bn - 1) / t.bn);
+        const double rounds = (double)((n + 255) / 256);
+        const double deep = (double)((n + 256 * t.resident - 1) / (256 * t.resident));
+        const double a = t.lone_us * deep, b = t.chunk_us * rounds;
+        const double us = 5.6 + 0.14 * w_mb + chunks * (a > b ? a : b) + (t.resident == 1 ? 2.8 * (rounds - 1.0) : 0.0);
+        if (us < best) { best = us; *bm = t.bm; *bn = t.bn; }
+    }
+    return best < fp32_us;
 }
 
 hipError_t launch_reconstruct_split(const ReconArgs& a, int bm, int bn, hipStream_t s) {
     if (bm == 128 && bn == 128) return launch_split<2, 2>(a, s);
+    if (bm == 64 && bn == 128) return launch_split<1, 2>(a, s);
     if (bm == 64 && bn == 64) return launch_split<1, 1>(a, s);
     return hipErrorInvalidValue;
 }

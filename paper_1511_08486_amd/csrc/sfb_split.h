@@ -83,9 +83,9 @@ struct SplitTile {
     static constexpr int XCHG = 8 * MT * NT * 8 * 64 * 4;               // exchange of partial sums at the end
     static constexpr int LDS = 2 * BYTES > XCHG ? 2 * BYTES : XCHG;
 
-    // among eight consecutive rows any one item falls into eight different 16-byte bank groups of 128 bytes, among
-    // sixteen into sixteen of 256
-    static __device__ __forceinline__ int swz(int r) { return SWZ ? ((((r >> 1) ^ (r >> 3)) & 1) | (((r >> 2) & 1) << 1)) : 0; }
+    // Among eight consecutive rows any one item falls into eight different 16-byte bank groups of 128 bytes, among
+    // sixteen into sixteen of 256; of four consecutive rows (from a multiple of four) half a row each, too.
+    static __device__ __forceinline__ int swz(int r) { return SWZ ? (((r >> 2) & 1) | ((((r >> 1) ^ (r >> 3)) & 1) << 1)) : 0; }
 
     struct Frag { sp_u32x4 a[3][MT], b[3][NT]; };
     f32x16 acc[MT][NT];
