@@ -74,6 +74,8 @@ struct sfb_ctx {
     size_t ws_bytes;
     int last_hip;
     bool timing;
+    void* lists;                   // L2SVM: where in the workspace this step's column lists may go (null: no room), and
+    int64_t lists_stored;          //   the number of stored entries of its batch
     bool sparse_forward;           // L2SVM: scores from the CSR entries when W rows fit in LDS and that is the cheaper pass
     bool sparse_always;            //   ... whenever they fit (no cost comparison)
     std::vector<EventPair> used[kFamilies], spare;
@@ -117,6 +119,13 @@ size_t workspace_need(const sfb_ctx* c) {
         const size_t sp = masked_workspace(c->J, (int64_t)c->P * c->B) +
                           reconstruct_small_split_workspace(c->recon.n_split, c->J, c->D);
         if (sp > need) need = sp;
+    }
+    // sparse features: lists of the stored entries per column behind the scores, for one entry in twelve, unless that
+    // would take the context beyond what sfb_step_noalloc has
+    if (c->model == SFB_L2SVM) {
+        const size_t n = (size_t)c->P * c->B;
+        const size_t at = (n * round_up4(c->J) * sizeof(float) + 255) / 256 * 256 + sparse_update_workspace(c->D, (int64_t)(n * c->D / 12));
+        if (at > need && sparse_update_ok((int64_t)n) && at <= SFB_NOALLOC_SCRATCH_BYTES) need = at;
     }
     // the column projection of the proximal step reuses the front of the buffer between steps
     const size_t prox = prox_workspace(c->J, c->D);
@@ -221,23 +230,32 @@ sfb_status factors_rows(sfb_ctx* c, const FwdPlan& plan, const float* W, int64_t
     f.n_rows = n_rows; f.J = (int)c->J; f.D = (int)c->D;
     f.bf16 = bf16;
     bool sparse_scores = false;
+    c->lists = nullptr;
     if (c->model == SFB_L2SVM) {
+        // scores from the stored entries only (2*nnz*J flops), or the dense contraction on the densified rows
+        sparse_scores = c->sparse_forward && csr_scores_ok((int)c->D) && b->nnz <= (1LL << 30) - 1024 &&
+                        (c->sparse_always || csr_scores_wins(n_rows, c->J, c->D, b->nnz));
+        // the update of the same step may want lists of the entries per column, behind the planes of scores
+        if (n_rows == c->P * c->B && sparse_update_ok(n_rows)) {
+            const int planes = sparse_scores ? 1 : c->split_scores && c->D >= 4 ? c->fwd_split.split_k : plan.split_k;
+            const size_t at = ((size_t)planes * n_rows * ldz * sizeof(float) + 255) / 256 * 256;
+            if (at + sparse_update_workspace(c->D, b->nnz) <= c->ws_bytes) {
+                c->lists = (char*)c->ws + at;
+                c->lists_stored = b->nnz;
+            }
+        }
         // v_i first: the dense rows are what the reconstruction multiplies
-        DensifyArgs d{b->csr_rowptr, b->csr_col, b->csr_val, (float*)v_rows, ldv, n_rows, (int)c->D, b->nnz};
+        DensifyArgs d{b->csr_rowptr, b->csr_col, b->csr_val, (float*)v_rows, ldv, n_rows, (int)c->D, b->nnz, (uint32_t*)c->lists};
         {
             Timed t(c, 3);
             hipError_t e = launch_csr_densify(d, c->stream);
             if (e != hipSuccess) return hip_fail(c, e);
         }
-        if (c->sparse_forward && csr_scores_ok((int)c->D) && b->nnz <= (1LL << 30) - 1024 &&
-            (c->sparse_always || csr_scores_wins(n_rows, c->J, c->D, b->nnz))) {
-            // scores from the stored entries only: 2*nnz*J flops instead of 2*N*J*D
+        if (sparse_scores) {
             Timed t(c, 0);
             hipError_t e = launch_csr_scores(d, W, ldw, (float*)c->ws, ldz, (int)c->J, c->stream);
             if (e != hipSuccess) return hip_fail(c, e);
-            sparse_scores = true;
         } else {
-            // fall back to the dense contraction on the densified rows
             f.a = v_rows; f.a2 = nullptr; f.lda = ldv; f.v = nullptr; f.ldv = 0; f.diff = false;
         }
     } else {
@@ -284,9 +302,10 @@ sfb_status check_recon(const sfb_ctx* c, float eta, float scale, const uint8_t* 
 }
 
 // n_rows: factor pairs to contract over (0 = all P*B; a single worker's B otherwise, no mask)
+// same_step: U, V are what factors_rows has just left (the column lists it made room for may be used)
 sfb_status recon_launch(sfb_ctx* c, float* W, int64_t ldw, const float* U, int64_t ldu, const void* V,
                         int64_t ldv, float eta, float scale, const uint8_t* active, int n_rows = 0,
-                        int prox_kind = 0, float prox_a = 0.f) {
+                        int prox_kind = 0, float prox_a = 0.f, bool same_step = false) {
     ReconArgs r{};
     r.w = W; r.ldw = ldw; r.u = U; r.ldu = ldu; r.v = V; r.ldv = ldv;
     r.J = (int)c->J; r.D = (int)c->D; r.N = n_rows > 0 ? n_rows : c->P * c->B; r.B = c->B;
@@ -313,19 +332,25 @@ sfb_status recon_launch(sfb_ctx* c, float* W, int64_t ldw, const float* U, int64
         return SFB_OK;
     }
     int bm = 128, bn = 128;
-    bool on_split = false;
+    bool on_split = false, on_lists = false;
     const bool whole = reconstruct_takes_dma(r, c->recon);
-    if (c->split_recon != 0 && reconstruct_split_ok(r)) {
+    if (c->split_recon != 0) {
         // what the fp32 kernels would take, copies of ragged, misaligned or masked factors included
         const double macs = (double)r.N * (double)c->J * (double)c->D;
-        double fp32_us = reconstruct_fp32_us(c->padded_factors ? c->recon_padded : c->recon, c->J, c->D, r.N);
-        if (!whole) fp32_us += 3.5 + 1.6e-6 * (double)r.N * (double)(c->J + c->D);
-        on_split = reconstruct_split_plan(c->J, c->D, r.N, fp32_us, &bm, &bn);
-        // (up to some ten million multiply-adds copy and kernel together are all latency, about the same either way)
-        if (!whole && macs < 33e6) on_split = false;
-        if (c->split_recon == 1) on_split = true;
+        double us = reconstruct_fp32_us(c->padded_factors ? c->recon_padded : c->recon, c->J, c->D, r.N);
+        if (!whole) us += 3.5 + 1.6e-6 * (double)r.N * (double)(c->J + c->D);
+        if (reconstruct_split_ok(r)) {
+            const double split_us = reconstruct_split_plan(c->J, c->D, r.N, &bm, &bn);
+            // (small enough, copy and kernel together are all latency, about the same either way)
+            on_split = c->split_recon == 1 || (split_us < us && (whole || macs >= (r.use_mask ? 33e6 : 1e6)));
+            if (on_split) us = split_us;
+        }
+        on_lists = same_step && c->lists != nullptr && c->split_recon < 0 &&
+                   sparse_update_us(r.N, c->J, c->D, c->lists_stored) < us;
     }
-    if (on_split) {
+    if (on_lists) {
+        e = launch_sparse_update(r, c->lists_stored, c->lists, c->stream);
+    } else if (on_split) {
         e = launch_reconstruct_split(r, bm, bn, c->stream);
     } else {
         // calls that would end in the register-staged kernel first try a copy of the factors that the LDS-DMA
@@ -399,7 +424,7 @@ sfb_status sfb_create(sfb_ctx** out, sfb_model m, int64_t J, int64_t D, int32_t 
     c->fused_ok = input_dtype == SFB_BF16 && m == SFB_MLR && fused_shape_ok(J, D, (int64_t)P * B);
     c->use_fused = true;
     c->fused = c->fused_ok ? plan_fused(J, D, (int64_t)P * B) : FusedPlan{};
-    c->ws = nullptr; c->ws_bytes = 0; c->last_hip = 0; c->timing = false; c->sparse_forward = true; c->sparse_always = false;
+    c->ws = nullptr; c->ws_bytes = 0; c->lists = nullptr; c->lists_stored = 0; c->last_hip = 0; c->timing = false; c->sparse_forward = true; c->sparse_always = false;
     // Set-up for sfb_step_noalloc on the device that is current now: resolve the address of the
     // library's scratch array, so that the entry point itself only reads it.  On a machine without a
     // GPU this fails; the context is still good for everything that can be checked on the host, and
@@ -487,7 +512,7 @@ sfb_status sfb_step(sfb_ctx* c, float* W, int64_t ldw, const sfb_batch* batch, c
     if (s != SFB_OK) return s;
     s = factors_rows(c, c->fwd_all, W, ldw, batch, y, 0, c->P * c->B, U, ldu, V, ldv, loss);
     if (s != SFB_OK) return s;
-    return recon_launch(c, W, ldw, U, ldu, V, ldv, eta, scale, active);
+    return recon_launch(c, W, ldw, U, ldu, V, ldv, eta, scale, active, 0, 0, 0.f, true);
 }
 
 sfb_status sfb_step_pipelined(sfb_ctx* c, float* W, int64_t ldw, float* U, int64_t ldu, void* V, int64_t ldv,
@@ -564,7 +589,7 @@ sfb_status sfb_step_noalloc(sfb_ctx* c, float* W, int64_t ldw, const sfb_batch* 
     const size_t ws_bytes = c->ws_bytes;
     c->ws = ptr; c->ws_bytes = kStaticScratchBytes;
     s = factors_rows(c, c->fwd_all, W, ldw, batch, y, 0, c->P * c->B, U, ldu, V, ldv, loss);
-    if (s == SFB_OK) s = recon_launch(c, W, ldw, U, ldu, V, ldv, eta, scale, active);
+    if (s == SFB_OK) s = recon_launch(c, W, ldw, U, ldu, V, ldv, eta, scale, active, 0, 0, 0.f, true);
     c->ws = ws; c->ws_bytes = ws_bytes;
     return s;
 }
@@ -621,11 +646,11 @@ sfb_status sfb_prox(sfb_ctx* c, float* W, int64_t ldw, sfb_prox_kind kind, float
 // (no extra pass over W), the column projection runs as its own kernels afterwards.
 static sfb_status recon_then_prox(sfb_ctx* c, float* W, int64_t ldw, const float* U, int64_t ldu, const void* V,
                                   int64_t ldv, float eta, float scale, const uint8_t* active, sfb_prox_kind kind,
-                                  float param) {
+                                  float param, bool same_step) {
     if (kind == SFB_PROX_L2SQ)
-        return recon_launch(c, W, ldw, U, ldu, V, ldv, eta, scale, active, 0, 1, 1.0f / (1.0f + eta * param));
-    if (kind == SFB_PROX_L1) return recon_launch(c, W, ldw, U, ldu, V, ldv, eta, scale, active, 0, 2, eta * param);
-    sfb_status s = recon_launch(c, W, ldw, U, ldu, V, ldv, eta, scale, active);
+        return recon_launch(c, W, ldw, U, ldu, V, ldv, eta, scale, active, 0, 1, 1.0f / (1.0f + eta * param), same_step);
+    if (kind == SFB_PROX_L1) return recon_launch(c, W, ldw, U, ldu, V, ldv, eta, scale, active, 0, 2, eta * param, same_step);
+    sfb_status s = recon_launch(c, W, ldw, U, ldu, V, ldv, eta, scale, active, 0, 0, 0.f, same_step);
     if (s != SFB_OK || kind == SFB_PROX_NONE) return s;
     return sfb_prox(c, W, ldw, kind, eta, param);
 }
@@ -639,7 +664,7 @@ sfb_status sfb_reconstruct_apply_prox(sfb_ctx* c, float* W, int64_t ldw, const f
     if (s != SFB_OK) return s;
     s = check_prox(c, kind, eta, param, true);
     if (s != SFB_OK) return s;
-    return recon_then_prox(c, W, ldw, U, ldu, V, ldv, eta, scale, active, kind, param);
+    return recon_then_prox(c, W, ldw, U, ldu, V, ldv, eta, scale, active, kind, param, false);
 }
 
 sfb_status sfb_step_prox(sfb_ctx* c, float* W, int64_t ldw, const sfb_batch* batch, const int32_t* y, float* U,
@@ -657,7 +682,7 @@ sfb_status sfb_step_prox(sfb_ctx* c, float* W, int64_t ldw, const sfb_batch* bat
     if (s != SFB_OK) return s;
     s = factors_rows(c, c->fwd_all, W, ldw, batch, y, 0, c->P * c->B, U, ldu, V, ldv, loss);
     if (s != SFB_OK) return s;
-    return recon_then_prox(c, W, ldw, U, ldu, V, ldv, eta, scale, active, kind, param);
+    return recon_then_prox(c, W, ldw, U, ldu, V, ldv, eta, scale, active, kind, param, true);
 }
 
 sfb_status sfb_shape(const sfb_ctx* c, int64_t* J, int64_t* D, int32_t* P, int32_t* B, int32_t* input_dtype) {

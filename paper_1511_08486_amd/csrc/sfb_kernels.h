@@ -97,6 +97,7 @@ struct DensifyArgs {
     float* v; int64_t ldv;
     int n_rows, D;
     int64_t nnz;          // length of col / val
+    uint32_t* clear = nullptr;   // a word to zero on the way (the counter of launch_sparse_update), or none
 };
 hipError_t launch_csr_densify(const DensifyArgs& a, hipStream_t s);
 
@@ -210,8 +211,16 @@ hipError_t launch_reconstruct_pair(const ReconArgs& a, hipStream_t s);
 // fp32 reconstruction on the bf16 matrix cores, every operand split exactly into three bf16 terms
 // (sfb_reconstruct_split.hip); takes ragged, misaligned and masked factors as they are
 bool reconstruct_split_ok(const ReconArgs& a);
-bool reconstruct_split_plan(int64_t J, int64_t D, int64_t N, double fp32_us, int* bm, int* bn);
+double reconstruct_split_plan(int64_t J, int64_t D, int64_t N, int* bm, int* bn);   // tile, estimated microseconds
 hipError_t launch_reconstruct_split(const ReconArgs& a, int bm, int bn, hipStream_t s);
+
+// Reconstruction from the stored entries of sparse features (sfb_sparse_update.hip): column lists made from the dense
+// rows V, then W += alpha U^T V over the entries only.  workspace: sparse_update_workspace(D, stored) bytes, 256-byte
+// aligned, its first word zero; stored: at least the number of non-zero entries of V.  One launch_csr_densify before it.
+bool sparse_update_ok(int64_t N);
+size_t sparse_update_workspace(int64_t D, int64_t stored);
+double sparse_update_us(int64_t N, int64_t J, int64_t D, int64_t stored);   // estimate
+hipError_t launch_sparse_update(const ReconArgs& a, int64_t stored, void* workspace, hipStream_t s);
 
 // bf16-feature path on the bf16 matrix cores (sfb_bf16.hip)
 bool forward_bf16_ok(const FwdArgs& a);                       // alignment / shape the DMA kernel needs

@@ -184,13 +184,12 @@ static hipError_t launch_split(const ReconArgs& a, hipStream_t s) {
     return hipGetLastError();
 }
 
-// Tile, and whether this kernel beats the fp32 matrix instruction's: estimates in microseconds, fitted to 202 shapes
+// Tile and microseconds (the other kernels': reconstruct_fp32_us), fitted to 202 shapes
 // (J = 32 to 2000, D = 256 to 8192, N = 64 to 4096) on one MI355X.  A chunk of 32 pairs costs 1.04 / 0.63 us per round
 // of 256 tiles of 128 x 128 / 64 x 128 and 0.42 us with 64 x 64 tiles (three share a compute unit), on top of 5.6 us,
 // W's trip at 7 TB/s and 2.8 us per further round.  1000 x 4096: 21.7 -> 18.5 us at 256 pairs, 37.5 -> 28.9 at 512,
 // 256 -> 165 at 4096; 600 x 784 with 1024: 26 -> 20.5.
-// `fp32_us`: the estimate for the other kernels (reconstruct_fp32_us), copies of ragged or masked factors included.
-bool reconstruct_split_plan(int64_t J, int64_t D, int64_t N, double fp32_us, int* bm, int* bn) {
+double reconstruct_split_plan(int64_t J, int64_t D, int64_t N, int* bm, int* bn) {
     static const struct { int bm, bn, resident; double chunk_us, lone_us; } tiles[3] = {
         {128, 128, 1, 1.04, 1.04}, {64, 128, 1, 0.63, 0.63}, {64, 64, 3, 0.42, 0.38}};
     const double chunks = (double)((N + kSpChunk - 1) / kSpChunk), w_mb = 8e-6 * (double)J * (double)D;
@@ -203,7 +202,7 @@ bool reconstruct_split_plan(int64_t J, int64_t D, int64_t N, double fp32_us, int
         const double us = 5.6 + 0.14 * w_mb + chunks * (a > b ? a : b) + (t.resident == 1 ? 2.8 * (rounds - 1.0) : 0.0);
         if (us < best) { best = us; *bm = t.bm; *bn = t.bn; }
     }
-    return best < fp32_us;
+    return best;
 }
 
 hipError_t launch_reconstruct_split(const ReconArgs& a, int bm, int bn, hipStream_t s) {

@@ -20,7 +20,8 @@ constexpr int kDensifyThreads = 256;
 template <bool IN_LDS>
 __global__ __launch_bounds__(kDensifyThreads) void csr_densify_kernel(
     const int32_t* __restrict__ rowptr, const int32_t* __restrict__ col, const float* __restrict__ val,
-    float* __restrict__ V, int64_t ldv, int D, int64_t nnz, bool vec_v) {
+    float* __restrict__ V, int64_t ldv, int D, int64_t nnz, bool vec_v, uint32_t* __restrict__ clear) {
+    if (clear != nullptr && blockIdx.x == 0 && threadIdx.x == 0) *clear = 0;
     extern __shared__ __attribute__((aligned(16))) float dense_row[];   // [round_up4(D)] when IN_LDS
     const int row = blockIdx.x;
     float* out = V + (int64_t)row * ldv;
@@ -52,10 +53,10 @@ hipError_t launch_csr_densify(const DensifyArgs& a, hipStream_t s) {
     const size_t lds_bytes = ((size_t)a.D + 3) / 4 * 16;
     if (lds_bytes <= 64 * 1024) {
         SFB_LAUNCH(csr_densify_kernel<true>, dim3(a.n_rows), dim3(kDensifyThreads), lds_bytes, s, a.rowptr, a.col,
-                   a.val, a.v, a.ldv, a.D, a.nnz, vec_v);
+                   a.val, a.v, a.ldv, a.D, a.nnz, vec_v, a.clear);
     } else {
         SFB_LAUNCH(csr_densify_kernel<false>, dim3(a.n_rows), dim3(kDensifyThreads), 0, s, a.rowptr, a.col,
-                   a.val, a.v, a.ldv, a.D, a.nnz, vec_v);
+                   a.val, a.v, a.ldv, a.D, a.nnz, vec_v, a.clear);
     }
     return hipGetLastError();
 }
@@ -270,7 +271,7 @@ bool csr_scores_ok(int D) { return (size_t)D * kSpRows * sizeof(float) <= 160 * 
 // 5000, D = 1024 to 10000, 2 % and 20 % stored).  From the entries: J / 4 workgroups, one per compute unit at a time,
 // each walks every row; a row costs about 20 ns plus 2 ns per 64-entry slab up to the three the kernel keeps in
 // flight and 19 ns per slab beyond, counted from 3.5 (long rows wait for their own loads and gathers).  Dense, on the densified
-// rows: the fp32 contraction at about 110 TFLOP/s on at least one 64-class block, and no faster than its walk
+// rows: the dense contraction at about 160 TFLOP/s on at least one 64-class block, and no faster than its walk
 // through D.  The entries win at the
 // benchmark's 2 % of 8192 columns with 2000 classes (66 against 283 us) and lose with few classes (J = 64: 30
 // against 13 us), short rows (D = 1024) or dense ones (20 %: 962 against 280 us).
@@ -281,7 +282,7 @@ bool csr_scores_wins(int64_t n_rows, int64_t J, int64_t D, int64_t nnz) {
     const double per_row = 0.020 + 0.0019 * (slabs < 3.0 ? slabs : 3.0) + 0.019 * (slabs > 3.5 ? slabs - 3.5 : 0.0);
     const double rounds = (double)(((J + kSpRows - 1) / kSpRows + 255) / 256);
     const double from_entries = 1.1 * rounds * (4.0 + (double)n_rows * per_row);
-    const double flops_us = 2.0 * (double)n_rows * (double)(J > 64 ? J : 64) * (double)D / 1.1e8;
+    const double flops_us = 2.0 * (double)n_rows * (double)(J > 64 ? J : 64) * (double)D / 1.6e8;
     const double walk_us = 0.0012 * (double)D;               // a small grid still walks its slices of D stage by stage
     const double dense = 4.0 + (flops_us > walk_us ? flops_us : walk_us);
     return from_entries < dense;
