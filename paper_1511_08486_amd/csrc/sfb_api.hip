@@ -65,6 +65,7 @@ struct sfb_ctx {
     FwdPlan fwd_split, fwd_split_worker;   // the same on the bf16 matrix cores, fp32 operands split exactly into bf16 terms
     bool split_scores;             // use them where the shape allows
     int split_recon;               // reconstruction with split-bf16 products: 1 where the shape allows, 0 never, -1 where it is the cheaper one
+    SplitReconPlan split_plans[2][2];      // its tile and slices: all pairs or one worker's, without or with a workspace
     ReconPlan recon;
     ReconPlan recon_padded;        // the plan of the padded shape (ragged fp32 contexts: see padded_factors)
     bool padded_factors;           // fp32 and J, D or P*B not what the LDS-DMA reconstructions take as they are
@@ -74,6 +75,7 @@ struct sfb_ctx {
     size_t ws_bytes;
     int last_hip;
     bool timing;
+    bool few;                      // at most 32 classes: whole steps in one pass over the features (sfb_few.hip)
     void* lists;                   // L2SVM: where in the workspace this step's column lists may go (null: no room), and
     int64_t lists_stored;          //   the number of stored entries of its batch
     bool sparse_forward;           // L2SVM: scores from the CSR entries when W rows fit in LDS and that is the cheaper pass
@@ -119,6 +121,11 @@ size_t workspace_need(const sfb_ctx* c) {
         const size_t sp = masked_workspace(c->J, (int64_t)c->P * c->B) +
                           reconstruct_small_split_workspace(c->recon.n_split, c->J, c->D);
         if (sp > need) need = sp;
+    }
+    // few classes: planes of sums, one per workgroup (sfb_create has made sure that they stay within bounds)
+    if (c->few) {
+        const size_t planes = few_workspace((int64_t)c->P * c->B, c->J, c->D);
+        if (planes > need) need = planes;
     }
     // sparse features: lists of the stored entries per column behind the scores, for one entry in twelve, unless that
     // would take the context beyond what sfb_step_noalloc has
@@ -214,11 +221,51 @@ sfb_status factor_rows(sfb_ctx* c, int split_k, int64_t zstride, const int32_t* 
     return SFB_OK;
 }
 
+uint64_t live_workers(const sfb_ctx* c, const uint8_t* active, bool* use_mask) {
+    *use_mask = false;
+    if (!active) return ~0ull;
+    uint64_t m = 0;
+    for (int p = 0; p < c->P; ++p) {
+        if (active[p]) m |= (1ull << p); else *use_mask = true;
+    }
+    return m;
+}
+
+// At most 32 classes, dense features: the factors of `n_rows` samples (outputs from row `row0` on) and, with `update`, the
+// update of W by them, in one pass over the features.
+sfb_status few_rows(sfb_ctx* c, float* W, int64_t ldw, const sfb_batch* b, const int32_t* y, int64_t row0, int n_rows, float* U,
+                    int64_t ldu, void* V, int64_t ldv, float* loss, bool update, float alpha = 0.f, const uint8_t* active = nullptr,
+                    int prox_kind = 0, float prox_a = 0.f) {
+    if (c->ws == nullptr || c->ws_bytes < workspace_need(c)) return SFB_EWORKSPACE;
+    FewArgs f{};
+    f.bf16 = c->dtype == SFB_BF16;
+    f.diff = c->model == SFB_DML;
+    f.a = b->a; f.a2 = f.diff ? b->a2 : nullptr; f.lda = b->lda;
+    f.w = W; f.ldw = ldw; f.y = y;
+    f.u = U + row0 * ldu; f.ldu = ldu;
+    f.v = (char*)V + (size_t)row0 * ldv * (f.bf16 ? 2 : 4); f.ldv = ldv;
+    f.loss = loss ? loss + row0 : nullptr;
+    f.planes = (float*)c->ws;
+    f.n_rows = n_rows; f.J = (int)c->J; f.D = (int)c->D; f.B = c->B;
+    f.alpha = alpha;
+    f.live_mask = live_workers(c, active, &f.use_mask);
+    f.vec_a = ((uintptr_t)f.a % 8) == 0 && (f.lda % 4) == 0;
+    f.vec_v = ((uintptr_t)f.v % 8) == 0 && (f.ldv % 4) == 0;
+    f.prox_kind = prox_kind; f.prox_a = prox_a;
+    Timed t(c, 0);
+    hipError_t e = launch_few(f, update, c->stream);
+    if (e != hipSuccess) return hip_fail(c, e);
+    return SFB_OK;
+}
+
 // Factors of `n_rows` samples whose outputs start at row `row0` of U, V, loss.
 sfb_status factors_rows(sfb_ctx* c, const FwdPlan& plan, const float* W, int64_t ldw, const sfb_batch* b,
                         const int32_t* y, int64_t row0, int n_rows, float* U, int64_t ldu, void* V,
                         int64_t ldv, float* loss, const sfb_sdca* sdca = nullptr) {
     if (c->ws == nullptr || c->ws_bytes < workspace_need(c)) return SFB_EWORKSPACE;
+    c->lists = nullptr;
+    if (c->few && !sdca && few_ok(n_rows, c->J, c->D, c->model == SFB_DML))
+        return few_rows(c, const_cast<float*>(W), ldw, b, y, row0, n_rows, U, ldu, V, ldv, loss, false);
     const bool bf16 = c->dtype == SFB_BF16;
     const size_t vsz = bf16 ? 2 : 4;
     void* v_rows = (char*)V + (size_t)row0 * ldv * vsz;
@@ -230,7 +277,6 @@ sfb_status factors_rows(sfb_ctx* c, const FwdPlan& plan, const float* W, int64_t
     f.n_rows = n_rows; f.J = (int)c->J; f.D = (int)c->D;
     f.bf16 = bf16;
     bool sparse_scores = false;
-    c->lists = nullptr;
     if (c->model == SFB_L2SVM) {
         // scores from the stored entries only (2*nnz*J flops), or the dense contraction on the densified rows
         sparse_scores = c->sparse_forward && csr_scores_ok((int)c->D) && b->nnz <= (1LL << 30) - 1024 &&
@@ -311,18 +357,8 @@ sfb_status recon_launch(sfb_ctx* c, float* W, int64_t ldw, const float* U, int64
     r.J = (int)c->J; r.D = (int)c->D; r.N = n_rows > 0 ? n_rows : c->P * c->B; r.B = c->B;
     r.alpha = -eta * scale;
     r.bf16 = c->dtype == SFB_BF16;
-    r.use_mask = false;
-    r.live_mask = ~0ull;
+    r.live_mask = live_workers(c, active, &r.use_mask);
     r.prox_kind = prox_kind; r.prox_a = prox_a;
-    if (active) {
-        uint64_t m = 0;
-        bool all = true;
-        for (int p = 0; p < c->P; ++p) {
-            if (active[p]) m |= (1ull << p); else all = false;
-        }
-        r.live_mask = m;
-        r.use_mask = !all;
-    }
     Timed t(c, 2);
     hipError_t e;
     if (r.bf16) {
@@ -331,19 +367,22 @@ sfb_status recon_launch(sfb_ctx* c, float* W, int64_t ldw, const float* U, int64
         if (e != hipSuccess) return hip_fail(c, e);
         return SFB_OK;
     }
-    int bm = 128, bn = 128;
     bool on_split = false, on_lists = false;
+    const bool have_ws = c->ws != nullptr && c->ws_bytes >= workspace_need(c);
+    const SplitReconPlan* sp = nullptr;
     const bool whole = reconstruct_takes_dma(r, c->recon);
     if (c->split_recon != 0) {
         // what the fp32 kernels would take, copies of ragged, misaligned or masked factors included
         const double macs = (double)r.N * (double)c->J * (double)c->D;
-        double us = reconstruct_fp32_us(c->padded_factors ? c->recon_padded : c->recon, c->J, c->D, r.N);
+        double us = c->padded_factors && have_ws ? reconstruct_fp32_us(c->recon_padded, c->J, c->D, conform_rows(r.N))
+                                                 : reconstruct_fp32_us(c->recon, c->J, c->D, r.N);
         if (!whole) us += 3.5 + 1.6e-6 * (double)r.N * (double)(c->J + c->D);
         if (reconstruct_split_ok(r)) {
-            const double split_us = reconstruct_split_plan(c->J, c->D, r.N, &bm, &bn);
+            sp = &c->split_plans[n_rows > 0][have_ws];
+            if (sp->slices > 1 && (size_t)sp->slices * (size_t)c->J * (size_t)c->D * sizeof(float) > workspace_need(c)) sp = &c->split_plans[n_rows > 0][0];
             // (small enough, copy and kernel together are all latency, about the same either way)
-            on_split = c->split_recon == 1 || (split_us < us && (whole || macs >= (r.use_mask ? 33e6 : 1e6)));
-            if (on_split) us = split_us;
+            on_split = c->split_recon == 1 || (sp->us < us && (whole || macs >= (r.use_mask ? 33e6 : 1e6)));
+            if (on_split) us = sp->us;
         }
         on_lists = same_step && c->lists != nullptr && c->split_recon < 0 &&
                    sparse_update_us(r.N, c->J, c->D, c->lists_stored) < us;
@@ -351,13 +390,13 @@ sfb_status recon_launch(sfb_ctx* c, float* W, int64_t ldw, const float* U, int64
     if (on_lists) {
         e = launch_sparse_update(r, c->lists_stored, c->lists, c->stream);
     } else if (on_split) {
-        e = launch_reconstruct_split(r, bm, bn, c->stream);
+        r.partial = sp->slices > 1 ? (float*)c->ws : nullptr;
+        e = launch_reconstruct_split(r, *sp, c->stream);
     } else {
         // calls that would end in the register-staged kernel first try a copy of the factors that the LDS-DMA
         // kernels accept: padded ones for ragged shapes, U with a dead worker's rows zeroed for a masked call
         // (N x ceil4(J) floats: never more than the partial scores, whose bytes it takes)
         e = hipErrorNotSupported;
-        const bool have_ws = c->ws != nullptr && c->ws_bytes >= workspace_need(c);
         const int64_t n_all = (int64_t)c->P * c->B;
         if (have_ws && !whole) {
             if (c->padded_factors && conformed_variant_ok(c->recon_padded.variant)) {
@@ -424,6 +463,17 @@ sfb_status sfb_create(sfb_ctx** out, sfb_model m, int64_t J, int64_t D, int32_t 
     c->fused_ok = input_dtype == SFB_BF16 && m == SFB_MLR && fused_shape_ok(J, D, (int64_t)P * B);
     c->use_fused = true;
     c->fused = c->fused_ok ? plan_fused(J, D, (int64_t)P * B) : FusedPlan{};
+    c->few = false;
+    if (m != SFB_L2SVM && few_ok((int64_t)P * B, J, D, m == SFB_DML)) {
+        // (contexts that sfb_step_noalloc could hold stay that way)
+        const size_t planes = few_workspace((int64_t)P * B, J, D);
+        c->few = planes <= SFB_NOALLOC_SCRATCH_BYTES || planes <= workspace_need(c);
+    }
+    if (input_dtype == SFB_F32) {
+        for (int one = 0; one < 2; ++one)
+            for (int with_ws = 0; with_ws < 2; ++with_ws)
+                c->split_plans[one][with_ws] = reconstruct_split_plan(J, D, one ? B : (int64_t)P * B, with_ws ? workspace_need(c) : 0);
+    }
     c->ws = nullptr; c->ws_bytes = 0; c->lists = nullptr; c->lists_stored = 0; c->last_hip = 0; c->timing = false; c->sparse_forward = true; c->sparse_always = false;
     // Set-up for sfb_step_noalloc on the device that is current now: resolve the address of the
     // library's scratch array, so that the entry point itself only reads it.  On a machine without a
@@ -510,6 +560,7 @@ sfb_status sfb_step(sfb_ctx* c, float* W, int64_t ldw, const sfb_batch* batch, c
     (void)sfb_default_scale(c, &scale);
     s = check_recon(c, eta, scale, active);
     if (s != SFB_OK) return s;
+    if (c->few) return few_rows(c, W, ldw, batch, y, 0, c->P * c->B, U, ldu, V, ldv, loss, true, -eta * scale, active);
     s = factors_rows(c, c->fwd_all, W, ldw, batch, y, 0, c->P * c->B, U, ldu, V, ldv, loss);
     if (s != SFB_OK) return s;
     return recon_launch(c, W, ldw, U, ldu, V, ldv, eta, scale, active, 0, 0, 0.f, true);
@@ -535,15 +586,7 @@ sfb_status sfb_step_pipelined(sfb_ctx* c, float* W, int64_t ldw, float* U, int64
         f.zp = (float*)c->ws; f.ldz = round_up4(c->J); f.zstride = (int64_t)N * f.ldz;
         f.J = (int)c->J; f.D = (int)c->D; f.N = N; f.B = c->B;
         f.alpha = -eta * scale;
-        f.live_mask = ~0ull; f.use_mask = false;
-        if (active) {
-            uint64_t m = 0;
-            bool all = true;
-            for (int p = 0; p < c->P; ++p) {
-                if (active[p]) m |= (1ull << p); else all = false;
-            }
-            f.live_mask = m; f.use_mask = !all;
-        }
+        f.live_mask = live_workers(c, active, &f.use_mask);
         if (fused_call_ok(f)) {
             char* ws_factors = (char*)c->ws + scores_need(c);
             char* ws_next = ws_factors + bf16_recon_workspace(c->J, c->D, N);
@@ -588,8 +631,9 @@ sfb_status sfb_step_noalloc(sfb_ctx* c, float* W, int64_t ldw, const sfb_batch* 
     void* const ws = c->ws;
     const size_t ws_bytes = c->ws_bytes;
     c->ws = ptr; c->ws_bytes = kStaticScratchBytes;
-    s = factors_rows(c, c->fwd_all, W, ldw, batch, y, 0, c->P * c->B, U, ldu, V, ldv, loss);
-    if (s == SFB_OK) s = recon_launch(c, W, ldw, U, ldu, V, ldv, eta, scale, active, 0, 0, 0.f, true);
+    if (c->few) s = few_rows(c, W, ldw, batch, y, 0, c->P * c->B, U, ldu, V, ldv, loss, true, -eta * scale, active);
+    else s = factors_rows(c, c->fwd_all, W, ldw, batch, y, 0, c->P * c->B, U, ldu, V, ldv, loss);
+    if (s == SFB_OK && !c->few) s = recon_launch(c, W, ldw, U, ldu, V, ldv, eta, scale, active, 0, 0, 0.f, true);
     c->ws = ws; c->ws_bytes = ws_bytes;
     return s;
 }
@@ -680,6 +724,13 @@ sfb_status sfb_step_prox(sfb_ctx* c, float* W, int64_t ldw, const sfb_batch* bat
     if (s != SFB_OK) return s;
     s = check_prox(c, kind, eta, param, true);
     if (s != SFB_OK) return s;
+    if (c->few) {
+        const int entry = kind == SFB_PROX_L2SQ ? 1 : kind == SFB_PROX_L1 ? 2 : 0;      // entrywise kinds ride along
+        s = few_rows(c, W, ldw, batch, y, 0, c->P * c->B, U, ldu, V, ldv, loss, true, -eta * scale, active, entry,
+                     entry == 1 ? 1.0f / (1.0f + eta * param) : eta * param);
+        if (s != SFB_OK || kind != SFB_PROX_COLUMN_BALL) return s;
+        return sfb_prox(c, W, ldw, kind, eta, param);
+    }
     s = factors_rows(c, c->fwd_all, W, ldw, batch, y, 0, c->P * c->B, U, ldu, V, ldv, loss);
     if (s != SFB_OK) return s;
     return recon_then_prox(c, W, ldw, U, ldu, V, ldv, eta, scale, active, kind, param, true);
@@ -744,6 +795,7 @@ sfb_status sfb_set_plan(sfb_ctx* c, int32_t fwd_bm, int32_t fwd_bn, int32_t fwd_
     if ((fwd_bm > 0 && fwd_bm != 64 && fwd_bm != 128) || (fwd_bn > 0 && fwd_bn != 64 && fwd_bn != 128))
         return SFB_EINVAL;
     if (recon_variant >= num_reconstruct_variants() || fwd_split_k > 64) return SFB_EINVAL;
+    c->few = false;                                              // a plan of the caller's is about the separate kernels
     FwdPlan p = c->fwd_all;
     if (fwd_bm > 0) p.bm = fwd_bm;
     if (fwd_bn > 0) p.bn = fwd_bn;

@@ -199,6 +199,8 @@ hipError_t launch_reconstruct_small(const ReconArgs& a, hipStream_t s);
 int reconstruct_small_split(int64_t J, int64_t D, int64_t N, int* k_rows);
 size_t reconstruct_small_split_workspace(int n_split, int64_t J, int64_t D);
 hipError_t launch_reconstruct_small_split(const ReconArgs& a, int n_split, int k_rows, hipStream_t s);
+// W <- prox(W + alpha * the sum of n_split planes of J x ldp floats at a.partial)
+hipError_t launch_apply_partials(const ReconArgs& a, int n_split, int64_t ldp, hipStream_t s);
 // (96..160) x 64 tiles whose eight wavefronts split the two column blocks, every stage's pairs and the stages
 // (sfb_reconstruct_ksplit.hip): for shapes where even single blocks leave the busiest SIMD well above the average
 bool reconstruct_ksplit_ok(const ReconArgs& a);
@@ -211,8 +213,9 @@ hipError_t launch_reconstruct_pair(const ReconArgs& a, hipStream_t s);
 // fp32 reconstruction on the bf16 matrix cores, every operand split exactly into three bf16 terms
 // (sfb_reconstruct_split.hip); takes ragged, misaligned and masked factors as they are
 bool reconstruct_split_ok(const ReconArgs& a);
-double reconstruct_split_plan(int64_t J, int64_t D, int64_t N, int* bm, int* bn);   // tile, estimated microseconds
-hipError_t launch_reconstruct_split(const ReconArgs& a, int bm, int bn, hipStream_t s);
+struct SplitReconPlan { int bm, bn, slices; double us; };                            // tile, slices of the pairs, estimated time
+SplitReconPlan reconstruct_split_plan(int64_t J, int64_t D, int64_t N, size_t room);   // room: bytes for planes of sums
+hipError_t launch_reconstruct_split(const ReconArgs& a, const SplitReconPlan& p, hipStream_t s);
 
 // Reconstruction from the stored entries of sparse features (sfb_sparse_update.hip): column lists made from the dense
 // rows V, then W += alpha U^T V over the entries only.  workspace: sparse_update_workspace(D, stored) bytes, 256-byte
@@ -230,6 +233,29 @@ size_t bf16_recon_workspace(int64_t J, int64_t D, int64_t N);  // bytes of devic
 int bf16_recon_grid(int64_t J, int64_t D);                     // workgroups of the W += C launch
 // ws: bf16_recon_workspace bytes, 256-byte aligned.  Two launches: transpose/pack, then W += C.
 hipError_t launch_reconstruct_bf16(const ReconArgs& a, void* ws, hipStream_t s);
+
+// Whole step (or its factors) of MLR and pair models with at most 32 classes in one pass over the features (sfb_few.hip).
+struct FewArgs {
+    const void* a;                     // [n_rows][lda] features (fp32 or bf16)
+    const void* a2;                    // second point of the pair or nullptr
+    int64_t lda;
+    float* w; int64_t ldw;             // [J][ldw] read; updated if the launch is asked to
+    const int32_t* y;
+    float* u; int64_t ldu;             // out
+    void* v; int64_t ldv;              // out: a (or a - a2)
+    float* loss;                       // [n_rows] or nullptr
+    float* planes;                     // few_workspace bytes, 256-byte aligned
+    int n_rows, J, D, B;
+    float alpha;
+    uint64_t live_mask;
+    bool use_mask, bf16, diff;
+    bool vec_a, vec_v;                 // bf16 rows of a / v are 8-byte aligned
+    int prox_kind;
+    float prox_a;
+};
+bool few_ok(int64_t N, int64_t J, int64_t D, bool diff);
+size_t few_workspace(int64_t N, int64_t J, int64_t D);
+hipError_t launch_few(const FewArgs& a, bool update, hipStream_t s);
 
 // Update of iteration t fused with the scores of iteration t+1, one pass over W (sfb_fused.hip; bf16 contexts).
 struct FusedPlan {

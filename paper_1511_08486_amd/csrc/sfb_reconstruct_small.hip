@@ -197,15 +197,25 @@ hipError_t launch_reconstruct_small(const ReconArgs& a, hipStream_t s) {
 // ---------------------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void apply_partials_kernel(float* __restrict__ W, int64_t ldw,
                                                              const float* __restrict__ P, int64_t ldp, int64_t pstride,
-                                                             int n_split, int J, int D, float alpha, int n_cb,
-                                                             int prox_kind, float prox_a) {
-    const int row = blockIdx.x / n_cb, col = (blockIdx.x % n_cb) * 256 + threadIdx.x;
-    if (row >= J || col >= D) return;
+                                                             int n_split, int J, int D, float alpha, int prox_kind,
+                                                             float prox_a) {
+    const uint32_t at = blockIdx.x * 256u + threadIdx.x;                  // host: J * D below 2^31
+    const uint32_t row = at / (uint32_t)D, col = at % (uint32_t)D;
+    if (row >= (uint32_t)J) return;
     const float* p = P + (int64_t)row * ldp + col;
-    float sum = 0.f;
-    for (int k = 0; k < n_split; ++k) sum += p[(int64_t)k * pstride];
     float* w = W + (int64_t)row * ldw + col;
-    *w = prox_entry(*w + alpha * sum, prox_kind, prox_a);
+    const float old = *w;
+    float sum = 0.f;
+#pragma unroll 8
+    for (int k = 0; k < n_split; ++k) sum += p[(int64_t)k * pstride];
+    *w = prox_entry(old + alpha * sum, prox_kind, prox_a);
+}
+
+hipError_t launch_apply_partials(const ReconArgs& a, int n_split, int64_t ldp, hipStream_t s) {
+    if ((int64_t)a.J * a.D >= (1LL << 31)) return hipErrorNotSupported;
+    hipLaunchKernelGGL(apply_partials_kernel, dim3((uint32_t)(((int64_t)a.J * a.D + 255) / 256)), dim3(256), 0, s, a.w, a.ldw,
+                       a.partial, ldp, (int64_t)a.J * ldp, n_split, a.J, a.D, a.alpha, a.prox_kind, a.prox_a);
+    return hipGetLastError();
 }
 
 // Slices of the pairs for a (J, D, N) whose plan is the single-block tile: the count that minimises, in
@@ -247,10 +257,7 @@ hipError_t launch_reconstruct_small_split(const ReconArgs& a, int n_split, int k
                (const float*)a.v, a.ldv, a.J, a.D, a.N, 1.0f, n_jb, total, 0, 0.f, tiles, k_rows, pstride);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const int n_cb = (a.D + 255) / 256;
-    hipLaunchKernelGGL(apply_partials_kernel, dim3(a.J * n_cb), dim3(256), 0, s, a.w, a.ldw, a.partial, ldp, pstride,
-                       n_split, a.J, a.D, a.alpha, n_cb, a.prox_kind, a.prox_a);
-    return hipGetLastError();
+    return launch_apply_partials(a, n_split, ldp, s);
 }
 
 }  // namespace sfb

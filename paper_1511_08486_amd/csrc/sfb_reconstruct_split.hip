@@ -30,11 +30,13 @@ __device__ __forceinline__ int rs_column(int r) {
     return NT == 2 ? (r & ~63) + 4 * (r & 15) + ((r >> 4) & 3) : r;
 }
 
-template <int MT, int NT>
+// PLANES: the workgroups of slice k contract over k_chunks chunks of pairs and store their bare sums in plane k of W
+// (a workspace then); apply_partials_kernel adds the planes up.
+template <int MT, int NT, bool PLANES>
 __global__ __launch_bounds__(kSplitThreads, 2) void reconstruct_split_kernel(
     float* __restrict__ W, int64_t ldw, const float* __restrict__ U, int64_t ldu, const float* __restrict__ V,
-    int64_t ldv, int J, int D, int N, float alpha, int n_jb, int total, int prox_kind, float prox_a, uint64_t live_mask,
-    uint32_t inv_b) {
+    int64_t ldv, int J, int D, int N, float alpha, int n_jb, int tiles, int total, int k_chunks, int prox_kind, float prox_a,
+    uint64_t live_mask, uint32_t inv_b) {
     using Tile = ReconTile<MT, NT>;
     constexpr int BM = Tile::BM, BN = Tile::BN;
     constexpr bool PAIRS = NT == 2;                                      // the permuted layout: two columns of W per lane
@@ -42,9 +44,11 @@ __global__ __launch_bounds__(kSplitThreads, 2) void reconstruct_split_kernel(
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int id = xcd_contiguous_id(blockIdx.x, total);
-    const int jb = id % n_jb, db = id / n_jb;
+    const int slice = PLANES ? id / tiles : 0, tile = PLANES ? id % tiles : id;
+    const int jb = tile % n_jb, db = tile / n_jb;
     const int j0 = jb * BM, d0 = db * BN;
     const int n_chunks = (N + kSpChunk - 1) / kSpChunk;
+    const int c_begin = PLANES ? slice * k_chunks : 0;                   // host: no slice is empty
 
     // lane block: pairs 4 kb .. 4 kb + 3, columns 4 rb .. 4 rb + 3 of the BM columns of U and BN of V side by side
     // (four consecutive lanes read 64 contiguous bytes: with lanes of different rows side by side, rows a multiple of 32
@@ -68,13 +72,13 @@ __global__ __launch_bounds__(kSplitThreads, 2) void reconstruct_split_kernel(
 
     struct Raw { f32x4 x[4]; };
     auto fetch = [&](Raw& raw, int c) {
-        const uint32_t o = (uint32_t)min(c, n_chunks - 1) * (32u * pitch) + off;
+        const uint32_t o = (uint32_t)min(c_begin + c, n_chunks - 1) * (32u * pitch) + off;
 #pragma unroll
         for (int i = 0; i < 4; ++i)                                      // pairs beyond N repeat the last one
             raw.x[i] = *reinterpret_cast<const sp_f32x4u*>(src + min(o + i * pitch, off_last));
     };
-    auto prep = [&](Raw& raw, int c) {
-        const int n0 = c * kSpChunk + 4 * kb;
+    auto prep = [&](Raw& raw, int local) {
+        const int c = c_begin + local, n0 = c * kSpChunk + 4 * kb;
         if (inv_b != 0) {                                                // some workers are dead (uniform)
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
@@ -111,7 +115,7 @@ __global__ __launch_bounds__(kSplitThreads, 2) void reconstruct_split_kernel(
 
     Tile t;
     t.init(wave, lane);
-    t.template run<Raw, State, 16, false, 2>(n_chunks, rs_lds, fetch, prep, park);
+    t.template run<Raw, State, 16, false, 2>(PLANES ? min(k_chunks, n_chunks - c_begin) : n_chunks, rs_lds, fetch, prep, park);
 
     // the entries of W this wavefront finishes: requested before the exchange, used after it (requested before the
     // contraction they stand in front of its loads in the in-order queue: 0.3 to 0.8 us slower)
@@ -125,7 +129,9 @@ __global__ __launch_bounds__(kSplitThreads, 2) void reconstruct_split_kernel(
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
             const float* row = W + (int64_t)min(w_row(i, q), J - 1) * ldw;
-            if constexpr (PAIRS) {
+            if constexpr (PLANES) {
+                w[i][0][q] = w[i][NT - 1][q] = 0.f;
+            } else if constexpr (PAIRS) {
                 const rs_f32x2u x = *reinterpret_cast<const rs_f32x2u*>(row + min(dcol, D - 2));
                 w[i][0][q] = dcol > D - 2 ? x.y : x.x;
                 w[i][1][q] = x.y;
@@ -140,19 +146,19 @@ __global__ __launch_bounds__(kSplitThreads, 2) void reconstruct_split_kernel(
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
             const int row = w_row(i, q);
-            float* out = W + (int64_t)row * ldw + dcol;
+            float* out = W + (PLANES ? (int64_t)slice * J * ldw : 0) + (int64_t)row * ldw + dcol;
             if constexpr (PAIRS) {
                 // lanes 16..31 (48..63) give their first block's sum for the second block's of lanes 0..15 (32..47)
                 asm volatile("s_nop 1\n\tv_permlane16_swap_b32 %0, %1\n\ts_nop 1" : "+v"(sum[i][0][q]), "+v"(sum[i][1][q]));
                 rs_f32x2u x;
-                x.x = prox_entry(w[i][0][q] + alpha * sum[i][0][q], prox_kind, prox_a);
-                x.y = prox_entry(w[i][1][q] + alpha * sum[i][1][q], prox_kind, prox_a);
+                x.x = PLANES ? sum[i][0][q] : prox_entry(w[i][0][q] + alpha * sum[i][0][q], prox_kind, prox_a);
+                x.y = PLANES ? sum[i][1][q] : prox_entry(w[i][1][q] + alpha * sum[i][1][q], prox_kind, prox_a);
                 if (row < J) {
                     if (dcol + 1 < D) *reinterpret_cast<rs_f32x2u*>(out) = x;
                     else if (dcol < D) *out = x.x;
                 }
             } else {
-                const float x = prox_entry(w[i][0][q] + alpha * sum[i][0][q], prox_kind, prox_a);
+                const float x = PLANES ? sum[i][0][q] : prox_entry(w[i][0][q] + alpha * sum[i][0][q], prox_kind, prox_a);
                 if (row < J && dcol < D) *out = x;
             }
         }
@@ -165,50 +171,69 @@ bool reconstruct_split_ok(const ReconArgs& a) {
            (!a.use_mask || (a.B > 1 && (int64_t)a.N * a.B < (1LL << 32)));
 }
 
-template <int MT, int NT>
-static hipError_t launch_split(const ReconArgs& a, hipStream_t s) {
+template <int MT, int NT, bool PLANES>
+static hipError_t launch_split(const ReconArgs& a, int slices, hipStream_t s) {
     using Tile = ReconTile<MT, NT>;
     constexpr size_t lds_bytes = Tile::LDS;
     static std::atomic<bool> raised{false};
     if (!raised) {
-        hipError_t e = hipFuncSetAttribute((const void*)reconstruct_split_kernel<MT, NT>,
+        hipError_t e = hipFuncSetAttribute((const void*)reconstruct_split_kernel<MT, NT, PLANES>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
         if (e != hipSuccess) return e;
         raised = true;
     }
     const int n_jb = (a.J + Tile::BM - 1) / Tile::BM, n_db = (a.D + Tile::BN - 1) / Tile::BN;
-    const int total = n_jb * n_db;
+    const int tiles = n_jb * n_db, chunks = (a.N + kSpChunk - 1) / kSpChunk;
+    const int k_chunks = (chunks + slices - 1) / slices;
     const uint32_t inv_b = a.use_mask ? (uint32_t)(((1ull << 32) + a.B - 1) / a.B) : 0;
-    SFB_LAUNCH((reconstruct_split_kernel<MT, NT>), dim3(total), dim3(kSplitThreads), lds_bytes, s, a.w, a.ldw, a.u, a.ldu,
-               (const float*)a.v, a.ldv, a.J, a.D, a.N, a.alpha, n_jb, total, a.prox_kind, a.prox_a, a.live_mask, inv_b);
+    SFB_LAUNCH((reconstruct_split_kernel<MT, NT, PLANES>), dim3(tiles * slices), dim3(kSplitThreads), lds_bytes, s,
+               PLANES ? a.partial : a.w, PLANES ? (int64_t)a.D : a.ldw, a.u, a.ldu, (const float*)a.v, a.ldv, a.J, a.D, a.N,
+               a.alpha, n_jb, tiles, tiles * slices, k_chunks, a.prox_kind, a.prox_a, a.live_mask, inv_b);
     return hipGetLastError();
 }
 
-// Tile and microseconds (the other kernels': reconstruct_fp32_us), fitted to 202 shapes
+// Tile, slices of the pairs and microseconds (the other kernels': reconstruct_fp32_us), fitted to 202 shapes
 // (J = 32 to 2000, D = 256 to 8192, N = 64 to 4096) on one MI355X.  A chunk of 32 pairs costs 1.04 / 0.63 us per round
 // of 256 tiles of 128 x 128 / 64 x 128 and 0.42 us with 64 x 64 tiles (three share a compute unit), on top of 5.6 us,
 // W's trip at 7 TB/s and 2.8 us per further round.  1000 x 4096: 21.7 -> 18.5 us at 256 pairs, 37.5 -> 28.9 at 512,
 // 256 -> 165 at 4096; 600 x 784 with 1024: 26 -> 20.5.
-double reconstruct_split_plan(int64_t J, int64_t D, int64_t N, int* bm, int* bn) {
+// Where the tiles leave compute units idle the pairs are cut into slices, at most 64 and as many as `room` bytes hold
+// planes of J x D sums for; adding those up is a second kernel.
+SplitReconPlan reconstruct_split_plan(int64_t J, int64_t D, int64_t N, size_t room) {
     static const struct { int bm, bn, resident; double chunk_us, lone_us; } tiles[3] = {
         {128, 128, 1, 1.04, 1.04}, {64, 128, 1, 0.63, 0.63}, {64, 64, 3, 0.42, 0.38}};
-    const double chunks = (double)((N + kSpChunk - 1) / kSpChunk), w_mb = 8e-6 * (double)J * (double)D;
-    double best = 1e300;
+    const int64_t chunks = (N + kSpChunk - 1) / kSpChunk;
+    const double w_mb = 8e-6 * (double)J * (double)D;
+    SplitReconPlan best{0, 0, 1, 1e300};
     for (const auto& t : tiles) {
         const int64_t n = ((J + t.bm - 1) / t.bm) * ((D + t.bn - 1) / t.bn);
-        const double rounds = (double)((n + 255) / 256);
-        const double deep = (double)((n + 256 * t.resident - 1) / (256 * t.resident));
-        const double a = t.lone_us * deep, b = t.chunk_us * rounds;
-        const double us = 5.6 + 0.14 * w_mb + chunks * (a > b ? a : b) + (t.resident == 1 ? 2.8 * (rounds - 1.0) : 0.0);
-        if (us < best) { best = us; *bm = t.bm; *bn = t.bn; }
+        for (int64_t s = 1; s <= 64 && (s == 1 || ((size_t)(s * J * D) * sizeof(float) <= room && chunks >= 2 * s && n * s <= 1536)); ++s) {
+            const int64_t per = (chunks + s - 1) / s;
+            if ((chunks + per - 1) / per != s) continue;                          // the same cut as a smaller count, or an empty slice
+            const double rounds = (double)((n * s + 255) / 256);
+            const double deep = (double)((n * s + 256 * t.resident - 1) / (256 * t.resident));
+            const double a = t.lone_us * deep, b = t.chunk_us * rounds;
+            double us = 5.6 + (double)per * (a > b ? a : b) + (t.resident == 1 ? 2.8 * (rounds - 1.0) : 0.0);
+            us += s == 1 ? 0.14 * w_mb : 3.5 + 0.1 * (double)s * w_mb;            // planes written and read, W read and written
+            if (us < best.us) best = SplitReconPlan{t.bm, t.bn, (int)s, us};
+        }
     }
     return best;
 }
 
-hipError_t launch_reconstruct_split(const ReconArgs& a, int bm, int bn, hipStream_t s) {
-    if (bm == 128 && bn == 128) return launch_split<2, 2>(a, s);
-    if (bm == 64 && bn == 128) return launch_split<1, 2>(a, s);
-    if (bm == 64 && bn == 64) return launch_split<1, 1>(a, s);
+template <int MT, int NT>
+static hipError_t launch_tile(const ReconArgs& a, int slices, hipStream_t s) {
+    if (slices == 1) return launch_split<MT, NT, false>(a, 1, s);
+    const hipError_t e = launch_split<MT, NT, true>(a, slices, s);
+    return e != hipSuccess ? e : launch_apply_partials(a, slices, a.D, s);
+}
+
+// plan.slices > 1: a.partial holds that many planes of J x D floats
+hipError_t launch_reconstruct_split(const ReconArgs& a, const SplitReconPlan& p, hipStream_t s) {
+    if (p.slices < 1 || (p.slices > 1 && a.partial == nullptr)) return hipErrorInvalidValue;
+    if (p.bm == 128 && p.bn == 128) return launch_tile<2, 2>(a, p.slices, s);
+    if (p.bm == 64 && p.bn == 128) return launch_tile<1, 2>(a, p.slices, s);
+    if (p.bm == 64 && p.bn == 64) return launch_tile<1, 1>(a, p.slices, s);
     return hipErrorInvalidValue;
 }
 

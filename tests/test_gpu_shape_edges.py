@@ -1,0 +1,77 @@
+"""The kernels that a context picks by size, each at the edges of its range, against the fp64 oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import workloads
+from gpu_util import alloc_factors, assert_close, fresh_update, run_chain, to_device
+
+pytestmark = pytest.mark.gpu
+
+TOL32 = 1e-4
+
+
+def _one_step(wl, active, plan=None, prox=None):
+    """One step with a mask of live workers (and a proximal operator), W and the update alone against the oracle."""
+    import paper_1511_08486_amd as sfb
+    dev = "cuda:0"
+    ctx = sfb.Sfb(wl.model, wl.J, wl.D, wl.P, wl.B, dtype=wl.dtype, device=dev)
+    if plan:
+        ctx.set_plan(**plan)
+    db, dy = to_device(wl, wl.batch(0), dev)
+    W = torch.from_numpy(wl.W0).to(dev)
+    U, V, loss = alloc_factors(wl, dev)
+    Uo, Vo, want, fo = oracle.step(wl.model, wl.W0, wl.batch(0), wl.P, wl.B, wl.eta, active=active)
+    if prox:
+        ctx.step_prox(W, db, dy, U, V, wl.eta, prox[0], prox[1], loss=loss, active=active)
+        want = {"l2sq": lambda w: w / (1 + wl.eta * prox[1]),
+                "l1": lambda w: np.sign(w) * np.maximum(np.abs(w) - wl.eta * prox[1], 0)}[prox[0]](want)
+    else:
+        ctx.step(W, db, dy, U, V, wl.eta, loss=loss, active=active)
+    ctx.sync()
+    tol = TOL32 if wl.dtype == "f32" else 2e-2
+    for got, exact, what in ((W, want, "W"), (U, Uo, "U"), (V.float(), Vo, "V"), (loss, fo, "loss")):
+        assert_close(got.cpu().numpy(), exact, tol, what)
+    mag = wl.eta * oracle.delta_w(np.abs(Uo), np.abs(Vo), wl.P, wl.B, active)
+    upd = fresh_update(ctx, U, V, wl.eta, W, active=active)
+    assert_close(upd.cpu().numpy(), -wl.eta * oracle.delta_w(Uo, Vo, wl.P, wl.B, active), tol, "update", terms=mag)
+    ctx.close()
+
+
+@pytest.mark.parametrize("name,J,D,P,B,active,prox", [
+    ("mlr_tiny", 1, 4, 1, 1, None, None),                       # smallest
+    ("mlr_tiny", 16, 67, 3, 5, [1, 0, 1], None),                # one workgroup, one block of classes
+    ("mlr_tiny", 17, 131, 2, 33, [0, 1], ("l1", 0.05)),         # just over 64 samples: planes; second block of classes
+    ("mlr_tiny", 32, 2048, 5, 16, None, ("l2sq", 0.5)),         # most classes, longest rows
+    ("mlr_tiny", 10, 784, 7, 613, [1, 1, 0, 1, 1, 1, 1], None),  # many samples, the last workgroup short
+    ("dml", 20, 1024, 3, 31, None, None),
+    ("dml", 31, 133, 2, 16, [1, 0], None),
+])
+def test_few_classes(name, J, D, P, B, active, prox):
+    _one_step(workloads.make(name, seed=J + D, J=J, D=D, P=P, B=B), active, prox=prox)
+
+
+def test_few_classes_bf16():
+    _one_step(workloads.make("mlr_large", seed=3, J=19, D=258, P=4, B=37), [1, 1, 0, 1])
+
+
+@pytest.mark.parametrize("J,D,P,B,active", [
+    (4, 4, 1, 33, None),                                        # smallest, a second chunk of one pair
+    (65, 63, 3, 350, [1, 0, 1]),                                # two tiles, slices of the pairs, a dead worker
+    (130, 257, 3, 7, None),                                     # every tile ragged, last columns alone in theirs
+    (354, 66, 2, 1000, [1, 1]),                                 # slices, an unaligned last pair of columns
+    (129, 1030, 1, 2050, None),
+])
+def test_split_products(J, D, P, B, active):
+    _one_step(workloads.make("mlr_tiny", seed=J + D, J=J, D=D, P=P, B=B), active, plan=dict(fwd_dma=13))
+
+
+@pytest.mark.parametrize("J,D,P,B,active,density", [
+    (33, 65, 1, 1, None, 0.5),                                  # one pair
+    (31, 4097, 4, 100, [1, 0, 1, 1], 0.01),                     # empty columns, a dead worker
+    (129, 600, 2, 512, None, 0.03),                             # the most pairs, classes over several blocks
+])
+def test_update_from_the_stored_entries(J, D, P, B, active, density):
+    wl = workloads.make("l2svm", seed=J, J=J, D=D, P=P, B=B, density=density)
+    _one_step(wl, active)
