@@ -367,11 +367,15 @@ sfb_status recon_launch(sfb_ctx* c, float* W, int64_t ldw, const float* U, int64
         if (e != hipSuccess) return hip_fail(c, e);
         return SFB_OK;
     }
-    bool on_split = false, on_lists = false;
+    bool on_split = false, on_lists = false, on_thin = false;
     const bool have_ws = c->ws != nullptr && c->ws_bytes >= workspace_need(c);
     const SplitReconPlan* sp = nullptr;
     const bool whole = reconstruct_takes_dma(r, c->recon);
-    if (c->split_recon != 0) {
+    if (c->split_recon < 0 && reconstruct_thin_ok(r)) {
+        // (the smallest ragged calls, all latency, keep leaving padded copies of their factors in the workspace)
+        on_thin = whole || !have_ws || (double)r.N * (double)c->J * (double)c->D >= 1.2e5;
+    }
+    if (c->split_recon != 0 && !on_thin) {
         // what the fp32 kernels would take, copies of ragged, misaligned or masked factors included
         const double macs = (double)r.N * (double)c->J * (double)c->D;
         double us = c->padded_factors && have_ws ? reconstruct_fp32_us(c->recon_padded, c->J, c->D, conform_rows(r.N))
@@ -387,7 +391,9 @@ sfb_status recon_launch(sfb_ctx* c, float* W, int64_t ldw, const float* U, int64
         on_lists = same_step && c->lists != nullptr && c->split_recon < 0 &&
                    sparse_update_us(r.N, c->J, c->D, c->lists_stored) < us;
     }
-    if (on_lists) {
+    if (on_thin) {
+        e = launch_reconstruct_thin(r, c->stream);
+    } else if (on_lists) {
         e = launch_sparse_update(r, c->lists_stored, c->lists, c->stream);
     } else if (on_split) {
         r.partial = sp->slices > 1 ? (float*)c->ws : nullptr;

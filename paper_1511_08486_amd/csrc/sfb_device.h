@@ -220,6 +220,10 @@ __device__ __forceinline__ void split3_pair(float x0, float x1, uint32_t& h, uin
 __device__ __forceinline__ void lds_dma16(const float* g, uint32_t lds_addr) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds_addr), "v"(g) : "memory");
 }
+// The same with one word per lane (any alignment), lane l's to lds_addr + 4 l.
+__device__ __forceinline__ void lds_dma4(const float* g, uint32_t lds_addr) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" ::"s"(lds_addr), "v"(g) : "memory");
+}
 template <int N>
 __device__ __forceinline__ void wait_vmcnt() {
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");

@@ -213,6 +213,9 @@ hipError_t launch_reconstruct_pair(const ReconArgs& a, hipStream_t s);
 // fp32 reconstruction on the bf16 matrix cores, every operand split exactly into three bf16 terms
 // (sfb_reconstruct_split.hip); takes ragged, misaligned and masked factors as they are
 bool reconstruct_split_ok(const ReconArgs& a);
+// few factor pairs, bound by W's trip through memory (sfb_reconstruct_thin.hip); any shape and alignment
+bool reconstruct_thin_ok(const ReconArgs& a);
+hipError_t launch_reconstruct_thin(const ReconArgs& a, hipStream_t s);
 struct SplitReconPlan { int bm, bn, slices; double us; };                            // tile, slices of the pairs, estimated time
 SplitReconPlan reconstruct_split_plan(int64_t J, int64_t D, int64_t N, size_t room);   // room: bytes for planes of sums
 hipError_t launch_reconstruct_split(const ReconArgs& a, const SplitReconPlan& p, hipStream_t s);

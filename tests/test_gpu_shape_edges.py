@@ -75,3 +75,15 @@ def test_split_products(J, D, P, B, active):
 def test_update_from_the_stored_entries(J, D, P, B, active, density):
     wl = workloads.make("l2svm", seed=J, J=J, D=D, P=P, B=B, density=density)
     _one_step(wl, active)
+
+
+@pytest.mark.parametrize("J,D,P,B,active,prox", [
+    (33, 130, 1, 28, None, None),                               # a block of one row, one of two columns
+    (64, 4099, 1, 1, None, ("l1", 0.05)),                       # one pair
+    (131, 65, 3, 21, [1, 0, 1], None),                          # a dead worker, the last stage short by one
+    (97, 1000, 4, 16, None, ("l2sq", 0.5)),                     # four whole stages
+    (257, 203, 1, 65, None, None),                              # more than one stage's worth over 64
+    (77, 515, 2, 64, None, None),                               # the most pairs
+])
+def test_few_pairs(J, D, P, B, active, prox):
+    _one_step(workloads.make("mlr_tiny", seed=J + D, J=J, D=D, P=P, B=B), active, prox=prox)
