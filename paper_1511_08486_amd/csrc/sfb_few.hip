@@ -176,7 +176,7 @@ __global__ __launch_bounds__(kFewThreads) void few_step_kernel(FewArgs a, int ro
         }
     }
     if constexpr (UPDATE == 0) return;
-    // (the rows behind the last sample, up to whole sixteens, count as zero)
+    // (the rows behind the last sample, up to whole sixteens, count as zero: u here, the features where they are read)
     __syncthreads();
     for (int i = rows * JP + tid; i < row_blocks * 16 * JP; i += kFewThreads) us[i] = 0.f;
     __syncthreads();
@@ -199,7 +199,8 @@ __global__ __launch_bounds__(kFewThreads) void few_step_kernel(FewArgs a, int ro
         }
         const int col = min(dc, Dp - 4);
         for (int n = 0; n < row_blocks * 4; ++n) {                        // samples 4 n + quad
-            const f32x4 v = *reinterpret_cast<const f32x4*>(feat + min(4 * n + quad, rows - 1) * pitch + col);
+            f32x4 v = *reinterpret_cast<const f32x4*>(feat + min(4 * n + quad, rows - 1) * pitch + col);
+            if (4 * n + 3 >= rows && 4 * n + quad >= rows) v = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int j = 0; j < NJ; ++j) {
                 const float u = us[(4 * n + quad) * JP + 16 * j + l16];

@@ -112,6 +112,8 @@ __global__ __launch_bounds__(kSplitThreads, 2) void scores_split_kernel(
     t.exchange(wave, lane, ss_lds, sum);
     float* zout = Z + (int64_t)ks * zstride;
     const int wm = (wave & 3) >> 1, wn = wave & 1;
+    auto row_of = [&](int i, int q) { return m0 + (wm * MT + i) * 32 + Tile::entry_row(wave >> 2, q, lane); };
+    uint32_t again = 0;                                                  // entries to sum without the split (see split_finite)
 #pragma unroll
     for (int j = 0; j < NT; ++j) {
         const int col = n0 + (wn * NT + j) * 32 + (lane & 31);
@@ -119,9 +121,19 @@ __global__ __launch_bounds__(kSplitThreads, 2) void scores_split_kernel(
         for (int i = 0; i < MT; ++i)
 #pragma unroll
             for (int q = 0; q < 8; ++q) {
-                const int row = m0 + (wm * MT + i) * 32 + Tile::entry_row(wave >> 2, q, lane);
-                if (row < M && col < N) zout[(int64_t)row * ldz + col] = sum[i][j][q];
+                const int row = row_of(i, q);
+                if (row < M && col < N) {
+                    if (split_finite(sum[i][j][q])) zout[(int64_t)row * ldz + col] = sum[i][j][q];
+                    else again |= 1u << ((j * MT + i) * 8 + q);
+                }
             }
+    }
+    for (; again != 0; again &= again - 1) {
+        const int e = __builtin_ctz(again), row = row_of((e >> 3) % MT, e & 7), col = n0 + (wn * NT + (e >> 3) / MT) * 32 + (lane & 31);
+        const float *a = A + (int64_t)row * lda, *a2 = DIFF ? A2 + (int64_t)row * lda : nullptr, *w = W + (int64_t)col * ldw;
+        float z = 0.f;
+        for (int k = k_begin; k < k_end && z == z; ++k) z = fmaf(DIFF ? a[k] - a2[k] : a[k], w[k], z);
+        zout[(int64_t)row * ldz + col] = z;
     }
 }
 

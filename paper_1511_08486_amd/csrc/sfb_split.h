@@ -37,6 +37,11 @@ __device__ __forceinline__ f32x16 split_mfma(sp_u32x4 a, sp_u32x4 b, f32x16 c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(sp_bf16x8, a), __builtin_bit_cast(sp_bf16x8, b), c, 0, 0, 0);
 }
 
+// An infinity (or a finite value beyond bf16's largest, 3.39e38: it rounds to one) leaves NaN in its second term, and six
+// term products may overflow where their sum does not.  All of that ends in a sum that is not finite, so such a sum, and
+// no other, is formed again from the operands as they are: what is then infinite or NaN is so in fp32, too.
+__device__ __forceinline__ bool split_finite(float x) { return __builtin_isfinite(x); }
+
 template <int FIRST, int LAST, class F>
 __device__ __forceinline__ void split_for(F f) {
     if constexpr (FIRST < LAST) {

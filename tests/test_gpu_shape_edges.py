@@ -87,3 +87,46 @@ def test_update_from_the_stored_entries(J, D, P, B, active, density):
 ])
 def test_few_pairs(J, D, P, B, active, prox):
     _one_step(workloads.make("mlr_tiny", seed=J + D, J=J, D=D, P=P, B=B), active, prox=prox)
+
+
+# Values that no three bf16 terms hold: infinities, and finite ones that round to an infinity in bf16.  What is infinite, or
+# as finite as in fp32, stays so; a whole row or column that depends on them is compared with numpy in fp64.
+@pytest.mark.parametrize("J,D,N", [(66, 130, 70), (130, 1030, 200), (200, 515, 1030)])
+@pytest.mark.parametrize("big", [float("-inf"), -3.4028e38])
+def test_split_products_of_unbounded_values(J, D, N, big):
+    import paper_1511_08486_amd as sfb
+    dev = "cuda:0"
+    wl = workloads.make("mlr_tiny", seed=J, J=J, D=D, P=1, B=N)
+    ctx = sfb.Sfb("mlr", J, D, 1, N, device=dev)
+    ctx.set_plan(fwd_dma=13)
+    A = np.abs(np.random.default_rng(J).standard_normal((N, D))).astype(np.float32) / np.float32(np.sqrt(D)) + np.float32(1e-3)
+    A[:, 5] = 1.0
+    y = torch.zeros(N, dtype=torch.int32, device=dev)
+    W0 = wl.W0.copy()
+    W0[3, 5] = W0[J - 1, 5] = big                               # classes that are switched off by a feature that is always one
+    W, a = torch.from_numpy(W0).to(dev), sfb.SfbBatch(a=torch.from_numpy(A).to(dev))
+    U, V, loss = torch.empty((N, J), device=dev), torch.empty((N, D), device=dev), torch.empty(N, device=dev)
+    ctx.compute_factors(W, a, y, U, V, loss=loss)
+    ctx.sync()
+    z = A.astype(np.float64) @ W0.astype(np.float64).T
+    p = np.exp(z - z.max(1, keepdims=True))
+    want_loss = np.log(p.sum(1)) + z.max(1) - z[:, 0]
+    p /= p.sum(1, keepdims=True)
+    p[:, 0] -= 1.0
+    assert_close(U.cpu().numpy(), p, TOL32, "U")
+    assert_close(loss.cpu().numpy(), want_loss, TOL32, "loss")
+
+    V0 = A.copy()
+    V0[N - 1, D - 1] = V0[2, 7] = big                            # one entry of each of two columns
+    U0 = (np.random.default_rng(N).uniform(0.25, 0.5, (N, J)) / N).astype(np.float32)
+    W1 = torch.from_numpy(wl.W0).to(dev)
+    ctx.reconstruct_apply(W1, torch.from_numpy(U0).to(dev), torch.from_numpy(V0).to(dev), 0.5, scale=1.0)
+    ctx.sync()
+    want, got = wl.W0 - 0.5 * (U0.astype(np.float64).T @ V0.astype(np.float64)), W1.cpu().numpy().astype(np.float64)
+    cols = np.isin(np.arange(D), [7, D - 1])
+    assert_close(got[:, ~cols], want[:, ~cols], TOL32, "W")
+    if np.isinf(big):
+        assert np.array_equal(got[:, cols], want[:, cols])
+    else:
+        assert_close(got[:, cols], want[:, cols], TOL32, "columns of large values")
+    ctx.close()
