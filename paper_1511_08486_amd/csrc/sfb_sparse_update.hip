@@ -15,7 +15,8 @@
 // the rows) and two multiply-adds; row and value are broadcast inside the sixteen lanes by the instruction's own
 // lane operand (row_newbcast), so an entry costs three vector instructions and one LDS read for four columns at once.
 // The sums of half a block turn through LDS into rows of W, which were requested before the walk.  The sum over a
-// column runs over ascending rows: the same bits every time.
+// column runs over ascending rows: the same bits every time.  A class with a factor that is not finite takes every pair
+// of its columns from V instead, as the dense contraction does: infinity times a zero that is not stored is NaN.
 #include <type_traits>
 
 #include "sfb_device.h"
@@ -104,14 +105,18 @@ __device__ __forceinline__ void lane_loop(F f) {
 __global__ __launch_bounds__(kSuThreads) void sparse_update_kernel(
     float* __restrict__ W, int64_t ldw, const float* __restrict__ U, int64_t ldu, const int32_t* __restrict__ starts,
     const uint2* __restrict__ entries, int N, int J, int D, int B, float alpha, uint64_t live_mask, int use_mask, int n_jb,
-    int n_blocks, int splits, int prox_kind, float prox_a, bool vec_u) {
+    int n_blocks, int splits, int prox_kind, float prox_a, bool vec_u, const float* __restrict__ V, int64_t ldv) {
     extern __shared__ __attribute__((aligned(16))) float su_lds[];          // U [N][32], then a 32 x 32 tile per wavefront
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int id = xcd_contiguous_id(blockIdx.x, n_jb * splits);
     const int jb = id % n_jb, sp = id / n_jb;
     const int j0 = jb * kSuClasses;
 
-    // U: eight lanes to a row
+    // U: eight lanes to a row; a bit per class for factors that are not finite (kept where the first tile will be: 1024 pairs
+    // and the tiles fill the LDS)
+    uint32_t* const bad_at = reinterpret_cast<uint32_t*>(su_lds + (int64_t)N * kSuClasses);
+    uint32_t bad = 0;
+    if (tid == 0) *bad_at = 0;
     for (int r = tid >> 3; r < N; r += kSuThreads / 8) {
         const int j = j0 + 4 * (tid & 7);
         bool live = true;
@@ -119,7 +124,14 @@ __global__ __launch_bounds__(kSuThreads) void sparse_update_kernel(
         f32x4 u = {0.f, 0.f, 0.f, 0.f};
         if (live && j < J) u = load4(U + (int64_t)r * ldu, j, J, vec_u);
         *reinterpret_cast<f32x4*>(&su_lds[r * kSuClasses + 4 * (tid & 7)]) = u;
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (!(fabsf(u[k]) < INFINITY)) bad |= 1u << (4 * (tid & 7) + k);
     }
+    __syncthreads();
+    if (bad != 0) atomicOr(bad_at, bad);
+    __syncthreads();
+    bad = __builtin_amdgcn_readfirstlane(*bad_at);
     __syncthreads();
 
     float* const tile = su_lds + (int64_t)N * kSuClasses + wave * kSuTile;
@@ -195,6 +207,15 @@ __global__ __launch_bounds__(kSuThreads) void sparse_update_kernel(
             f32x4 s;
 #pragma unroll
             for (int k = 0; k < 4; ++k) s[k] = tile[(wc + k) * 32 + ((wr + 16 * t) ^ (2 * wc))];
+            if (bad != 0 && ((bad >> (wr + 16 * t)) & 1u)) {
+                s = f32x4{0.f, 0.f, 0.f, 0.f};
+                for (int r = 0; r < N; ++r) {
+                    if (use_mask && !((live_mask >> (r / B)) & 1ull)) continue;
+                    const float u = su_lds[r * kSuClasses + wr + 16 * t];
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) s[k] += u * V[(int64_t)r * ldv + min(d0 + wc + k, D - 1)];
+                }
+            }
             if (row < J) store4(W + (int64_t)row * ldw, d0 + wc, D, vec_w, prox_entry4(w[t] + alpha * s, prox_kind, prox_a));
         }
     }
@@ -234,16 +255,16 @@ hipError_t launch_sparse_update(const ReconArgs& a, int64_t stored, void* worksp
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const size_t lds_bytes = ((size_t)a.N * kSuClasses + kSuWaves * kSuTile) * sizeof(float);
-    static std::atomic<size_t> raised{0};
-    if (lds_bytes > 64 * 1024 && lds_bytes > raised) {
-        e = hipFuncSetAttribute((const void*)sparse_update_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
+    static std::atomic<bool> raised{false};
+    if (lds_bytes > 64 * 1024 && !raised) {
+        e = hipFuncSetAttribute((const void*)sparse_update_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
         if (e != hipSuccess) return e;
-        raised = lds_bytes;
+        raised = true;
     }
     const int splits = sparse_update_splits(a.J, a.D);
     SFB_LAUNCH(sparse_update_kernel, dim3(n_jb * splits), dim3(kSuThreads), lds_bytes, s, a.w, a.ldw, a.u, a.ldu, starts, entries,
                a.N, a.J, a.D, a.B, a.alpha, a.live_mask, a.use_mask ? 1 : 0, n_jb, n_blocks, splits, a.prox_kind, a.prox_a,
-               ((uintptr_t)a.u % 16) == 0 && (a.ldu % 4) == 0);
+               ((uintptr_t)a.u % 16) == 0 && (a.ldu % 4) == 0, (const float*)a.v, a.ldv);
     return hipGetLastError();
 }
 

@@ -77,6 +77,30 @@ def test_update_from_the_stored_entries(J, D, P, B, active, density):
     _one_step(wl, active)
 
 
+def test_update_from_the_stored_entries_with_infinite_factors():
+    """Infinite factors make NaN against every zero of the features, whether or not it is stored, as in the dense update."""
+    import paper_1511_08486_amd as sfb
+    wl = workloads.make("l2svm", seed=7, J=600, D=4096, P=2, B=512, density=0.01)
+    dev = "cuda:0"
+    ctx = sfb.Sfb(wl.model, wl.J, wl.D, wl.P, wl.B, device=dev)
+    db, dy = to_device(wl, wl.batch(0), dev)
+    W0 = wl.W0.copy()
+    W0[40, int(torch.bincount(db.col.cpu()).argmax())] = np.inf  # infinite scores of the samples that have this feature
+    W = torch.from_numpy(W0).to(dev)
+    U, V, loss = alloc_factors(wl, dev)
+    ctx.step(W, db, dy, U, V, wl.eta, loss=loss)
+    ctx.sync()
+    U64, V64 = U.cpu().numpy().astype(np.float64), V.cpu().numpy().astype(np.float64)
+    assert not np.isfinite(U64[:, 40]).all() and np.isfinite(np.delete(U64, 40, 1)).all()
+    with np.errstate(invalid="ignore"):
+        want = W0 - wl.eta * ctx.default_scale() * (U64.T @ V64)
+    got = W.cpu().numpy()
+    assert np.isnan(want[40]).all() and np.isnan(got[40]).all()
+    rest = np.arange(wl.J) != 40
+    assert_close(got[rest], want[rest], TOL32, "W")
+    ctx.close()
+
+
 @pytest.mark.parametrize("J,D,P,B,active,prox", [
     (33, 130, 1, 28, None, None),                               # a block of one row, one of two columns
     (64, 4099, 1, 1, None, ("l1", 0.05)),                       # one pair
