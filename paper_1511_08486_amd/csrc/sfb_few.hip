@@ -301,12 +301,12 @@ size_t few_workspace(int64_t N, int64_t J, int64_t D) {
 
 template <typename TIn, bool DIFF, int NJ, int UPDATE>
 static hipError_t launch_few_t(const FewArgs& a, int rows, int k_slices, size_t lds, hipStream_t s) {
-    static std::atomic<size_t> raised{64 * 1024};
-    if (lds > raised) {
+    static std::atomic<bool> raised{false};
+    if (lds > 64 * 1024 && !raised) {
         hipError_t e = hipFuncSetAttribute((const void*)few_step_kernel<TIn, DIFF, NJ, UPDATE>,
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
         if (e != hipSuccess) return e;
-        raised = lds;
+        raised = true;
     }
     SFB_LAUNCH((few_step_kernel<TIn, DIFF, NJ, UPDATE>), dim3((a.n_rows + rows - 1) / rows), dim3(kFewThreads), lds, s, a, rows,
                few_dp(a.D), k_slices, (a.D + 63) / 64);
