@@ -333,9 +333,9 @@ SFB_API sfb_status sfb_plan_info(const sfb_ctx *ctx, int32_t *fwd_split_k, int32
  * bit 5 = always from the CSR entries where that kernel can take them (four rows of W in LDS: D <= 10240)
  * (neither: whichever a fitted cost comparison on N, J, D and nnz expects to be faster); bit 2 = fp32 scores on the bf16 matrix cores, every fp32 operand split
  * exactly into three bf16 terms and every product taken as its six leading term products (error
- * at the level of one fp32 rounding; full batch and 16-byte aligned rows only, else ignored);
- * bit 3 = the same for the fp32 reconstruction (J, D multiples of 4, N a multiple of 32, no dead
- * workers, else ignored); bit 4 = sfb_step_pipelined always runs its two separate passes; < 0 = keep.  A value <= 0 (variant < 0) keeps the current choice.
+ * at the level of one fp32 rounding; D >= 4 and leading dimensions within 32-bit offsets, else ignored),
+ * the way a new fp32 context forms them unless the product is small; bit 3 = the same for the fp32 reconstruction, which a new
+ * context takes where a fitted cost comparison expects it to be the fastest kernel; bit 4 = sfb_step_pipelined always runs its two separate passes; < 0 = keep.  A value <= 0 (variant < 0) keeps the current choice.
  * The workspace requirement may grow: query sfb_workspace_bytes again.  SFB_EINVAL for a value outside the table. */
 SFB_API sfb_status sfb_set_plan(sfb_ctx *ctx, int32_t fwd_bm, int32_t fwd_bn, int32_t fwd_split_k,
                                 int32_t recon_variant, int32_t fwd_dma);

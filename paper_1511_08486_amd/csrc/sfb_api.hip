@@ -446,7 +446,12 @@ sfb_status sfb_create(sfb_ctx** out, sfb_model m, int64_t J, int64_t D, int32_t 
     c->fwd_all = plan_forward((int64_t)P * B, J, D);
     c->fwd_worker = plan_forward(B, J, D);
     c->fwd_bf16 = plan_forward_bf16((int64_t)P * B, J, D);
-    c->split_scores = input_dtype == SFB_F32;
+    // Small products are all latency: splitting operands into LDS takes longer to start than the fp32 instruction's copies.
+    // 128 x 1152: 9.0 us (fp32) against 9.8 with 72 samples, 11.8 against 12.5 with 976; 320 x 2304, 384 samples: 14.0
+    // against 14.7; even at 320 x 3072, 384, and 64 x 3072, 1800; 320 x 2304, 976: 22.4 against 21.9; longer rows (128 x
+    // 5504, 72: 13.9 against 13.1) and rows that those copies do not take (D not in chunks of 32) are faster split.
+    c->split_scores = input_dtype == SFB_F32 &&
+                      !(m != SFB_DML && (D % 32) == 0 && D <= 3072 && (double)P * B * (double)J * (double)D < 3e8);
     c->split_recon = -1;
     c->recon = plan_reconstruct(J, D, (int64_t)P * B);
     {
