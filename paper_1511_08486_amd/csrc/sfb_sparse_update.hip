@@ -3,8 +3,8 @@
 // The dense contraction multiplies every pair by every column; at a few stored entries per hundred nearly all of that is
 // multiplication by zero.  Two kernels instead:
 //
-// column_lists_kernel turns the dense rows V (already written, repeated entries already added up) into lists of the
-// non-zero entries per column, rows ascending, grouped by blocks of 32 columns.  One workgroup per block; lanes run
+// column_lists_kernel turns the dense rows V of the live workers (already written, repeated entries already added up) into
+// lists of the non-zero entries per column, rows ascending, grouped by blocks of 32 columns.  One workgroup per block; lanes run
 // along a row's 32 columns (128 contiguous bytes), every thread owns one column of 32 rows in registers: count, prefix
 // sum over (column, part of the rows), write.  A block takes its place in the
 // entry array with one atomic add: where a block lies depends on timing, what it holds does not.
@@ -30,20 +30,38 @@ constexpr int kSuTile = 16 * 32;                                          // sum
 
 __global__ __launch_bounds__(kClThreads) void column_lists_kernel(const float* __restrict__ V, int64_t ldv, int N, int D,
                                                                   uint32_t* __restrict__ counter, int32_t* __restrict__ starts,
-                                                                  uint2* __restrict__ entries, uint32_t room) {
+                                                                  uint2* __restrict__ entries, uint32_t room, int B, uint64_t live_mask,
+                                                                  int use_mask) {
     __shared__ uint32_t cnt[32 * 33];
     __shared__ uint32_t wsum[16], base_s;
     const int tid = threadIdx.x, c = tid & 31, part = tid >> 5;            // part: a contiguous range of rows
     const int d = blockIdx.x * 32 + c;
     const int r0 = part * kClRows;
-    const float* col = V + min(d, D - 1);
+    const float* at_row = V + (int64_t)min(r0, N - 1) * ldv + min(d, D - 1);
     float v[kClRows];                                                      // all loads in flight at once
 #pragma unroll
-    for (int r = 0; r < kClRows; ++r) v[r] = col[(int64_t)min(r0 + r, N - 1) * ldv];
+    for (int r = 0; r < kClRows; ++r) {
+        v[r] = *at_row;
+        if (r0 + r + 1 < N) at_row += ldv;
+    }
+    // bit r: row r0 + r counts (a dead worker's rows count as zero whatever they hold: an infinity of theirs would leave NaN
+    // against the zeros in place of their factors)
+    uint32_t rows = d >= D || r0 >= N ? 0u : N - r0 >= kClRows ? ~0u : (1u << (N - r0)) - 1u;
+    if (use_mask) {
+        int p = r0 / B, left = B - (r0 - p * B);                           // worker of the row, its rows from here on
+#pragma unroll 1
+        for (int r = 0; r < kClRows && r0 + r < N; ++r) {
+            if (!((live_mask >> p) & 1ull)) rows &= ~(1u << r);
+            if (--left == 0) {
+                left = B;
+                ++p;
+            }
+        }
+    }
     uint32_t n = 0;
 #pragma unroll
     for (int r = 0; r < kClRows; ++r) {
-        if (r0 + r >= N || d >= D) v[r] = 0.f;
+        v[r] = ((rows >> r) & 1u) ? v[r] : 0.f;
         n += v[r] != 0.f;
     }
     // exclusive prefix sum in the order (column, part): thread tid handles position tid of that order
@@ -251,7 +269,7 @@ hipError_t launch_sparse_update(const ReconArgs& a, int64_t stored, void* worksp
     int32_t* starts = (int32_t*)((char*)workspace + 256);
     uint2* entries = (uint2*)((char*)workspace + lists_head(a.D));
     hipLaunchKernelGGL(column_lists_kernel, dim3(n_blocks), dim3(kClThreads), 0, s, (const float*)a.v, a.ldv, a.N, a.D,
-                       counter, starts, entries, (uint32_t)stored);
+                       counter, starts, entries, (uint32_t)stored, a.B, a.live_mask, a.use_mask ? 1 : 0);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const size_t lds_bytes = ((size_t)a.N * kSuClasses + kSuWaves * kSuTile) * sizeof(float);

@@ -101,6 +101,31 @@ def test_update_from_the_stored_entries_with_infinite_factors():
     ctx.close()
 
 
+@pytest.mark.parametrize("J,D", [(1000, 4100), (600, 4096)])
+def test_update_from_the_stored_entries_leaves_out_whatever_a_dead_worker_holds(J, D):
+    """NaN and infinities among a dead worker's features: W is what it is with finite values in their place."""
+    import paper_1511_08486_amd as sfb
+    wl = workloads.make("l2svm", seed=11, J=J, D=D, P=8, B=64, density=0.02)
+    active = [1, 1, 0, 1, 1, 1, 1, 1]
+    b, got = wl.batch(0), []
+    for bad in (False, True):
+        val = np.array(b["val"])
+        if bad:
+            mine = slice(int(b["rowptr"][2 * wl.B]), int(b["rowptr"][3 * wl.B]))
+            val[mine] = np.resize(np.float32([np.nan, np.inf, -np.inf]), val[mine].shape)
+        ctx = sfb.Sfb(wl.model, J, D, wl.P, wl.B, device="cuda:0")
+        db, dy = to_device(wl, dict(b, val=val), "cuda:0")
+        W = torch.from_numpy(wl.W0).to("cuda:0")
+        U, V, loss = alloc_factors(wl, "cuda:0")
+        ctx.step(W, db, dy, U, V, wl.eta, loss=loss, active=active)
+        ctx.sync()
+        got.append(W)
+        ctx.close()
+    _, _, want, _ = oracle.step(wl.model, wl.W0, b, wl.P, wl.B, wl.eta, active=active)
+    assert_close(got[0].cpu().numpy(), want, TOL32, "W")
+    assert torch.equal(got[0], got[1])
+
+
 @pytest.mark.parametrize("J,D,P,B,active,prox", [
     (33, 130, 1, 28, None, None),                               # a block of one row, one of two columns
     (64, 4099, 1, 1, None, ("l1", 0.05)),                       # one pair
