@@ -132,7 +132,7 @@ size_t workspace_need(const sfb_ctx* c) {
     if (c->model == SFB_L2SVM) {
         const size_t n = (size_t)c->P * c->B;
         const size_t at = (n * round_up4(c->J) * sizeof(float) + 255) / 256 * 256 + sparse_update_workspace(c->D, (int64_t)(n * c->D / 12));
-        if (at > need && sparse_update_ok((int64_t)n) && at <= SFB_NOALLOC_SCRATCH_BYTES) need = at;
+        if (at > need && sparse_update_ok((int64_t)n, c->D, (int64_t)(n * c->D / 12)) && at <= SFB_NOALLOC_SCRATCH_BYTES) need = at;
     }
     // the column projection of the proximal step reuses the front of the buffer between steps
     const size_t prox = prox_workspace(c->J, c->D);
@@ -282,7 +282,7 @@ sfb_status factors_rows(sfb_ctx* c, const FwdPlan& plan, const float* W, int64_t
         sparse_scores = c->sparse_forward && csr_scores_ok((int)c->D) && b->nnz <= (1LL << 30) - 1024 &&
                         (c->sparse_always || csr_scores_wins(n_rows, c->J, c->D, b->nnz));
         // the update of the same step may want lists of the entries per column, behind the planes of scores
-        if (n_rows == c->P * c->B && sparse_update_ok(n_rows)) {
+        if (n_rows == c->P * c->B && sparse_update_ok(n_rows, c->D, b->nnz)) {
             const int planes = sparse_scores ? 1 : c->split_scores && c->D >= 4 ? c->fwd_split.split_k : plan.split_k;
             const size_t at = ((size_t)planes * n_rows * ldz * sizeof(float) + 255) / 256 * 256;
             if (at + sparse_update_workspace(c->D, b->nnz) <= c->ws_bytes) {

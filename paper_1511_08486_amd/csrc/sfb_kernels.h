@@ -222,8 +222,8 @@ hipError_t launch_reconstruct_split(const ReconArgs& a, const SplitReconPlan& p,
 
 // Reconstruction from the stored entries of sparse features (sfb_sparse_update.hip): column lists made from the dense
 // rows V, then W += alpha U^T V over the entries only.  workspace: sparse_update_workspace(D, stored) bytes, 256-byte
-// aligned, its first word zero; stored: at least the number of non-zero entries of V.  One launch_csr_densify before it.
-bool sparse_update_ok(int64_t N);
+// aligned, its first word zero; stored: the entries there is room for (columns that find none are taken from V).  One launch_csr_densify before it.
+bool sparse_update_ok(int64_t N, int64_t D, int64_t stored);
 size_t sparse_update_workspace(int64_t D, int64_t stored);
 double sparse_update_us(int64_t N, int64_t J, int64_t D, int64_t stored);   // estimate
 hipError_t launch_sparse_update(const ReconArgs& a, int64_t stored, void* workspace, hipStream_t s);

@@ -7,7 +7,9 @@
 // lists of the non-zero entries per column, rows ascending, grouped by blocks of 32 columns.  One workgroup per block; lanes run
 // along a row's 32 columns (128 contiguous bytes), every thread owns one column of 32 rows in registers: count, prefix
 // sum over (column, part of the rows), write.  A block takes its place in the
-// entry array with one atomic add: where a block lies depends on timing, what it holds does not.
+// entry array with one atomic add: where a block lies depends on timing, what it holds does not.  The array holds the stored
+// entries of the batch; row pointers that overlap make more non-zeros of them, and a block that finds no room then leaves no
+// list but a mark (kNoList): its columns take every pair from V.
 //
 // sparse_update_kernel: a workgroup parks U[all pairs][32 classes] in LDS (128 KB at 1024 pairs) and walks its share
 // of the column blocks, a wavefront per half block.  Sixteen lanes take a column, two classes each: every entry is one
@@ -27,9 +29,10 @@ namespace sfb {
 constexpr int kClThreads = 1024, kClRows = 32;                           // 32 parts of 32 rows: at most 1024 pairs
 constexpr int kSuThreads = 1024, kSuWaves = kSuThreads / 64, kSuClasses = 32;
 constexpr int kSuTile = 16 * 32;                                          // sums of half a block, floats
+constexpr uint32_t kNoList = 0x80000000u;                                // in place of a block's bounds: empty lists, take V
 
 __global__ __launch_bounds__(kClThreads) void column_lists_kernel(const float* __restrict__ V, int64_t ldv, int N, int D,
-                                                                  uint32_t* __restrict__ counter, int32_t* __restrict__ starts,
+                                                                  uint32_t* __restrict__ counter, uint32_t* __restrict__ starts,
                                                                   uint2* __restrict__ entries, uint32_t room, int B, uint64_t live_mask,
                                                                   int use_mask) {
     __shared__ uint32_t cnt[32 * 33];
@@ -85,19 +88,16 @@ __global__ __launch_bounds__(kClThreads) void column_lists_kernel(const float* _
     if (tid == 0) base_s = atomicAdd(counter, total);
     cnt[oc * 33 + op] = before + inc - x;
     __syncthreads();
-    const uint32_t base = base_s;
-    int32_t* st = starts + (int64_t)blockIdx.x * 33;
-    if (tid < 32) st[tid] = (int32_t)(base + cnt[tid * 33]);
-    if (tid == 32) st[32] = (int32_t)(base + total);
+    const uint32_t base = base_s;                                          // (host: N * D below 2^32, the counter cannot wrap)
+    const bool fits = (uint64_t)base + total <= room;
+    uint32_t* st = starts + (int64_t)blockIdx.x * 33;
+    if (tid < 32) st[tid] = fits ? base + cnt[tid * 33] : kNoList;
+    if (tid == 32) st[32] = fits ? base + total : kNoList;
     uint32_t at = base + cnt[c * 33 + part];
-    if (n != 0) {
+    if (n != 0 && fits) {
 #pragma unroll
-        for (int r = 0; r < kClRows; ++r) {
-            if (v[r] != 0.f) {
-                if (at < room) entries[at] = make_uint2((uint32_t)(r0 + r), __float_as_uint(v[r]));   // (host: room >= stored entries)
-                ++at;
-            }
-        }
+        for (int r = 0; r < kClRows; ++r)
+            if (v[r] != 0.f) entries[at++] = make_uint2((uint32_t)(r0 + r), __float_as_uint(v[r]));
     }
 }
 
@@ -121,7 +121,7 @@ __device__ __forceinline__ void lane_loop(F f) {
 }
 
 __global__ __launch_bounds__(kSuThreads) void sparse_update_kernel(
-    float* __restrict__ W, int64_t ldw, const float* __restrict__ U, int64_t ldu, const int32_t* __restrict__ starts,
+    float* __restrict__ W, int64_t ldw, const float* __restrict__ U, int64_t ldu, const uint32_t* __restrict__ starts,
     const uint2* __restrict__ entries, int N, int J, int D, int B, float alpha, uint64_t live_mask, int use_mask, int n_jb,
     int n_blocks, int splits, int prox_kind, float prox_a, bool vec_u, const float* __restrict__ V, int64_t ldv) {
     extern __shared__ __attribute__((aligned(16))) float su_lds[];          // U [N][32], then a 32 x 32 tile per wavefront
@@ -170,13 +170,16 @@ __global__ __launch_bounds__(kSuThreads) void sparse_update_kernel(
             const int row = j0 + wr + 16 * t;
             w[t] = row < J ? load4(W + (int64_t)row * ldw, d0 + wc, D, vec_w) : f32x4{0.f, 0.f, 0.f, 0.f};
         }
-        const int32_t* st = starts + (int64_t)(h >> 1) * 33 + 16 * (h & 1);
+        const uint32_t* st = starts + (int64_t)(h >> 1) * 33 + 16 * (h & 1);
         // columns 4 q + g: four at a time, all four rounds' bounds first
         int beg[4], len[4];
+        uint32_t no_list = 0;                                               // the same in every lane: the whole block's
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            beg[q] = st[4 * q + g];
-            len[q] = st[4 * q + g + 1] - beg[q];
+            const uint32_t b = st[4 * q + g];
+            no_list = b & kNoList;
+            beg[q] = (int)(b & ~kNoList);
+            len[q] = (int)(st[4 * q + g + 1] - b);
         }
         uint2 e = entries[beg[0] + min(l16, max(len[0] - 1, 0))];
 #pragma unroll
@@ -225,7 +228,7 @@ __global__ __launch_bounds__(kSuThreads) void sparse_update_kernel(
             f32x4 s;
 #pragma unroll
             for (int k = 0; k < 4; ++k) s[k] = tile[(wc + k) * 32 + ((wr + 16 * t) ^ (2 * wc))];
-            if (bad != 0 && ((bad >> (wr + 16 * t)) & 1u)) {
+            if (no_list != 0 || (bad != 0 && ((bad >> (wr + 16 * t)) & 1u))) {
                 s = f32x4{0.f, 0.f, 0.f, 0.f};
                 for (int r = 0; r < N; ++r) {
                     if (use_mask && !((live_mask >> (r / B)) & 1ull)) continue;
@@ -244,8 +247,12 @@ static size_t lists_head(int64_t D) { return 256 + ((size_t)((D + 31) / 32) * 33
 // (the walk may look at one entry behind the last list)
 size_t sparse_update_workspace(int64_t D, int64_t stored) { return lists_head(D) + (size_t)(stored + 1) * sizeof(uint2); }
 
-// U of 32 classes and the wavefronts' tiles have to fit in LDS
-bool sparse_update_ok(int64_t N) { return ((size_t)N * kSuClasses + kSuWaves * kSuTile) * sizeof(float) <= 160 * 1024; }
+// U of 32 classes and the wavefronts' tiles have to fit in LDS; entry numbers are below kNoList, and V can hold no more
+// non-zeros than the lists' 32-bit counter counts
+bool sparse_update_ok(int64_t N, int64_t D, int64_t stored) {
+    return ((size_t)N * kSuClasses + kSuWaves * kSuTile) * sizeof(float) <= 160 * 1024 && N * D < (1LL << 32) &&
+           stored < (int64_t)kNoList - 1;
+}
 
 static int sparse_update_splits(int64_t J, int64_t D) {
     const int64_t n_blocks = (D + 31) / 32, n_jb = (J + kSuClasses - 1) / kSuClasses;
@@ -266,7 +273,7 @@ double sparse_update_us(int64_t N, int64_t J, int64_t D, int64_t stored) {
 hipError_t launch_sparse_update(const ReconArgs& a, int64_t stored, void* workspace, hipStream_t s) {
     const int n_blocks = (a.D + 31) / 32, n_jb = (a.J + kSuClasses - 1) / kSuClasses;
     uint32_t* counter = (uint32_t*)workspace;                              // zero: csr_densify_kernel of this step cleared it
-    int32_t* starts = (int32_t*)((char*)workspace + 256);
+    uint32_t* starts = (uint32_t*)((char*)workspace + 256);
     uint2* entries = (uint2*)((char*)workspace + lists_head(a.D));
     hipLaunchKernelGGL(column_lists_kernel, dim3(n_blocks), dim3(kClThreads), 0, s, (const float*)a.v, a.ldv, a.N, a.D,
                        counter, starts, entries, (uint32_t)stored, a.B, a.live_mask, a.use_mask ? 1 : 0);

@@ -77,6 +77,37 @@ def test_update_from_the_stored_entries(J, D, P, B, active, density):
     _one_step(wl, active)
 
 
+@pytest.mark.parametrize("J,D,long,repeats", [(600, 4096, 300, 4), (1001, 2003, 64, 2)])
+def test_update_from_the_stored_entries_with_row_pointers_that_overlap(J, D, long, repeats):
+    """Row pointers that step back share their entries: V then holds more non-zeros than are stored, and the lists have no
+    room for some columns.  Nothing is read beyond them, and W is what the rows make it."""
+    import paper_1511_08486_amd as sfb
+    dev, P, B, eta = "cuda:0", 2, 512, 0.05
+    N, rng = P * B, np.random.default_rng(J)
+    stored = long * repeats
+    rowptr = np.array([long * ((r // 2) % repeats) + (long if r % 2 else 0) for r in range(N + 1)], dtype=np.int32)
+    col = np.concatenate([rng.choice(D, size=long, replace=False) for _ in range(repeats)]).astype(np.int32)
+    val = np.abs(rng.standard_normal(stored)).astype(np.float32)
+    V0 = np.zeros((N, D), np.float32)
+    for r in range(N):                                           # (odd rows that step back are empty)
+        at = slice(int(rowptr[r]), max(int(rowptr[r]), int(rowptr[r + 1])))
+        V0[r, col[at]] = val[at]
+    assert np.count_nonzero(V0) > 100 * stored
+    W0 = (0.1 * rng.standard_normal((J, D))).astype(np.float32)
+    y = rng.integers(0, J, size=N).astype(np.int32)
+    ctx = sfb.Sfb("l2svm", J, D, P, B, device=dev)
+    up = lambda x: torch.from_numpy(x).to(dev)                   # noqa: E731
+    W, U, V = up(W0), torch.empty((N, J), device=dev), torch.empty((N, D), device=dev)
+    ctx.step(W, sfb.SfbBatch(rowptr=up(rowptr), col=up(col), val=up(val)), up(y), U, V, eta)
+    ctx.sync()
+    assert np.array_equal(V.cpu().numpy(), V0)
+    _, Uo = oracle.loss_and_u("l2svm", V0.astype(np.float64) @ W0.astype(np.float64).T, y)
+    assert_close(U.cpu().numpy(), Uo, TOL32, "U")
+    got, U64, V64 = W.cpu().numpy(), U.cpu().numpy().astype(np.float64), V0.astype(np.float64)
+    assert_close(got, W0 - eta / B * (U64.T @ V64), TOL32, "W", terms=eta / B * (np.abs(U64).T @ V64))
+    ctx.close()
+
+
 def test_update_from_the_stored_entries_with_infinite_factors():
     """Infinite factors make NaN against every zero of the features, whether or not it is stored, as in the dense update."""
     import paper_1511_08486_amd as sfb
