@@ -110,30 +110,46 @@ __global__ __launch_bounds__(kSplitThreads, 2) void scores_split_kernel(
 
     float sum[MT][NT][8];
     t.exchange(wave, lane, ss_lds, sum);
+    const int wm = (wave & 3) >> 1, wn = wave & 1, l32 = lane & 31, half = lane >> 5;
+    t.mend(wave, sum, [&](int i, int j) {
+        const int64_t row = min(m0 + (wm * MT + i) * 32 + l32, M - 1), col = min(n0 + (wn * NT + j) * 32 + l32, N - 1);
+        const float *a = A + row * lda, *a2 = DIFF ? A2 + row * lda : nullptr, *w = W + col * ldw;
+        f32x16 x;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) x[e] = 0.f;
+        int k = k_begin;
+        for (; k + kSpChunk <= k_end; k += kSpChunk) {                   // any order of k will do: four for each half of the lanes
+            f32x4 p[4], q[4];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const int o = k + 8 * c + 4 * half;
+                p[c] = *reinterpret_cast<const sp_f32x4u*>(a + o);
+                if (DIFF) p[c] -= *reinterpret_cast<const sp_f32x4u*>(a2 + o);
+                q[c] = *reinterpret_cast<const sp_f32x4u*>(w + o);
+            }
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) x = split_mfma_f32(p[c][e], q[c][e], x);
+        }
+        for (; k < k_end; k += 2) {
+            const int o = min(k + half, k_end - 1);
+            const bool on = k + half < k_end;
+            x = split_mfma_f32(on ? (DIFF ? a[o] - a2[o] : a[o]) : 0.f, on ? w[o] : 0.f, x);
+        }
+        return x;
+    });
     float* zout = Z + (int64_t)ks * zstride;
-    const int wm = (wave & 3) >> 1, wn = wave & 1;
-    auto row_of = [&](int i, int q) { return m0 + (wm * MT + i) * 32 + Tile::entry_row(wave >> 2, q, lane); };
-    uint32_t again = 0;                                                  // entries to sum without the split (see split_finite)
 #pragma unroll
     for (int j = 0; j < NT; ++j) {
-        const int col = n0 + (wn * NT + j) * 32 + (lane & 31);
+        const int col = n0 + (wn * NT + j) * 32 + l32;
 #pragma unroll
         for (int i = 0; i < MT; ++i)
 #pragma unroll
             for (int q = 0; q < 8; ++q) {
-                const int row = row_of(i, q);
-                if (row < M && col < N) {
-                    if (split_finite(sum[i][j][q])) zout[(int64_t)row * ldz + col] = sum[i][j][q];
-                    else again |= 1u << ((j * MT + i) * 8 + q);
-                }
+                const int row = m0 + (wm * MT + i) * 32 + Tile::entry_row(wave >> 2, q, lane);
+                if (row < M && col < N) zout[(int64_t)row * ldz + col] = sum[i][j][q];
             }
-    }
-    for (; again != 0; again &= again - 1) {
-        const int e = __builtin_ctz(again), row = row_of((e >> 3) % MT, e & 7), col = n0 + (wn * NT + (e >> 3) / MT) * 32 + (lane & 31);
-        const float *a = A + (int64_t)row * lda, *a2 = DIFF ? A2 + (int64_t)row * lda : nullptr, *w = W + (int64_t)col * ldw;
-        float z = 0.f;
-        for (int k = k_begin; k < k_end && z == z; ++k) z = fmaf(DIFF ? a[k] - a2[k] : a[k], w[k], z);
-        zout[(int64_t)row * ldz + col] = z;
     }
 }
 

@@ -141,45 +141,52 @@ __global__ __launch_bounds__(kSplitThreads, 2) void reconstruct_split_kernel(
         }
     float sum[MT][NT][8];
     t.exchange(wave, lane, rs_lds, sum);
+    const int n_begin = c_begin * kSpChunk, n_end = PLANES ? min(N, n_begin + k_chunks * kSpChunk) : N;
+    t.mend(wave, sum, [&](int i, int j) {
+        const int half = lane >> 5;
+        const float* u = U + min(j0 + rs_column<NT>((wm * MT + i) * 32 + l32), J - 1);
+        const float* v = V + min(d0 + rs_column<NT>((wn * NT + j) * 32 + l32), D - 1);
+        f32x16 x;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) x[e] = 0.f;
+        for (int n0 = n_begin; n0 < n_end; n0 += 16) {
+            float p[8], q[8];
+#pragma unroll
+            for (int c = 0; c < 8; ++c) {
+                const int n = n0 + 2 * c + half;
+                const int64_t o = min(n, n_end - 1);
+                const bool on = n < n_end && (inv_b == 0 || ((live_mask >> __umulhi((uint32_t)o, inv_b)) & 1ull));
+                p[c] = u[o * ldu];
+                q[c] = v[o * ldv];
+                if (!on) p[c] = q[c] = 0.f;
+            }
+#pragma unroll
+            for (int c = 0; c < 8; ++c) x = split_mfma_f32(p[c], q[c], x);
+        }
+        return x;
+    });
     float* const w_out = W + (PLANES ? (int64_t)slice * J * ldw : 0);
-    uint32_t again = 0;                                                  // entries to sum without the split (see split_finite)
 #pragma unroll
     for (int i = 0; i < MT; ++i)
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
             const int row = w_row(i, q);
             float* out = w_out + (int64_t)row * ldw + dcol;
-            bool finite = split_finite(sum[i][0][q]);
             if constexpr (PAIRS) {
                 // lanes 16..31 (48..63) give their first block's sum for the second block's of lanes 0..15 (32..47)
                 asm volatile("s_nop 1\n\tv_permlane16_swap_b32 %0, %1\n\ts_nop 1" : "+v"(sum[i][0][q]), "+v"(sum[i][1][q]));
-                finite = split_finite(sum[i][0][q]) && split_finite(sum[i][1][q]);
                 rs_f32x2u x;
                 x.x = PLANES ? sum[i][0][q] : prox_entry(w[i][0][q] + alpha * sum[i][0][q], prox_kind, prox_a);
                 x.y = PLANES ? sum[i][1][q] : prox_entry(w[i][1][q] + alpha * sum[i][1][q], prox_kind, prox_a);
-                if (row < J && finite) {
+                if (row < J) {
                     if (dcol + 1 < D) *reinterpret_cast<rs_f32x2u*>(out) = x;
                     else if (dcol < D) *out = x.x;
                 }
             } else {
                 const float x = PLANES ? sum[i][0][q] : prox_entry(w[i][0][q] + alpha * sum[i][0][q], prox_kind, prox_a);
-                if (row < J && dcol < D && finite) *out = x;
+                if (row < J && dcol < D) *out = x;
             }
-            if (!finite) again |= 1u << (i * 8 + q);
         }
-    const int n_begin = c_begin * kSpChunk, n_end = PLANES ? min(N, n_begin + k_chunks * kSpChunk) : N;
-    for (; again != 0; again &= again - 1) {
-        const int e = __builtin_ctz(again), row = w_row(e >> 3, e & 7);
-        if (row >= J) continue;
-        for (int col = dcol; col < min(D, dcol + (PAIRS ? 2 : 1)); ++col) {
-            float x = 0.f;
-            for (int n = n_begin; n < n_end && x == x; ++n)
-                if (inv_b == 0 || ((live_mask >> __umulhi((uint32_t)n, inv_b)) & 1ull))
-                    x = fmaf(U[(int64_t)n * ldu + row], V[(int64_t)n * ldv + col], x);
-            float* out = w_out + (int64_t)row * ldw + col;
-            *out = PLANES ? x : prox_entry(*out + alpha * x, prox_kind, prox_a);
-        }
-    }
 }
 
 bool reconstruct_split_ok(const ReconArgs& a) {

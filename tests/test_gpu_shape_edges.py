@@ -210,3 +210,82 @@ def test_split_products_of_unbounded_values(J, D, N, big):
     else:
         assert_close(got[:, cols], want[:, cols], TOL32, "columns of large values")
     ctx.close()
+
+
+def _split_update(J, D, P, B, V0, active=None, seed=0):
+    """W after one update formed as split products, and what it should be (numpy, fp64)."""
+    import paper_1511_08486_amd as sfb
+    N, rng = P * B, np.random.default_rng(seed)
+    U0 = (rng.uniform(0.25, 0.5, (N, J)) / N).astype(np.float32)
+    W0 = (0.1 * rng.standard_normal((J, D))).astype(np.float32)
+    ctx = sfb.Sfb("mlr", J, D, P, B, device="cuda:0")
+    ctx.set_plan(fwd_dma=13)
+    W = torch.from_numpy(W0).to("cuda:0")
+    U, V = torch.from_numpy(U0).to("cuda:0"), torch.from_numpy(V0).to("cuda:0")
+    ctx.reconstruct_apply(W, U, V, 0.5, scale=1.0, active=active)
+    ctx.sync()
+    ctx.close()
+    live = np.repeat(np.ones(P, bool) if active is None else np.asarray(active, bool), B)
+    return W.cpu().numpy().astype(np.float64), W0 - 0.5 * (U0[live].astype(np.float64).T @ V0[live].astype(np.float64))
+
+
+@pytest.mark.parametrize("J,D,P,B", [
+    (515, 2051, 4, 64),                                         # tiles of 64 x 128, an odd last column
+    (1001, 4097, 6, 85),                                        # tiles of 128 x 128
+    (602, 779, 3, 343),                                         # 64 x 128, slices of the pairs
+    (65, 66, 3, 350),                                           # 64 x 64, slices of the pairs
+])
+@pytest.mark.parametrize("masked", [False, True])
+def test_split_update_with_infinities_in_one_of_two_neighbouring_columns(J, D, P, B, masked):
+    """Infinities in single columns, the last one among them, and, with a mask, NaN in everything a dead worker left: the
+    neighbours of such a column and every other entry are those of finite features."""
+    rng = np.random.default_rng(D)
+    V0 = np.abs(rng.standard_normal((P * B, D))).astype(np.float32)
+    active = [p != 1 for p in range(P)] if masked else None
+    if masked:
+        V0[B:2 * B] = np.nan
+    V0[2, 6], V0[3, 37], V0[P * B - 1, D - 1] = np.inf, -np.inf, np.inf
+    got, want = _split_update(J, D, P, B, V0, active, seed=J)
+    cols = np.isin(np.arange(D), [6, 37, D - 1])
+    assert np.array_equal(got[:, cols], want[:, cols])
+    assert_close(got[:, ~cols], want[:, ~cols], TOL32, "W")
+
+
+def test_classes_switched_off_by_infinite_weights_do_not_stall_the_split_products():
+    """One class of a thousand with a weight of minus infinity on a feature that is always one, and one feature that is
+    infinite: scores and update are formed again by the fp32 instruction in the tiles concerned.  The bound is four times
+    the time without them (22 and 82 times where a lane sums such an entry alone)."""
+    import paper_1511_08486_amd as sfb
+    J, D, P, B, dev = 1000, 4096, 8, 64, "cuda:0"
+    rng = np.random.default_rng(0)
+    A = torch.from_numpy((rng.standard_normal((P * B, D)) / 64).astype(np.float32)).to(dev)
+    A[:, 5] = 1.0
+    y = torch.full((P * B,), J - 1, dtype=torch.int32, device=dev)
+    ctx = sfb.Sfb("mlr", J, D, P, B, device=dev)
+    U, V = torch.empty((P * B, J), device=dev), torch.empty((P * B, D), device=dev)
+
+    def us(call, n=20):
+        out = []
+        for _ in range(7):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(n):
+                call()
+            b.record()
+            torch.cuda.synchronize()
+            out.append(a.elapsed_time(b) * 1e3 / n)
+        return sorted(out)[3]
+
+    times = []
+    for bad in (False, True):
+        W = torch.from_numpy((0.1 * rng.standard_normal((J, D))).astype(np.float32)).to(dev)
+        F = A.clone()
+        if bad:
+            W[3, 5], F[3, 9] = -float("inf"), float("inf")
+        Z = torch.zeros((J, D), device=dev)
+        scores = us(lambda: ctx.compute_factors(W, sfb.SfbBatch(a=A), y, U, V))
+        assert bool(torch.isfinite(U).all()) and (not bad or bool((U[:, 3] == 0).all()))
+        times.append((scores, us(lambda: ctx.reconstruct_apply(Z, U, F, 1e-3))))
+    print("scores and update, us: finite", times[0], "with infinities", times[1])
+    ctx.close()
+    assert times[1][0] < 4 * times[0][0] and times[1][1] < 4 * times[0][1]
