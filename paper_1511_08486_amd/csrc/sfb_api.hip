@@ -127,12 +127,13 @@ size_t workspace_need(const sfb_ctx* c) {
         const size_t planes = few_workspace((int64_t)c->P * c->B, c->J, c->D);
         if (planes > need) need = planes;
     }
-    // sparse features: lists of the stored entries per column behind the scores, for one entry in twelve, unless that
-    // would take the context beyond what sfb_step_noalloc has
+    // sparse features: lists of the stored entries per column behind the scores, for one entry in twelve or as many as the
+    // bytes that sfb_step_noalloc has leave room for
     if (c->model == SFB_L2SVM) {
         const size_t n = (size_t)c->P * c->B;
-        const size_t at = (n * round_up4(c->J) * sizeof(float) + 255) / 256 * 256 + sparse_update_workspace(c->D, (int64_t)(n * c->D / 12));
-        if (at > need && sparse_update_ok((int64_t)n, c->D, (int64_t)(n * c->D / 12)) && at <= SFB_NOALLOC_SCRATCH_BYTES) need = at;
+        size_t at = (n * round_up4(c->J) * sizeof(float) + 255) / 256 * 256 + sparse_update_workspace(c->D, (int64_t)(n * c->D / 12));
+        if (at > SFB_NOALLOC_SCRATCH_BYTES) at = SFB_NOALLOC_SCRATCH_BYTES;
+        if (at > need && sparse_update_ok((int64_t)n, c->D, (int64_t)(n * c->D / 12))) need = at;
     }
     // the column projection of the proximal step reuses the front of the buffer between steps
     const size_t prox = prox_workspace(c->J, c->D);
@@ -281,11 +282,14 @@ sfb_status factors_rows(sfb_ctx* c, const FwdPlan& plan, const float* W, int64_t
         // scores from the stored entries only (2*nnz*J flops), or the dense contraction on the densified rows
         sparse_scores = c->sparse_forward && csr_scores_ok((int)c->D) && b->nnz <= (1LL << 30) - 1024 &&
                         (c->sparse_always || csr_scores_wins(n_rows, c->J, c->D, b->nnz));
-        // the update of the same step may want lists of the entries per column, behind the planes of scores
+        // the update of the same step may want lists of the entries per column, behind the planes of scores: where the bytes
+        // that the context asks for hold them, so that sfb_step and sfb_step_noalloc, which differ in the bytes they have,
+        // take the same kernel (contexts that ask for more than the latter's array are refused there and may use what they got)
         if (n_rows == c->P * c->B && sparse_update_ok(n_rows, c->D, b->nnz)) {
             const int planes = sparse_scores ? 1 : c->split_scores && c->D >= 4 ? c->fwd_split.split_k : plan.split_k;
             const size_t at = ((size_t)planes * n_rows * ldz * sizeof(float) + 255) / 256 * 256;
-            if (at + sparse_update_workspace(c->D, b->nnz) <= c->ws_bytes) {
+            const size_t asked = workspace_need(c), room = asked <= SFB_NOALLOC_SCRATCH_BYTES ? asked : c->ws_bytes;
+            if (at + sparse_update_workspace(c->D, b->nnz) <= room) {
                 c->lists = (char*)c->ws + at;
                 c->lists_stored = b->nnz;
             }

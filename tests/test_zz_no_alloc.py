@@ -52,6 +52,15 @@ def test_noalloc_step_equals_step_on_two_calls_in_a_row(first, second):
         assert_close(got[3].cpu().numpy(), fo, tol, "loss")
 
 
+def test_noalloc_step_equals_step_where_the_column_lists_fit_one_scratch_and_not_twelve_per_hundred_entries():
+    """L2-SVM, 3000 x 8192, 1024 pairs at 2 %: lists of the stored entries fit the library's array beside the scores, lists
+    for one entry in twelve (what a context asks for where it can) do not.  Both calls have to take the same update."""
+    import paper_1511_08486_amd as sfb
+    _, (want, got) = _both(sfb, "l2svm", dict(J=3000, D=8192, P=16, B=64, density=0.02))
+    for w, g, what in zip(want, got, ("W", "U", "V", "loss")):
+        assert torch.equal(w, g), f"{what} differs between sfb_step and sfb_step_noalloc"
+
+
 def test_noalloc_step_with_a_dead_worker_and_no_registered_workspace_interference():
     """The registered workspace is neither needed nor touched: it is filled with NaN before the call
     and still all NaN afterwards; a dead worker's mask works as in sfb_step."""
