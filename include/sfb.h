@@ -317,6 +317,11 @@ SFB_API int sfb_last_hip_error(const sfb_ctx *ctx);
  */
 SFB_API sfb_status sfb_plan_info(const sfb_ctx *ctx, int32_t *fwd_split_k, int32_t *fwd_grid,
                          int32_t *recon_grid);
+/* The kernel that did the work of kernel family `which` (as above) in this context's last call that ran it, and its
+ * workgroups: a plan says what a context would choose, the operands' alignment, a mask and the stored entries decide per
+ * call.  name receives at most bytes - 1 characters ("" before the first launch); either pointer may be NULL.  A step of few
+ * classes is one kernel, reported for families 0, 1 and 2.  SFB_EINVAL: no such family, a name with 0 bytes. */
+SFB_API sfb_status sfb_last_kernel(const sfb_ctx *ctx, int32_t which, char *name, size_t bytes, int32_t *grid);
 /* Tuning override of the launch plan: forward tile (bm, bn in {64, 128}), split-K slices,
  * reconstruct tile variant (rows x columns of W / wavefronts: 0: 128x128/4, 1: 64x128/2,
  * 2: 32x128/1, 3: 256x128/4, 4: 128x128/8, 5: 64x128/4, 6: 128x128/4 with 64-row wavefronts;
@@ -335,7 +340,8 @@ SFB_API sfb_status sfb_plan_info(const sfb_ctx *ctx, int32_t *fwd_split_k, int32
  * exactly into three bf16 terms and every product taken as its six leading term products (error
  * at the level of one fp32 rounding; D >= 4 and leading dimensions within 32-bit offsets, else ignored),
  * the way a new fp32 context forms them unless the product is small; bit 3 = the same for the fp32 reconstruction, which a new
- * context takes where a fitted cost comparison expects it to be the fastest kernel; bit 4 = sfb_step_pipelined always runs its two separate passes; < 0 = keep.  A value <= 0 (variant < 0) keeps the current choice.
+ * context takes where a fitted cost comparison expects it to be the fastest kernel; bit 4 = sfb_step_pipelined always runs its two separate passes;
+ * bit 6 = L2SVM steps update W from lists of the stored entries wherever those fit (neither 3 nor 6: never); < 0 = keep.  A value <= 0 (variant < 0) keeps the current choice.
  * The workspace requirement may grow: query sfb_workspace_bytes again.  SFB_EINVAL for a value outside the table. */
 SFB_API sfb_status sfb_set_plan(sfb_ctx *ctx, int32_t fwd_bm, int32_t fwd_bn, int32_t fwd_split_k,
                                 int32_t recon_variant, int32_t fwd_dma);

@@ -61,6 +61,7 @@ def _load():
         "sfb_strerror": (C.c_char_p, [C.c_int]),
         "sfb_last_hip_error": (C.c_int, [vp]),
         "sfb_plan_info": (C.c_int, [vp, C.POINTER(i32), C.POINTER(i32), C.POINTER(i32)]),
+        "sfb_last_kernel": (C.c_int, [vp, i32, C.c_char_p, C.c_size_t, C.POINTER(i32)]),
         "sfb_set_plan": (C.c_int, [vp, i32, i32, i32, i32, i32]),
         "sfb_stream_copy": (C.c_int, [vp, vp, vp, C.c_size_t]),
         "sfb_probe": (C.c_int, [vp, C.c_int, vp, i64, i32]),
@@ -309,6 +310,12 @@ class Sfb:
         a, b, c = C.c_int32(), C.c_int32(), C.c_int32()
         self._check(lib.sfb_plan_info(self._ctx, C.byref(a), C.byref(b), C.byref(c)), "sfb_plan_info")
         return {"fwd_split_k": a.value, "fwd_grid": b.value, "recon_grid": c.value}
+
+    def last_kernel(self, which):
+        """(name, workgroups) of the kernel that family `which` (0 scores, 1 factor u, 2 update, ...) ran last."""
+        buf, grid = C.create_string_buffer(64), C.c_int32()
+        self._check(lib.sfb_last_kernel(self._ctx, which, buf, len(buf), C.byref(grid)), "sfb_last_kernel")
+        return buf.value.decode(), grid.value
 
     def set_plan(self, fwd_bm=0, fwd_bn=0, fwd_split_k=0, recon_variant=-1, fwd_dma=-1):
         self._check(lib.sfb_set_plan(self._ctx, fwd_bm, fwd_bn, fwd_split_k, recon_variant, fwd_dma),

@@ -17,6 +17,7 @@ using namespace sfb;
 namespace {
 constexpr int kFamilies = 6;  // 0 scores, 1 factor u, 2 reconstruct-apply, 3 sparse helpers, 4 proximal step, 5 one-pass update + next scores
 struct EventPair { hipEvent_t a, b; };
+struct LastKernel { const char* name; uint32_t grid; };   // what SFB_LAUNCH left
 
 // Scratch of the entry point that allocates nothing (sfb_step_noalloc): device memory that belongs
 // to the library's code object, one copy per GPU the library is loaded on, held until the process
@@ -49,7 +50,7 @@ hipError_t resolve_static_scratch(void** out) {
 
 namespace sfb {
 LaunchEvents& launch_events() {
-    static thread_local LaunchEvents le{nullptr, nullptr, false};
+    static thread_local LaunchEvents le{nullptr, nullptr, false, nullptr, 0};
     return le;
 }
 }  // namespace sfb
@@ -80,6 +81,8 @@ struct sfb_ctx {
     int64_t lists_stored;          //   the number of stored entries of its batch
     bool sparse_forward;           // L2SVM: scores from the CSR entries when W rows fit in LDS and that is the cheaper pass
     bool sparse_always;            //   ... whenever they fit (no cost comparison)
+    bool lists_always;             // L2SVM: the update from the column lists wherever they fit (no cost comparison)
+    LastKernel last[kFamilies];    // main kernel of every family's last launch (name null: none yet)
     std::vector<EventPair> used[kFamilies], spare;
 };
 
@@ -145,13 +148,15 @@ sfb_status hip_fail(sfb_ctx* c, hipError_t e) {
     return SFB_EHIP;
 }
 
-// Arms a pair of events for the next kernel launch when timing is on (see SFB_LAUNCH).
+// Arms a pair of events for the next kernel launch when timing is on (see SFB_LAUNCH), and notes the last kernel
+// launched in its scope as the family's.
 struct Timed {
     sfb_ctx* c;
     int fam;
     EventPair ev;
     bool on;
     Timed(sfb_ctx* ctx, int family) : c(ctx), fam(family), on(ctx->timing) {
+        launch_events().name = nullptr;
         if (!on) return;
         if (!c->spare.empty()) {
             ev = c->spare.back();
@@ -174,8 +179,9 @@ struct Timed {
         le.armed = true;
     }
     ~Timed() {
-        if (!on) return;
         LaunchEvents& le = launch_events();
+        if (le.name) c->last[fam] = LastKernel{le.name, le.blocks};
+        if (!on) return;
         if (le.armed) {             // nothing was launched: the events hold no timestamps
             le.armed = false;
             c->spare.push_back(ev);
@@ -253,9 +259,13 @@ sfb_status few_rows(sfb_ctx* c, float* W, int64_t ldw, const sfb_batch* b, const
     f.vec_a = ((uintptr_t)f.a % 8) == 0 && (f.lda % 4) == 0;
     f.vec_v = ((uintptr_t)f.v % 8) == 0 && (f.ldv % 4) == 0;
     f.prox_kind = prox_kind; f.prox_a = prox_a;
-    Timed t(c, 0);
-    hipError_t e = launch_few(f, update, c->stream);
-    if (e != hipSuccess) return hip_fail(c, e);
+    {
+        Timed t(c, 0);
+        hipError_t e = launch_few(f, update, c->stream);
+        if (e != hipSuccess) return hip_fail(c, e);
+    }
+    c->last[1] = c->last[0];                                     // one kernel is all of the step, or of its factors
+    if (update) c->last[2] = c->last[0];
     return SFB_OK;
 }
 
@@ -395,6 +405,10 @@ sfb_status recon_launch(sfb_ctx* c, float* W, int64_t ldw, const float* U, int64
         on_lists = same_step && c->lists != nullptr && c->split_recon < 0 &&
                    sparse_update_us(r.N, c->J, c->D, c->lists_stored) < us;
     }
+    if (c->lists_always && same_step && c->lists != nullptr) {
+        on_lists = true;
+        on_thin = false;
+    }
     if (on_thin) {
         e = launch_reconstruct_thin(r, c->stream);
     } else if (on_lists) {
@@ -490,6 +504,8 @@ sfb_status sfb_create(sfb_ctx** out, sfb_model m, int64_t J, int64_t D, int32_t 
                 c->split_plans[one][with_ws] = reconstruct_split_plan(J, D, one ? B : (int64_t)P * B, with_ws ? workspace_need(c) : 0);
     }
     c->ws = nullptr; c->ws_bytes = 0; c->lists = nullptr; c->lists_stored = 0; c->last_hip = 0; c->timing = false; c->sparse_forward = true; c->sparse_always = false;
+    c->lists_always = false;
+    for (LastKernel& k : c->last) k = LastKernel{nullptr, 0};
     // Set-up for sfb_step_noalloc on the device that is current now: resolve the address of the
     // library's scratch array, so that the entry point itself only reads it.  On a machine without a
     // GPU this fails; the context is still good for everything that can be checked on the host, and
@@ -804,6 +820,20 @@ sfb_status sfb_plan_info(const sfb_ctx* c, int32_t* fwd_split_k, int32_t* fwd_gr
     return SFB_OK;
 }
 
+sfb_status sfb_last_kernel(const sfb_ctx* c, int32_t which, char* name, size_t bytes, int32_t* grid) {
+    if (!c || which < 0 || which >= kFamilies || (name && bytes == 0)) return SFB_EINVAL;
+    if (name) {                                                  // as it stands at the launch, up to its template arguments
+        const char* k = c->last[which].name ? c->last[which].name : "";
+        if (*k == '(') ++k;
+        size_t n = 0;
+        while (n + 1 < bytes && k[n] != '\0' && k[n] != '<') ++n;
+        for (size_t i = 0; i < n; ++i) name[i] = k[i];
+        name[n] = '\0';
+    }
+    if (grid) *grid = (int32_t)c->last[which].grid;
+    return SFB_OK;
+}
+
 sfb_status sfb_set_plan(sfb_ctx* c, int32_t fwd_bm, int32_t fwd_bn, int32_t fwd_split_k, int32_t recon_variant,
                         int32_t fwd_dma) {
     if (!c) return SFB_EINVAL;
@@ -823,6 +853,7 @@ sfb_status sfb_set_plan(sfb_ctx* c, int32_t fwd_bm, int32_t fwd_bn, int32_t fwd_
     else if (fwd_bm > 0 || fwd_bn > 0 || fwd_split_k > 0) c->split_scores = false;
     if (fwd_dma >= 0) c->split_recon = (fwd_dma & 8) != 0;      // bit 3 set: the reconstruction likewise
     else if (recon_variant >= 0) c->split_recon = 0;
+    if (fwd_dma >= 0) c->lists_always = (fwd_dma & 64) != 0;    // bit 6 set: L2SVM steps update from the column lists wherever they fit
     if (fwd_dma >= 0) c->use_fused = (fwd_dma & 16) == 0;       // bit 4 set: sfb_step_pipelined runs two separate passes
     finish_forward_plan(&p, (int64_t)c->P * c->B, c->J, c->D);
     c->fwd_all = p;

@@ -15,15 +15,20 @@ enum Model { kMLR = 0, kDML = 1, kL2SVM = 2 };
 // Timing hook.  When a pair of events is armed on the calling thread, the next kernel launched
 // through SFB_LAUNCH carries them: they take the start and stop timestamps of that dispatch
 // itself, so what they measure is the kernel's duration with no stream packets in between.
+// SFB_LAUNCH also leaves its kernel's name and grid (sfb_last_kernel).
 struct LaunchEvents {
     hipEvent_t start, stop;
     bool armed;
+    const char* name;        // of the kernel, as written at the launch, template arguments included
+    uint32_t blocks;         // workgroups
 };
 LaunchEvents& launch_events();
 
 #define SFB_LAUNCH(kernel, grid, block, lds, stream, ...)                                                  \
     do {                                                                                                    \
         ::sfb::LaunchEvents& sfb_le_ = ::sfb::launch_events();                                              \
+        sfb_le_.name = #kernel;                                                                             \
+        sfb_le_.blocks = dim3(grid).x;                                                                       \
         if (sfb_le_.armed) {                                                                                \
             sfb_le_.armed = false;                                                                          \
             hipExtLaunchKernelGGL(kernel, grid, block, lds, stream, sfb_le_.start, sfb_le_.stop, 0,         \

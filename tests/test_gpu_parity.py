@@ -158,22 +158,23 @@ def test_a_dead_worker_in_a_whole_shape_goes_through_a_masked_copy_of_u(sfb):
 @pytest.mark.parametrize("name,over,tiles", [
     ("mlr_tiny", dict(J=10, D=784, P=12, B=100), 14),        # ragged: padded copies, then slices of their 1216 rows
     ("mlr_tiny", dict(J=64, D=128, P=16, B=128), 2),         # whole: two tiles, 64 stages
-    ("dml", dict(J=100, D=192, P=8, B=256), 8),              # 192 -> 256 columns: 2 x 4 tiles
+    ("dml", dict(J=100, D=192, P=8, B=256), 8),              # 192 -> 256 columns: 2 x 4 tiles, where the factors are copied
     ("l2svm", dict(J=48, D=320, P=4, B=300, density=0.05), 6),   # 320 -> 384 columns
 ])
 def test_few_tiles_many_pairs_split_the_pairs_over_workgroups(sfb, name, over, tiles):
     """J x D of a few 64 x 64 tiles with thousands of factor pairs: the plan cuts the pairs into slices, one
     workgroup per tile and slice stores bare sums, a second kernel adds them in slice order.  Two steps against
-    the oracle, the same call twice bit for bit, and with a dead worker."""
+    the oracle (as the context plans them, and with the fp32 instruction, whose kernel this is about), the same call
+    twice bit for bit, and with a dead worker."""
     wl = make_clear_of_kink(name, 91, 2, steps=2, pool=2, **over)
     dev = "cuda:0"
-    ctx = sfb.Sfb(wl.model, wl.J, wl.D, wl.P, wl.B, device=dev)
-    grid = ctx.plan_info()["recon_grid"]
-    assert grid % tiles == 0 and grid // tiles > 1, f"the plan does not split: {grid} workgroups for {tiles} tiles"
-    ctx.close()
     run_chain(wl, 2, TOL32, pad=0)
+    run_chain(wl, 2, TOL32, pad=0, plan=dict(fwd_dma=1))
     # determinism and the mask, on the reconstruction alone
     ctx = sfb.Sfb(wl.model, wl.J, wl.D, wl.P, wl.B, device=dev)
+    ctx.set_plan(fwd_dma=1)
+    grid = ctx.plan_info()["recon_grid"]
+    assert grid % tiles == 0 and grid // tiles > 1, f"the plan does not split: {grid} workgroups for {tiles} tiles"
     rng = np.random.default_rng(3)
     Uh = rng.standard_normal((wl.N, wl.J)).astype(np.float32)
     Vh = rng.standard_normal((wl.N, wl.D)).astype(np.float32)
@@ -185,6 +186,9 @@ def test_few_tiles_many_pairs_split_the_pairs_over_workgroups(sfb, name, over, t
             W = torch.from_numpy(wl.W0).to(dev)
             ctx.reconstruct_apply(W, torch.from_numpy(Uh).to(dev), torch.from_numpy(Vh).to(dev), wl.eta, active=mask)
             ctx.sync()
+            # (a context that keeps padded copies has no planes for a call that needs none: 100 x 192 without a mask)
+            as_is = mask is None and wl.D == 192
+            assert ctx.last_kernel(2) == ("reconstruct_apply_small_kernel", 2 * 3 if as_is else grid)
             got.append(W)
         assert torch.equal(got[0], got[1])
         dW = oracle.delta_w(Uh, Vh, wl.P, wl.B, active=mask)
@@ -206,12 +210,14 @@ def test_w_alone_off_the_16_byte_grid_keeps_the_pair_kernel(sfb):
     Uh = rng.standard_normal((N, J)).astype(np.float32)
     Vh = rng.standard_normal((N, D)).astype(np.float32)
     ctx = sfb.Sfb("mlr", J, D, P, B, device=dev)
+    ctx.set_plan(recon_variant=12)                               # (64 pairs: by itself the call takes the kernel for few pairs)
     assert ctx.plan_info()["recon_grid"] == 256
     Wbuf = torch.full((J, D + 1), 7.0, dtype=torch.float32, device=dev)
     W = Wbuf[:, :D]
     W.copy_(torch.from_numpy(W0))
     ctx.reconstruct_apply(W, torch.from_numpy(Uh).to(dev), torch.from_numpy(Vh).to(dev), eta)
     ctx.sync()
+    assert ctx.last_kernel(2) == ("reconstruct_apply_pair_kernel", 256)
     dW = oracle.delta_w(Uh, Vh, P, B)
     mag = eta * oracle.delta_w(np.abs(Uh), np.abs(Vh), P, B)
     assert_close(W.cpu().numpy(), oracle.apply_update(W0.astype(np.float64), dW, eta), TOL32, "W", terms=mag)
@@ -552,7 +558,7 @@ def test_determinism_same_call_twice_is_bit_identical(sfb):
     ("dml", 1, 20, {}),
     ("mlr_tiny", 5, 3, dict(J=130, D=256, P=3, B=40)),      # ragged tiles, one slice of D
     ("mlr_tiny", 6, 3, dict(J=64, D=96, P=2, B=16)),        # D = 3 chunks: the loop's tail
-    ("mlr_tiny", 7, 3, dict(J=37, D=203, P=3, B=5)),        # D % 32 != 0: the switch is ignored
+    ("mlr_tiny", 7, 3, dict(J=37, D=203, P=3, B=5)),        # D % 32 != 0, rows off the 16-byte grid
 ])
 def test_split_bf16_scores(sfb, name, seed, steps, override):
     """fp32 scores computed as six bf16 term products per product (plan bit 2): same parity bar
@@ -569,7 +575,7 @@ def test_split_bf16_scores(sfb, name, seed, steps, override):
     ("mlr_tiny", 5, 3, dict(J=132, D=260, P=2, B=32)),      # ragged tiles in both directions
     ("mlr_tiny", 6, 3, dict(J=64, D=128, P=3, B=32)),       # N = 96 = 3 chunks: the loop's tail
     ("mlr_tiny", 8, 3, dict(J=8, D=4, P=1, B=32)),          # one chunk, tile far larger than W
-    ("mlr_tiny", 7, 3, dict(J=37, D=203, P=3, B=5)),        # J % 4 != 0, N % 32 != 0: the switch is ignored
+    ("mlr_tiny", 7, 3, dict(J=37, D=203, P=3, B=5)),        # J % 4 != 0, N % 32 != 0
 ])
 def test_split_bf16_scores_and_reconstruction(sfb, name, seed, steps, override):
     """Both contractions as split-bf16 products (plan bits 2 and 3), whole chains against the oracle."""
@@ -578,8 +584,8 @@ def test_split_bf16_scores_and_reconstruction(sfb, name, seed, steps, override):
     print(f"{name} {override}: split-bf16 scores and reconstruction, worst error/allowance {worst}")
 
 
-def test_split_bf16_reconstruction_with_a_dead_worker_falls_back(sfb):
-    """A mask of live workers is not covered by the split kernel: the call must still be right."""
+def test_split_bf16_reconstruction_with_a_dead_worker(sfb):
+    """The split kernel takes a mask of live workers as it is."""
     dev = "cuda:0"
     wl = workloads.make("mlr_tiny", seed=9, J=64, D=128, P=4, B=32)
     ctx = sfb.Sfb(wl.model, wl.J, wl.D, wl.P, wl.B, device=dev)
@@ -591,6 +597,7 @@ def test_split_bf16_reconstruction_with_a_dead_worker_falls_back(sfb):
     active = [1, 0, 1, 1]
     ctx.step(W, db, dy, U, V, wl.eta, active=active)
     ctx.sync()
+    assert ctx.last_kernel(2)[0] == "reconstruct_split_kernel"
     _, _, want, _ = oracle.step(wl.model, wl.W0, b, wl.P, wl.B, wl.eta, active=active)
     assert_close(W.cpu().numpy(), want, TOL32, "W, split plan, dead worker")
     ctx.close()

@@ -12,8 +12,9 @@ pytestmark = pytest.mark.gpu
 TOL32 = 1e-4
 
 
-def _one_step(wl, active, plan=None, prox=None):
-    """One step with a mask of live workers (and a proximal operator), W and the update alone against the oracle."""
+def _one_step(wl, active, plan=None, prox=None, update=None):
+    """One step with a mask of live workers (and a proximal operator), W and the update alone against the oracle.
+    update: the kernel that the step's update has to run."""
     import paper_1511_08486_amd as sfb
     dev = "cuda:0"
     ctx = sfb.Sfb(wl.model, wl.J, wl.D, wl.P, wl.B, dtype=wl.dtype, device=dev)
@@ -30,6 +31,8 @@ def _one_step(wl, active, plan=None, prox=None):
     else:
         ctx.step(W, db, dy, U, V, wl.eta, loss=loss, active=active)
     ctx.sync()
+    if update:
+        assert ctx.last_kernel(2)[0] == update
     tol = TOL32 if wl.dtype == "f32" else 2e-2
     for got, exact, what in ((W, want, "W"), (U, Uo, "U"), (V.float(), Vo, "V"), (loss, fo, "loss")):
         assert_close(got.cpu().numpy(), exact, tol, what)
@@ -49,11 +52,11 @@ def _one_step(wl, active, plan=None, prox=None):
     ("dml", 31, 133, 2, 16, [1, 0], None),
 ])
 def test_few_classes(name, J, D, P, B, active, prox):
-    _one_step(workloads.make(name, seed=J + D, J=J, D=D, P=P, B=B), active, prox=prox)
+    _one_step(workloads.make(name, seed=J + D, J=J, D=D, P=P, B=B), active, prox=prox, update="few_step_kernel")
 
 
 def test_few_classes_bf16():
-    _one_step(workloads.make("mlr_large", seed=3, J=19, D=258, P=4, B=37), [1, 1, 0, 1])
+    _one_step(workloads.make("mlr_large", seed=3, J=19, D=258, P=4, B=37), [1, 1, 0, 1], update="few_step_kernel")
 
 
 @pytest.mark.parametrize("J,D,P,B,active", [
@@ -64,7 +67,8 @@ def test_few_classes_bf16():
     (129, 1030, 1, 2050, None),
 ])
 def test_split_products(J, D, P, B, active):
-    _one_step(workloads.make("mlr_tiny", seed=J + D, J=J, D=D, P=P, B=B), active, plan=dict(fwd_dma=13))
+    _one_step(workloads.make("mlr_tiny", seed=J + D, J=J, D=D, P=P, B=B), active, plan=dict(fwd_dma=13),
+              update="reconstruct_split_kernel")
 
 
 @pytest.mark.parametrize("J,D,P,B,active,density", [
@@ -74,7 +78,7 @@ def test_split_products(J, D, P, B, active):
 ])
 def test_update_from_the_stored_entries(J, D, P, B, active, density):
     wl = workloads.make("l2svm", seed=J, J=J, D=D, P=P, B=B, density=density)
-    _one_step(wl, active)
+    _one_step(wl, active, plan=dict(fwd_dma=65), update="sparse_update_kernel")
 
 
 @pytest.mark.parametrize("J,D,long,repeats", [(600, 4096, 300, 4), (1001, 2003, 64, 2)])
@@ -100,6 +104,7 @@ def test_update_from_the_stored_entries_with_row_pointers_that_overlap(J, D, lon
     W, U, V = up(W0), torch.empty((N, J), device=dev), torch.empty((N, D), device=dev)
     ctx.step(W, sfb.SfbBatch(rowptr=up(rowptr), col=up(col), val=up(val)), up(y), U, V, eta)
     ctx.sync()
+    assert ctx.last_kernel(2)[0] == "sparse_update_kernel"
     assert np.array_equal(V.cpu().numpy(), V0)
     _, Uo = oracle.loss_and_u("l2svm", V0.astype(np.float64) @ W0.astype(np.float64).T, y)
     assert_close(U.cpu().numpy(), Uo, TOL32, "U")
@@ -121,6 +126,7 @@ def test_update_from_the_stored_entries_with_infinite_factors():
     U, V, loss = alloc_factors(wl, dev)
     ctx.step(W, db, dy, U, V, wl.eta, loss=loss)
     ctx.sync()
+    assert ctx.last_kernel(2)[0] == "sparse_update_kernel"
     U64, V64 = U.cpu().numpy().astype(np.float64), V.cpu().numpy().astype(np.float64)
     assert not np.isfinite(U64[:, 40]).all() and np.isfinite(np.delete(U64, 40, 1)).all()
     with np.errstate(invalid="ignore"):
@@ -150,6 +156,7 @@ def test_update_from_the_stored_entries_leaves_out_whatever_a_dead_worker_holds(
         U, V, loss = alloc_factors(wl, "cuda:0")
         ctx.step(W, db, dy, U, V, wl.eta, loss=loss, active=active)
         ctx.sync()
+        assert ctx.last_kernel(2)[0] == "sparse_update_kernel"
         got.append(W)
         ctx.close()
     _, _, want, _ = oracle.step(wl.model, wl.W0, b, wl.P, wl.B, wl.eta, active=active)
@@ -166,7 +173,7 @@ def test_update_from_the_stored_entries_leaves_out_whatever_a_dead_worker_holds(
     (77, 515, 2, 64, None, None),                               # the most pairs
 ])
 def test_few_pairs(J, D, P, B, active, prox):
-    _one_step(workloads.make("mlr_tiny", seed=J + D, J=J, D=D, P=P, B=B), active, prox=prox)
+    _one_step(workloads.make("mlr_tiny", seed=J + D, J=J, D=D, P=P, B=B), active, prox=prox, update="reconstruct_thin_kernel")
 
 
 # Values that no three bf16 terms hold: infinities, and finite ones that round to an infinity in bf16.  What is infinite, or
@@ -213,7 +220,7 @@ def test_split_products_of_unbounded_values(J, D, N, big):
 
 
 def _split_update(J, D, P, B, V0, active=None, seed=0):
-    """W after one update formed as split products, and what it should be (numpy, fp64)."""
+    """W after one update formed as split products, what it should be (numpy, fp64), and its workgroups."""
     import paper_1511_08486_amd as sfb
     N, rng = P * B, np.random.default_rng(seed)
     U0 = (rng.uniform(0.25, 0.5, (N, J)) / N).astype(np.float32)
@@ -224,19 +231,21 @@ def _split_update(J, D, P, B, V0, active=None, seed=0):
     U, V = torch.from_numpy(U0).to("cuda:0"), torch.from_numpy(V0).to("cuda:0")
     ctx.reconstruct_apply(W, U, V, 0.5, scale=1.0, active=active)
     ctx.sync()
+    name, grid = ctx.last_kernel(2)
+    assert name == "reconstruct_split_kernel"
     ctx.close()
     live = np.repeat(np.ones(P, bool) if active is None else np.asarray(active, bool), B)
-    return W.cpu().numpy().astype(np.float64), W0 - 0.5 * (U0[live].astype(np.float64).T @ V0[live].astype(np.float64))
+    return W.cpu().numpy().astype(np.float64), W0 - 0.5 * (U0[live].astype(np.float64).T @ V0[live].astype(np.float64)), grid
 
 
-@pytest.mark.parametrize("J,D,P,B", [
-    (515, 2051, 4, 64),                                         # tiles of 64 x 128, an odd last column
-    (1001, 4097, 6, 85),                                        # tiles of 128 x 128
-    (602, 779, 3, 343),                                         # 64 x 128, slices of the pairs
-    (65, 66, 3, 350),                                           # 64 x 64, slices of the pairs
+@pytest.mark.parametrize("J,D,P,B,tile,sliced", [
+    (515, 2051, 4, 64, (64, 128), False),                       # an odd last column
+    (1001, 4093, 6, 85, (128, 128), False),
+    (602, 779, 3, 343, (64, 128), True),                        # slices of the pairs
+    (65, 66, 3, 350, (64, 64), True),
 ])
 @pytest.mark.parametrize("masked", [False, True])
-def test_split_update_with_infinities_in_one_of_two_neighbouring_columns(J, D, P, B, masked):
+def test_split_update_with_infinities_in_one_of_two_neighbouring_columns(J, D, P, B, tile, sliced, masked):
     """Infinities in single columns, the last one among them, and, with a mask, NaN in everything a dead worker left: the
     neighbours of such a column and every other entry are those of finite features."""
     rng = np.random.default_rng(D)
@@ -245,7 +254,9 @@ def test_split_update_with_infinities_in_one_of_two_neighbouring_columns(J, D, P
     if masked:
         V0[B:2 * B] = np.nan
     V0[2, 6], V0[3, 37], V0[P * B - 1, D - 1] = np.inf, -np.inf, np.inf
-    got, want = _split_update(J, D, P, B, V0, active, seed=J)
+    got, want, grid = _split_update(J, D, P, B, V0, active, seed=J)
+    tiles = -(-J // tile[0]) * -(-D // tile[1])
+    assert grid % tiles == 0 and (grid > tiles) == sliced
     cols = np.isin(np.arange(D), [6, 37, D - 1])
     assert np.array_equal(got[:, cols], want[:, cols])
     assert_close(got[:, ~cols], want[:, ~cols], TOL32, "W")

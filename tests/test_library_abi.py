@@ -296,6 +296,11 @@ def test_measurement_aids_validate_their_arguments(lib):
     assert lib.sfb_kernel_time_ms(ctx, 0, None, C.byref(n)) == -1
     assert lib.sfb_enable_timing(None, 1) == -1 and lib.sfb_reset_timing(None) == -1
     assert lib.sfb_plan_info(None, None, None, None) == -1
+    name, g = C.create_string_buffer(8), C.c_int32(-1)
+    assert lib.sfb_last_kernel(ctx, 2, name, 8, C.byref(g)) == 0 and name.value == b"" and g.value == 0   # nothing ran yet
+    assert lib.sfb_last_kernel(ctx, 2, None, 0, None) == 0 and lib.sfb_last_kernel(ctx, 2, name, 0, None) == -1
+    assert lib.sfb_last_kernel(ctx, 6, name, 8, None) == -1 and lib.sfb_last_kernel(ctx, -1, name, 8, None) == -1
+    assert lib.sfb_last_kernel(None, 2, name, 8, None) == -1
     assert lib.sfb_last_hip_error(ctx) == 0
     lib.sfb_destroy(ctx)
     lib.sfb_destroy(None)                                                     # harmless
