@@ -392,8 +392,11 @@ sfb_status recon_launch(sfb_ctx* c, float* W, int64_t ldw, const float* U, int64
     if (c->split_recon != 0 && !on_thin) {
         // what the fp32 kernels would take, copies of ragged, misaligned or masked factors included
         const double macs = (double)r.N * (double)c->J * (double)c->D;
-        double us = c->padded_factors && have_ws ? reconstruct_fp32_us(c->recon_padded, c->J, c->D, conform_rows(r.N))
-                                                 : reconstruct_fp32_us(c->recon, c->J, c->D, r.N);
+        // (a call that needs no copy in a context that keeps room for them has no planes for slices of the pairs: 100 x 192
+        // with 2048 pairs walks them in six workgroups, 41 us)
+        double us = c->padded_factors && have_ws && !whole
+                        ? reconstruct_fp32_us(c->recon_padded, c->J, c->D, conform_rows(r.N), true)
+                        : reconstruct_fp32_us(c->recon, c->J, c->D, r.N, have_ws && !c->padded_factors);
         if (!whole) us += 3.5 + 1.6e-6 * (double)r.N * (double)(c->J + c->D);
         if (reconstruct_split_ok(r)) {
             sp = &c->split_plans[n_rows > 0][have_ws];

@@ -173,8 +173,8 @@ struct ReconArgs {
     int tile_cols() const { return Dp > 0 ? Dp : D; }
 };
 hipError_t launch_reconstruct(const ReconArgs& a, const ReconPlan& p, hipStream_t s);
-// estimated microseconds of the plan's kernel for n_rows pairs (fitted to one MI355X)
-double reconstruct_fp32_us(const ReconPlan& p, int64_t J, int64_t D, int64_t n_rows);
+// estimated microseconds of the plan's kernel for n_rows pairs (fitted to one MI355X); planes: there is room for slices of them
+double reconstruct_fp32_us(const ReconPlan& p, int64_t J, int64_t D, int64_t n_rows, bool planes);
 // Ragged or misaligned fp32 factors through the LDS-DMA kernels: the factors are first copied
 // into `workspace` (conform_workspace(J, D, N) bytes, 256-byte aligned) with every row padded to
 // what those kernels assume, then the plan's kernel runs on the copies and updates W entry by

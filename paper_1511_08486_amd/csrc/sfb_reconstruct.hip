@@ -612,8 +612,8 @@ ReconPlan plan_reconstruct(int64_t J, int64_t D, int64_t N) {
 
 // A workgroup's walk takes 18 ns per pair with single blocks, 41 with the pair-splitting tiles, 63 with 128 x 128;
 // rounds of 256 workgroups add up; slices of the pairs cost 3 us for adding their planes.
-double reconstruct_fp32_us(const ReconPlan& p, int64_t J, int64_t D, int64_t n_rows) {
-    const bool slices = p.n_split > 1 && n_rows == p.n_rows;
+double reconstruct_fp32_us(const ReconPlan& p, int64_t J, int64_t D, int64_t n_rows, bool planes) {
+    const bool slices = planes && p.n_split > 1 && n_rows == p.n_rows;
     const double rounds = (double)(((slices ? p.grid : p.grid / (p.n_split > 1 ? p.n_split : 1)) + 255) / 256);
     const double pair_us = p.variant == kSmallVariant ? 0.018 : p.variant == kKsplitVariant ? 0.041 : 0.063;
     return 4.6 + 0.4e-6 * (double)J * (double)D + rounds * pair_us * (double)(slices ? p.k_rows : n_rows) + (slices ? 3.0 : 0.0);

@@ -176,6 +176,23 @@ def test_few_pairs(J, D, P, B, active, prox):
     _one_step(workloads.make("mlr_tiny", seed=J + D, J=J, D=D, P=P, B=B), active, prox=prox, update="reconstruct_thin_kernel")
 
 
+def test_many_pairs_on_few_tiles_are_spread_over_the_chip():
+    """100 x 192 with 2048 pairs: whole 64-column tiles, but rows that other calls copy into padded ones.  The fp32
+    instruction's kernel would walk all pairs in six workgroups there, its slices are for the copies; the costs know."""
+    import paper_1511_08486_amd as sfb
+    J, D, P, B, dev = 100, 192, 8, 256, "cuda:0"
+    rng = np.random.default_rng(1)
+    Uh, Vh = rng.standard_normal((P * B, J)).astype(np.float32), rng.standard_normal((P * B, D)).astype(np.float32)
+    ctx = sfb.Sfb("dml", J, D, P, B, device=dev)
+    W = torch.zeros((J, D), device=dev)
+    ctx.reconstruct_apply(W, torch.from_numpy(Uh).to(dev), torch.from_numpy(Vh).to(dev), 0.1, scale=1.0)
+    ctx.sync()
+    assert ctx.last_kernel(2)[1] >= 64
+    U64, V64 = Uh.astype(np.float64), Vh.astype(np.float64)
+    assert_close(W.cpu().numpy(), -0.1 * (U64.T @ V64), TOL32, "W", terms=0.1 * (np.abs(U64).T @ np.abs(V64)))
+    ctx.close()
+
+
 # Values that no three bf16 terms hold: infinities, and finite ones that round to an infinity in bf16.  What is infinite, or
 # as finite as in fp32, stays so; a whole row or column that depends on them is compared with numpy in fp64.
 @pytest.mark.parametrize("J,D,N", [(66, 130, 70), (130, 1030, 200), (200, 515, 1030)])
