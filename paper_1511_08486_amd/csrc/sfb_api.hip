@@ -385,13 +385,10 @@ sfb_status recon_launch(sfb_ctx* c, float* W, int64_t ldw, const float* U, int64
     const bool have_ws = c->ws != nullptr && c->ws_bytes >= workspace_need(c);
     const SplitReconPlan* sp = nullptr;
     const bool whole = reconstruct_takes_dma(r, c->recon);
-    if (c->split_recon < 0 && reconstruct_thin_ok(r)) {
-        // (the smallest ragged calls, all latency, keep leaving padded copies of their factors in the workspace)
-        on_thin = whole || !have_ws || (double)r.N * (double)c->J * (double)c->D >= 1.2e5;
-    }
+    // (ragged calls included, down to the smallest: 37 x 203 with 15 pairs 5.2 us, 8.8 by a copy and a kernel)
+    if (c->split_recon < 0) on_thin = reconstruct_thin_ok(r);
     if (c->split_recon != 0 && !on_thin) {
         // what the fp32 kernels would take, copies of ragged, misaligned or masked factors included
-        const double macs = (double)r.N * (double)c->J * (double)c->D;
         // (a call that needs no copy in a context that keeps room for them has no planes for slices of the pairs: 100 x 192
         // with 2048 pairs walks them in six workgroups, 41 us)
         double us = c->padded_factors && have_ws && !whole
@@ -401,8 +398,7 @@ sfb_status recon_launch(sfb_ctx* c, float* W, int64_t ldw, const float* U, int64
         if (reconstruct_split_ok(r)) {
             sp = &c->split_plans[n_rows > 0][have_ws];
             if (sp->slices > 1 && (size_t)sp->slices * (size_t)c->J * (size_t)c->D * sizeof(float) > workspace_need(c)) sp = &c->split_plans[n_rows > 0][0];
-            // (small enough, copy and kernel together are all latency, about the same either way)
-            on_split = c->split_recon == 1 || (sp->us < us && (whole || macs >= (r.use_mask ? 33e6 : 1e6)));
+            on_split = c->split_recon == 1 || sp->us < us;
             if (on_split) us = sp->us;
         }
         on_lists = same_step && c->lists != nullptr && c->split_recon < 0 &&

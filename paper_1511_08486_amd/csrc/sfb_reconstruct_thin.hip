@@ -124,6 +124,7 @@ static hipError_t launch_thin(const ReconArgs& a, hipStream_t s) {
 // Up to 64 pairs always (1000 x 4096: 7.9 us with 8 pairs, 10.6 with 64, against 14.9 and 12.0 with the kernels that stage
 // tiles; 2000 x 8192: 25 and 36 against 61 and 45; 300 x 1000: one launch, 5.6); up to 128 while W is small enough for
 // the matrix pipe's share not to show (4000 x 700 with 128: 15.0 against 16.8; 1000 x 4096: 17.5 against 16.1).
+// Not with a mask, which looks up the worker of every pair (256 x 1024 with 128: 10.6 against 6.8 by split products; 64 x 64: 10.2, 6.4).
 bool reconstruct_thin_ok(const ReconArgs& a) {
     const int64_t tiles = (int64_t)((a.J + 63) / 64) * ((a.D + 63) / 64);
     return !a.bf16 && tiles < (1LL << 31) && (a.N <= 64 || (a.N <= 128 && tiles <= 768 && !a.use_mask));

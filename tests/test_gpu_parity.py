@@ -66,7 +66,7 @@ def test_ragged_fp32_shapes_through_padded_factor_copies(sfb, name, over, varian
 
 
 def test_padded_factor_copies_are_what_the_reconstruction_reads(sfb):
-    """Ragged shape: after sfb_reconstruct_apply the workspace holds the factors as [32 x 40] and
+    """Ragged shape, fp32 instruction: after sfb_reconstruct_apply the workspace holds the factors as [32 x 40] and
     [32 x 256] (37 -> 40 columns, 203 -> 256, 15 -> 32 rows), zero outside, and a dead worker's rows
     zero whatever its slot held.  A register-staged variant, or a shape the kernels take as it is,
     leaves the workspace alone."""
@@ -81,6 +81,7 @@ def test_padded_factor_copies_are_what_the_reconstruction_reads(sfb):
     Uh_dead = Uh.copy()
     Uh_dead[B:2 * B] = np.nan                                   # what a dead worker's slot may hold
     ctx = sfb.Sfb("mlr", J, D, P, B, device=dev)
+    ctx.set_plan(fwd_dma=1)                                     # (by itself the call takes the kernel for few pairs)
     assert ctx.workspace_bytes() >= (Np * Jp + Np * Dp) * 4
     ws = ctx._ws.view(torch.float32)
     for variant, mask in ((-1, None), (-1, active), (0, None)):
@@ -118,7 +119,7 @@ def test_padded_factor_copies_are_what_the_reconstruction_reads(sfb):
 
 
 def test_a_dead_worker_in_a_whole_shape_goes_through_a_masked_copy_of_u(sfb):
-    """Whole shape, one dead worker: the reconstruction copies U with that worker's rows as zeros
+    """Whole shape, one dead worker, fp32 instruction: the reconstruction copies U with that worker's rows as zeros
     (whatever the slot held) into the front of the workspace and runs its usual kernel without a
     mask.  With V off the 16-byte grid the call falls back to the register-staged kernel, which
     carries the mask itself and leaves the workspace alone.  Both match the oracle."""
@@ -135,6 +136,7 @@ def test_a_dead_worker_in_a_whole_shape_goes_through_a_masked_copy_of_u(sfb):
     want = oracle.apply_update(W0.astype(np.float64), oracle.delta_w(U_masked, Vh, P, B, active=active), eta)
     Uh_dead = np.where(live[:, None], Uh, np.float32("nan"))
     ctx = sfb.Sfb("mlr", J, D, P, B, device=dev)
+    ctx.set_plan(fwd_dma=1)                                     # (by itself the call takes the split products)
     ws = ctx._ws.view(torch.float32)
     for misaligned in (False, True):
         ws.fill_(float("nan"))

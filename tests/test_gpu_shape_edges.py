@@ -193,6 +193,18 @@ def test_many_pairs_on_few_tiles_are_spread_over_the_chip():
     ctx.close()
 
 
+@pytest.mark.parametrize("J,D,P,B,masked,kernel", [
+    (37, 203, 3, 5, False, "reconstruct_thin_kernel"),          # ragged and small
+    (37, 203, 3, 5, True, "reconstruct_thin_kernel"),
+    (60, 90, 3, 60, False, "reconstruct_split_kernel"),         # 5 and 3 us less than a copy of the factors and a kernel
+    (260, 512, 4, 32, True, "reconstruct_split_kernel"),        # whole, but masked
+])
+def test_small_calls_leave_no_copies_of_their_factors(J, D, P, B, masked, kernel):
+    """Calls that the fp32 instruction's kernels take by way of a copy only: other kernels take them as they are."""
+    wl = workloads.make("l2svm", seed=J, J=J, D=D, P=P, B=B, density=0.5)
+    _one_step(wl, [p != 1 for p in range(P)] if masked else None, update=kernel)
+
+
 # Values that no three bf16 terms hold: infinities, and finite ones that round to an infinity in bf16.  What is infinite, or
 # as finite as in fp32, stays so; a whole row or column that depends on them is compared with numpy in fp64.
 @pytest.mark.parametrize("J,D,N", [(66, 130, 70), (130, 1030, 200), (200, 515, 1030)])
