@@ -283,6 +283,20 @@ def test_launch_plans_of_the_benchmark_shapes(lib):
         lib.sfb_destroy(ctx)
 
 
+def test_a_plan_that_keeps_everything_changes_nothing(lib):
+    """sfb_set_plan(0, 0, 0, -1, -1): a context of few classes keeps its one-pass step, whose planes it asks room for (80
+    samples of 2048 columns in five workgroups, 32 classes); a choice of the caller's is about the separate kernels."""
+    import paper_1511_08486_amd as sfb
+    ctx, need = C.c_void_p(), C.c_size_t()
+    assert lib.sfb_create(C.byref(ctx), sfb.SFB_MLR, 32, 2048, 5, 16, sfb.SFB_F32, None) == 0
+    assert lib.sfb_workspace_bytes(ctx, C.byref(need)) == 0 and need.value == 5 * 32 * 2048 * 4
+    assert lib.sfb_set_plan(ctx, 0, 0, 0, -1, -1) == 0
+    assert lib.sfb_workspace_bytes(ctx, C.byref(need)) == 0 and need.value == 5 * 32 * 2048 * 4
+    assert lib.sfb_set_plan(ctx, 0, 0, 0, 0, -1) == 0
+    assert lib.sfb_workspace_bytes(ctx, C.byref(need)) == 0 and need.value < 5 * 32 * 2048 * 4
+    lib.sfb_destroy(ctx)
+
+
 def test_measurement_aids_validate_their_arguments(lib):
     import paper_1511_08486_amd as sfb
     ctx = C.c_void_p()
