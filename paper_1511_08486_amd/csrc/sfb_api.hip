@@ -143,6 +143,28 @@ size_t workspace_need(const sfb_ctx* c) {
     return need > prox ? need : prox;
 }
 
+// The split products' plans.  apart: the caller chose them (sfb_set_plan), the smaller term products get sums of their own.
+void plan_split_scores(sfb_ctx* c, bool apart) {
+    const int64_t N = (int64_t)c->P * c->B;
+    // room for the partial scores: what ragged contexts reserve for their padded factor copies anyway, or a few MiB; the
+    // others the 16 MiB that sfb_step_noalloc has; or what the fp32 instruction's plan would take, where that is more
+    size_t most = SFB_NOALLOC_SCRATCH_BYTES;
+    if (c->padded_factors) {
+        most = conform_workspace(c->J, c->D, N);
+        if (most < ((size_t)4 << 20)) most = (size_t)4 << 20;
+    }
+    const size_t f32_need = (size_t)c->fwd_all.split_k * (size_t)N * (size_t)round_up4(c->J) * sizeof(float);
+    if (f32_need > most) most = f32_need;
+    c->fwd_split = plan_forward_split(N, c->J, c->D, most, apart);
+    c->fwd_split_worker = plan_forward_split(c->B, c->J, c->D, (size_t)c->fwd_split.split_k * (size_t)N * (size_t)round_up4(c->J) * sizeof(float), apart);
+}
+void plan_split_recon(sfb_ctx* c, bool apart) {
+    if (c->dtype != SFB_F32) return;
+    for (int one = 0; one < 2; ++one)
+        for (int with_ws = 0; with_ws < 2; ++with_ws)
+            c->split_plans[one][with_ws] = reconstruct_split_plan(c->J, c->D, one ? c->B : (int64_t)c->P * c->B, with_ws ? workspace_need(c) : 0, apart);
+}
+
 sfb_status hip_fail(sfb_ctx* c, hipError_t e) {
     c->last_hip = (int)e;
     return SFB_EHIP;
@@ -476,18 +498,8 @@ sfb_status sfb_create(sfb_ctx** out, sfb_model m, int64_t J, int64_t D, int32_t 
         c->padded_factors = input_dtype == SFB_F32 &&
                             !((J % 4) == 0 && J >= 4 && (D % 128) == 0 && (N % 32) == 0 && N >= 32);
         c->recon_padded = plan_reconstruct_padded(J, D, N, -1);
-        // room for the partial scores: what ragged contexts reserve for their padded factor copies anyway, or a few MiB; the
-        // others the 16 MiB that sfb_step_noalloc has; or what the fp32 instruction's plan would take, where that is more
-        size_t most = SFB_NOALLOC_SCRATCH_BYTES;
-        if (c->padded_factors) {
-            most = conform_workspace(J, D, N);
-            if (most < ((size_t)4 << 20)) most = (size_t)4 << 20;
-        }
-        const size_t f32_need = (size_t)c->fwd_all.split_k * (size_t)N * (size_t)round_up4(J) * sizeof(float);
-        if (f32_need > most) most = f32_need;
-        c->fwd_split = plan_forward_split(N, J, D, most);
-        c->fwd_split_worker = plan_forward_split(B, J, D, (size_t)c->fwd_split.split_k * (size_t)N * (size_t)round_up4(J) * sizeof(float));
     }
+    plan_split_scores(c, false);
     c->fused_ok = input_dtype == SFB_BF16 && m == SFB_MLR && fused_shape_ok(J, D, (int64_t)P * B);
     c->use_fused = true;
     c->fused = c->fused_ok ? plan_fused(J, D, (int64_t)P * B) : FusedPlan{};
@@ -497,11 +509,7 @@ sfb_status sfb_create(sfb_ctx** out, sfb_model m, int64_t J, int64_t D, int32_t 
         const size_t planes = few_workspace((int64_t)P * B, J, D);
         c->few = planes <= SFB_NOALLOC_SCRATCH_BYTES || planes <= workspace_need(c);
     }
-    if (input_dtype == SFB_F32) {
-        for (int one = 0; one < 2; ++one)
-            for (int with_ws = 0; with_ws < 2; ++with_ws)
-                c->split_plans[one][with_ws] = reconstruct_split_plan(J, D, one ? B : (int64_t)P * B, with_ws ? workspace_need(c) : 0);
-    }
+    plan_split_recon(c, false);
     c->ws = nullptr; c->ws_bytes = 0; c->lists = nullptr; c->lists_stored = 0; c->last_hip = 0; c->timing = false; c->sparse_forward = true; c->sparse_always = false;
     c->lists_always = false;
     for (LastKernel& k : c->last) k = LastKernel{nullptr, 0};
@@ -856,11 +864,13 @@ sfb_status sfb_set_plan(sfb_ctx* c, int32_t fwd_bm, int32_t fwd_bn, int32_t fwd_
     if (fwd_dma >= 0) c->lists_always = (fwd_dma & 64) != 0;    // bit 6 set: L2SVM steps update from the column lists wherever they fit
     if (fwd_dma >= 0) c->use_fused = (fwd_dma & 16) == 0;       // bit 4 set: sfb_step_pipelined runs two separate passes
     finish_forward_plan(&p, (int64_t)c->P * c->B, c->J, c->D);
+    if (fwd_dma >= 0 && c->split_scores) plan_split_scores(c, true);
     c->fwd_all = p;
     if (recon_variant >= 0) {
         c->recon = plan_reconstruct_variant(c->J, c->D, recon_variant);
         c->recon_padded = plan_reconstruct_padded(c->J, c->D, (int64_t)c->P * c->B, recon_variant);
     }
+    if (fwd_dma >= 0 && c->split_recon == 1) plan_split_recon(c, true);
     return SFB_OK;
 }
 

@@ -12,12 +12,12 @@
 
 namespace sfb {
 
-template <int MT, int NT, bool DIFF>
+template <int MT, int NT, bool DIFF, bool APART>
 __global__ __launch_bounds__(kSplitThreads, 2) void scores_split_kernel(
     const float* __restrict__ A, const float* __restrict__ A2, int64_t lda, const float* __restrict__ W, int64_t ldw,
     float* __restrict__ Z, int64_t ldz, int64_t zstride, float* __restrict__ Vout, int64_t ldv, int M, int N, int K,
     int k_slice, int n_mb, int n_nb, int total) {
-    using Tile = SplitTile<MT, NT, 64, true>;
+    using Tile = SplitTile<MT, NT, 64, true, APART>;
     constexpr int BM = Tile::BM, BN = Tile::BN;
     constexpr int A_IT = BM / 64, IT = (BM + BN) / 64;                   // 16-byte items per lane and chunk: of A, of A and W
     extern __shared__ __attribute__((aligned(16))) unsigned char ss_lds[];
@@ -158,20 +158,20 @@ bool forward_split_ok(const FwdArgs& a) {
     return !a.bf16 && a.D >= 4 && a.lda < (1 << 22) && a.ldw < (1 << 22);
 }
 
-template <int MT, int NT, bool DIFF>
+template <int MT, int NT, bool DIFF, bool APART>
 static hipError_t launch_split(const FwdArgs& a, const FwdPlan& p, hipStream_t s) {
-    using Tile = SplitTile<MT, NT, 64, true>;
+    using Tile = SplitTile<MT, NT, 64, true, APART>;
     constexpr size_t lds_bytes = Tile::LDS;
     static std::atomic<bool> raised{false};
     if (!raised) {
-        hipError_t e = hipFuncSetAttribute((const void*)scores_split_kernel<MT, NT, DIFF>,
+        hipError_t e = hipFuncSetAttribute((const void*)scores_split_kernel<MT, NT, DIFF, APART>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
         if (e != hipSuccess) return e;
         raised = true;
     }
     const int n_mb = (a.n_rows + Tile::BM - 1) / Tile::BM, n_nb = (a.J + Tile::BN - 1) / Tile::BN;
     const int total = n_mb * n_nb * p.split_k;
-    SFB_LAUNCH((scores_split_kernel<MT, NT, DIFF>), dim3(total), dim3(kSplitThreads), lds_bytes, s, (const float*)a.a,
+    SFB_LAUNCH((scores_split_kernel<MT, NT, DIFF, APART>), dim3(total), dim3(kSplitThreads), lds_bytes, s, (const float*)a.a,
                (const float*)a.a2, a.lda, a.w, a.ldw, a.zp, a.ldz, a.zstride, (float*)a.v, a.ldv, a.n_rows, a.J, a.D,
                p.k_slice, n_mb, n_nb, total);
     return hipGetLastError();
@@ -179,10 +179,15 @@ static hipError_t launch_split(const FwdArgs& a, const FwdPlan& p, hipStream_t s
 
 template <bool DIFF>
 static hipError_t launch_split_tile(const FwdArgs& a, const FwdPlan& p, hipStream_t s) {
-    if (p.bm == 128 && p.bn == 128) return launch_split<2, 2, DIFF>(a, p, s);
-    if (p.bm == 128 && p.bn == 64) return launch_split<2, 1, DIFF>(a, p, s);
-    if (p.bm == 64 && p.bn == 128) return launch_split<1, 2, DIFF>(a, p, s);
-    if (p.bm == 64 && p.bn == 64) return launch_split<1, 1, DIFF>(a, p, s);
+    if (p.apart) {
+        if (p.bm == 64 && p.bn == 128) return launch_split<1, 2, DIFF, true>(a, p, s);
+        if (p.bm == 64 && p.bn == 64) return launch_split<1, 1, DIFF, true>(a, p, s);
+        return hipErrorInvalidValue;
+    }
+    if (p.bm == 128 && p.bn == 128) return launch_split<2, 2, DIFF, false>(a, p, s);
+    if (p.bm == 128 && p.bn == 64) return launch_split<2, 1, DIFF, false>(a, p, s);
+    if (p.bm == 64 && p.bn == 128) return launch_split<1, 2, DIFF, false>(a, p, s);
+    if (p.bm == 64 && p.bn == 64) return launch_split<1, 1, DIFF, false>(a, p, s);
     return hipErrorInvalidValue;
 }
 
@@ -192,8 +197,9 @@ static hipError_t launch_split_tile(const FwdArgs& a, const FwdPlan& p, hipStrea
 // pay more LDS traffic per product), three 64 x 64 workgroups share a unit, every further round of 256 workgroups
 // restarts for 1.7 us, and a slice's partial scores are written and read back at about 2.2 TB/s together, one plane after
 // the other: 0.1 us more each (3 classes x 3072, 976 samples: 20 slices instead of 27, 14.9 -> 13.0 us; 20 x 5504: 18.7 -> 16.7).
-// `most` bounds the bytes of partial scores (the caller's room for them); one slice is always allowed.
-FwdPlan plan_forward_split(int64_t n_rows, int64_t J, int64_t D, size_t most) {
+// `most` bounds the bytes of partial scores (the caller's room for them); one slice is always allowed.  apart: the tiles of
+// 64 samples (the smaller products' sums apart).
+FwdPlan plan_forward_split(int64_t n_rows, int64_t J, int64_t D, size_t most, bool apart) {
     static const struct { int bm, bn, resident; double chunk_us, lone_us; } tiles[4] = {
         {128, 128, 1, 1.10, 1.10}, {64, 128, 1, 0.72, 0.72}, {128, 64, 1, 0.72, 0.72}, {64, 64, 3, 0.40, 0.44}};
     FwdPlan p{};
@@ -201,7 +207,9 @@ FwdPlan plan_forward_split(int64_t n_rows, int64_t J, int64_t D, size_t most) {
     double best = 1e300;
     const int64_t chunks = (D + kSpChunk - 1) / kSpChunk;
     const double plane = (double)n_rows * (double)((J + 3) / 4 * 4) * 4.0;
+    p.apart = apart;
     for (const auto& t : tiles) {
+        if (apart && t.bm != 64) continue;
         const int64_t n = ((n_rows + t.bm - 1) / t.bm) * ((J + t.bn - 1) / t.bn);
         for (int64_t s = 1; s <= 32; ++s) {
             if (s > 1 && (s * 2 > chunks || (double)s * plane > (double)most)) break;

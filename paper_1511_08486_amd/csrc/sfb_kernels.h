@@ -44,6 +44,7 @@ struct FwdPlan {
     int k_slice;     // columns of D per slice (multiple of the K chunk)
     int grid;        // workgroups
     bool dma;        // stage tiles by LDS-DMA where the shape allows
+    bool apart;      // split products: the smaller term products in sums of their own
 };
 
 // Chooses tile and split for Z[n_rows][J] = A W^T with contraction length D.
@@ -68,7 +69,7 @@ struct FwdArgs {
 hipError_t launch_forward(const FwdArgs& a, const FwdPlan& p, hipStream_t s);
 // fp32 scores on the bf16 matrix cores, every operand split exactly into three bf16 terms (sfb_forward_split.hip)
 bool forward_split_ok(const FwdArgs& a);
-FwdPlan plan_forward_split(int64_t n_rows, int64_t J, int64_t D, size_t most);
+FwdPlan plan_forward_split(int64_t n_rows, int64_t J, int64_t D, size_t most, bool apart);
 hipError_t launch_forward_split(const FwdArgs& a, const FwdPlan& p, hipStream_t s);
 
 // Dual side of SDCA (Section 2.1): with `dual` set, the MLR factor kernel turns its
@@ -221,8 +222,8 @@ bool reconstruct_split_ok(const ReconArgs& a);
 // few factor pairs, bound by W's trip through memory (sfb_reconstruct_thin.hip); any shape and alignment
 bool reconstruct_thin_ok(const ReconArgs& a);
 hipError_t launch_reconstruct_thin(const ReconArgs& a, hipStream_t s);
-struct SplitReconPlan { int bm, bn, slices; double us; };                            // tile, slices of the pairs, estimated time
-SplitReconPlan reconstruct_split_plan(int64_t J, int64_t D, int64_t N, size_t room);   // room: bytes for planes of sums
+struct SplitReconPlan { int bm, bn, slices; bool apart; double us; };                // tile, slices of the pairs, sums apart, estimated time
+SplitReconPlan reconstruct_split_plan(int64_t J, int64_t D, int64_t N, size_t room, bool apart);   // room: bytes for planes of sums
 hipError_t launch_reconstruct_split(const ReconArgs& a, const SplitReconPlan& p, hipStream_t s);
 
 // Reconstruction from the stored entries of sparse features (sfb_sparse_update.hip): column lists made from the dense

@@ -21,8 +21,8 @@ namespace sfb {
 
 typedef float rs_f32x2u __attribute__((ext_vector_type(2), aligned(4)));
 
-template <int MT, int NT>
-using ReconTile = SplitTile<MT, NT, NT == 2 ? 64 : 80, NT == 2>;
+template <int MT, int NT, bool APART>
+using ReconTile = SplitTile<MT, NT, NT == 2 ? 64 : 80, NT == 2, APART>;
 
 // column of the tile's A or B part that LDS row r holds
 template <int NT>
@@ -32,12 +32,12 @@ __device__ __forceinline__ int rs_column(int r) {
 
 // PLANES: the workgroups of slice k contract over k_chunks chunks of pairs and store their bare sums in plane k of W
 // (a workspace then); apply_partials_kernel adds the planes up.
-template <int MT, int NT, bool PLANES>
+template <int MT, int NT, bool PLANES, bool APART>
 __global__ __launch_bounds__(kSplitThreads, 2) void reconstruct_split_kernel(
     float* __restrict__ W, int64_t ldw, const float* __restrict__ U, int64_t ldu, const float* __restrict__ V,
     int64_t ldv, int J, int D, int N, float alpha, int n_jb, int tiles, int total, int k_chunks, int prox_kind, float prox_a,
     uint64_t live_mask, uint32_t inv_b) {
-    using Tile = ReconTile<MT, NT>;
+    using Tile = ReconTile<MT, NT, APART>;
     constexpr int BM = Tile::BM, BN = Tile::BN;
     constexpr bool PAIRS = NT == 2;                                      // the permuted layout: two columns of W per lane
     extern __shared__ __attribute__((aligned(16))) unsigned char rs_lds[];
@@ -196,13 +196,13 @@ bool reconstruct_split_ok(const ReconArgs& a) {
            (!a.use_mask || (a.B > 1 && (int64_t)a.N * a.B < (1LL << 32)));
 }
 
-template <int MT, int NT, bool PLANES>
+template <int MT, int NT, bool PLANES, bool APART>
 static hipError_t launch_split(const ReconArgs& a, int slices, hipStream_t s) {
-    using Tile = ReconTile<MT, NT>;
+    using Tile = ReconTile<MT, NT, APART>;
     constexpr size_t lds_bytes = Tile::LDS;
     static std::atomic<bool> raised{false};
     if (!raised) {
-        hipError_t e = hipFuncSetAttribute((const void*)reconstruct_split_kernel<MT, NT, PLANES>,
+        hipError_t e = hipFuncSetAttribute((const void*)reconstruct_split_kernel<MT, NT, PLANES, APART>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
         if (e != hipSuccess) return e;
         raised = true;
@@ -211,7 +211,7 @@ static hipError_t launch_split(const ReconArgs& a, int slices, hipStream_t s) {
     const int tiles = n_jb * n_db, chunks = (a.N + kSpChunk - 1) / kSpChunk;
     const int k_chunks = (chunks + slices - 1) / slices;
     const uint32_t inv_b = a.use_mask ? (uint32_t)(((1ull << 32) + a.B - 1) / a.B) : 0;
-    SFB_LAUNCH((reconstruct_split_kernel<MT, NT, PLANES>), dim3(tiles * slices), dim3(kSplitThreads), lds_bytes, s,
+    SFB_LAUNCH((reconstruct_split_kernel<MT, NT, PLANES, APART>), dim3(tiles * slices), dim3(kSplitThreads), lds_bytes, s,
                PLANES ? a.partial : a.w, PLANES ? (int64_t)a.D : a.ldw, a.u, a.ldu, (const float*)a.v, a.ldv, a.J, a.D, a.N,
                a.alpha, n_jb, tiles, tiles * slices, k_chunks, a.prox_kind, a.prox_a, a.live_mask, inv_b);
     return hipGetLastError();
@@ -224,13 +224,14 @@ static hipError_t launch_split(const ReconArgs& a, int slices, hipStream_t s) {
 // 256 -> 165 at 4096; 600 x 784 with 1024: 26 -> 20.5.
 // Where the tiles leave compute units idle the pairs are cut into slices, at most 64 and as many as `room` bytes hold
 // planes of J x D sums for; adding those up is a second kernel.
-SplitReconPlan reconstruct_split_plan(int64_t J, int64_t D, int64_t N, size_t room) {
+SplitReconPlan reconstruct_split_plan(int64_t J, int64_t D, int64_t N, size_t room, bool apart) {
     static const struct { int bm, bn, resident; double chunk_us, lone_us; } tiles[3] = {
         {128, 128, 1, 1.04, 1.04}, {64, 128, 1, 0.63, 0.63}, {64, 64, 3, 0.42, 0.38}};
     const int64_t chunks = (N + kSpChunk - 1) / kSpChunk;
     const double w_mb = 8e-6 * (double)J * (double)D;
-    SplitReconPlan best{0, 0, 1, 1e300};
+    SplitReconPlan best{0, 0, 1, apart, 1e300};
     for (const auto& t : tiles) {
+        if (apart && t.bm != 64) continue;                                        // (the smaller products' sums apart)
         const int64_t n = ((J + t.bm - 1) / t.bm) * ((D + t.bn - 1) / t.bn);
         for (int64_t s = 1; s <= 64 && (s == 1 || ((size_t)(s * J * D) * sizeof(float) <= room && chunks >= 2 * s && n * s <= 1536)); ++s) {
             const int64_t per = (chunks + s - 1) / s;
@@ -240,25 +241,30 @@ SplitReconPlan reconstruct_split_plan(int64_t J, int64_t D, int64_t N, size_t ro
             const double a = t.lone_us * deep, b = t.chunk_us * rounds;
             double us = 5.6 + (double)per * (a > b ? a : b) + (t.resident == 1 ? 2.8 * (rounds - 1.0) : 0.0);
             us += s == 1 ? 0.14 * w_mb : 3.5 + 0.1 * (double)s * w_mb;            // planes written and read, W read and written
-            if (us < best.us) best = SplitReconPlan{t.bm, t.bn, (int)s, us};
+            if (us < best.us) best = SplitReconPlan{t.bm, t.bn, (int)s, apart, us};
         }
     }
     return best;
 }
 
-template <int MT, int NT>
+template <int MT, int NT, bool APART>
 static hipError_t launch_tile(const ReconArgs& a, int slices, hipStream_t s) {
-    if (slices == 1) return launch_split<MT, NT, false>(a, 1, s);
-    const hipError_t e = launch_split<MT, NT, true>(a, slices, s);
+    if (slices == 1) return launch_split<MT, NT, false, APART>(a, 1, s);
+    const hipError_t e = launch_split<MT, NT, true, APART>(a, slices, s);
     return e != hipSuccess ? e : launch_apply_partials(a, slices, a.D, s);
 }
 
 // plan.slices > 1: a.partial holds that many planes of J x D floats
 hipError_t launch_reconstruct_split(const ReconArgs& a, const SplitReconPlan& p, hipStream_t s) {
     if (p.slices < 1 || (p.slices > 1 && a.partial == nullptr)) return hipErrorInvalidValue;
-    if (p.bm == 128 && p.bn == 128) return launch_tile<2, 2>(a, p.slices, s);
-    if (p.bm == 64 && p.bn == 128) return launch_tile<1, 2>(a, p.slices, s);
-    if (p.bm == 64 && p.bn == 64) return launch_tile<1, 1>(a, p.slices, s);
+    if (p.apart) {
+        if (p.bm == 64 && p.bn == 128) return launch_tile<1, 2, true>(a, p.slices, s);
+        if (p.bm == 64 && p.bn == 64) return launch_tile<1, 1, true>(a, p.slices, s);
+        return hipErrorInvalidValue;
+    }
+    if (p.bm == 128 && p.bn == 128) return launch_tile<2, 2, false>(a, p.slices, s);
+    if (p.bm == 64 && p.bn == 128) return launch_tile<1, 2, false>(a, p.slices, s);
+    if (p.bm == 64 && p.bn == 64) return launch_tile<1, 1, false>(a, p.slices, s);
     return hipErrorInvalidValue;
 }
 

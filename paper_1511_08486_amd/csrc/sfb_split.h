@@ -3,7 +3,8 @@
 //
 // gfx950 multiplies bf16 sixteen times faster than fp32 on its matrix cores.  Every fp32 operand is split EXACTLY into
 // three bf16 terms, x = h + m + l (h = bf16(x), m = bf16(x - h), l = bf16(x - h - m): 3 x 8 significand bits cover
-// fp32's 24, and both differences are exact in fp32), and a product a * b is taken as the six term products whose
+// fp32's 24, and both differences are exact in fp32; below 2^-109 l runs out of bf16's exponents: sums of operands of 2^-118
+// are off by 3e-7, of 2^-120 by 1e-6, of 2^-125 by 3e-5, where the fp32 instruction keeps 1e-7), and a product a * b is taken as the six term products whose
 // weight is at least 2^-16 of the leading one:
 //     a_h b_h  +  (a_h b_m + a_m b_h)  +  (a_h b_l + a_l b_h + a_m b_m).
 // Each is exact in the fp32 accumulator's input (8 x 8 bits).  What is left out (a_m b_l + a_l b_m + a_l b_l) is below
@@ -78,7 +79,11 @@ struct SplitQuad {
 
 // The multiplying side.  Tile (2 MT x 32) x (2 NT x 32), four wavefronts as 2 x 2, each MT x NT blocks of 32 x 32.
 // PITCH: bytes from one LDS row to the next; SWZ: 16-byte item c of row r sits at c ^ f(r) instead of c.
-template <int MT, int NT, int PITCH, bool SWZ>
+// APART: the five smaller term products have sums of their own, so that the leading ones' running sum is rounded once for
+// every sixteen k instead of six times (error of a sum of 4096 products 1.4e-7 instead of 2.5e-7, of 512 1.3e-7 instead of
+// 2.4e-7; the fp32 instruction 5.8e-7 and 2.9e-7): for callers who chose these products for their accuracy (sfb_set_plan).
+// No time of its own, but 64 x 64 blocks of a wavefront have no registers left for it.
+template <int MT, int NT, int PITCH, bool SWZ, bool APART>
 struct SplitTile {
     static constexpr int BM = 64 * MT, BN = 64 * NT, ROWS = BM + BN;
     static constexpr int PLANE = ROWS * PITCH, BYTES = 3 * PLANE;      // one group's buffer
@@ -90,7 +95,8 @@ struct SplitTile {
     static __device__ __forceinline__ int swz(int r) { return SWZ ? (((r >> 2) & 1) | ((((r >> 1) ^ (r >> 3)) & 1) << 1)) : 0; }
 
     struct Frag { sp_u32x4 a[3][MT], b[3][NT]; };
-    f32x16 acc[MT][NT];
+    static_assert(!APART || MT * NT <= 2, "registers");
+    f32x16 acc[MT][NT], rest[APART ? MT : 1][APART ? NT : 1];
     int a_base, b_base;            // byte offset of this lane's item in the A and the B part
 
     __device__ __forceinline__ void init(int wave, int lane) {
@@ -104,7 +110,10 @@ struct SplitTile {
 #pragma unroll
             for (int j = 0; j < NT; ++j)
 #pragma unroll
-                for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+                for (int e = 0; e < 16; ++e) {
+                    acc[i][j][e] = 0.f;
+                    if constexpr (APART) rest[i][j][e] = 0.f;
+                }
     }
     // fragment read Q of the 3 (MT + NT): plane by plane, A blocks then B blocks
     static constexpr int READS = 3 * (MT + NT), MFMAS = 6 * MT * NT;
@@ -119,7 +128,8 @@ struct SplitTile {
     __device__ __forceinline__ void mma(const Frag& f) {
         constexpr int PA[6] = {2, 0, 1, 1, 0, 0}, PB[6] = {0, 2, 1, 0, 1, 0};
         constexpr int T = Q / (MT * NT), I = Q / NT % MT, J = Q % NT;
-        acc[I][J] = split_mfma(f.a[PA[T]][I], f.b[PB[T]][J], acc[I][J]);
+        if constexpr (APART && T < 5) rest[I][J] = split_mfma(f.a[PA[T]][I], f.b[PB[T]][J], rest[I][J]);
+        else acc[I][J] = split_mfma(f.a[PA[T]][I], f.b[PB[T]][J], acc[I][J]);
     }
     // fetch(raw, c): requests this lane's raw words of chunk c (c may be past the end: anything valid).
     // prep(raw, c):  what has to happen to them before they are split, branches included.
@@ -184,6 +194,14 @@ struct SplitTile {
     // g = wave / 4: this wavefront finishes half of the entries of its blocks, its partner in the other group the other
     // half.  (k 0..15) + (k 16..31): one fixed order.
     __device__ __forceinline__ void exchange(int wave, int lane, unsigned char* lds, float (&sum)[MT][NT][8]) {
+        if constexpr (APART) {
+#pragma unroll
+            for (int i = 0; i < MT; ++i)
+#pragma unroll
+                for (int j = 0; j < NT; ++j)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) acc[i][j][e] += rest[i][j][e];
+        }
         const int g = wave >> 2;
         split_barrier();                                 // everybody is done with the buffers
         float* x = reinterpret_cast<float*>(lds);
