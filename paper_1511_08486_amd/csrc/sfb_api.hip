@@ -403,7 +403,7 @@ sfb_status recon_launch(sfb_ctx* c, float* W, int64_t ldw, const float* U, int64
         if (e != hipSuccess) return hip_fail(c, e);
         return SFB_OK;
     }
-    bool on_split = false, on_lists = false, on_thin = false;
+    bool on_split = false, halves = false, on_lists = false, on_thin = false;
     const bool have_ws = c->ws != nullptr && c->ws_bytes >= workspace_need(c);
     const SplitReconPlan* sp = nullptr;
     const bool whole = reconstruct_takes_dma(r, c->recon);
@@ -420,8 +420,14 @@ sfb_status recon_launch(sfb_ctx* c, float* W, int64_t ldw, const float* U, int64
         if (reconstruct_split_ok(r)) {
             sp = &c->split_plans[n_rows > 0][have_ws];
             if (sp->slices > 1 && (size_t)sp->slices * (size_t)c->J * (size_t)c->D * sizeof(float) > workspace_need(c)) sp = &c->split_plans[n_rows > 0][0];
-            on_split = c->split_recon == 1 || sp->us < us;
-            if (on_split) us = sp->us;
+            // The kernel these products stand in for adds its sums in four parts where J is 600 or 1160, say, and is the more
+            // accurate one unless they are cut in two: 600 x 4096 with 1024 pairs, of the norm, 2.9e-7 (mixed signs) and
+            // 1.3e-7 (all positive) against 3.4e-7 and 1.9e-7 in one piece (39.6 us), 2.4e-7 and 1.1e-7 in two (42.7; that
+            // kernel 51)
+            halves = c->split_recon < 0 && sp->slices == 1 && r.N > 128 && reconstruct_plan_cuts_pairs(whole ? c->recon : c->recon_padded);
+            const double split_us = sp->us + (halves ? 3.2 : 0.0);
+            on_split = c->split_recon == 1 || split_us < us;
+            if (on_split) us = split_us;
         }
         on_lists = same_step && c->lists != nullptr && c->split_recon < 0 &&
                    sparse_update_us(r.N, c->J, c->D, c->lists_stored) < us;
@@ -436,7 +442,7 @@ sfb_status recon_launch(sfb_ctx* c, float* W, int64_t ldw, const float* U, int64
         e = launch_sparse_update(r, c->lists_stored, c->lists, c->stream);
     } else if (on_split) {
         r.partial = sp->slices > 1 ? (float*)c->ws : nullptr;
-        e = launch_reconstruct_split(r, *sp, c->stream);
+        e = launch_reconstruct_split(r, *sp, halves, c->stream);
     } else {
         // calls that would end in the register-staged kernel first try a copy of the factors that the LDS-DMA
         // kernels accept: padded ones for ragged shapes, U with a dead worker's rows zeroed for a masked call

@@ -224,7 +224,10 @@ bool reconstruct_thin_ok(const ReconArgs& a);
 hipError_t launch_reconstruct_thin(const ReconArgs& a, hipStream_t s);
 struct SplitReconPlan { int bm, bn, slices; bool apart; double us; };                // tile, slices of the pairs, sums apart, estimated time
 SplitReconPlan reconstruct_split_plan(int64_t J, int64_t D, int64_t N, size_t room, bool apart);   // room: bytes for planes of sums
-hipError_t launch_reconstruct_split(const ReconArgs& a, const SplitReconPlan& p, hipStream_t s);
+// halves: calls without slices let the running sums start anew half way through the pairs
+hipError_t launch_reconstruct_split(const ReconArgs& a, const SplitReconPlan& p, bool halves, hipStream_t s);
+// true where the fp32 instruction's plan is the kernel that cuts every contraction in four (variant 11)
+bool reconstruct_plan_cuts_pairs(const ReconPlan& p);
 
 // Reconstruction from the stored entries of sparse features (sfb_sparse_update.hip): column lists made from the dense
 // rows V, then W += alpha U^T V over the entries only.  workspace: sparse_update_workspace(D, stored) bytes, 256-byte

@@ -35,7 +35,7 @@ __device__ __forceinline__ int rs_column(int r) {
 template <int MT, int NT, bool PLANES, bool APART>
 __global__ __launch_bounds__(kSplitThreads, 2) void reconstruct_split_kernel(
     float* __restrict__ W, int64_t ldw, const float* __restrict__ U, int64_t ldu, const float* __restrict__ V,
-    int64_t ldv, int J, int D, int N, float alpha, int n_jb, int tiles, int total, int k_chunks, int prox_kind, float prox_a,
+    int64_t ldv, int J, int D, int N, float alpha, int n_jb, int tiles, int total, int k_chunks, bool halves, int prox_kind, float prox_a,
     uint64_t live_mask, uint32_t inv_b) {
     using Tile = ReconTile<MT, NT, APART>;
     constexpr int BM = Tile::BM, BN = Tile::BN;
@@ -48,7 +48,9 @@ __global__ __launch_bounds__(kSplitThreads, 2) void reconstruct_split_kernel(
     const int jb = tile % n_jb, db = tile / n_jb;
     const int j0 = jb * BM, d0 = db * BN;
     const int n_chunks = (N + kSpChunk - 1) / kSpChunk;
-    const int c_begin = PLANES ? slice * k_chunks : 0;                   // host: no slice is empty
+    int c_begin = PLANES ? slice * k_chunks : 0;                         // host: no slice is empty
+    const int c_end = PLANES ? min(n_chunks, c_begin + k_chunks) : n_chunks;
+    const int n_begin = c_begin * kSpChunk, n_end = min(N, c_end * kSpChunk);
 
     // lane block: pairs 4 kb .. 4 kb + 3, columns 4 rb .. 4 rb + 3 of the BM columns of U and BN of V side by side
     // (four consecutive lanes read 64 contiguous bytes: with lanes of different rows side by side, rows a multiple of 32
@@ -115,7 +117,23 @@ __global__ __launch_bounds__(kSplitThreads, 2) void reconstruct_split_kernel(
 
     Tile t;
     t.init(wave, lane);
-    t.template run<Raw, State, 16, false, 2>(PLANES ? min(k_chunks, n_chunks - c_begin) : n_chunks, rs_lds, fetch, prep, park);
+    // halves: the first half's sums wait in LDS behind the buffers while the second half's start anew
+    float* const first = reinterpret_cast<float*>(rs_lds + Tile::LDS) + wave * (MT * NT * 8 * 64) + lane;
+    float sum[MT][NT][8];
+    if (!PLANES && halves) {
+        t.template run<Raw, State, 16, false, 2>(n_chunks / 2, rs_lds, fetch, prep, park);
+        c_begin = n_chunks / 2;
+        t.exchange(wave, lane, rs_lds, sum);
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+#pragma unroll
+            for (int j = 0; j < NT; ++j)
+#pragma unroll
+                for (int q = 0; q < 8; ++q) first[((i * NT + j) * 8 + q) * 64] = sum[i][j][q];
+        split_barrier();                                                 // (the second half's first chunk goes where others still read)
+        t.init(wave, lane);
+    }
+    t.template run<Raw, State, 16, false, 2>(c_end - c_begin, rs_lds, fetch, prep, park);
 
     // the entries of W this wavefront finishes: requested before the exchange, used after it (requested before the
     // contraction they stand in front of its loads in the in-order queue: 0.3 to 0.8 us slower)
@@ -139,9 +157,15 @@ __global__ __launch_bounds__(kSplitThreads, 2) void reconstruct_split_kernel(
                 w[i][0][q] = row[min(dcol, D - 1)];
             }
         }
-    float sum[MT][NT][8];
     t.exchange(wave, lane, rs_lds, sum);
-    const int n_begin = c_begin * kSpChunk, n_end = PLANES ? min(N, n_begin + k_chunks * kSpChunk) : N;
+    if (!PLANES && halves) {
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+#pragma unroll
+            for (int j = 0; j < NT; ++j)
+#pragma unroll
+                for (int q = 0; q < 8; ++q) sum[i][j][q] += first[((i * NT + j) * 8 + q) * 64];
+    }
     t.mend(wave, sum, [&](int i, int j) {
         const int half = lane >> 5;
         const float* u = U + min(j0 + rs_column<NT>((wm * MT + i) * 32 + l32), J - 1);
@@ -197,13 +221,15 @@ bool reconstruct_split_ok(const ReconArgs& a) {
 }
 
 template <int MT, int NT, bool PLANES, bool APART>
-static hipError_t launch_split(const ReconArgs& a, int slices, hipStream_t s) {
+static hipError_t launch_split(const ReconArgs& a, int slices, bool halves, hipStream_t s) {
     using Tile = ReconTile<MT, NT, APART>;
-    constexpr size_t lds_bytes = Tile::LDS;
+    constexpr size_t most = Tile::LDS + (PLANES ? 0 : Tile::XCHG);
+    static_assert(most <= 160 * 1024, "LDS");
+    const size_t lds_bytes = halves ? most : (size_t)Tile::LDS;
     static std::atomic<bool> raised{false};
     if (!raised) {
         hipError_t e = hipFuncSetAttribute((const void*)reconstruct_split_kernel<MT, NT, PLANES, APART>,
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)most);
         if (e != hipSuccess) return e;
         raised = true;
     }
@@ -213,7 +239,7 @@ static hipError_t launch_split(const ReconArgs& a, int slices, hipStream_t s) {
     const uint32_t inv_b = a.use_mask ? (uint32_t)(((1ull << 32) + a.B - 1) / a.B) : 0;
     SFB_LAUNCH((reconstruct_split_kernel<MT, NT, PLANES, APART>), dim3(tiles * slices), dim3(kSplitThreads), lds_bytes, s,
                PLANES ? a.partial : a.w, PLANES ? (int64_t)a.D : a.ldw, a.u, a.ldu, (const float*)a.v, a.ldv, a.J, a.D, a.N,
-               a.alpha, n_jb, tiles, tiles * slices, k_chunks, a.prox_kind, a.prox_a, a.live_mask, inv_b);
+               a.alpha, n_jb, tiles, tiles * slices, k_chunks, halves, a.prox_kind, a.prox_a, a.live_mask, inv_b);
     return hipGetLastError();
 }
 
@@ -248,23 +274,24 @@ SplitReconPlan reconstruct_split_plan(int64_t J, int64_t D, int64_t N, size_t ro
 }
 
 template <int MT, int NT, bool APART>
-static hipError_t launch_tile(const ReconArgs& a, int slices, hipStream_t s) {
-    if (slices == 1) return launch_split<MT, NT, false, APART>(a, 1, s);
-    const hipError_t e = launch_split<MT, NT, true, APART>(a, slices, s);
+static hipError_t launch_tile(const ReconArgs& a, int slices, bool halves, hipStream_t s) {
+    if (slices == 1) return launch_split<MT, NT, false, APART>(a, 1, halves, s);
+    const hipError_t e = launch_split<MT, NT, true, APART>(a, slices, false, s);
     return e != hipSuccess ? e : launch_apply_partials(a, slices, a.D, s);
 }
 
 // plan.slices > 1: a.partial holds that many planes of J x D floats
-hipError_t launch_reconstruct_split(const ReconArgs& a, const SplitReconPlan& p, hipStream_t s) {
+hipError_t launch_reconstruct_split(const ReconArgs& a, const SplitReconPlan& p, bool halves, hipStream_t s) {
+    halves = halves && a.N > 4 * kSpChunk;                               // two chunks or more in each
     if (p.slices < 1 || (p.slices > 1 && a.partial == nullptr)) return hipErrorInvalidValue;
     if (p.apart) {
-        if (p.bm == 64 && p.bn == 128) return launch_tile<1, 2, true>(a, p.slices, s);
-        if (p.bm == 64 && p.bn == 64) return launch_tile<1, 1, true>(a, p.slices, s);
+        if (p.bm == 64 && p.bn == 128) return launch_tile<1, 2, true>(a, p.slices, halves, s);
+        if (p.bm == 64 && p.bn == 64) return launch_tile<1, 1, true>(a, p.slices, halves, s);
         return hipErrorInvalidValue;
     }
-    if (p.bm == 128 && p.bn == 128) return launch_tile<2, 2, false>(a, p.slices, s);
-    if (p.bm == 64 && p.bn == 128) return launch_tile<1, 2, false>(a, p.slices, s);
-    if (p.bm == 64 && p.bn == 64) return launch_tile<1, 1, false>(a, p.slices, s);
+    if (p.bm == 128 && p.bn == 128) return launch_tile<2, 2, false>(a, p.slices, halves, s);
+    if (p.bm == 64 && p.bn == 128) return launch_tile<1, 2, false>(a, p.slices, halves, s);
+    if (p.bm == 64 && p.bn == 64) return launch_tile<1, 1, false>(a, p.slices, halves, s);
     return hipErrorInvalidValue;
 }
 

@@ -59,9 +59,14 @@ __global__ __launch_bounds__(256, STAGES > 4 ? 2 : 4) void reconstruct_thin_kern
     __builtin_amdgcn_s_barrier();
     const float* a_at = rt_lds + half * 64 + (wave >> 1) * 32 + l32;
     const float* b_at = rt_lds + (PAIRS + half) * 64 + (wave & 1) * 32 + l32;
-    f32x16 acc;
+    // Running sums: two, as in the 128 x 128 kernel that this one mostly stands in for, four where there are registers for them
+    // (of the norm, 64 pairs: 1.07e-7, one sum 1.44e-7; 128: 1.1e-7 and 2.0e-7; the same time)
+    constexpr int SUMS = STAGES > 4 ? 4 : 2;
+    f32x16 acc[SUMS];
 #pragma unroll
-    for (int e = 0; e < 16; ++e) acc[e] = 0.f;
+    for (int p = 0; p < SUMS; ++p)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[p][e] = 0.f;
     // a stage's fragments are read while the products of the one before are formed
     struct Frags { float a[kThinStage / 2], b[kThinStage / 2]; } fr[2];
     auto read = [&](Frags& f, int c) {
@@ -86,12 +91,16 @@ __global__ __launch_bounds__(256, STAGES > 4 ? 2 : 4) void reconstruct_thin_kern
                 x = on ? x : 0.f;
                 y = on ? y : 0.f;
             }
-            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x, y, acc, 0, 0, 0);
+            acc[i % SUMS] = __builtin_amdgcn_mfma_f32_32x32x2f32(x, y, acc[i % SUMS], 0, 0, 0);
         }
         __builtin_amdgcn_sched_barrier(0);
     }
 #pragma unroll
-    for (int e = 0; e < 16; ++e) w[e] += alpha * acc[e];
+    for (int e = 0; e < 16; ++e) {
+        float sum = acc[0][e] + acc[1][e];
+        if constexpr (SUMS == 4) sum += acc[2][e] + acc[3][e];
+        w[e] += alpha * sum;
+    }
     if (prox_kind != 0) {
 #pragma unroll
         for (int e = 0; e < 16; ++e) w[e] = prox_entry(w[e], prox_kind, prox_a);

@@ -317,6 +317,37 @@ def test_split_products_that_were_chosen_keep_the_smaller_terms_apart(J, D, N):
     assert max(errs) < 1.8e-7
 
 
+@pytest.mark.parametrize("J,D,N,kernel", [
+    (600, 4096, 1024, "reconstruct_split_kernel"),              # stand-ins for the kernel that cuts every sum in four
+    (1160, 2048, 1088, "reconstruct_split_kernel"),
+    (600, 4096, 128, "reconstruct_thin_kernel"),
+    (1000, 4096, 64, "reconstruct_thin_kernel"),                # ... in two
+    (1000, 4096, 512, "reconstruct_split_kernel"),
+    (300, 1000, 128, "reconstruct_thin_kernel"),                # ... that does not cut them
+])
+@pytest.mark.parametrize("positive", [False, True])
+def test_updates_are_as_accurate_as_with_the_fp32_instruction_kernels(J, D, N, kernel, positive):
+    """Error of the default update against fp64, of the norm: no larger than that of the kernels the caller can have instead
+    (2 % for the rounding of the result)."""
+    import paper_1511_08486_amd as sfb
+    g = torch.Generator().manual_seed(J + N)
+    draw = (lambda *s: torch.rand(*s, generator=g) + 0.1) if positive else (lambda *s: torch.randn(*s, generator=g))
+    U, V = draw(N, J).to("cuda:0"), draw(N, D).to("cuda:0")
+    want, errs = U.double().T @ V.double(), []
+    for plan in (None, dict(fwd_dma=1)):
+        ctx = sfb.Sfb("mlr", J, D, N // 32, 32, device="cuda:0")
+        if plan:
+            ctx.set_plan(**plan)
+        W = torch.zeros((J, D), device="cuda:0")
+        ctx.reconstruct_apply(W, U, V, -1.0, scale=1.0)
+        ctx.sync()
+        assert plan or ctx.last_kernel(2)[0] == kernel
+        errs.append(float((W.double() - want).norm() / want.norm()))
+        ctx.close()
+    print("error: default", errs[0], "fp32 instruction", errs[1])
+    assert errs[0] <= 1.02 * errs[1]
+
+
 def test_classes_switched_off_by_infinite_weights_do_not_stall_the_split_products():
     """One class of a thousand with a weight of minus infinity on a feature that is always one, and one feature that is
     infinite: scores and update are formed again by the fp32 instruction in the tiles concerned.  The bound is four times
