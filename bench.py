@@ -34,6 +34,7 @@ PEAK_FP32_MFMA_TFLOPS = 157.3     # MI355X dense fp32 matrix-core peak
 PEAK_BF16_MFMA_TFLOPS = 2500.0    # dense bf16
 PEAK_SPLIT_TFLOPS = PEAK_BF16_MFMA_TFLOPS / 6.0   # fp32 products formed as six bf16 term products (the default for fp32)
 PEAK_HBM_GBS = 8000.0
+PEAK_LDS_GBS = 256 * 128 * 2.4    # 128 bytes a cycle and compute unit
 FAMILIES = {0: "scores", 1: "factor u", 2: "reconstruct-apply", 3: "csr densify", 5: "update + next scores (one pass)"}
 ALL_CONFIGS = ["mlr_large", "mlr_medium", "dml", "l2svm", "mlr_tiny"]      # headline first
 REPEATS = 5
@@ -113,23 +114,31 @@ def timed_repeats(run, restore, torch, steps, repeats=REPEATS):
     return out
 
 
-def roofline_of(wl, per_kernel, split_k, traffic_table, pipelined, split_products=True):
-    """Roofline record of the dominant contraction.  fp32 workloads: both contractions are priced
-    against the bf16 matrix cores at six term products per product, or against the fp32 instruction where a plan asks for it
-    (2*N*J*D flops per launch; L2-SVM: those of the stored entries).  bf16 workload: bound by streaming W through
-    HBM; algorithmic bytes per launch are W once (scores) / twice (reconstruction) plus the factor
-    operands; the fused update-and-score pass reads and writes W once and carries both contractions."""
+def fp32_bound(kernel, flops):
+    """(bound, work, peak, unit) of an fp32 family's main kernel, by what it runs on: split products and the fp32 instruction
+    on the matrix cores; the kernels that work from the stored entries read one word of LDS for every entry and class; the
+    one-pass step of few classes holds both contractions, formed by the fp32 instruction.  flops: of one contraction (L2-SVM:
+    over the stored entries)."""
+    if kernel in ("csr_scores_kernel", "sparse_update_kernel"):
+        return "lds", flops / 2.0 * 4.0, PEAK_LDS_GBS, "GB/s"
+    if kernel == "few_step_kernel":
+        return "mfma", 2.0 * flops, PEAK_FP32_MFMA_TFLOPS, "TFLOP/s"
+    split = kernel in ("scores_split_kernel", "reconstruct_split_kernel")
+    return "mfma", flops, PEAK_SPLIT_TFLOPS if split else PEAK_FP32_MFMA_TFLOPS, "TFLOP/s"
+
+
+def roofline_of(wl, per_kernel, split_k, traffic_table, pipelined, kernels):
+    """Roofline record of the dominant contraction, priced by the kernel that ran (`kernels`: family -> name).  fp32 workloads:
+    fp32_bound on 2*N*J*D flops per launch (kernels that work from the stored entries: those of the entries).  bf16
+    workload: bound by streaming W through HBM; algorithmic bytes per launch are W once (scores) / twice (reconstruction) plus
+    the factor operands; the fused update-and-score pass reads and writes W once and carries both contractions.  Times are
+    those of a family's main kernel: packing, list-making and plane-adding kernels are launches of their own."""
     flops = 2.0 * wl.N * wl.J * wl.D
-    cands = [f for f in per_kernel if f in (0, 2)]
-    if wl.model == "l2svm" and 0 in cands:
-        cands.remove(0)                                     # CSR scores: a gather kernel, no dense roofline
-    dom = max(cands, key=lambda f: per_kernel[f][1])
+    dom = max((f for f in per_kernel if f in (0, 2)), key=lambda f: per_kernel[f][1])
     if pipelined and 5 in per_kernel:
         dom = 5                                             # every step but the chain's two ends is this one kernel
     us = per_kernel[dom][1]
     traffic = traffic_table.get(f"{wl.name}:{'fused' if pipelined else dom}")
-    if wl.dtype == "f32" and split_products:
-        traffic = None                                      # counted for the fp32 instruction's kernels
     if wl.dtype == "bf16":
         wbytes = 4.0 * wl.J * wl.D
         if pipelined:
@@ -145,14 +154,17 @@ def roofline_of(wl, per_kernel, split_k, traffic_table, pipelined, split_product
              "algorithmic_bytes": alg, "us_per_launch": us,
              "frac_of_bf16_mfma_peak": (2.0 if pipelined else 1.0) * flops / (us * 1e-6) / 1e12 / PEAK_BF16_MFMA_TFLOPS}
     else:
-        if wl.model == "l2svm":
+        if kernels[dom] in ("csr_scores_kernel", "sparse_update_kernel"):
             flops *= len(wl.batches[0]["col"]) / (wl.N * wl.D)
-        achieved = flops / (us * 1e-6) / 1e12
-        peak = PEAK_SPLIT_TFLOPS if split_products else PEAK_FP32_MFMA_TFLOPS
-        r = {"bound": "mfma", "kernel": per_kernel[dom][0], "achieved": achieved,
-             "peak": peak, "unit": "TFLOP/s", "frac": achieved / peak,
-             "traffic": traffic, "algorithmic_flops": flops, "us_per_launch": us}
+        bound, work, peak, unit = fp32_bound(kernels[dom], flops)
+        achieved = work / (us * 1e-6) / (1e12 if bound == "mfma" else 1e9)
+        if kernels[dom] in ("scores_split_kernel", "reconstruct_split_kernel", "few_step_kernel", "sparse_update_kernel"):
+            traffic = None                                  # counted for the fp32 instruction's kernels
+        r = {"bound": bound, "kernel": per_kernel[dom][0], "achieved": achieved,
+             "peak": peak, "unit": unit, "frac": achieved / peak,
+             "traffic": traffic, "algorithmic_flops" if bound == "mfma" else "algorithmic_lds_bytes": work, "us_per_launch": us}
     r["kernels_us"] = {v[0]: round(v[1], 2) for v in per_kernel.values()}
+    r["kernels"] = {per_kernel[f][0]: kernels[f] for f in per_kernel}
     return r
 
 
@@ -240,6 +252,7 @@ def bench_config(name, args, sfb, torch, workloads, traffic_table, cpu_seconds, 
         ms, n = ctx.kernel_time_ms(fam)
         if n:
             per_kernel[fam] = (fname, ms / n * 1e3, n)       # microseconds per launch
+    kernels = {fam: ctx.last_kernel(fam)[0] for fam in per_kernel}
     ctx.enable_timing(False)
     ctx.reset_timing()
 
@@ -258,7 +271,7 @@ def bench_config(name, args, sfb, torch, workloads, traffic_table, cpu_seconds, 
         "data": "synthetic",
         "config": {"workload": f"{wl.name}: {wl.model} J={wl.J} D={wl.D} P={wl.P} B={wl.B} eta={wl.eta}",
                    "plan": plan, "launch": launch},
-        "roofline": roofline_of(wl, per_kernel, plan["fwd_split_k"], {} if over else traffic_table, pipelined, not args.plan),
+        "roofline": roofline_of(wl, per_kernel, plan["fwd_split_k"], {} if over else traffic_table, pipelined, kernels),
     }
     if extras:
         rec.update(extras_of(args, wl, ctx, sfb, torch, pool, W, W0, U, V, steps, warmup))
@@ -446,8 +459,8 @@ def bench_sdca(args):
         if n:
             per[name] = round(ms / n * 1e3, 2)
     ctx.enable_timing(False)
-    flops = 2.0 * wl.N * wl.J * wl.D
     us = per["reconstruct-apply"]
+    bound, flops, peak, unit = fp32_bound(ctx.last_kernel(2)[0], 2.0 * wl.N * wl.J * wl.D)
     achieved = flops / (us * 1e-6) / 1e12
     out = {"metric": "sfb_samples_per_sec", "value": wl.N * args.steps / elapsed, "unit": "samples/s",
            "steps_per_sec": args.steps / elapsed, "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
@@ -455,8 +468,8 @@ def bench_sdca(args):
            "vs_baseline": None, "dtype": "f32", "data": "synthetic",
            "config": {"workload": f"{wl.name}: SDCA on l2-regularised MLR, J={wl.J} D={wl.D} n_data={wl.n_data} "
                                   f"P={wl.P} B={wl.B} lam={wl.lam} s={s}", "plan": ctx.plan_info(), "launch": "eager"},
-           "roofline": {"bound": "mfma", "kernel": "reconstruct-apply", "achieved": achieved,
-                        "peak": PEAK_SPLIT_TFLOPS, "unit": "TFLOP/s", "frac": achieved / PEAK_SPLIT_TFLOPS,
+           "roofline": {"bound": bound, "kernel": "reconstruct-apply", "achieved": achieved,
+                        "peak": peak, "unit": unit, "frac": achieved / peak,
                         "traffic": None, "algorithmic_flops": flops, "us_per_launch": us, "kernels_us": per}}
     if args.cpu_seconds > 0:
         from oracle.sdca_oracle import SdcaMlrOracle
