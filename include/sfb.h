@@ -115,7 +115,12 @@ SFB_API void sfb_destroy(sfb_ctx *ctx);
  * of U, V and W, without it the slower element-by-element kernel (same results to rounding).  A
  * call with a dead worker (`active`) likewise takes a masked copy of U in the partial scores' bytes, and
  * shapes of a few 64 x 64 tiles of W with thousands of factor pairs count planes of partial sums (the
- * pairs are then cut into slices over workgroups and added in a fixed order).  The
+ * pairs are then cut into slices over workgroups and added in a fixed order).  MLR and DML contexts of at most
+ * 32 classes whose step is one pass over the features count a plane of J x D sums for every workgroup of it, and fp32
+ * updates formed as split products take planes for slices of the pairs from whatever the rest asks for.  SFB_L2SVM contexts
+ * count, behind one plane of scores, lists of the batch's stored entries by column (8 bytes an entry for one in twelve of N x D,
+ * 132 bytes for every 32 columns), up to SFB_NOALLOC_SCRATCH_BYTES in all: a step whose lists find no room updates W from the
+ * dense rows.  The
  * caller allocates at least that many bytes, 256-byte aligned, and registers them; the library
  * uses the buffer until it is replaced or the ctx destroyed. */
 SFB_API sfb_status sfb_workspace_bytes(const sfb_ctx *ctx, size_t *bytes);
@@ -167,7 +172,9 @@ SFB_API sfb_status sfb_reconstruct_apply_worker(sfb_ctx *ctx, float *W, int64_t 
                                         float scale);
 
 /* sfb_compute_factors followed by sfb_reconstruct_apply with scale = 1/B: one full BSP
- * iteration.  U, V (and loss) hold the step's factors afterwards. */
+ * iteration.  U, V (and loss) hold the step's factors afterwards.  W is that of the two calls to rounding: knowing that U
+ * and V are its own, the step may add the same products in another order (few classes: one pass over the features; L2-SVM:
+ * the stored entries only). */
 SFB_API sfb_status sfb_step(sfb_ctx *ctx, float *W, int64_t ldw, const sfb_batch *batch, const int32_t *y,
                     float *U, int64_t ldu, void *V, int64_t ldv, float *loss, float eta,
                     const uint8_t *active);
@@ -305,14 +312,17 @@ SFB_API const char *sfb_strerror(sfb_status s);
 SFB_API int sfb_last_hip_error(const sfb_ctx *ctx);
 
 /*
- * Read back the launch plan chosen at creation (for benches and tests): number of split-K
- * slices of the score contraction, and the elapsed-time bookkeeping switch.  When timing is
+ * Read back the launch plan chosen at creation (for benches and tests): slices of D and workgroups of the score
+ * contraction that all N rows take by default (few classes: if their one-pass step were switched off), and the workgroups of
+ * the fp32 instruction's (bf16: the bf16) reconstruction, one of the kernels that an fp32 update may take: sfb_last_kernel
+ * says which one did the work.  And the elapsed-time bookkeeping switch.  When timing is
  * enabled the main kernel of every family is launched with a pair of HIP events attached to its
  * own dispatch (start and stop timestamps of that kernel, nothing else in between; do not
  * enable it while the stream is being captured into a graph); sfb_kernel_time_ms synchronises
  * and returns the accumulated milliseconds and launch count of kernel family `which`
- * (0 = scores, 1 = factor u, 2 = reconstruct-apply: the contraction, without the bf16 path's
- * operand-packing kernel, 3 = CSR densify / stream copy, 4 = proximal step, 5 = the one-pass update +
+ * (0 = scores, or the one-pass kernel of few classes, without the kernel that adds its planes; 1 = factor u, 2 =
+ * reconstruct-apply: the contraction, without the kernels that pack bf16 operands, copy ragged factors, make the stored
+ * entries' lists or add planes, 3 = CSR densify / stream copy, 4 = proximal step, 5 = the one-pass update +
  * next scores kernel of sfb_step_pipelined, without its packing kernel) since the last reset.
  */
 SFB_API sfb_status sfb_plan_info(const sfb_ctx *ctx, int32_t *fwd_split_k, int32_t *fwd_grid,
