@@ -246,8 +246,8 @@ static hipError_t launch_split(const ReconArgs& a, int slices, bool halves, hipS
 // Tile, slices of the pairs and microseconds (the other kernels': reconstruct_fp32_us), fitted to 202 shapes
 // (J = 32 to 2000, D = 256 to 8192, N = 64 to 4096) on one MI355X.  A chunk of 32 pairs costs 1.04 / 0.63 us per round
 // of 256 tiles of 128 x 128 / 64 x 128 and 0.42 us with 64 x 64 tiles (three share a compute unit), on top of 5.6 us,
-// W's trip at 7 TB/s and 2.8 us per further round.  1000 x 4096: 21.7 -> 18.5 us at 256 pairs, 37.5 -> 28.9 at 512,
-// 256 -> 165 at 4096; 600 x 784 with 1024: 26 -> 20.5.
+// W's trip at 7 TB/s and 2.8 us per further round.  1000 x 4096 (fp32 instruction -> here): 23.1 -> 19.2 us at 256 pairs,
+// 40 -> 29.5 at 512, 255 -> 169 at 4096; 600 x 784 with 1024: 32.6 -> 17.5.
 // Where the tiles leave compute units idle the pairs are cut into slices, at most 64 and as many as `room` bytes hold
 // planes of J x D sums for; adding those up is a second kernel.
 SplitReconPlan reconstruct_split_plan(int64_t J, int64_t D, int64_t N, size_t room, bool apart) {
