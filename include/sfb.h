@@ -190,7 +190,7 @@ SFB_API sfb_status sfb_step(sfb_ctx *ctx, float *W, int64_t ldw, const sfb_batch
  * and gives what T calls of sfb_step give.  For bf16 contexts whose shape the fused kernel covers
  * (P*B in {128, 256, 512}, D a multiple of 32, J*ldw < 2^31, 16-byte aligned operands) the update and
  * the next scores run in ONE kernel that reads and writes every tile of W once; otherwise the call runs
- * sfb_reconstruct_apply and sfb_compute_factors one after the other (same results as sfb_step).
+ * sfb_reconstruct_apply and sfb_compute_factors one after the other (the results of sfb_step, to rounding).
  * `active` masks the workers of the PENDING factors.  The next batch's features must not overlap V
  * (V is read as v_t and overwritten with the next features piece by piece).  Needs the registered
  * workspace (query sfb_workspace_bytes).  Errors as sfb_step; nothing is launched if an argument is refused.
