@@ -107,7 +107,8 @@ SFB_API void sfb_destroy(sfb_ctx *ctx);
 
 /* Bytes of device workspace the context needs: the scores Z[N][J] as split-K partial sums,
  * plus, for bf16 contexts, the transposed bf16 copies of the factors that the
- * reconstruction multiplies (so sfb_reconstruct_apply needs the workspace too).  fp32 contexts
+ * reconstruction of a large W multiplies (so sfb_reconstruct_apply needs the workspace too; that of a
+ * small W takes planes for slices of the pairs from the same bytes).  fp32 contexts
  * whose J is not a multiple of 4, D not one of 128 or P*B not one of 32 also count room for padded
  * fp32 copies of U and V (rows of J rounded up to 4 and D rounded up to 128 floats, P*B rounded up
  * to 32 rows; the same bytes as the partial scores, which are dead by then): with it registered
@@ -313,9 +314,9 @@ SFB_API int sfb_last_hip_error(const sfb_ctx *ctx);
 
 /*
  * Read back the launch plan chosen at creation (for benches and tests): slices of D and workgroups of the score
- * contraction that all N rows take by default (few classes: if their one-pass step were switched off), and the workgroups of
- * the fp32 instruction's (bf16: the bf16) reconstruction, one of the kernels that an fp32 update may take: sfb_last_kernel
- * says which one did the work.  And the elapsed-time bookkeeping switch.  When timing is
+ * contraction that all N rows take by default (few classes: if their one-pass step were switched off; bf16: on operands whose
+ * rows are 16-byte aligned), and the workgroups of the fp32 instruction's reconstruction, one of the kernels that an fp32 update
+ * may take, or of the bf16 update: sfb_last_kernel says which one did the work.  And the elapsed-time bookkeeping switch.  When timing is
  * enabled the main kernel of every family is launched with a pair of HIP events attached to its
  * own dispatch (start and stop timestamps of that kernel, nothing else in between; do not
  * enable it while the stream is being captured into a graph); sfb_kernel_time_ms synchronises
@@ -355,7 +356,8 @@ SFB_API sfb_status sfb_last_kernel(const sfb_ctx *ctx, int32_t which, char *name
  * bit 6 = L2SVM steps update W from lists of the stored entries wherever those fit (neither 3 nor 6: never); < 0 = keep.  A value <= 0 (variant < 0) keeps the current choice.
  * Any choice ends what a context does by itself with the kernels it is about, for good (a new context has it again): the
  * one-pass step of few classes (any argument), the choice between split products and the fp32 instruction (fwd_bm, fwd_bn,
- * fwd_split_k or fwd_dma: the scores; recon_variant or fwd_dma: the update, few pairs and stored entries included).
+ * fwd_split_k or fwd_dma: the scores; recon_variant or fwd_dma: the update, few pairs and stored entries included), the exact
+ * split of W in bf16 contexts (fwd_bm, fwd_bn, fwd_split_k).
  * The workspace requirement may grow: query sfb_workspace_bytes again.  SFB_EINVAL for a value outside the table. */
 SFB_API sfb_status sfb_set_plan(sfb_ctx *ctx, int32_t fwd_bm, int32_t fwd_bn, int32_t fwd_split_k,
                                 int32_t recon_variant, int32_t fwd_dma);

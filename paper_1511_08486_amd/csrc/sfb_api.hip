@@ -63,6 +63,9 @@ struct sfb_ctx {
     hipStream_t stream;
     FwdPlan fwd_all, fwd_worker;   // scores of all N rows / of one worker's B rows
     FwdPlan fwd_bf16;              // all N rows on the bf16 matrix cores (bf16 contexts)
+    Bf16TilePlan tile_scores[2][2];   // bf16 contexts: scores in tiles, all rows or one worker's, W rounded or exact
+    Bf16TilePlan tile_update[2];   // bf16 contexts: update in tiles, all pairs or one worker's
+    bool tile_bf16;                // take them (a score tile of the caller's choice is about the kernels that were there before)
     FwdPlan fwd_split, fwd_split_worker;   // the same on the bf16 matrix cores, fp32 operands split exactly into bf16 terms
     bool split_scores;             // use them where the shape allows
     int split_recon;               // reconstruction with split-bf16 products: 1 where the shape allows, 0 never, -1 where it is the cheaper one
@@ -163,6 +166,15 @@ void plan_split_recon(sfb_ctx* c, bool apart) {
     for (int one = 0; one < 2; ++one)
         for (int with_ws = 0; with_ws < 2; ++with_ws)
             c->split_plans[one][with_ws] = reconstruct_split_plan(c->J, c->D, one ? c->B : (int64_t)c->P * c->B, with_ws ? workspace_need(c) : 0, apart);
+}
+
+void plan_bf16_tiles(sfb_ctx* c) {
+    if (c->dtype != SFB_BF16) return;
+    for (int one = 0; one < 2; ++one) {
+        const int64_t N = one ? c->B : (int64_t)c->P * c->B;
+        for (int exact = 0; exact < 2; ++exact) c->tile_scores[one][exact] = plan_scores_bf16(N, c->J, c->D, exact ? 3 : 1, scores_need(c));
+        c->tile_update[one] = plan_update_bf16(c->J, c->D, N, workspace_need(c));
+    }
 }
 
 sfb_status hip_fail(sfb_ctx* c, hipError_t e) {
@@ -346,6 +358,17 @@ sfb_status factors_rows(sfb_ctx* c, const FwdPlan& plan, const float* W, int64_t
     }
     // bf16 features, full batch, aligned: the bf16 matrix-core kernel with its own plan
     const bool on_bf16_cores = bf16 && n_rows == c->P * c->B && n_rows >= 128 && forward_bf16_ok(f);
+    // W is rounded to bf16 where that kernel would, and taken exactly in all other bf16 calls
+    const Bf16TilePlan& tiles = c->tile_scores[n_rows != c->P * c->B][!on_bf16_cores];
+    if (bf16 && c->tile_bf16 && scores_bf16_ok(f) && tiles.bm > 0 &&
+        !(on_bf16_cores && forward_bf16_wins(c->fwd_bf16, n_rows, c->J, c->D, tiles.us))) {
+        {
+            Timed t(c, 0);
+            hipError_t e = launch_scores_bf16(f, tiles, c->stream);
+            if (e != hipSuccess) return hip_fail(c, e);
+        }
+        return factor_rows(c, tiles.slices, f.zstride, y, row0, n_rows, U, ldu, loss, sdca);
+    }
     // fp32 features: split-bf16 products, unless the caller chose the fp32 matrix instruction (sfb_set_plan).  Leading
     // dimensions beyond its 32-bit offsets take the fp32 kernels, whose plan may cut D into more slices than there is room for
     const bool all_rows = n_rows == c->P * c->B;
@@ -399,7 +422,13 @@ sfb_status recon_launch(sfb_ctx* c, float* W, int64_t ldw, const float* U, int64
     hipError_t e;
     if (r.bf16) {
         if (c->ws == nullptr || c->ws_bytes < workspace_need(c)) return SFB_EWORKSPACE;
-        e = launch_reconstruct_bf16(r, (char*)c->ws + scores_need(c), c->stream);
+        const Bf16TilePlan& tiles = c->tile_update[n_rows > 0];
+        if (update_bf16_ok(r) && tiles.bm > 0 && tiles.us < reconstruct_bf16_us(c->J, c->D, r.N)) {
+            r.partial = tiles.slices > 1 ? (float*)c->ws : nullptr;      // (the partial scores are dead)
+            e = launch_update_bf16(r, tiles, c->stream);
+        } else {
+            e = launch_reconstruct_bf16(r, (char*)c->ws + scores_need(c), c->stream);
+        }
         if (e != hipSuccess) return hip_fail(c, e);
         return SFB_OK;
     }
@@ -516,6 +545,8 @@ sfb_status sfb_create(sfb_ctx** out, sfb_model m, int64_t J, int64_t D, int32_t 
         c->few = planes <= SFB_NOALLOC_SCRATCH_BYTES || planes <= workspace_need(c);
     }
     plan_split_recon(c, false);
+    c->tile_bf16 = true;
+    plan_bf16_tiles(c);
     c->ws = nullptr; c->ws_bytes = 0; c->lists = nullptr; c->lists_stored = 0; c->last_hip = 0; c->timing = false; c->sparse_forward = true; c->sparse_always = false;
     c->lists_always = false;
     for (LastKernel& k : c->last) k = LastKernel{nullptr, 0};
@@ -824,11 +855,25 @@ sfb_status sfb_plan_info(const sfb_ctx* c, int32_t* fwd_split_k, int32_t* fwd_gr
     const FwdPlan& f = c->dtype == SFB_BF16 ? c->fwd_bf16 : c->split_scores && c->D >= 4 ? c->fwd_split : c->fwd_all;
     if (fwd_split_k) *fwd_split_k = f.split_k;
     if (fwd_grid) *fwd_grid = f.grid;
-    if (recon_grid) {
+    bool tile_update = false;
+    if (c->dtype == SFB_BF16) {                                  // as the calls on aligned operands choose (factors_rows, recon_launch)
+        const int64_t N = (int64_t)c->P * c->B;
+        const bool rounded = N >= 128 && c->D % 32 == 0;
+        const Bf16TilePlan& t = c->tile_scores[0][!rounded];
+        if (c->tile_bf16 && t.bm > 0 && !(rounded && forward_bf16_wins(c->fwd_bf16, N, c->J, c->D, t.us))) {
+            if (fwd_split_k) *fwd_split_k = t.slices;
+            if (fwd_grid) *fwd_grid = (int32_t)(((N + t.bm - 1) / t.bm) * ((c->J + t.bn - 1) / t.bn) * t.slices);
+        }
+        const Bf16TilePlan& u = c->tile_update[0];
+        tile_update = u.bm > 0 && u.us < reconstruct_bf16_us(c->J, c->D, N);
+        if (recon_grid && tile_update)
+            *recon_grid = (int32_t)(((c->J + u.bm - 1) / u.bm) * ((c->D + u.bn - 1) / u.bn) * u.slices);
+    }
+    if (recon_grid && !tile_update) {
         // ragged fp32 shapes run the padded shape's plan once a workspace is registered (recon_launch)
         const bool padded = c->padded_factors && conformed_variant_ok(c->recon_padded.variant) && c->ws != nullptr &&
                             c->ws_bytes >= workspace_need(c);
-        *recon_grid = c->dtype == SFB_BF16 ? bf16_recon_grid(c->J, c->D) : padded ? c->recon_padded.grid : c->recon.grid;
+        *recon_grid = c->dtype == SFB_BF16 ? (int32_t)bf16_recon_grid(c->J, c->D) : padded ? c->recon_padded.grid : c->recon.grid;
     }
     return SFB_OK;
 }
@@ -872,6 +917,7 @@ sfb_status sfb_set_plan(sfb_ctx* c, int32_t fwd_bm, int32_t fwd_bn, int32_t fwd_
     finish_forward_plan(&p, (int64_t)c->P * c->B, c->J, c->D);
     if (fwd_dma >= 0 && c->split_scores) plan_split_scores(c, true);
     c->fwd_all = p;
+    if (fwd_bm > 0 || fwd_bn > 0 || fwd_split_k > 0) c->tile_bf16 = false;
     if (recon_variant >= 0) {
         c->recon = plan_reconstruct_variant(c->J, c->D, recon_variant);
         c->recon_padded = plan_reconstruct_padded(c->J, c->D, (int64_t)c->P * c->B, recon_variant);

@@ -341,8 +341,8 @@ size_t bf16_recon_workspace(int64_t J, int64_t D, int64_t N) {
     return up((size_t)J * ldn * 2) + up((size_t)D * ldn * 2);
 }
 
-int bf16_recon_grid(int64_t J, int64_t D) {
-    return (int)(((J + kBfReconBM - 1) / kBfReconBM) * ((D + kBfReconBN - 1) / kBfReconBN));
+int64_t bf16_recon_grid(int64_t J, int64_t D) {
+    return (((J + kBfReconBM - 1) / kBfReconBM) * ((D + kBfReconBN - 1) / kBfReconBN));
 }
 
 hipError_t launch_reconstruct_bf16(const ReconArgs& a, void* ws, hipStream_t s) {
@@ -419,6 +419,23 @@ FwdPlan plan_forward_bf16(int64_t n_rows, int64_t J, int64_t D) {
     p.k_slice = (int)(per * kBfFwdBK);
     p.grid = (int)(tiles * s);
     return p;
+}
+
+// Microseconds of the two passes, fitted to one MI355X (scores with the factor kernel: 90 shapes of J = 44 to 9112; updates with
+// the packing kernel: 196): what the tiles for smaller shapes (sfb_bf16_tiles.hip) are compared with.  The choice by the two
+// estimates is 0.4 % off the better one on average; this file's update wins from about 500 of its tiles, its scores from about
+// 1e10 multiply-adds where 256 x 256 tiles fill the chip (8064 x 3712, N = 1024: 95 us against 113; 1792 x 8832, 2560: 123, 157).
+// (the scores keep these tiles where the two estimates are within 5 %)
+bool forward_bf16_wins(const FwdPlan& p, int64_t n_rows, int64_t J, int64_t D, double tiles_us) {
+    const double rounds = (double)((p.grid + 255) / 256), walk = (double)(p.k_slice / kBfFwdBK) * rounds * 1.01;
+    const double w_us = 0.257 * 4e-6 * (double)J * (double)D;
+    return 8.8 + (walk > w_us ? walk : w_us) + (double)p.split_k * (0.46 * 4e-6 * (double)n_rows * (double)J + 0.08) < 1.05 * tiles_us;
+}
+double reconstruct_bf16_us(int64_t J, int64_t D, int64_t N) {
+    const int64_t tiles = bf16_recon_grid(J, D);
+    const double chunks = (double)((N + 63) / 64), lone = 0.9 * (double)((tiles + 255) / 256), full = 0.96 * (double)tiles / 256.0;
+    return 8.5 + chunks * (lone > full ? lone : full) + 0.24 * 4e-6 * (double)J * (double)D +
+           0.95 * 64e-6 * chunks * (double)(J + D) + 7.5 * (double)((tiles + 511) / 512);
 }
 
 hipError_t launch_forward_bf16(const FwdArgs& a, const FwdPlan& p, hipStream_t s) {

@@ -242,9 +242,28 @@ bool forward_bf16_ok(const FwdArgs& a);                       // alignment / sha
 FwdPlan plan_forward_bf16(int64_t n_rows, int64_t J, int64_t D);
 hipError_t launch_forward_bf16(const FwdArgs& a, const FwdPlan& p, hipStream_t s);
 size_t bf16_recon_workspace(int64_t J, int64_t D, int64_t N);  // bytes of device scratch
-int bf16_recon_grid(int64_t J, int64_t D);                     // workgroups of the W += C launch
+int64_t bf16_recon_grid(int64_t J, int64_t D);                 // workgroups of the W += C launch
+bool forward_bf16_wins(const FwdPlan& p, int64_t n_rows, int64_t J, int64_t D, double tiles_us);   // against the tiles' estimate
+double reconstruct_bf16_us(int64_t J, int64_t D, int64_t N);
 // ws: bf16_recon_workspace bytes, 256-byte aligned.  Two launches: transpose/pack, then W += C.
 hipError_t launch_reconstruct_bf16(const ReconArgs& a, void* ws, hipStream_t s);
+
+// bf16 features, tiles for W of any shape (sfb_bf16_tiles.hip).  Any alignment and leading dimension.
+template <int TERMS> constexpr int kBfTileChunk = TERMS == 1 ? 64 : 32;   // columns of D per chunk of the scores
+constexpr int kBfUpdateChunk = 64;                                        // pairs per chunk of the update
+struct Bf16TilePlan {
+    int bm, bn;          // scores: samples x classes; update: classes x columns
+    int slices;          // of the contraction
+    int per_slice;       // scores: columns of D; update: chunks of pairs
+    int terms;           // scores: bf16 terms W's entries are taken in (1 rounded, 3 exact)
+    double us;           // estimate
+};
+Bf16TilePlan plan_scores_bf16(int64_t n_rows, int64_t J, int64_t D, int terms, size_t most);   // most: bytes for the partial scores
+Bf16TilePlan plan_update_bf16(int64_t J, int64_t D, int64_t N, size_t room);                   // room: bytes for planes of sums
+bool scores_bf16_ok(const FwdArgs& a);
+bool update_bf16_ok(const ReconArgs& a);
+hipError_t launch_scores_bf16(const FwdArgs& a, const Bf16TilePlan& p, hipStream_t s);
+hipError_t launch_update_bf16(const ReconArgs& a, const Bf16TilePlan& p, hipStream_t s);
 
 // Whole step (or its factors) of MLR and pair models with at most 32 classes in one pass over the features (sfb_few.hip).
 struct FewArgs {
