@@ -1,0 +1,46 @@
+"""Updates from 17 to 64 pairs as split products: edges of tiles, rows at any alignment, dead workers, infinities, against fp64.
+
+Bound of an entry: what the split drops is below 2^-24 |u v| a product and the leading sums are rounded four times, the small ones
+twenty times at 2^-8 of their size: 2^-22 sum |u v|, and a unit in the last place of the result for the update itself."""
+import pytest
+import torch
+
+import paper_1511_08486_amd as sfb
+from test_gpu_bf16_tiles import strided
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+@pytest.mark.parametrize("J,D,P,B", [
+    (4, 4, 2, 9), (5, 7, 3, 6), (63, 129, 2, 16), (64, 128, 3, 11), (66, 131, 2, 17), (130, 258, 4, 12), (257, 513, 8, 8), (1000, 2050, 4, 16),
+    (2100, 3200, 2, 30),
+])
+@pytest.mark.parametrize("pad,shift,dead,kind", [(1, 1, False, "none"), (2, 3, True, "l1"), (0, 0, True, "none"), (0, 0, False, "l2sq")])
+def test_update(J, D, P, B, pad, shift, dead, kind):
+    N = P * B
+    g = torch.Generator(device=DEV).manual_seed(J * D + N)
+    U, V, W = (torch.randn(*s, generator=g, device=DEV) for s in ((N, J), (N, D), (J, D)))
+    Ul, Vl = U.double(), V.double()
+    if dead:
+        U[B:2 * B], V[B:2 * B] = float("nan"), float("inf")           # a dead worker's slot may hold anything
+        Ul[B:2 * B], Vl[B:2 * B] = 0.0, 0.0
+    V[0, D - 1] = Vl[0, D - 1] = -float("inf")                          # its column, and nothing else, is not finite
+    ctx = sfb.Sfb("mlr", J, D, P, B, device=DEV)
+    W2 = strided(W, pad, shift)
+    around = W2.untyped_storage()
+    active = [p != 1 for p in range(P)] if dead else None
+    ctx.reconstruct_apply_prox(W2, strided(U, pad, shift), strided(V, pad, shift), 0.25, kind, 0.02, scale=0.5, active=active)
+    ctx.sync()
+    assert ctx.last_kernel(2)[0] == "reconstruct_thin_kernel"
+    want = W.double() - 0.125 * (Ul.T @ Vl)
+    if kind == "l2sq":
+        want = want / (1.0 + 0.25 * 0.02)
+    if kind == "l1":
+        want = torch.sign(want) * (want.abs() - 0.25 * 0.02).clamp(min=0.0)
+    room = 2.0 ** -22 * (0.125 * (Ul.abs().T @ Vl[:, :D - 1].abs()) + W[:, :D - 1].double().abs())
+    assert ((W2[:, :D - 1].double() - want[:, :D - 1]).abs() <= room).all()
+    assert torch.equal(W2[:, D - 1].double(), want[:, D - 1])
+    flat = torch.empty(0, device=DEV).set_(around)                      # nothing but W's own entries was written
+    assert int(torch.isnan(flat).sum()) == flat.numel() - J * D
+    ctx.close()
