@@ -448,7 +448,9 @@ sfb_status recon_launch(sfb_ctx* c, float* W, int64_t ldw, const float* U, int64
         if (!whole) us += 3.5 + 1.6e-6 * (double)r.N * (double)(c->J + c->D);
         if (reconstruct_split_ok(r)) {
             sp = &c->split_plans[n_rows > 0][have_ws];
-            if (sp->slices > 1 && (size_t)sp->slices * (size_t)c->J * (size_t)c->D * sizeof(float) > workspace_need(c)) sp = &c->split_plans[n_rows > 0][0];
+            const size_t planes = sp->slices > 1 ? (size_t)sp->slices : sp->main_rows + sp->main_cols > 0 && sp->rest_slices > 1 ? (size_t)sp->rest_slices : 0;
+            const size_t rows = (size_t)(c->J - sp->main_rows), cols = (size_t)(c->D - sp->main_cols);
+            if (planes * rows * cols * sizeof(float) > workspace_need(c)) sp = &c->split_plans[n_rows > 0][0];
             // The kernel these products stand in for adds its sums in four parts where J is 600 or 1160, say, and is the more
             // accurate one unless they are cut in two: 600 x 4096 with 1024 pairs, of the norm, 2.9e-7 (mixed signs) and
             // 1.3e-7 (all positive) against 3.4e-7 and 1.9e-7 in one piece (39.6 us), 2.4e-7 and 1.1e-7 in two (42.7; that
@@ -470,7 +472,7 @@ sfb_status recon_launch(sfb_ctx* c, float* W, int64_t ldw, const float* U, int64
     } else if (on_lists) {
         e = launch_sparse_update(r, c->lists_stored, c->lists, c->stream);
     } else if (on_split) {
-        r.partial = sp->slices > 1 ? (float*)c->ws : nullptr;
+        r.partial = have_ws ? (float*)c->ws : nullptr;                   // (plans without a workspace have no slices)
         e = launch_reconstruct_split(r, *sp, halves, c->stream);
     } else {
         // calls that would end in the register-staged kernel first try a copy of the factors that the LDS-DMA

@@ -222,7 +222,13 @@ bool reconstruct_split_ok(const ReconArgs& a);
 // few factor pairs, bound by W's trip through memory (sfb_reconstruct_thin.hip); any shape and alignment
 bool reconstruct_thin_ok(const ReconArgs& a);
 hipError_t launch_reconstruct_thin(const ReconArgs& a, hipStream_t s);
-struct SplitReconPlan { int bm, bn, slices; bool apart; double us; };                // tile, slices of the pairs, sums apart, estimated time
+struct SplitReconPlan {
+    int bm, bn, slices;                // tile, slices of the pairs
+    bool apart;                        // the smaller products' sums apart
+    double us;                         // estimate
+    int main_rows, main_cols;          // 0, or the rows or columns that these tiles take: the others are a launch with
+    int rest_bm, rest_bn, rest_slices; //   these
+};
 SplitReconPlan reconstruct_split_plan(int64_t J, int64_t D, int64_t N, size_t room, bool apart);   // room: bytes for planes of sums
 // halves: calls without slices let the running sums start anew half way through the pairs
 hipError_t launch_reconstruct_split(const ReconArgs& a, const SplitReconPlan& p, bool halves, hipStream_t s);

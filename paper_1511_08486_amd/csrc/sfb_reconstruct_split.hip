@@ -21,8 +21,9 @@ namespace sfb {
 
 typedef float rs_f32x2u __attribute__((ext_vector_type(2), aligned(4)));
 
+// (three blocks: a strip of 96 rows by one wavefront's 32 columns)
 template <int MT, int NT, bool APART>
-using ReconTile = SplitTile<MT, NT, NT == 2 ? 64 : 80, NT == 2, APART>;
+using ReconTile = SplitTile<MT, NT, NT == 2 ? 64 : 80, NT == 2, APART, MT == 3 ? 1 : 2>;
 
 // column of the tile's A or B part that LDS row r holds
 template <int NT>
@@ -137,7 +138,7 @@ __global__ __launch_bounds__(kSplitThreads, 2) void reconstruct_split_kernel(
 
     // the entries of W this wavefront finishes: requested before the exchange, used after it (requested before the
     // contraction they stand in front of its loads in the in-order queue: 0.3 to 0.8 us slower)
-    const int wm = (wave & 3) >> 1, wn = wave & 1, l32 = lane & 31;
+    const int wm = (wave & 3) / Tile::WN, wn = wave % Tile::WN, l32 = lane & 31;
     auto w_row = [&](int i, int q) { return j0 + rs_column<NT>((wm * MT + i) * 32 + Tile::entry_row(wave >> 2, q, lane)); };
     // one column per block, or (PAIRS) the first of two neighbours
     const int dcol = PAIRS ? d0 + wn * 64 + 4 * (l32 & 15) + 2 * (l32 >> 4) : d0 + wn * 32 + l32;
@@ -248,30 +249,54 @@ static hipError_t launch_split(const ReconArgs& a, int slices, bool halves, hipS
 // of 256 tiles of 128 x 128 / 64 x 128 and 0.42 us with 64 x 64 tiles (three share a compute unit), on top of 5.6 us,
 // W's trip at 7 TB/s and 2.8 us per further round.  1000 x 4096 (fp32 instruction -> here): 23.1 -> 19.2 us at 256 pairs,
 // 40 -> 29.5 at 512, 255 -> 169 at 4096; 600 x 784 with 1024: 32.6 -> 17.5.
+// 96 x 128 tiles (0.88 us a chunk) are for the J whose 128-row tiles leave compute units idle or just pass a round of 256: 600 x 4096
+// with 1024 pairs 43.0 -> 40.9 us (160 -> 224 workgroups), 576 rows 42.4 -> 38.4, 1001 x 4100 with 488 in place of 64 x 64 tiles 46.6 ->
+// 42.7; below 16 chunks they save 2 us at most, and in walks of more than 64 the chip's power sets the pace, not its idle units (2894 x
+// 512, 6912 pairs in two slices: 2 % slower).
 // Where the tiles leave compute units idle the pairs are cut into slices, at most 64 and as many as `room` bytes hold
 // planes of J x D sums for; adding those up is a second kernel.
-SplitReconPlan reconstruct_split_plan(int64_t J, int64_t D, int64_t N, size_t room, bool apart) {
-    static const struct { int bm, bn, resident; double chunk_us, lone_us; } tiles[3] = {
-        {128, 128, 1, 1.04, 1.04}, {64, 128, 1, 0.63, 0.63}, {64, 64, 3, 0.42, 0.38}};
+static SplitReconPlan plan_part(int64_t J, int64_t D, int64_t N, size_t room, bool apart, bool alone) {
+    static const struct { int bm, bn, resident; double chunk_us, lone_us; } tiles[4] = {
+        {128, 128, 1, 1.04, 1.04}, {96, 128, 1, 0.88, 0.88}, {64, 128, 1, 0.63, 0.63}, {64, 64, 3, 0.42, 0.38}};
     const int64_t chunks = (N + kSpChunk - 1) / kSpChunk;
-    const double w_mb = 8e-6 * (double)J * (double)D;
-    SplitReconPlan best{0, 0, 1, apart, 1e300};
+    SplitReconPlan best{0, 0, 1, apart, 1e300, 0, 0, 0, 0, 1};
     for (const auto& t : tiles) {
         if (apart && t.bm != 64) continue;                                        // (the smaller products' sums apart)
+        if (t.bm == 96 && chunks < 16) continue;
         const int64_t n = ((J + t.bm - 1) / t.bm) * ((D + t.bn - 1) / t.bn);
+        auto cost = [&](int64_t rows, int64_t cols, int64_t s, int64_t per) {
+            const int64_t wgs = ((rows + t.bm - 1) / t.bm) * ((cols + t.bn - 1) / t.bn) * s;
+            const double w_mb = 8e-6 * (double)rows * (double)cols, rounds = (double)((wgs + 255) / 256);
+            const double deep = (double)((wgs + 256 * t.resident - 1) / (256 * t.resident));
+            const double a = t.lone_us * deep, b = t.chunk_us * rounds;
+            return 5.6 + (double)per * (a > b ? a : b) + (t.resident == 1 ? 2.8 * (rounds - 1.0) : 0.0) +
+                   (s == 1 ? 0.14 * w_mb : 3.5 + 0.1 * (double)s * w_mb);         // planes written and read, W read and written
+        };
         for (int64_t s = 1; s <= 64 && (s == 1 || ((size_t)(s * J * D) * sizeof(float) <= room && chunks >= 2 * s && n * s <= 1536)); ++s) {
             const int64_t per = (chunks + s - 1) / s;
             if ((chunks + per - 1) / per != s) continue;                          // the same cut as a smaller count, or an empty slice
-            const double rounds = (double)((n * s + 255) / 256);
-            const double deep = (double)((n * s + 256 * t.resident - 1) / (256 * t.resident));
-            const double a = t.lone_us * deep, b = t.chunk_us * rounds;
-            double us = 5.6 + (double)per * (a > b ? a : b) + (t.resident == 1 ? 2.8 * (rounds - 1.0) : 0.0);
-            us += s == 1 ? 0.14 * w_mb : 3.5 + 0.1 * (double)s * w_mb;            // planes written and read, W read and written
-            if (us < best.us) best = SplitReconPlan{t.bm, t.bn, (int)s, apart, us};
+            if (t.bm == 96 && per > 64) continue;
+            const double us = cost(J, D, s, per);
+            if (us < best.us) best = SplitReconPlan{t.bm, t.bn, (int)s, apart, us, 0, 0, 0, 0, 1};
+        }
+        if (!alone || t.resident != 1 || (t.bm == 96 && chunks > 64)) continue;
+        const int64_t rows = (J - 4) / t.bm * t.bm, cols = (D - 4) / t.bn * t.bn; // (a launch takes four rows and columns and more)
+        if (cols > 0 && (((J + t.bm - 1) / t.bm) * (cols / t.bn) + 255) / 256 < (n + 255) / 256) {
+            const SplitReconPlan rest = plan_part(J, D - cols, N, room, apart, false);
+            const double us = cost(J, cols, 1, chunks) + rest.us;
+            if (us < 0.97 * best.us) best = SplitReconPlan{t.bm, t.bn, 1, apart, us, 0, (int)cols, rest.bm, rest.bn, rest.slices};
+        }
+        if (rows > 0 && ((rows / t.bm) * ((D + t.bn - 1) / t.bn) + 255) / 256 < (n + 255) / 256) {
+            const SplitReconPlan rest = plan_part(J - rows, D, N, room, apart, false);
+            const double us = cost(rows, D, 1, chunks) + rest.us;
+            if (us < 0.97 * best.us) best = SplitReconPlan{t.bm, t.bn, 1, apart, us, (int)rows, 0, rest.bm, rest.bn, rest.slices};
         }
     }
     return best;
 }
+// Where the last row or column of tiles is what begins another round of 256, it is a second, smaller launch with a plan of its
+// own (1001 x 4100, 488 pairs: 256 tiles of 128 x 128 and four columns, 42.7 -> 39.3 us; 1001 x 4129, 1000: 88.6 -> 59.7).
+SplitReconPlan reconstruct_split_plan(int64_t J, int64_t D, int64_t N, size_t room, bool apart) { return plan_part(J, D, N, room, apart, true); }
 
 template <int MT, int NT, bool APART>
 static hipError_t launch_tile(const ReconArgs& a, int slices, bool halves, hipStream_t s) {
@@ -280,19 +305,40 @@ static hipError_t launch_tile(const ReconArgs& a, int slices, bool halves, hipSt
     return e != hipSuccess ? e : launch_apply_partials(a, slices, a.D, s);
 }
 
-// plan.slices > 1: a.partial holds that many planes of J x D floats
-hipError_t launch_reconstruct_split(const ReconArgs& a, const SplitReconPlan& p, bool halves, hipStream_t s) {
-    halves = halves && a.N > 4 * kSpChunk;                               // two chunks or more in each
-    if (p.slices < 1 || (p.slices > 1 && a.partial == nullptr)) return hipErrorInvalidValue;
-    if (p.apart) {
-        if (p.bm == 64 && p.bn == 128) return launch_tile<1, 2, true>(a, p.slices, halves, s);
-        if (p.bm == 64 && p.bn == 64) return launch_tile<1, 1, true>(a, p.slices, halves, s);
+static hipError_t launch_part(const ReconArgs& a, int bm, int bn, int slices, bool apart, bool halves, hipStream_t s) {
+    if (slices < 1 || (slices > 1 && a.partial == nullptr)) return hipErrorInvalidValue;
+    if (apart) {
+        if (bm == 64 && bn == 128) return launch_tile<1, 2, true>(a, slices, halves, s);
+        if (bm == 64 && bn == 64) return launch_tile<1, 1, true>(a, slices, halves, s);
         return hipErrorInvalidValue;
     }
-    if (p.bm == 128 && p.bn == 128) return launch_tile<2, 2, false>(a, p.slices, halves, s);
-    if (p.bm == 64 && p.bn == 128) return launch_tile<1, 2, false>(a, p.slices, halves, s);
-    if (p.bm == 64 && p.bn == 64) return launch_tile<1, 1, false>(a, p.slices, halves, s);
+    if (bm == 128 && bn == 128) return launch_tile<2, 2, false>(a, slices, halves, s);
+    if (bm == 96 && bn == 128) return launch_tile<3, 1, false>(a, slices, halves, s);
+    if (bm == 64 && bn == 128) return launch_tile<1, 2, false>(a, slices, halves, s);
+    if (bm == 64 && bn == 64) return launch_tile<1, 1, false>(a, slices, halves, s);
     return hipErrorInvalidValue;
+}
+
+// plan.slices > 1 (or rest_slices): a.partial holds that many planes of J x D (of the rest's rows and columns) floats
+hipError_t launch_reconstruct_split(const ReconArgs& a, const SplitReconPlan& p, bool halves, hipStream_t s) {
+    halves = halves && a.N > 4 * kSpChunk;                               // two chunks or more in each
+    if (p.main_rows == 0 && p.main_cols == 0) return launch_part(a, p.bm, p.bn, p.slices, p.apart, halves, s);
+    ReconArgs b = a;
+    if (p.main_rows > 0) b.J = p.main_rows;
+    else b.D = p.main_cols;
+    const hipError_t e = launch_part(b, p.bm, p.bn, p.slices, p.apart, halves, s);
+    if (e != hipSuccess) return e;
+    const LaunchEvents main = launch_events();                           // the launch that is reported as the family's
+    b = a;
+    b.w += (int64_t)p.main_rows * a.ldw + p.main_cols;
+    b.u += p.main_rows;
+    b.v = (const float*)a.v + p.main_cols;
+    b.J -= p.main_rows;
+    b.D -= p.main_cols;
+    const hipError_t e2 = launch_part(b, p.rest_bm, p.rest_bn, p.rest_slices, p.apart, halves && p.rest_slices == 1, s);
+    launch_events().name = main.name;
+    launch_events().blocks = main.blocks;
+    return e2;
 }
 
 }  // namespace sfb

@@ -77,15 +77,15 @@ struct SplitQuad {
     }
 };
 
-// The multiplying side.  Tile (2 MT x 32) x (2 NT x 32), four wavefronts as 2 x 2, each MT x NT blocks of 32 x 32.
+// The multiplying side.  Tile (WM MT x 32) x (WN NT x 32), four wavefronts as WM x WN, each MT x NT blocks of 32 x 32.
 // PITCH: bytes from one LDS row to the next; SWZ: 16-byte item c of row r sits at c ^ f(r) instead of c.
 // APART: the five smaller term products have sums of their own, so that the leading ones' running sum is rounded once for
 // every sixteen k instead of six times (error of a sum of 4096 products 1.4e-7 instead of 2.5e-7, of 512 1.3e-7 instead of
 // 2.4e-7; the fp32 instruction 5.8e-7 and 2.9e-7): for callers who chose these products for their accuracy (sfb_set_plan).
 // No time of its own, but 64 x 64 blocks of a wavefront have no registers left for it.
-template <int MT, int NT, int PITCH, bool SWZ, bool APART>
+template <int MT, int NT, int PITCH, bool SWZ, bool APART, int WM = 2>
 struct SplitTile {
-    static constexpr int BM = 64 * MT, BN = 64 * NT, ROWS = BM + BN;
+    static constexpr int WN = 4 / WM, BM = 32 * WM * MT, BN = 32 * WN * NT, ROWS = BM + BN;
     static constexpr int PLANE = ROWS * PITCH, BYTES = 3 * PLANE;      // one group's buffer
     static constexpr int XCHG = 8 * MT * NT * 8 * 64 * 4;               // exchange of partial sums at the end
     static constexpr int LDS = 2 * BYTES > XCHG ? 2 * BYTES : XCHG;
@@ -100,7 +100,7 @@ struct SplitTile {
     int a_base, b_base;            // byte offset of this lane's item in the A and the B part
 
     __device__ __forceinline__ void init(int wave, int lane) {
-        const int wm = (wave & 3) >> 1, wn = wave & 1, l32 = lane & 31, half = lane >> 5;
+        const int wm = (wave & 3) / WN, wn = wave % WN, l32 = lane & 31, half = lane >> 5;
         // every row this lane reads is l32 modulo 32
         const int item = 16 * ((2 * (wave >> 2) + half) ^ swz(l32));
         a_base = (wm * 32 * MT + l32) * PITCH + item;

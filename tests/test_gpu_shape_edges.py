@@ -387,3 +387,41 @@ def test_classes_switched_off_by_infinite_weights_do_not_stall_the_split_product
     print("scores and update, us: finite", times[0], "with infinities", times[1])
     ctx.close()
     assert times[1][0] < 8 * times[0][0] and times[1][1] < 8 * times[0][1]
+
+
+@pytest.mark.parametrize("J,D,P,B,grid", [
+    (1001, 4100, 8, 61, 256),                                   # 256 tiles of 128 x 128 and four columns
+    (1030, 4096, 8, 64, 256),                                   # ... and six rows
+    (1001, 4129, 4, 130, 256),                                  # ... and 33 columns
+    (600, 4096, 4, 128, 224),                                   # tiles of 96 rows
+    (1152, 2750, 6, 90, 198),
+])
+@pytest.mark.parametrize("masked", [False, True])
+def test_updates_whose_last_tiles_are_a_launch_of_their_own(J, D, P, B, grid, masked):
+    """Every entry against fp64, with infinities in the last column and row, in rows of W that have words between them.  Sums of
+    N products rounded six times for every sixteen: 2^-24 (6 N / 16 + 2) sum |u v|, and the update's own rounding."""
+    import paper_1511_08486_amd as sfb
+    dev, N, g = "cuda:0", P * B, torch.Generator(device="cuda:0").manual_seed(J)
+    U, V = torch.randn((N, J), generator=g, device=dev), torch.randn((N, D), generator=g, device=dev)
+    W = torch.randn((J, D + 3), generator=g, device=dev)
+    W[:, D:] = float("nan")
+    W0, active = W.clone(), [p != 1 for p in range(P)] if masked else None
+    U[3, J - 1] = V[5, D - 1] = float("inf")
+    if masked:
+        U[B:2 * B] = float("nan")
+    live = torch.ones(N, dtype=torch.bool, device=dev)
+    if masked:
+        live[B:2 * B] = False
+    ctx = sfb.Sfb("l2svm", J, D, P, B, device=dev)
+    ctx.reconstruct_apply(W[:, :D], U, V, 0.5, scale=1.0, active=active)
+    ctx.sync()
+    name, blocks = ctx.last_kernel(2)
+    assert name == "reconstruct_split_kernel" and blocks == grid
+    Ul, Vl = U[live].double(), V[live].double()
+    want, got = W0[:, :D].double() - 0.5 * (Ul.T @ Vl), W[:, :D].double()
+    assert torch.equal(torch.isnan(got), torch.isnan(want)) and torch.equal(got[torch.isinf(want)], want[torch.isinf(want)])
+    room = 0.5 * 2.0 ** -24 * (6 * N / 16 + 2) * (Ul.abs().T @ Vl.abs()) + 2.0 ** -23 * want.abs()
+    ok = torch.isfinite(want)
+    assert ((got - want)[ok].abs() <= room[ok]).all()
+    assert torch.isnan(W[:, D:]).all()
+    ctx.close()
