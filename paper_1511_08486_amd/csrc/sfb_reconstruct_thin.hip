@@ -341,15 +341,15 @@ static hipError_t launch_thin(const ReconArgs& a, hipStream_t s) {
     return launch_form<ThinFp32<STAGES, false, false>>(a, 64, s);
 }
 
-// Split products: 17 to 64 pairs, where the fp32 instruction's copies into LDS go word by word (unaligned rows, masks: 1001 x 4099, 20
-// pairs: 9.9 us against 12.9, 61: 12.2 and 15.2), or W is large enough for its products to show: more than 48 pairs on more than
-// 512 tiles of 64 x 64 (1000 x 4096, 64: 9.6 us against 9.5 to 10.6, by where W lies), fewer on more than 1536 (4000 x 2000, 32: 14.8 and
-// 15.7; 2000 x 8192: 22.6 and 25.9; 64: 27 and 32.5).  Below, their chain of splits takes longer than it saves (1000 x 2048, 64: 5.8 and 5.4;
-// 1000 x 4096, 48: 9.7 and 8.5).
+// Split products: 17 to 64 pairs on a W large enough for its products to show.  Where the fp32 instruction's copies into LDS go word by
+// word (unaligned rows, masks) that is from 256 tiles of 64 x 64 on (601 x 2000, 24 pairs: 5.1 us against 5.5, 64: 5.5 and 6.7; 1001 x 4099, 61:
+// 12.2 and 15.2; 401 x 2000, 40: 5.5 and 5.1); elsewhere from 512 with more than 48 pairs (1000 x 4096, 64: 9.6 us against 9.5 to 10.6, by
+// where W lies; 1000 x 2048: 5.8 and 5.4) and from 1536 with fewer (4000 x 2000, 32: 14.8 and 15.7; 2000 x 8192: 22.6 and 25.9; 1000 x
+// 4096, 48: 9.7 and 8.5).
 static bool thin_split_wins(const ReconArgs& a) {
     const int64_t tiles = (int64_t)((a.J + 63) / 64) * ((a.D + 63) / 64);
     return a.N > 16 && a.N <= 64 && a.J >= 4 && a.D >= 4 && (!a.use_mask || a.B > 1) && a.ldu < (1 << 23) && a.ldv < (1 << 23) &&
-           (!thin_wide(a) || tiles > (a.N > 48 ? 512 : 1536));
+           tiles > (!thin_wide(a) ? 256 : a.N > 48 ? 512 : 1536);
 }
 
 // Up to 64 pairs always (1000 x 4096: 7.9 us with 8 pairs, 10.6 with 64, against 14.9 and 12.0 with the kernels that stage

@@ -1,4 +1,4 @@
-"""Updates from 17 to 64 pairs as split products: edges of tiles, rows at any alignment, dead workers, infinities, against fp64.
+"""Updates from 17 to 64 pairs, as split products (256 tiles of 64 x 64 and more) and, on a smaller W, by the fp32 instruction: edges of tiles, rows at any alignment, dead workers, infinities, against fp64.
 
 Bound of an entry: what the split drops is below 2^-24 |u v| a product and the leading sums are rounded four times, the small ones
 twenty times at 2^-8 of their size: 2^-22 sum |u v|, and a unit in the last place of the result for the update itself."""
@@ -13,8 +13,8 @@ DEV = "cuda:0"
 
 
 @pytest.mark.parametrize("J,D,P,B", [
-    (4, 4, 2, 9), (5, 7, 3, 6), (63, 129, 2, 16), (64, 128, 3, 11), (66, 131, 2, 17), (130, 258, 4, 12), (257, 513, 8, 8), (1000, 2050, 4, 16),
-    (2100, 3200, 2, 30),
+    (4, 16450, 2, 9), (16451, 5, 3, 6), (63, 16513, 2, 16), (1025, 1027, 3, 11), (1030, 1090, 2, 17), (1090, 1025, 4, 12), (1000, 2050, 4, 16),
+    (2100, 3200, 2, 30), (66, 131, 2, 17), (130, 258, 4, 12),
 ])
 @pytest.mark.parametrize("pad,shift,dead,kind", [(1, 1, False, "none"), (2, 3, True, "l1"), (0, 0, True, "none"), (0, 0, False, "l2sq")])
 def test_update(J, D, P, B, pad, shift, dead, kind):
