@@ -253,8 +253,7 @@ sfb_status factor_rows(sfb_ctx* c, int split_k, int64_t zstride, const int32_t* 
     g.y = y; g.u = U + row0 * ldu; g.ldu = ldu; g.loss = loss ? loss + row0 : nullptr;
     g.n_rows = n_rows; g.J = (int)c->J; g.model = (Model)c->model;
     if (sdca) {
-        const bool vec = ((uintptr_t)sdca->dual % 16) == 0 && (sdca->ld_dual % 4) == 0;
-        g.sdca = SdcaDev{sdca->sample, sdca->dual, sdca->ld_dual, sdca->conj, sdca->s, vec};
+        g.sdca = SdcaDev{sdca->sample, sdca->dual, sdca->ld_dual, sdca->conj, sdca->s};
     }
     Timed t(c, 1);
     hipError_t e = launch_factor(g, c->stream);
@@ -290,8 +289,6 @@ sfb_status few_rows(sfb_ctx* c, float* W, int64_t ldw, const sfb_batch* b, const
     f.n_rows = n_rows; f.J = (int)c->J; f.D = (int)c->D; f.B = c->B;
     f.alpha = alpha;
     f.live_mask = live_workers(c, active, &f.use_mask);
-    f.vec_a = ((uintptr_t)f.a % 8) == 0 && (f.lda % 4) == 0;
-    f.vec_v = ((uintptr_t)f.v % 8) == 0 && (f.ldv % 4) == 0;
     f.prox_kind = prox_kind; f.prox_a = prox_a;
     {
         Timed t(c, 0);

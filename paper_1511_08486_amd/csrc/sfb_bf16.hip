@@ -296,7 +296,7 @@ __global__ __launch_bounds__(WGM * WGN * 64, WPS) void nt_bf16_kernel(
 __global__ __launch_bounds__(256) void transpose_pack_kernel(
     const float* __restrict__ U, int64_t ldu, const bf16_t* __restrict__ V, int64_t ldv, bf16_t* __restrict__ UT,
     bf16_t* __restrict__ VT, int64_t ldn, int N, int J, int D, int B, float alpha, uint64_t live_mask,
-    bool use_mask, int n_jblk, int n_dblk, bool vec_u, bool vec_v) {
+    bool use_mask, int n_jblk, int n_dblk) {
     __shared__ __attribute__((aligned(16))) bf16_t tile[64][72];   // [column of the source][n], 144-byte rows
     const int tid = threadIdx.x;
     const int n_cblk = n_jblk + n_dblk;
@@ -312,9 +312,8 @@ __global__ __launch_bounds__(256) void transpose_pack_kernel(
         if (use_mask && live) live = (live_mask >> (n / B)) & 1ull;
         f32x4 v = {0.f, 0.f, 0.f, 0.f};
         if (live) {
-            // one wide load where the host found the rows aligned for it and the four entries exist
-            if (is_u) v = load4(U + (int64_t)n * ldu, c, ncols, vec_u) * alpha;
-            else v = load4(V + (int64_t)n * ldv, c, ncols, vec_v);
+            if (is_u) v = load4(U + (int64_t)n * ldu, c, ncols) * alpha;
+            else v = load4(V + (int64_t)n * ldv, c, ncols);
         }
 #pragma unroll
         for (int e = 0; e < 4; ++e) tile[(tid & 15) * 4 + e][(tid >> 4) + 16 * i] = f32_to_bf16(v[e]);
@@ -354,8 +353,7 @@ hipError_t launch_reconstruct_bf16(const ReconArgs& a, void* ws, hipStream_t s) 
     // plain launch: an armed pair of timing events belongs to the contraction below
     hipLaunchKernelGGL(transpose_pack_kernel, dim3((n_jblk + n_dblk) * n_kblk), dim3(256), 0, s, a.u, a.ldu,
                        (const bf16_t*)a.v, a.ldv, UT, VT, ldn, a.N, a.J, a.D, a.B, a.alpha, a.live_mask, a.use_mask,
-                       n_jblk, n_dblk, ((uintptr_t)a.u % 16) == 0 && (a.ldu % 4) == 0,
-                       ((uintptr_t)a.v % 8) == 0 && (a.ldv % 4) == 0);
+                       n_jblk, n_dblk);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     constexpr int NST = 3, BK = kBfReconBK, WPS = kBfReconWPS;

@@ -42,21 +42,11 @@ __device__ __forceinline__ float group_max(float v, float* red) {
     return fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
 }
 
-__device__ __forceinline__ f32x4 load4_guarded(const float* row, int col, int ncols, bool vec) {
-    if (vec && col + 3 < ncols) return *reinterpret_cast<const f32x4*>(row + col);
-    f32x4 v{0.f, 0.f, 0.f, 0.f};
-    if (col + 0 < ncols) v.x = row[col + 0];
-    if (col + 1 < ncols) v.y = row[col + 1];
-    if (col + 2 < ncols) v.z = row[col + 2];
-    if (col + 3 < ncols) v.w = row[col + 3];
-    return v;
-}
-
 // R = 128-bit items per thread held in registers: covers J <= GROUP * 4 * R.
 template <int MODEL, int GROUP, int R, bool SDCA>
 __global__ __launch_bounds__(kFactorThreads) void factor_u_kernel(
     const float* __restrict__ Zp, int64_t ldz, int64_t zstride, int split_k, const int32_t* __restrict__ y,
-    float* __restrict__ U, int64_t ldu, float* __restrict__ loss, int n_rows, int J, bool vec_u, SdcaDev sd) {
+    float* __restrict__ U, int64_t ldu, float* __restrict__ loss, int n_rows, int J, SdcaDev sd) {
     static_assert(!SDCA || MODEL == kMLR, "the dual update is defined for the logistic loss only");
     __shared__ float red[4];
     constexpr int ROWS = kFactorThreads / GROUP;
@@ -130,7 +120,7 @@ __global__ __launch_bounds__(kFactorThreads) void factor_u_kernel(
 #pragma unroll
             for (int r = 0; r < R; ++r) {
                 const int col = 4 * (t + GROUP * r);
-                f32x4 dv = load4_guarded(drow, col < J ? col : 0, J, sd.vec);
+                f32x4 dv = load4(drow, col < J ? col : 0, J);
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     const float du = sd.frac * (dv[e] + z[r][e]);
@@ -139,7 +129,7 @@ __global__ __launch_bounds__(kFactorThreads) void factor_u_kernel(
                     const float pj = ((col + e == label) ? 1.0f : 0.0f) - dv[e];
                     cj += (col + e < J && pj > 0.f) ? pj * __logf(pj) : 0.f;
                 }
-                if (live && col < J) store4(drow, col, J, sd.vec, dv);
+                if (live && col < J) store4(drow, col, J, dv);
             }
             cj = group_sum<GROUP>(cj, red);
             if (live && sd.conj != nullptr && t == 0) sd.conj[si] = cj;
@@ -174,7 +164,7 @@ __global__ __launch_bounds__(kFactorThreads) void factor_u_kernel(
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             const int col = 4 * (t + GROUP * r);
-            if (col < J) store4(U + (int64_t)row * ldu, col, J, vec_u, z[r]);
+            if (col < J) store4(U + (int64_t)row * ldu, col, J, z[r]);
         }
         if (loss != nullptr && t == 0) loss[row] = f;
     }
@@ -252,12 +242,11 @@ __global__ __launch_bounds__(kFactorThreads) void factor_u_long_kernel(
 
 template <int MODEL, bool SDCA>
 static hipError_t launch_factor_m(const FactorArgs& a, hipStream_t s) {
-    const bool vec_u = ((uintptr_t)a.u % 16) == 0 && (a.ldu % 4) == 0;
 #define SFB_FACTOR_LAUNCH(GROUP, R)                                                                     \
     SFB_LAUNCH((factor_u_kernel<MODEL, GROUP, R, SDCA>),                                                \
                        dim3((a.n_rows + (kFactorThreads / GROUP) - 1) / (kFactorThreads / GROUP)),      \
                        dim3(kFactorThreads), 0, s, a.zp, a.ldz, a.zstride, a.split_k, a.y, a.u, a.ldu,  \
-                       a.loss, a.n_rows, a.J, vec_u, a.sdca)
+                       a.loss, a.n_rows, a.J, a.sdca)
     if (a.J <= 64 * 4 * 1) SFB_FACTOR_LAUNCH(64, 1);
     else if (a.J <= 256 * 4 * 1) SFB_FACTOR_LAUNCH(256, 1);
     else if (a.J <= 256 * 4 * 4) SFB_FACTOR_LAUNCH(256, 4);

@@ -36,8 +36,7 @@ __device__ __forceinline__ f32x4 few_load4(const float* __restrict__ row, int co
         if (col + e < cols) r[e] = row[col + e];
     return r;
 }
-__device__ __forceinline__ f32x4 few_load4(const float* __restrict__ row, int col, int cols, bool) { return few_load4(row, col, cols); }
-__device__ __forceinline__ f32x4 few_load4(const bf16_t* __restrict__ row, int col, int cols, bool vec) { return load4(row, col, cols, vec); }
+__device__ __forceinline__ f32x4 few_load4(const bf16_t* __restrict__ row, int col, int cols) { return load4(row, col, cols); }
 __device__ __forceinline__ void few_store4(float* __restrict__ row, int col, int cols, f32x4 v) {
     if (col + 4 <= cols) {
         *reinterpret_cast<few_f32x4u*>(row + col) = v;
@@ -47,8 +46,7 @@ __device__ __forceinline__ void few_store4(float* __restrict__ row, int col, int
             if (col + e < cols) row[col + e] = v[e];
     }
 }
-__device__ __forceinline__ void few_store4(float* __restrict__ row, int col, int cols, bool, f32x4 v) { few_store4(row, col, cols, v); }
-__device__ __forceinline__ void few_store4(bf16_t* __restrict__ row, int col, int cols, bool vec, f32x4 v) { store4(row, col, cols, vec, v); }
+__device__ __forceinline__ void few_store4(bf16_t* __restrict__ row, int col, int cols, f32x4 v) { store4(row, col, cols, v); }
 
 // NJ: class blocks of 16.  UPDATE: 0 factors only, 1 sums into plane blockIdx.x of `planes`, 2 straight into W (one workgroup).
 template <typename TIn, bool DIFF, int NJ, int UPDATE>
@@ -77,14 +75,14 @@ __global__ __launch_bounds__(kFewThreads) void few_step_kernel(FewArgs a, int ro
                 const int i = min(i0 + q * kFewThreads + tid, total - 1);
                 r[q] = i / items;
                 c[q] = 4 * (i - r[q] * items);
-                x[q] = few_load4(A + (int64_t)r[q] * a.lda, c[q], a.D, a.vec_a);
-                if (DIFF) x[q] -= few_load4(A2 + (int64_t)r[q] * a.lda, c[q], a.D, a.vec_a);
+                x[q] = few_load4(A + (int64_t)r[q] * a.lda, c[q], a.D);
+                if (DIFF) x[q] -= few_load4(A2 + (int64_t)r[q] * a.lda, c[q], a.D);
             }
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 if (i0 + q * kFewThreads + tid < total) {
                     *reinterpret_cast<f32x4*>(&feat[r[q] * pitch + c[q]]) = x[q];
-                    few_store4(V + (int64_t)r[q] * a.ldv, c[q], a.D, a.vec_v, x[q]);
+                    few_store4(V + (int64_t)r[q] * a.ldv, c[q], a.D, x[q]);
                 }
             }
         }

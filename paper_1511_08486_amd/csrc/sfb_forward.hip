@@ -36,8 +36,7 @@ template <int BM, int BN, typename TIn, bool DIFF, bool FAST>
 __global__ __launch_bounds__(kFwdThreads) void fwd_scores_kernel(
     const TIn* __restrict__ A, const TIn* __restrict__ A2, int64_t lda, const float* __restrict__ W,
     int64_t ldw, float* __restrict__ Zp, int64_t ldz, int64_t zstride, TIn* __restrict__ V, int64_t ldv,
-    int n_rows, int J, int D, int k_slice, int n_nb, int n_jb, int total, bool vec_a, bool vec_w,
-    bool vec_v) {
+    int n_rows, int J, int D, int k_slice, int n_nb, int n_jb, int total) {
     constexpr int BK = kFwdBK, LS = kFwdLds;
     constexpr int WM = BM / 2, WN = BN / 2;       // 2 x 2 waves
     constexpr int MT = WM / 32, NT = WN / 32;
@@ -118,7 +117,7 @@ __global__ __launch_bounds__(kFwdThreads) void fwd_scores_kernel(
             *reinterpret_cast<f32x4*>(&As[buf * BM * LS + rr * LS + cc]) = v;
             if (my_v && in) {
                 if constexpr (FAST) *reinterpret_cast<RawA*>(V + (int64_t)row * ldv + col) = to_raw<TIn>(v);
-                else store4(V + (int64_t)row * ldv, col, k_end, vec_v, v);
+                else store4(V + (int64_t)row * ldv, col, k_end, v);
             }
         }
 #pragma unroll
@@ -459,8 +458,7 @@ void finish_forward_plan(FwdPlan* p, int64_t n_rows, int64_t J, int64_t D) {
 }
 
 template <int BM, int BN, typename TIn, bool DIFF, bool FAST>
-static hipError_t launch_fwd_f(const FwdArgs& a, const FwdPlan& p, hipStream_t s, bool vec_a, bool vec_w,
-                               bool vec_v) {
+static hipError_t launch_fwd_f(const FwdArgs& a, const FwdPlan& p, hipStream_t s) {
     const int n_nb = (a.n_rows + BM - 1) / BM, n_jb = (a.J + BN - 1) / BN;
     const int total = n_nb * n_jb * p.split_k;
     constexpr size_t lds_bytes = 2 * (BM + BN) * kFwdLds * sizeof(float);
@@ -473,7 +471,7 @@ static hipError_t launch_fwd_f(const FwdArgs& a, const FwdPlan& p, hipStream_t s
     }
     SFB_LAUNCH((fwd_scores_kernel<BM, BN, TIn, DIFF, FAST>), dim3(total), dim3(kFwdThreads), lds_bytes,
                        s, (const TIn*)a.a, (const TIn*)a.a2, a.lda, a.w, a.ldw, a.zp, a.ldz, a.zstride,
-                       (TIn*)a.v, a.ldv, a.n_rows, a.J, a.D, p.k_slice, n_nb, n_jb, total, vec_a, vec_w, vec_v);
+                       (TIn*)a.v, a.ldv, a.n_rows, a.J, a.D, p.k_slice, n_nb, n_jb, total);
     return hipGetLastError();
 }
 
@@ -487,8 +485,8 @@ static hipError_t launch_fwd_t(const FwdArgs& a, const FwdPlan& p, hipStream_t s
     const bool vec_w = aligned(a.w, a.ldw, 16);
     const bool vec_v = aligned(a.v, a.ldv, 4 * esz);
     const bool fast = vec_a && vec_w && vec_v && (a.D % 4) == 0 && a.D >= 4;
-    if (fast) return launch_fwd_f<BM, BN, TIn, DIFF, true>(a, p, s, vec_a, vec_w, vec_v);
-    return launch_fwd_f<BM, BN, TIn, DIFF, false>(a, p, s, vec_a, vec_w, vec_v);
+    if (fast) return launch_fwd_f<BM, BN, TIn, DIFF, true>(a, p, s);
+    return launch_fwd_f<BM, BN, TIn, DIFF, false>(a, p, s);
 }
 
 template <typename TIn, bool DIFF>

@@ -325,7 +325,7 @@ __global__ __launch_bounds__(kFuThreads) void update_score_kernel(
 __global__ __launch_bounds__(256) void fused_pack_kernel(
     const float* __restrict__ U, int64_t ldu, bf16_t* __restrict__ V, int64_t ldv, const bf16_t* __restrict__ A,
     int64_t lda, bf16_t* __restrict__ UT, bf16_t* __restrict__ VTp, bf16_t* __restrict__ AnP, int N, int J, int D, int B,
-    float alpha, uint64_t live_mask, bool use_mask, int n_jblk, int n_dblk, bool vec_u) {
+    float alpha, uint64_t live_mask, bool use_mask, int n_jblk, int n_dblk) {
     // [column of the source][pair of samples]: a word holds samples 2 w and 2 w + 1 of one column as bf16.  Rows of
     // 36 words (144 bytes); the 4-word group g of row r sits at group g ^ (r / 4 % 8), so that the 64 lanes of a
     // write (16 column quads x 4 pairs) fall two to a bank, and a 16-byte read still finds its 8 samples together.
@@ -357,8 +357,8 @@ __global__ __launch_bounds__(256) void fused_pack_kernel(
             v[h] = f32x4{0.f, 0.f, 0.f, 0.f};
             if (live) {
                 // one 16-byte (U) or 8-byte (V: host guarantees 16-byte aligned rows) load where the four entries exist
-                if (is_u) v[h] = load4(U + (int64_t)n * ldu, c, ncols, vec_u) * alpha;
-                else v[h] = load4(V + (int64_t)n * ldv, c, ncols, true);
+                if (is_u) v[h] = load4(U + (int64_t)n * ldu, c, ncols) * alpha;
+                else v[h] = load4(V + (int64_t)n * ldv, c, ncols);
             }
         }
         const int word = np ^ (4 * ((tid & 15) & 7));                       // row / 4 = tid & 15
@@ -466,7 +466,7 @@ hipError_t launch_fused(const FusedArgs& a, const FusedPlan& p, void* ws_factors
     // a plain launch: an armed pair of timing events belongs to the fused kernel below
     hipLaunchKernelGGL(fused_pack_kernel, dim3((n_jblk + n_dblk) * n_kblk), dim3(256), 0, s, a.u, a.ldu, (bf16_t*)a.v, a.ldv,
                        (const bf16_t*)a.a_next, a.lda, UT, VTp, AnP, a.N, a.J, a.D, a.B, a.alpha, a.live_mask, a.use_mask,
-                       n_jblk, n_dblk, ((uintptr_t)a.u % 16) == 0 && (a.ldu % 4) == 0);
+                       n_jblk, n_dblk);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     switch (a.N) {

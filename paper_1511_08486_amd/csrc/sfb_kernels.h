@@ -81,7 +81,6 @@ struct SdcaDev {
     int64_t ldd;
     float* conj;             // [n_data] or nullptr: f_i*(-u_i) after the update
     float frac;
-    bool vec;                // rows of `dual` are 16-byte aligned
 };
 
 struct FactorArgs {
@@ -286,7 +285,6 @@ struct FewArgs {
     float alpha;
     uint64_t live_mask;
     bool use_mask, bf16, diff;
-    bool vec_a, vec_v;                 // bf16 rows of a / v are 8-byte aligned
     int prox_kind;
     float prox_a;
 };

@@ -39,20 +39,10 @@ size_t prox_workspace(int64_t J, int64_t D) {
     return (size_t)(chunks + 1) * ldp * sizeof(float);     // partial sums, then one row of scale factors
 }
 
-__device__ __forceinline__ f32x4 prox_load(const float* row, int col, int D, bool vec) {
-    if (vec && col + 3 < D) return *reinterpret_cast<const f32x4*>(row + col);
-    f32x4 v{0.f, 0.f, 0.f, 0.f};
-    if (col + 0 < D) v.x = row[col + 0];
-    if (col + 1 < D) v.y = row[col + 1];
-    if (col + 2 < D) v.z = row[col + 2];
-    if (col + 3 < D) v.w = row[col + 3];
-    return v;
-}
-
 // KIND 1: w * a (a = 1 / (1 + eta lam));  KIND 2: soft threshold at a = eta lam
 template <int KIND>
 __global__ __launch_bounds__(kProxThreads) void prox_entry_kernel(float* __restrict__ W, int64_t ldw, int J, int D,
-                                                                  int rows_per_chunk, float a, bool vec) {
+                                                                  int rows_per_chunk, float a) {
     const int col = blockIdx.x * kProxCols + threadIdx.x * 4;
     if (col >= D) return;
     const int r0 = blockIdx.y * rows_per_chunk;
@@ -61,21 +51,21 @@ __global__ __launch_bounds__(kProxThreads) void prox_entry_kernel(float* __restr
     for (int r = r0; r < r1; r += UN) {
         f32x4 v[UN];
 #pragma unroll
-        for (int i = 0; i < UN; ++i) v[i] = prox_load(W + (int64_t)min(r + i, r1 - 1) * ldw, col, D, vec);
+        for (int i = 0; i < UN; ++i) v[i] = load4(W + (int64_t)min(r + i, r1 - 1) * ldw, col, D);
 #pragma unroll
         for (int i = 0; i < UN; ++i) {
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 v[i][e] = prox_entry(v[i][e], KIND, a);
             }
-            if (r + i < r1) store4(W + (int64_t)(r + i) * ldw, col, D, vec, v[i]);
+            if (r + i < r1) store4(W + (int64_t)(r + i) * ldw, col, D, v[i]);
         }
     }
 }
 
 __global__ __launch_bounds__(kProxThreads) void column_sumsq_kernel(const float* __restrict__ W, int64_t ldw, int J,
                                                                     int D, int rows_per_chunk,
-                                                                    float* __restrict__ partial, int64_t ldp, bool vec) {
+                                                                    float* __restrict__ partial, int64_t ldp) {
     const int col = blockIdx.x * kProxCols + threadIdx.x * 4;
     if (col >= D) return;
     const int r0 = blockIdx.y * rows_per_chunk;
@@ -85,7 +75,7 @@ __global__ __launch_bounds__(kProxThreads) void column_sumsq_kernel(const float*
     for (int r = r0; r < r1; r += UN) {
         f32x4 v[UN];
 #pragma unroll
-        for (int i = 0; i < UN; ++i) v[i] = prox_load(W + (int64_t)min(r + i, r1 - 1) * ldw, col, D, vec);
+        for (int i = 0; i < UN; ++i) v[i] = load4(W + (int64_t)min(r + i, r1 - 1) * ldw, col, D);
 #pragma unroll
         for (int i = 0; i < UN; ++i)
             if (r + i < r1) acc += v[i] * v[i];
@@ -118,7 +108,7 @@ __global__ __launch_bounds__(kProxThreads) void column_scale_kernel(const float*
 
 __global__ __launch_bounds__(kProxThreads) void column_rescale_kernel(float* __restrict__ W, int64_t ldw, int J, int D,
                                                                       int rows_per_chunk,
-                                                                      const float* __restrict__ scale, bool vec) {
+                                                                      const float* __restrict__ scale) {
     const int col = blockIdx.x * kProxCols + threadIdx.x * 4;
     if (col >= D) return;
     // the scale row is padded to a multiple of 4 floats; entries at or beyond D are never used
@@ -132,10 +122,10 @@ __global__ __launch_bounds__(kProxThreads) void column_rescale_kernel(float* __r
     for (int r = r0; r < r1; r += UN) {
         f32x4 v[UN];
 #pragma unroll
-        for (int i = 0; i < UN; ++i) v[i] = prox_load(W + (int64_t)min(r + i, r1 - 1) * ldw, col, D, vec);
+        for (int i = 0; i < UN; ++i) v[i] = load4(W + (int64_t)min(r + i, r1 - 1) * ldw, col, D);
 #pragma unroll
         for (int i = 0; i < UN; ++i)
-            if (r + i < r1) store4(W + (int64_t)(r + i) * ldw, col, D, vec, v[i] * s);
+            if (r + i < r1) store4(W + (int64_t)(r + i) * ldw, col, D, v[i] * s);
     }
 }
 
@@ -143,16 +133,14 @@ hipError_t launch_prox(const ProxArgs& a, void* workspace, hipStream_t s) {
     const int rc = prox_rows_per_chunk(a.J, a.D);
     const int chunks = (a.J + rc - 1) / rc;
     const dim3 grid((a.D + kProxCols - 1) / kProxCols, chunks);
-    const bool vec = ((uintptr_t)a.w % 16) == 0 && (a.ldw % 4) == 0;
     switch (a.kind) {
         case 0: return hipSuccess;
         case 1:
             SFB_LAUNCH(prox_entry_kernel<1>, grid, dim3(kProxThreads), 0, s, a.w, a.ldw, a.J, a.D, rc,
-                       1.0f / (1.0f + a.eta * a.param), vec);
+                       1.0f / (1.0f + a.eta * a.param));
             return hipGetLastError();
         case 2:
-            SFB_LAUNCH(prox_entry_kernel<2>, grid, dim3(kProxThreads), 0, s, a.w, a.ldw, a.J, a.D, rc, a.eta * a.param,
-                       vec);
+            SFB_LAUNCH(prox_entry_kernel<2>, grid, dim3(kProxThreads), 0, s, a.w, a.ldw, a.J, a.D, rc, a.eta * a.param);
             return hipGetLastError();
         case 3: {
             const int64_t ldp = ((int64_t)a.D + 3) / 4 * 4;
@@ -160,11 +148,11 @@ hipError_t launch_prox(const ProxArgs& a, void* workspace, hipStream_t s) {
             float* scale = partial + (int64_t)chunks * ldp;
             // the timed kernel of this family: it always makes its full pass over W
             SFB_LAUNCH(column_sumsq_kernel, grid, dim3(kProxThreads), 0, s, (const float*)a.w, a.ldw, a.J, a.D, rc,
-                       partial, ldp, vec);
+                       partial, ldp);
             hipLaunchKernelGGL(column_scale_kernel, dim3((a.D + 63) / 64), dim3(kProxThreads), 0,
                                s, (const float*)partial, ldp, chunks, a.D, a.param, scale);
             hipLaunchKernelGGL(column_rescale_kernel, grid, dim3(kProxThreads), 0, s, a.w, a.ldw, a.J, a.D, rc,
-                               (const float*)scale, vec);
+                               (const float*)scale);
             return hipGetLastError();
         }
     }

@@ -44,8 +44,8 @@ constexpr int kReconGroup = 4; // MFMA k-steps (of 2 factor pairs each) per oper
 template <int MT, int NWR, int KS, typename TV, bool FAST, bool MASK>
 __global__ __launch_bounds__(NWR * KS * 64) void reconstruct_apply_kernel(
     float* __restrict__ W, int64_t ldw, const float* __restrict__ U, int64_t ldu, const TV* __restrict__ V,
-    int64_t ldv, int J, int D, int N, int B, float alpha, uint64_t live_mask, int n_jb, int total, bool vec_w,
-    bool vec_u, bool vec_v, int prox_kind, float prox_a) {
+    int64_t ldv, int J, int D, int N, int B, float alpha, uint64_t live_mask, int n_jb, int total,
+    int prox_kind, float prox_a) {
     constexpr int BK = kReconBK, BN = kReconBN, G = kReconGroup;
     constexpr int WMR = 32 * MT;            // rows per wavefront
     constexpr int BM = WMR * NWR;
@@ -285,7 +285,7 @@ __global__ __launch_bounds__(NWR * KS * 64) void reconstruct_apply_kernel(
                     w.w += acc[t][3][K * EH + x];
                     w = prox_entry4(w, prox_kind, prox_a);
                     if (FAST) *reinterpret_cast<f32x4*>(W + (int64_t)row * ldw + d0 + 4 * l32) = w;
-                    else store4(W + (int64_t)row * ldw, d0 + 4 * l32, D, vec_w, w);
+                    else store4(W + (int64_t)row * ldw, d0 + 4 * l32, D, w);
                 }
             }
     };
@@ -630,7 +630,7 @@ ReconPlan plan_reconstruct_variant(int64_t J, int64_t D, int variant) {
 }
 
 template <int MT, int NWR, int KS, typename TV, bool FAST, bool MASK>
-static hipError_t launch_recon_f(const ReconArgs& a, hipStream_t s, bool vec_w, bool vec_u, bool vec_v) {
+static hipError_t launch_recon_f(const ReconArgs& a, hipStream_t s) {
     constexpr int BM = 32 * MT * NWR;
     const int n_jb = (a.J + BM - 1) / BM, n_db = (a.D + kReconBN - 1) / kReconBN;
     const int total = n_jb * n_db;
@@ -644,7 +644,7 @@ static hipError_t launch_recon_f(const ReconArgs& a, hipStream_t s, bool vec_w, 
     }
     SFB_LAUNCH((reconstruct_apply_kernel<MT, NWR, KS, TV, FAST, MASK>), dim3(total),
                        dim3(NWR * KS * 64), lds_bytes, s, a.w, a.ldw, a.u, a.ldu, (const TV*)a.v, a.ldv, a.J, a.D,
-                       a.N, a.B, a.alpha, a.live_mask, n_jb, total, vec_w, vec_u, vec_v, a.prox_kind, a.prox_a);
+                       a.N, a.B, a.alpha, a.live_mask, n_jb, total, a.prox_kind, a.prox_a);
     return hipGetLastError();
 }
 
@@ -655,10 +655,10 @@ static hipError_t launch_recon_t(const ReconArgs& a, hipStream_t s) {
     const bool vec_v = ((uintptr_t)a.v % (4 * sizeof(TV))) == 0 && (a.ldv % 4) == 0;
     const bool fast = vec_w && vec_u && vec_v && (a.D % kReconBN) == 0 && (a.J % 4) == 0 && a.J >= 4;
     if (a.use_mask) {   // a worker is missing: rare, so only the generic kernel carries the mask
-        return launch_recon_f<MT, NWR, KS, TV, false, true>(a, s, vec_w, vec_u, vec_v);
+        return launch_recon_f<MT, NWR, KS, TV, false, true>(a, s);
     }
-    if (fast) return launch_recon_f<MT, NWR, KS, TV, true, false>(a, s, vec_w, vec_u, vec_v);
-    return launch_recon_f<MT, NWR, KS, TV, false, false>(a, s, vec_w, vec_u, vec_v);
+    if (fast) return launch_recon_f<MT, NWR, KS, TV, true, false>(a, s);
+    return launch_recon_f<MT, NWR, KS, TV, false, false>(a, s);
 }
 
 template <typename TV>

@@ -20,7 +20,7 @@ constexpr int kDensifyThreads = 256;
 template <bool IN_LDS>
 __global__ __launch_bounds__(kDensifyThreads) void csr_densify_kernel(
     const int32_t* __restrict__ rowptr, const int32_t* __restrict__ col, const float* __restrict__ val,
-    float* __restrict__ V, int64_t ldv, int D, int64_t nnz, bool vec_v, uint32_t* __restrict__ clear) {
+    float* __restrict__ V, int64_t ldv, int D, int64_t nnz, uint32_t* __restrict__ clear) {
     if (clear != nullptr && blockIdx.x == 0 && threadIdx.x == 0) *clear = 0;
     extern __shared__ __attribute__((aligned(16))) float dense_row[];   // [round_up4(D)] when IN_LDS
     const int row = blockIdx.x;
@@ -28,7 +28,7 @@ __global__ __launch_bounds__(kDensifyThreads) void csr_densify_kernel(
     const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
     for (int c = 4 * threadIdx.x; c < D; c += 4 * kDensifyThreads) {
         if (IN_LDS) *reinterpret_cast<f32x4*>(&dense_row[c]) = zero;
-        else store4(out, c, D, vec_v, zero);
+        else store4(out, c, D, zero);
     }
     __syncthreads();
     // a row pointer outside [0, nnz] is a caller error; clamp so that no access leaves the arrays
@@ -44,19 +44,18 @@ __global__ __launch_bounds__(kDensifyThreads) void csr_densify_kernel(
     if (IN_LDS) {
         __syncthreads();
         for (int c = 4 * threadIdx.x; c < D; c += 4 * kDensifyThreads)
-            store4(out, c, D, vec_v, *reinterpret_cast<const f32x4*>(&dense_row[c]));
+            store4(out, c, D, *reinterpret_cast<const f32x4*>(&dense_row[c]));
     }
 }
 
 hipError_t launch_csr_densify(const DensifyArgs& a, hipStream_t s) {
-    const bool vec_v = ((uintptr_t)a.v % 16) == 0 && (a.ldv % 4) == 0;
     const size_t lds_bytes = ((size_t)a.D + 3) / 4 * 16;
     if (lds_bytes <= 64 * 1024) {
         SFB_LAUNCH(csr_densify_kernel<true>, dim3(a.n_rows), dim3(kDensifyThreads), lds_bytes, s, a.rowptr, a.col,
-                   a.val, a.v, a.ldv, a.D, a.nnz, vec_v, a.clear);
+                   a.val, a.v, a.ldv, a.D, a.nnz, a.clear);
     } else {
         SFB_LAUNCH(csr_densify_kernel<false>, dim3(a.n_rows), dim3(kDensifyThreads), 0, s, a.rowptr, a.col,
-                   a.val, a.v, a.ldv, a.D, a.nnz, vec_v, a.clear);
+                   a.val, a.v, a.ldv, a.D, a.nnz, a.clear);
     }
     return hipGetLastError();
 }
@@ -105,8 +104,7 @@ constexpr int kSpPre = 3;          // 64-entry slabs per sample whose loads are 
 
 __global__ __launch_bounds__(kSpThreads) void csr_scores_kernel(
     const int32_t* __restrict__ rowptr, const int32_t* __restrict__ col, const float* __restrict__ val, int64_t nnz,
-    const float* __restrict__ W, int64_t ldw, float* __restrict__ Z, int64_t ldz, int n_rows, int J, int D,
-    bool vec_w) {
+    const float* __restrict__ W, int64_t ldw, float* __restrict__ Z, int64_t ldz, int n_rows, int J, int D) {
     extern __shared__ __attribute__((aligned(16))) float wcols[];   // [D][4]
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     constexpr int NW = kSpThreads / 64;
@@ -124,9 +122,8 @@ __global__ __launch_bounds__(kSpThreads) void csr_scores_kernel(
 #pragma unroll
         for (int r = 0; r < kSpRows; ++r) {
             const float* row = W + (int64_t)min(j0 + r, J - 1) * ldw;
-            // aligned rows and a whole quad inside the row: one unguarded 128-bit load
             // (uniform per quad except at the ragged end, so the loads stay back to back)
-            w[r] = (vec_w && 4 * c4 + 3 < D) ? ldg4(row + 4 * c4) : load4(row, 4 * c4, D, false);
+            w[r] = load4(row, 4 * c4, D);
         }
 #pragma unroll
         for (int q = 0; q < 4; ++q)
@@ -143,11 +140,10 @@ __global__ __launch_bounds__(kSpThreads) void csr_scores_kernel(
     //    a descriptor and the offsets are 32-bit);
     //  * the wavefront number is made scalar, so row pointers are scalar loads and their clamps scalar
     //    arithmetic;
-    //  * a lane past the end of its row gets value 0 (one compare + one select per slab); its column is
-    //    whatever the array holds there (an entry of a later row, or 0 past the end): a valid place in the
-    //    parked rows, multiplied by zero.
-    const __amdgpu_buffer_rsrc_t col_rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)col, (short)0, (int)((uint32_t)nnz * 4u), 0x00020000);
-    const __amdgpu_buffer_rsrc_t val_rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)val, (short)0, (int)((uint32_t)nnz * 4u), 0x00020000);
+    //  * the descriptors of a sample's slabs end where its row does: a lane past the end reads value 0 and column 0 by
+    //    hardware, with no compare and no select (the descriptor's length is a scalar).
+    // (arrays of the first `end` entries; every row pointer is clamped to nnz)
+    auto upto = [](const void* p, int end) { return __builtin_amdgcn_make_buffer_rsrc((void*)p, (short)0, (int)((uint32_t)end * 4u), 0x00020000); };
     const int wave_s = __builtin_amdgcn_readfirstlane(wave);
     const uint32_t dmax = (uint32_t)(D - 1);
     // row pointers of a batch of consecutive samples (clamped into [0, nnz]: a row pointer
@@ -161,12 +157,11 @@ __global__ __launch_bounds__(kSpThreads) void csr_scores_kernel(
 #pragma unroll
         for (int s = 0; s < kSpBatch; ++s) {
             const int off = (int)((uint32_t)(p[s] + lane) * 4u);   // byte offset of this lane's entry of slab 0
-            const int left = p[s + 1] - p[s] - lane;         // > 64 * it: the lane's entry of slab it belongs to the row
+            const __amdgpu_buffer_rsrc_t cols = upto(col, p[s + 1]), vals = upto(val, p[s + 1]);
 #pragma unroll
             for (int it = 0; it < kSpPre; ++it) {
-                const uint32_t cl = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(col_rsrc, off + it * 256, 0, 0);
-                const float vl = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(val_rsrc, off + it * 256, 0, 0));
-                v[s][it] = left > it * 64 ? vl : 0.f;
+                const uint32_t cl = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(cols, off + it * 256, 0, 0);
+                v[s][it] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(vals, off + it * 256, 0, 0));
                 c[s][it] = min(cl, dmax);                    // a column outside [0, D) is a caller error: stay inside the LDS tile
             }
         }
@@ -199,9 +194,9 @@ __global__ __launch_bounds__(kSpThreads) void csr_scores_kernel(
             // rows longer than the prefetched slabs (uniform trip count per wavefront)
             for (int e0 = ptr[s] + kSpPre * 64; e0 < ptr[s + 1]; e0 += 64) {
                 const int off = (int)((uint32_t)(e0 + lane) * 4u);
-                const uint32_t cl = min((uint32_t)__builtin_amdgcn_raw_buffer_load_b32(col_rsrc, off, 0, 0), dmax);
-                const float vl = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(val_rsrc, off, 0, 0));
-                a += (e0 + lane < ptr[s + 1] ? vl : 0.f) * *reinterpret_cast<const f32x4*>(&wcols[cl * 4]);
+                const uint32_t cl = min((uint32_t)__builtin_amdgcn_raw_buffer_load_b32(upto(col, ptr[s + 1]), off, 0, 0), dmax);
+                const float vl = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(upto(val, ptr[s + 1]), off, 0, 0));
+                a += vl * *reinterpret_cast<const f32x4*>(&wcols[cl * 4]);
             }
 #pragma unroll
             for (int r = 0; r < kSpRows; ++r) acc[s * kSpRows + r] = a[r];
@@ -298,9 +293,8 @@ hipError_t launch_csr_scores(const DensifyArgs& a, const float* W, int64_t ldw, 
         if (e != hipSuccess) return e;
         raised = lds_bytes;
     }
-    const bool vec_w = ((uintptr_t)W % 16) == 0 && (ldw % 4) == 0;
     SFB_LAUNCH(csr_scores_kernel, dim3((J + kSpRows - 1) / kSpRows), dim3(kSpThreads), lds_bytes, s,
-                       a.rowptr, a.col, a.val, a.nnz, W, ldw, Z, ldz, a.n_rows, J, a.D, vec_w);
+                       a.rowptr, a.col, a.val, a.nnz, W, ldw, Z, ldz, a.n_rows, J, a.D);
     return hipGetLastError();
 }
 

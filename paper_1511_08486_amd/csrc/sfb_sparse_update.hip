@@ -123,7 +123,7 @@ __device__ __forceinline__ void lane_loop(F f) {
 __global__ __launch_bounds__(kSuThreads) void sparse_update_kernel(
     float* __restrict__ W, int64_t ldw, const float* __restrict__ U, int64_t ldu, const uint32_t* __restrict__ starts,
     const uint2* __restrict__ entries, int N, int J, int D, int B, float alpha, uint64_t live_mask, int use_mask, int n_jb,
-    int n_blocks, int splits, int prox_kind, float prox_a, bool vec_u, const float* __restrict__ V, int64_t ldv) {
+    int n_blocks, int splits, int prox_kind, float prox_a, const float* __restrict__ V, int64_t ldv) {
     extern __shared__ __attribute__((aligned(16))) float su_lds[];          // U [N][32], then a 32 x 32 tile per wavefront
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int id = xcd_contiguous_id(blockIdx.x, n_jb * splits);
@@ -140,7 +140,7 @@ __global__ __launch_bounds__(kSuThreads) void sparse_update_kernel(
         bool live = true;
         if (use_mask) live = (live_mask >> (r / B)) & 1ull;
         f32x4 u = {0.f, 0.f, 0.f, 0.f};
-        if (live && j < J) u = load4(U + (int64_t)r * ldu, j, J, vec_u);
+        if (live && j < J) u = load4(U + (int64_t)r * ldu, j, J);
         *reinterpret_cast<f32x4*>(&su_lds[r * kSuClasses + 4 * (tid & 7)]) = u;
 #pragma unroll
         for (int k = 0; k < 4; ++k)
@@ -159,7 +159,6 @@ __global__ __launch_bounds__(kSuThreads) void sparse_update_kernel(
     const int per = (n_blocks + splits - 1) / splits;
     const int b_end = min(n_blocks, (sp + 1) * per);
     const int wr = lane >> 2, wc = 4 * (lane & 3);                         // W rows wr, wr + 16, columns wc .. wc + 3 of the half
-    const bool vec_w = ((uintptr_t)W % 16) == 0 && (ldw % 4) == 0;
 
     // half blocks of 16 columns, a wavefront each
     for (int h = 2 * sp * per + wave; h < 2 * b_end; h += kSuWaves) {
@@ -168,7 +167,7 @@ __global__ __launch_bounds__(kSuThreads) void sparse_update_kernel(
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
             const int row = j0 + wr + 16 * t;
-            w[t] = row < J ? load4(W + (int64_t)row * ldw, d0 + wc, D, vec_w) : f32x4{0.f, 0.f, 0.f, 0.f};
+            w[t] = row < J ? load4(W + (int64_t)row * ldw, d0 + wc, D) : f32x4{0.f, 0.f, 0.f, 0.f};
         }
         const uint32_t* st = starts + (int64_t)(h >> 1) * 33 + 16 * (h & 1);
         // columns 4 q + g: four at a time, all four rounds' bounds first
@@ -237,7 +236,7 @@ __global__ __launch_bounds__(kSuThreads) void sparse_update_kernel(
                     for (int k = 0; k < 4; ++k) s[k] += u * V[(int64_t)r * ldv + min(d0 + wc + k, D - 1)];
                 }
             }
-            if (row < J) store4(W + (int64_t)row * ldw, d0 + wc, D, vec_w, prox_entry4(w[t] + alpha * s, prox_kind, prox_a));
+            if (row < J) store4(W + (int64_t)row * ldw, d0 + wc, D, prox_entry4(w[t] + alpha * s, prox_kind, prox_a));
         }
     }
 }
@@ -289,7 +288,7 @@ hipError_t launch_sparse_update(const ReconArgs& a, int64_t stored, void* worksp
     const int splits = sparse_update_splits(a.J, a.D);
     SFB_LAUNCH(sparse_update_kernel, dim3(n_jb * splits), dim3(kSuThreads), lds_bytes, s, a.w, a.ldw, a.u, a.ldu, starts, entries,
                a.N, a.J, a.D, a.B, a.alpha, a.live_mask, a.use_mask ? 1 : 0, n_jb, n_blocks, splits, a.prox_kind, a.prox_a,
-               ((uintptr_t)a.u % 16) == 0 && (a.ldu % 4) == 0, (const float*)a.v, a.ldv);
+               (const float*)a.v, a.ldv);
     return hipGetLastError();
 }
 
