@@ -358,7 +358,7 @@ SFB_API sfb_status sfb_last_kernel(const sfb_ctx *ctx, int32_t which, char *name
  * one-pass step of few classes (any argument), the choice between split products and the fp32 instruction (fwd_bm, fwd_bn,
  * fwd_split_k or fwd_dma: the scores; recon_variant or fwd_dma: the update, few pairs and stored entries included), the exact
  * split of W in bf16 contexts (fwd_bm, fwd_bn, fwd_split_k).
- * The workspace requirement may grow: query sfb_workspace_bytes again.  SFB_EINVAL for a value outside the table. */
+ * The workspace requirement may grow or shrink: query sfb_workspace_bytes again (a registered workspace that is still large enough stays good).  SFB_EINVAL for a value outside the table. */
 SFB_API sfb_status sfb_set_plan(sfb_ctx *ctx, int32_t fwd_bm, int32_t fwd_bn, int32_t fwd_split_k,
                                 int32_t recon_variant, int32_t fwd_dma);
 /* Measurement aid, not part of the method: dst[0..bytes) = src[0..bytes) with a plain streaming

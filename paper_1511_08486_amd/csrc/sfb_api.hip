@@ -168,6 +168,7 @@ void plan_split_recon(sfb_ctx* c, bool apart) {
             c->split_plans[one][with_ws] = reconstruct_split_plan(c->J, c->D, one ? c->B : (int64_t)c->P * c->B, with_ws ? workspace_need(c) : 0, apart);
 }
 
+// The tiles' slices are cut to the bytes the context asks for: to be planned again whenever those change (sfb_set_plan).
 void plan_bf16_tiles(sfb_ctx* c) {
     if (c->dtype != SFB_BF16) return;
     for (int one = 0; one < 2; ++one) {
@@ -357,7 +358,8 @@ sfb_status factors_rows(sfb_ctx* c, const FwdPlan& plan, const float* W, int64_t
     const bool on_bf16_cores = bf16 && n_rows == c->P * c->B && n_rows >= 128 && forward_bf16_ok(f);
     // W is rounded to bf16 where that kernel would, and taken exactly in all other bf16 calls
     const Bf16TilePlan& tiles = c->tile_scores[n_rows != c->P * c->B][!on_bf16_cores];
-    if (bf16 && c->tile_bf16 && scores_bf16_ok(f) && tiles.bm > 0 &&
+    const size_t tile_planes = (size_t)tiles.slices * (size_t)n_rows * (size_t)ldz * sizeof(float);
+    if (bf16 && c->tile_bf16 && scores_bf16_ok(f) && tiles.bm > 0 && tile_planes <= scores_need(c) &&
         !(on_bf16_cores && forward_bf16_wins(c->fwd_bf16, n_rows, c->J, c->D, tiles.us))) {
         {
             Timed t(c, 0);
@@ -420,7 +422,8 @@ sfb_status recon_launch(sfb_ctx* c, float* W, int64_t ldw, const float* U, int64
     if (r.bf16) {
         if (c->ws == nullptr || c->ws_bytes < workspace_need(c)) return SFB_EWORKSPACE;
         const Bf16TilePlan& tiles = c->tile_update[n_rows > 0];
-        if (update_bf16_ok(r) && tiles.bm > 0 && tiles.us < reconstruct_bf16_us(c->J, c->D, r.N)) {
+        const size_t planes = tiles.slices > 1 ? (size_t)tiles.slices * (size_t)c->J * (size_t)c->D * sizeof(float) : 0;
+        if (update_bf16_ok(r) && tiles.bm > 0 && planes <= workspace_need(c) && tiles.us < reconstruct_bf16_us(c->J, c->D, r.N)) {
             r.partial = tiles.slices > 1 ? (float*)c->ws : nullptr;      // (the partial scores are dead)
             e = launch_update_bf16(r, tiles, c->stream);
         } else {
@@ -922,6 +925,7 @@ sfb_status sfb_set_plan(sfb_ctx* c, int32_t fwd_bm, int32_t fwd_bn, int32_t fwd_
         c->recon_padded = plan_reconstruct_padded(c->J, c->D, (int64_t)c->P * c->B, recon_variant);
     }
     if (fwd_dma >= 0 && c->split_recon == 1) plan_split_recon(c, true);
+    plan_bf16_tiles(c);                                          // (the choice may have changed the workspace, either way)
     return SFB_OK;
 }
 

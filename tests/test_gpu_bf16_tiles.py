@@ -118,6 +118,28 @@ def test_slices_of_the_pairs_add_up_and_one_worker_takes_its_own():
     ctx.close()
 
 
+@pytest.mark.parametrize("J,D,P,B", [(256, 435, 8, 128), (86, 239, 16, 71), (265, 373, 4, 193)])
+def test_sliced_update_stays_inside_a_workspace_that_a_plan_has_made_smaller(J, D, P, B):
+    """The bytes that the context asks for after a plan of one slice are all that the update writes: what lies behind them in
+    the same allocation stays as it was."""
+    import ctypes as C
+    lib, N, guard = sfb.lib, P * B, 4 << 20
+    V, W, _, g = batch(J, D, N, J + D)
+    U = torch.randn((N, J), generator=g, device=DEV)
+    ctx = sfb.Sfb("mlr", J, D, P, B, dtype="bf16", device=DEV)
+    ctx.set_plan(fwd_split_k=1)
+    need = ctx.workspace_bytes()
+    held = torch.full((need + guard,), 0xA5, dtype=torch.uint8, device=DEV)
+    assert held.data_ptr() % 256 == 0 and lib.sfb_set_workspace(ctx._ctx, C.c_void_p(held.data_ptr()), need) == 0
+    got = W.clone()
+    ctx.reconstruct_apply(got, U, V, eta=0.25, scale=0.5)
+    ctx.sync()
+    assert (held[need:] == 0xA5).all()
+    room = 0.125 * 2.0 ** -8 * (U.double().abs().T @ V.double().abs()) + 2.0 ** -22 * (W.double().abs() + 1.0)
+    assert ((got.double() - (W.double() - 0.125 * (U.double().T @ V.double()))).abs() <= room).all()
+    ctx.close()
+
+
 def test_values_without_a_three_term_split():
     """A class switched off by minus infinity scores minus infinity against positive features (the split's second term would
     be NaN), and a finite weight that rounds to an infinity in bf16 stays finite."""

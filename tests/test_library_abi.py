@@ -297,6 +297,36 @@ def test_a_plan_that_keeps_everything_changes_nothing(lib):
     lib.sfb_destroy(ctx)
 
 
+def test_slices_of_bf16_updates_and_scores_fit_the_workspace_after_any_plan(lib):
+    """Updates of few tiles keep one plane of J x D sums per slice in the workspace, scores one of N x J.  A plan of the caller's can
+    lower what the context asks for (256 x 435, 8 x 128 samples: 4.6 to 2.5 MB with one slice of D), and the slices follow.  The
+    update's count is at least its workgroups over the tiles of the smallest of its tilings that divides them."""
+    import random
+    import paper_1511_08486_amd as sfb
+    rng = random.Random(5)
+    shapes = [(256, 435, 8, 128), (86, 239, 16, 71), (42, 483, 12, 89), (265, 373, 4, 193), (32, 2048, 5, 16), (64, 64, 16, 500)]
+    shapes += [(rng.randint(2, 600), rng.randint(8, 900), rng.choice([2, 4, 8, 16]), rng.randint(8, 256)) for _ in range(300)]
+    need, k, g, r = C.c_size_t(), C.c_int32(), C.c_int32(), C.c_int32()
+    cut = 0
+    for J, D, P, B in shapes:
+        ctx = C.c_void_p()
+        assert lib.sfb_create(C.byref(ctx), sfb.SFB_MLR, J, D, P, B, sfb.SFB_BF16, None) == 0
+        # one slice, more of them (the workspace grows), few again, a plan about something else
+        for args in (None, (0, 0, 1, -1, -1), (64, 64, 16, -1, -1), (128, 64, 2, -1, -1), (0, 0, 0, -1, 1), (0, 0, 1, -1, -1)):
+            if args:
+                assert lib.sfb_set_plan(ctx, *args) == 0
+            assert lib.sfb_workspace_bytes(ctx, C.byref(need)) == 0
+            assert lib.sfb_plan_info(ctx, C.byref(k), C.byref(g), C.byref(r)) == 0
+            tiles = [-(-J // bm) * -(-D // bn) for bm, bn in ((64, 64), (64, 128), (128, 128))]
+            slices = min([r.value // t for t in tiles if r.value % t == 0], default=1)
+            cut += slices > 1
+            if slices > 1:
+                assert slices * J * D * 4 <= need.value, (J, D, P, B, args, slices)
+            assert k.value * P * B * -(-J // 4) * 16 <= need.value, (J, D, P, B, args)
+        lib.sfb_destroy(ctx)
+    assert cut > 200                                          # (most of these updates are cut)
+
+
 def test_measurement_aids_validate_their_arguments(lib):
     import paper_1511_08486_amd as sfb
     ctx = C.c_void_p()
