@@ -356,8 +356,9 @@ SFB_API sfb_status sfb_last_kernel(const sfb_ctx *ctx, int32_t which, char *name
  * bit 6 = L2SVM steps update W from lists of the stored entries wherever those fit (neither 3 nor 6: never); < 0 = keep.  A value <= 0 (variant < 0) keeps the current choice.
  * Any choice ends what a context does by itself with the kernels it is about, for good (a new context has it again): the
  * one-pass step of few classes (any argument), the choice between split products and the fp32 instruction (fwd_bm, fwd_bn,
- * fwd_split_k or fwd_dma: the scores; recon_variant or fwd_dma: the update, few pairs and stored entries included), the exact
- * split of W in bf16 contexts (fwd_bm, fwd_bn, fwd_split_k).
+ * fwd_split_k or fwd_dma: the scores; recon_variant or fwd_dma: the update, few pairs and stored entries included), the
+ * tiles for smaller W in bf16 contexts and the exact split of W with them (fwd_bm, fwd_bn, fwd_split_k: the scores; recon_variant: the
+ * update, which then is that of large W for any size and any variant).
  * The workspace requirement may grow or shrink: query sfb_workspace_bytes again (a registered workspace that is still large enough stays good).  SFB_EINVAL for a value outside the table. */
 SFB_API sfb_status sfb_set_plan(sfb_ctx *ctx, int32_t fwd_bm, int32_t fwd_bn, int32_t fwd_split_k,
                                 int32_t recon_variant, int32_t fwd_dma);

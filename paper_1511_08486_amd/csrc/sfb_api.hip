@@ -65,7 +65,7 @@ struct sfb_ctx {
     FwdPlan fwd_bf16;              // all N rows on the bf16 matrix cores (bf16 contexts)
     Bf16TilePlan tile_scores[2][2];   // bf16 contexts: scores in tiles, all rows or one worker's, W rounded or exact
     Bf16TilePlan tile_update[2];   // bf16 contexts: update in tiles, all pairs or one worker's
-    bool tile_bf16;                // take them (a score tile of the caller's choice is about the kernels that were there before)
+    bool tile_bf16_scores, tile_bf16_update;   // take them (a score tile or an update of the caller's choice is about the 256-row kernels)
     FwdPlan fwd_split, fwd_split_worker;   // the same on the bf16 matrix cores, fp32 operands split exactly into bf16 terms
     bool split_scores;             // use them where the shape allows
     int split_recon;               // reconstruction with split-bf16 products: 1 where the shape allows, 0 never, -1 where it is the cheaper one
@@ -359,7 +359,7 @@ sfb_status factors_rows(sfb_ctx* c, const FwdPlan& plan, const float* W, int64_t
     // W is rounded to bf16 where that kernel would, and taken exactly in all other bf16 calls
     const Bf16TilePlan& tiles = c->tile_scores[n_rows != c->P * c->B][!on_bf16_cores];
     const size_t tile_planes = (size_t)tiles.slices * (size_t)n_rows * (size_t)ldz * sizeof(float);
-    if (bf16 && c->tile_bf16 && scores_bf16_ok(f) && tiles.bm > 0 && tile_planes <= scores_need(c) &&
+    if (bf16 && c->tile_bf16_scores && scores_bf16_ok(f) && tiles.bm > 0 && tile_planes <= scores_need(c) &&
         !(on_bf16_cores && forward_bf16_wins(c->fwd_bf16, n_rows, c->J, c->D, tiles.us))) {
         {
             Timed t(c, 0);
@@ -423,7 +423,7 @@ sfb_status recon_launch(sfb_ctx* c, float* W, int64_t ldw, const float* U, int64
         if (c->ws == nullptr || c->ws_bytes < workspace_need(c)) return SFB_EWORKSPACE;
         const Bf16TilePlan& tiles = c->tile_update[n_rows > 0];
         const size_t planes = tiles.slices > 1 ? (size_t)tiles.slices * (size_t)c->J * (size_t)c->D * sizeof(float) : 0;
-        if (update_bf16_ok(r) && tiles.bm > 0 && planes <= workspace_need(c) && tiles.us < reconstruct_bf16_us(c->J, c->D, r.N)) {
+        if (c->tile_bf16_update && update_bf16_ok(r) && tiles.bm > 0 && planes <= workspace_need(c) && tiles.us < reconstruct_bf16_us(c->J, c->D, r.N)) {
             r.partial = tiles.slices > 1 ? (float*)c->ws : nullptr;      // (the partial scores are dead)
             e = launch_update_bf16(r, tiles, c->stream);
         } else {
@@ -547,7 +547,7 @@ sfb_status sfb_create(sfb_ctx** out, sfb_model m, int64_t J, int64_t D, int32_t 
         c->few = planes <= SFB_NOALLOC_SCRATCH_BYTES || planes <= workspace_need(c);
     }
     plan_split_recon(c, false);
-    c->tile_bf16 = true;
+    c->tile_bf16_scores = c->tile_bf16_update = true;
     plan_bf16_tiles(c);
     c->ws = nullptr; c->ws_bytes = 0; c->lists = nullptr; c->lists_stored = 0; c->last_hip = 0; c->timing = false; c->sparse_forward = true; c->sparse_always = false;
     c->lists_always = false;
@@ -862,12 +862,12 @@ sfb_status sfb_plan_info(const sfb_ctx* c, int32_t* fwd_split_k, int32_t* fwd_gr
         const int64_t N = (int64_t)c->P * c->B;
         const bool rounded = N >= 128 && c->D % 32 == 0;
         const Bf16TilePlan& t = c->tile_scores[0][!rounded];
-        if (c->tile_bf16 && t.bm > 0 && !(rounded && forward_bf16_wins(c->fwd_bf16, N, c->J, c->D, t.us))) {
+        if (c->tile_bf16_scores && t.bm > 0 && !(rounded && forward_bf16_wins(c->fwd_bf16, N, c->J, c->D, t.us))) {
             if (fwd_split_k) *fwd_split_k = t.slices;
             if (fwd_grid) *fwd_grid = (int32_t)(((N + t.bm - 1) / t.bm) * ((c->J + t.bn - 1) / t.bn) * t.slices);
         }
         const Bf16TilePlan& u = c->tile_update[0];
-        tile_update = u.bm > 0 && u.us < reconstruct_bf16_us(c->J, c->D, N);
+        tile_update = c->tile_bf16_update && u.bm > 0 && u.us < reconstruct_bf16_us(c->J, c->D, N);
         if (recon_grid && tile_update)
             *recon_grid = (int32_t)(((c->J + u.bm - 1) / u.bm) * ((c->D + u.bn - 1) / u.bn) * u.slices);
     }
@@ -919,8 +919,9 @@ sfb_status sfb_set_plan(sfb_ctx* c, int32_t fwd_bm, int32_t fwd_bn, int32_t fwd_
     finish_forward_plan(&p, (int64_t)c->P * c->B, c->J, c->D);
     if (fwd_dma >= 0 && c->split_scores) plan_split_scores(c, true);
     c->fwd_all = p;
-    if (fwd_bm > 0 || fwd_bn > 0 || fwd_split_k > 0) c->tile_bf16 = false;
+    if (fwd_bm > 0 || fwd_bn > 0 || fwd_split_k > 0) c->tile_bf16_scores = false;
     if (recon_variant >= 0) {
+        c->tile_bf16_update = false;
         c->recon = plan_reconstruct_variant(c->J, c->D, recon_variant);
         c->recon_padded = plan_reconstruct_padded(c->J, c->D, (int64_t)c->P * c->B, recon_variant);
     }

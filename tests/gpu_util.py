@@ -94,13 +94,14 @@ def make_clear_of_kink(name, seed, chain_steps, guard=1e-4, **over):
     raise AssertionError("no seed keeps the chain clear of the hinge kink")
 
 
-def run_chain(wl, steps, tol, check_every=1, dml_guard=1e-4, pad=0, plan=None, progress=None):
+def run_chain(wl, steps, tol, check_every=1, dml_guard=1e-4, pad=0, plan=None, progress=None, kernels=None):
     """Runs `steps` SFB steps on the GPU and in the oracle from the same W0 and batches and
     compares U, V, W, the per-sample loss and the update -eta*dW itself after every checked step.
     (W alone would not pin the reconstruction: one step's update is far below tol * |W| for most
     entries, so the same factors are also applied to a zero matrix and compared with the oracle's
     W_new - W.)  `progress` (optional) is called with a line of text after every step: long chains
-    report through it so that a watcher of the run's output sees them advance."""
+    report through it so that a watcher of the run's output sees them advance.  `kernels` (optional): the
+    names of the score and update kernels that every step has to run."""
     import paper_1511_08486_amd as sfb
     dev = "cuda:0"
     ctx = sfb.Sfb(wl.model, wl.J, wl.D, wl.P, wl.B, dtype=wl.dtype, device=dev)
@@ -117,6 +118,8 @@ def run_chain(wl, steps, tol, check_every=1, dml_guard=1e-4, pad=0, plan=None, p
         db, dy = dev_batches[t % len(dev_batches)]
         ctx.step(Wg, db, dy, U, V, wl.eta, loss=loss)
         ctx.sync()
+        if kernels:
+            assert (ctx.last_kernel(0)[0], ctx.last_kernel(2)[0]) == kernels
         Uo, Vo, Wo_new, fo = oracle.step(wl.model, Wo, b, wl.P, wl.B, wl.eta)
         if wl.model == "dml":
             margin = oracle.dml_margin_distance(oracle.scores(Wo, Vo), b["y"])

@@ -97,6 +97,44 @@ def test_update(J, D, P, B, pad, shift, dead):
     ctx.close()
 
 
+def prox(kind, w, a):
+    """The entrywise operators, no larger than the identity in the differences that they leave."""
+    return {"none": w, "l2sq": w / (1.0 + a), "l1": torch.sign(w) * (w.abs() - a).clamp(min=0.0)}[kind]
+
+
+@pytest.mark.parametrize("J,D,P,B,plan", [(J, D, P, B, dict(recon_variant=0)) for J, D, P, B in SHAPES if J > 32 or D > 2048] + [
+    (8065, 3715, 4, 60, None), (8064, 3712, 2, 64, None), (4099, 8191, 3, 41, None),          # a W that takes it by itself
+])
+@pytest.mark.parametrize("pad,shift,dead,kind", [(0, 0, False, "l1"), (3, 1, True, "none"), (0, 0, True, "l2sq")])
+def test_update_of_large_w(J, D, P, B, plan, pad, shift, dead, kind):
+    """The kernel with tiles of 256 rows and its packed factors: edges, dead workers and the entrywise operators, by the bound of test_update."""
+    N = P * B
+    V, W, _, g = batch(J, D, N, J + 3 * D)
+    U = torch.randn((N, J), generator=g, device=DEV)
+    active = [p != 1 for p in range(P)] if dead else None
+    Ul, Vl = U.double(), V.double()
+    if dead:
+        U[B:2 * B] = float("inf")
+        V[B:2 * B] = float("nan")
+        Ul[B:2 * B] = 0.0
+        Vl[B:2 * B] = 0.0
+    ctx = sfb.Sfb("mlr", J, D, P, B, dtype="bf16", device=DEV)
+    if plan:
+        ctx.set_plan(**plan)
+    W2 = strided(W, pad, shift)
+    around = W2.untyped_storage()
+    ctx.reconstruct_apply_prox(W2, strided(U, pad, shift), strided(V, pad, shift), 0.25, kind, 0.04, scale=0.5, active=active)
+    ctx.sync()
+    assert ctx.last_kernel(2) == ("nt_bf16_kernel", -(-J // 256) * -(-D // 128)) and ctx.plan_info()["recon_grid"] == ctx.last_kernel(2)[1]
+    want = W.double() - 0.125 * (Ul.T @ Vl)
+    room = 0.125 * 2.0 ** -8 * (Ul.abs().T @ Vl.abs()) + 2.0 ** -22 * (want.abs() + 1.0)
+    assert ((W2.double() - prox(kind, want, 0.25 * 0.04)).abs() <= room).all()
+    if pad:                                              # nothing but W's own entries was written
+        flat = torch.empty(0, device=DEV).set_(around)
+        assert int(torch.isnan(flat).sum()) == flat.numel() - J * D
+    ctx.close()
+
+
 def test_slices_of_the_pairs_add_up_and_one_worker_takes_its_own():
     J, D, P, B = 192, 200, 16, 80                        # few tiles, 20 chunks of pairs: planes of sums
     V, W, _, g = batch(J, D, P * B, 3)

@@ -424,22 +424,33 @@ def test_mlr_large_bf16_twenty_steps(sfb, capsys):
     print("mlr_large worst error/allowance", worst)
 
 
-def test_bf16_ragged(sfb):
+# bf16 contexts: the tiles that small W take by themselves, and the kernels of 256 rows that serve large W (sfb_set_plan)
+BF16_TILES = (None, ("scores_bf16_kernel", "update_bf16_kernel"))
+BF16_LARGE = (dict(fwd_split_k=1, recon_variant=0), ("nt_bf16_kernel", "nt_bf16_kernel"))
+
+
+@pytest.mark.parametrize("plan,kernels", [BF16_TILES, (BF16_LARGE[0], ("fwd_scores_kernel", "nt_bf16_kernel"))])
+@pytest.mark.parametrize("pad", [0, 3])
+def test_bf16_ragged(sfb, plan, kernels, pad):
     wl = workloads.make("mlr_large", seed=4, J=300, D=1004, P=3, B=30, steps=2, pool=2)
-    run_chain(wl, 2, TOLBF)
+    run_chain(wl, 2, TOLBF, plan=plan, pad=pad, kernels=kernels)
 
 
+@pytest.mark.parametrize("plan,kernels", [BF16_TILES, BF16_LARGE])
 @pytest.mark.parametrize("J,D,P,B", [(300, 1024, 4, 40), (130, 96, 2, 64), (1000, 2048, 8, 64)])
-def test_bf16_matrix_core_path(sfb, J, D, P, B):
+def test_bf16_matrix_core_path(sfb, J, D, P, B, plan, kernels):
     """Shapes that take the bf16 MFMA kernels (D % 32 == 0, N >= 128, aligned rows)."""
     wl = workloads.make("mlr_large", seed=J, J=J, D=D, P=P, B=B, steps=3, pool=2)
-    run_chain(wl, 3, TOLBF)
+    run_chain(wl, 3, TOLBF, plan=plan, kernels=kernels)
 
 
-def test_bf16_dead_worker_and_plain_sum(sfb):
+@pytest.mark.parametrize("plan,kernels", [BF16_TILES, BF16_LARGE])
+def test_bf16_dead_worker_and_plain_sum(sfb, plan, kernels):
     wl = workloads.make("mlr_large", seed=9, J=260, D=512, P=4, B=48, steps=1, pool=1)
     dev = "cuda:0"
     ctx = sfb.Sfb(wl.model, wl.J, wl.D, wl.P, wl.B, dtype="bf16", device=dev)
+    if plan:
+        ctx.set_plan(**plan)
     b = wl.batch(0)
     db, dy = to_device(wl, b, dev)
     W = torch.from_numpy(wl.W0).to(dev)
@@ -449,6 +460,7 @@ def test_bf16_dead_worker_and_plain_sum(sfb):
     U[wl.B:2 * wl.B] = float("nan")                     # a dead worker's slot may hold anything
     ctx.reconstruct_apply(W, U, V, eta=0.2, scale=1.0, active=active)
     ctx.sync()
+    assert (ctx.last_kernel(0)[0], ctx.last_kernel(2)[0]) == kernels
     Uo, Vo, fo = oracle.factors(wl.model, wl.W0, b)
     want = oracle.apply_update(wl.W0, oracle.delta_w(Uo, Vo, wl.P, wl.B, active) * wl.B, 0.2)
     assert_close(W.cpu().numpy(), want, TOLBF, "W, bf16, dead worker")

@@ -121,7 +121,8 @@ FUSED_CASES = [
     ("mlr_medium", {}, None),                                            # LDS-DMA fp32 kernels
     ("mlr_tiny", dict(J=37, D=203, P=3, B=5), None),                     # register-staged fp32 kernel, ragged
     ("mlr_medium", dict(J=520, D=1024, P=4, B=48), dict(fwd_dma=13)),    # split-bf16 contractions
-    ("mlr_large", dict(J=300, D=1024, P=4, B=40), None),                 # bf16 features: bf16 matrix-core kernels
+    ("mlr_large", dict(J=300, D=1024, P=4, B=40), None),                 # bf16 features: bf16 matrix-core kernels, tiles for small W
+    ("mlr_large", dict(J=300, D=1024, P=4, B=40), dict(fwd_split_k=1, recon_variant=0)),     # ... and those of 256 rows for large W
     ("dml", dict(J=72, D=256, P=2, B=32), None),
     ("l2svm", dict(J=64, D=512, P=2, B=16, density=0.05), None),
 ]

@@ -327,6 +327,22 @@ def test_slices_of_bf16_updates_and_scores_fit_the_workspace_after_any_plan(lib)
     assert cut > 200                                          # (most of these updates are cut)
 
 
+def test_an_update_of_the_callers_choice_is_that_of_large_w_in_bf16_contexts(lib):
+    """recon_variant: 256 x 128 tiles whatever the size, with the scores left alone; a plan about the scores leaves the update alone."""
+    import paper_1511_08486_amd as sfb
+    ctx, k, g, r = C.c_void_p(), C.c_int32(), C.c_int32(), C.c_int32()
+    seen = []
+    for args in (None, (0, 0, 0, 0, -1), (64, 64, 2, -1, -1)):
+        assert lib.sfb_create(C.byref(ctx), sfb.SFB_MLR, 1000, 2048, 8, 64, sfb.SFB_BF16, None) == 0
+        assert args is None or lib.sfb_set_plan(ctx, *args) == 0
+        assert lib.sfb_plan_info(ctx, C.byref(k), C.byref(g), C.byref(r)) == 0
+        seen.append((k.value, g.value, r.value))
+        lib.sfb_destroy(ctx)
+    own, update, scores = seen
+    assert own[2] != 64 and update == (own[0], own[1], 64)
+    assert scores[2] == own[2] and scores[:2] != own[:2]
+
+
 def test_measurement_aids_validate_their_arguments(lib):
     import paper_1511_08486_amd as sfb
     ctx = C.c_void_p()
