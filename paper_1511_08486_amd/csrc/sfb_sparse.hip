@@ -1,6 +1,8 @@
 // Sparse-feature helpers for the L2-SVM workload (the paper exploits sparse features to
 // cut computation, Section 6): v_i = a_i is delivered as the dense row of the CSR matrix,
 // because the reconstruction consumes V as a dense [N][D] operand.
+#include <type_traits>
+
 #include "sfb_device.h"
 #include "sfb_kernels.h"
 
@@ -141,7 +143,9 @@ __global__ __launch_bounds__(kSpThreads) void csr_scores_kernel(
     //  * the wavefront number is made scalar, so row pointers are scalar loads and their clamps scalar
     //    arithmetic;
     //  * the descriptors of a sample's slabs end where its row does: a lane past the end reads value 0 and column 0 by
-    //    hardware, with no compare and no select (the descriptor's length is a scalar).
+    //    hardware, with no compare and no select (the descriptor's length is a scalar).  Zero times W's column 0 is nothing
+    //    unless that is not finite in one of the four rows: such a workgroup walks once more, with the compare and the select,
+    //    so that feature 0 counts for the samples that store it and for no others.
     // (arrays of the first `end` entries; every row pointer is clamped to nnz)
     auto upto = [](const void* p, int end) { return __builtin_amdgcn_make_buffer_rsrc((void*)p, (short)0, (int)((uint32_t)end * 4u), 0x00020000); };
     const int wave_s = __builtin_amdgcn_readfirstlane(wave);
@@ -174,14 +178,18 @@ __global__ __launch_bounds__(kSpThreads) void csr_scores_kernel(
     uint32_t cc0[kSpBatch][kSpPre], cc1[kSpBatch][kSpPre];
     float vv0[kSpBatch][kSpPre], vv1[kSpBatch][kSpPre];
     constexpr int STRIDE = NW * kSpBatch;
-    int n = wave_s * kSpBatch;
-    if (n < n_rows) {
-        load_ptrs(n, ptr);
-        load_entries(ptr, cc0, vv0);
-    }
-    if (n + STRIDE < n_rows) load_ptrs(n + STRIDE, next_ptr);
+    int n;
+    auto start = [&]() {
+        n = wave_s * kSpBatch;
+        if (n < n_rows) {
+            load_ptrs(n, ptr);
+            load_entries(ptr, cc0, vv0);
+        }
+        if (n + STRIDE < n_rows) load_ptrs(n + STRIDE, next_ptr);
+    };
+    start();
     // one round: request the next batch's entries into (ncc, nvv), multiply the batch held in (cc, vv)
-    auto round = [&](uint32_t (&cc)[kSpBatch][kSpPre], float (&vv)[kSpBatch][kSpPre], uint32_t (&ncc)[kSpBatch][kSpPre],
+    auto round = [&](auto guarded, uint32_t (&cc)[kSpBatch][kSpPre], float (&vv)[kSpBatch][kSpPre], uint32_t (&ncc)[kSpBatch][kSpPre],
                      float (&nvv)[kSpBatch][kSpPre]) {
         if (n + 2 * STRIDE < n_rows) load_ptrs(n + 2 * STRIDE, after_ptr);
         if (n + STRIDE < n_rows) load_entries(next_ptr, ncc, nvv);
@@ -189,14 +197,19 @@ __global__ __launch_bounds__(kSpThreads) void csr_scores_kernel(
 #pragma unroll
         for (int s = 0; s < kSpBatch; ++s) {
             f32x4 a = {0.f, 0.f, 0.f, 0.f};
+            auto add = [&](int e0, uint32_t c, float v) {                // entry e0 + lane of the arrays
+                f32x4 w = *reinterpret_cast<const f32x4*>(&wcols[c * 4]);
+                if (decltype(guarded)::value && e0 + lane >= ptr[s + 1]) w = f32x4{0.f, 0.f, 0.f, 0.f};
+                a += v * w;
+            };
 #pragma unroll
-            for (int it = 0; it < kSpPre; ++it) a += vv[s][it] * *reinterpret_cast<const f32x4*>(&wcols[cc[s][it] * 4]);
+            for (int it = 0; it < kSpPre; ++it) add(ptr[s] + it * 64, cc[s][it], vv[s][it]);
             // rows longer than the prefetched slabs (uniform trip count per wavefront)
             for (int e0 = ptr[s] + kSpPre * 64; e0 < ptr[s + 1]; e0 += 64) {
                 const int off = (int)((uint32_t)(e0 + lane) * 4u);
                 const uint32_t cl = min((uint32_t)__builtin_amdgcn_raw_buffer_load_b32(upto(col, ptr[s + 1]), off, 0, 0), dmax);
                 const float vl = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(upto(val, ptr[s + 1]), off, 0, 0));
-                a += vl * *reinterpret_cast<const f32x4*>(&wcols[cl * 4]);
+                add(e0, cl, vl);
             }
 #pragma unroll
             for (int r = 0; r < kSpRows; ++r) acc[s * kSpRows + r] = a[r];
@@ -253,9 +266,18 @@ __global__ __launch_bounds__(kSpThreads) void csr_scores_kernel(
         n += STRIDE;
     };
     // the two register sets trade places every round (no copies)
-    while (n < n_rows) {
-        round(cc0, vv0, cc1, vv1);
-        if (n < n_rows) round(cc1, vv1, cc0, vv0);
+    auto walk = [&](auto guarded) {
+        while (n < n_rows) {
+            round(guarded, cc0, vv0, cc1, vv1);
+            if (n < n_rows) round(guarded, cc1, vv1, cc0, vv0);
+        }
+    };
+    walk(std::false_type{});
+    const f32x4 w0 = *reinterpret_cast<const f32x4*>(wcols);
+    const bool plain = __builtin_isfinite(w0.x) && __builtin_isfinite(w0.y) && __builtin_isfinite(w0.z) && __builtin_isfinite(w0.w);
+    if (!__builtin_amdgcn_readfirstlane(plain)) {
+        start();
+        walk(std::true_type{});
     }
 }
 

@@ -776,6 +776,48 @@ def test_csr_columns_in_any_order_within_a_row(sfb, dense_scores):
     run_chain(wl, 2, TOL32, plan=dict(fwd_dma=3) if dense_scores else dict(fwd_dma=33))
 
 
+@pytest.mark.parametrize("bad", [float("inf"), float("nan")])
+def test_scores_from_stored_entries_see_only_the_features_a_sample_stores(sfb, bad):
+    """Classes whose weight of feature 0 is not finite (lanes past a row's end read that feature's): samples that do not store
+    it score bit for bit what they score with a weight of zero there, in rows of no entry, of one, on and beside the slabs of 64 entries, and
+    longer than the kernel prefetches."""
+    J, D, dev = 70, 1200, "cuda:0"
+    lengths = [0, 1, 5, 63, 64, 65, 128, 191, 192, 193, 256, 300, 700] * 9 + [40] * 3
+    N, g = len(lengths), torch.Generator().manual_seed(3)
+    stores0 = torch.rand(N, generator=g) < 0.3
+    stores0 &= torch.tensor(lengths) > 0
+    cols = [(torch.randperm(D - 1, generator=g)[:n] + 1).sort().values for n in lengths]
+    for r in range(N):
+        if stores0[r]:
+            cols[r][0] = 0
+    rowptr = torch.zeros(N + 1, dtype=torch.int32)
+    rowptr[1:] = torch.cumsum(torch.tensor(lengths), 0).to(torch.int32)
+    col = torch.cat(cols).to(torch.int32)
+    val = torch.rand(len(col), generator=g) + 0.1
+    W = torch.randn((J, D), generator=g) * 0.05
+    W[:, 0] = 0.0
+    y = torch.randint(0, J, (N,), generator=g, dtype=torch.int32).to(dev)
+    ctx = sfb.Sfb("l2svm", J, D, 3, N // 3, device=dev)
+    ctx.set_plan(fwd_dma=33)
+    batch = sfb.SfbBatch(rowptr=rowptr.to(dev), col=col.to(dev), val=val.to(dev))
+    odd, out = torch.tensor([0, 7, 41, 69]), []
+    for w0 in (0.0, bad):
+        W[odd, 0] = w0
+        U, V = torch.zeros((N, J), device=dev), torch.zeros((N, D), device=dev)
+        ctx.compute_factors(W.to(dev), batch, y, U, V)
+        ctx.sync()
+        assert ctx.last_kernel(0)[0] == "csr_scores_kernel"
+        out.append(U.cpu())
+    want, got = out
+    assert torch.isfinite(want).all() and torch.equal(got[~stores0], want[~stores0])
+    others = torch.ones(J, dtype=torch.bool)
+    others[odd] = False
+    assert torch.equal(got[:, others], want[:, others])
+    there = got[stores0][:, odd]
+    assert (~torch.isfinite(there) | (there == 0.0)).all()                # no hinge where the margin is not positive, or not a number
+    ctx.close()
+
+
 @pytest.mark.parametrize("dense_scores,D,density", [(False, 320, 0.05), (True, 320, 0.05), (False, 16500, 0.002)])
 def test_csr_column_repeated_inside_a_row_counts_as_the_sum_of_its_values(sfb, dense_scores, D, density):
     """The header defines it: a column that appears twice in a row contributes the sum of its values,
