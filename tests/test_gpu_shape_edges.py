@@ -396,8 +396,8 @@ def test_classes_switched_off_by_infinite_weights_do_not_stall_the_split_product
     (600, 4096, 4, 128, 224),                                   # tiles of 96 rows
     (1152, 2750, 6, 90, 198),
 ])
-@pytest.mark.parametrize("masked", [False, True])
-def test_updates_whose_last_tiles_are_a_launch_of_their_own(J, D, P, B, grid, masked):
+@pytest.mark.parametrize("masked,kind", [(False, "none"), (True, "none"), (False, "l1"), (True, "l2sq")])
+def test_updates_whose_last_tiles_are_a_launch_of_their_own(J, D, P, B, grid, masked, kind):
     """Every entry against fp64, with infinities in the last column and row, in rows of W that have words between them.  Sums of
     N products rounded six times for every sixteen: 2^-24 (6 N / 16 + 2) sum |u v|, and the update's own rounding."""
     import paper_1511_08486_amd as sfb
@@ -413,12 +413,16 @@ def test_updates_whose_last_tiles_are_a_launch_of_their_own(J, D, P, B, grid, ma
     if masked:
         live[B:2 * B] = False
     ctx = sfb.Sfb("l2svm", J, D, P, B, device=dev)
-    ctx.reconstruct_apply(W[:, :D], U, V, 0.5, scale=1.0, active=active)
+    ctx.reconstruct_apply_prox(W[:, :D], U, V, 0.5, kind, 0.04, scale=1.0, active=active)
     ctx.sync()
     name, blocks = ctx.last_kernel(2)
     assert name == "reconstruct_split_kernel" and blocks == grid
     Ul, Vl = U[live].double(), V[live].double()
     want, got = W0[:, :D].double() - 0.5 * (Ul.T @ Vl), W[:, :D].double()
+    if kind == "l2sq":                                          # entry by entry, differences no larger than before
+        want = want / (1.0 + 0.5 * 0.04)
+    if kind == "l1":                                            # (what is neither above nor below the threshold is 0, NaN too)
+        want = torch.where(want > 0.02, want - 0.02, torch.where(want < -0.02, want + 0.02, torch.zeros_like(want)))
     assert torch.equal(torch.isnan(got), torch.isnan(want)) and torch.equal(got[torch.isinf(want)], want[torch.isinf(want)])
     room = 0.5 * 2.0 ** -24 * (6 * N / 16 + 2) * (Ul.abs().T @ Vl.abs()) + 2.0 ** -23 * want.abs()
     ok = torch.isfinite(want)
