@@ -10,8 +10,8 @@
 // runs over the pairs, the slow index of both operands in memory; the rows go to LDS as they come (U rounded to bf16 on
 // the way) and gfx950's transposing LDS read hands every lane four pairs of its column: no transposed copy, no launch for it.
 //
-// Both: four wavefronts as 2 x 2 over the tile, two LDS buffers, one barrier per chunk, chunks requested two ahead in registers.  Rows
-// are taken at any alignment (16-byte accesses at the element's own alignment).
+// Both: four wavefronts as 2 x 2 over the tile (128 x 128: eight as 2 x 4), two LDS buffers, one barrier per chunk, chunks requested two
+// ahead in registers.  Rows are taken at any alignment (16-byte accesses at the element's own alignment).
 #include "sfb_kernels.h"
 #include "sfb_split.h"
 
@@ -29,7 +29,7 @@ __device__ __forceinline__ int bt_swz(int r) { return ITEMS == 8 ? (r & 7) ^ ((r
 template <int COLS>
 __device__ __forceinline__ int bt_turn(int r) { return COLS == 64 ? r & 3 : 2 * (r & 3); }
 
-// eight bf16 moved down by sh places, zeros (or, FILL, the last one) behind them
+// eight bf16 (four floats) moved down by sh places, zeros behind them
 __device__ __forceinline__ sp_u32x4 bt_down8(sp_u32x4 x, int sh) {
     if (sh & 4) x = sp_u32x4{x[2], x[3], 0u, 0u};
     if (sh & 2) x = sp_u32x4{x[1], x[2], x[3], 0u};
@@ -481,13 +481,7 @@ template <int BM, int BN, int WGM, int WGN, int TERMS, bool NARROW>
 static hipError_t launch_scores(const FwdArgs& a, const Bf16TilePlan& p, hipStream_t s) {
     constexpr int BK = kBfTileChunk<TERMS>;
     constexpr size_t lds_bytes = 2 * (size_t)(BM + TERMS * BN) * BK * 2;
-    static std::atomic<bool> raised{false};
-    if (lds_bytes > 64 * 1024 && !raised) {
-        hipError_t e = hipFuncSetAttribute((const void*)scores_bf16_kernel<BM, BN, WGM, WGN, TERMS, NARROW>,
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
-        if (e != hipSuccess) return e;
-        raised = true;
-    }
+    static_assert(lds_bytes <= 64 * 1024, "what a launch may ask for without hipFuncSetAttribute");
     const int n_mb = (a.n_rows + BM - 1) / BM, n_nb = (a.J + BN - 1) / BN, total = n_mb * n_nb * p.slices;
     SFB_LAUNCH((scores_bf16_kernel<BM, BN, WGM, WGN, TERMS, NARROW>), dim3(total), dim3(WGM * WGN * 64), lds_bytes, s, (const bf16_t*)a.a, a.lda,
                a.w, a.ldw, a.zp, a.ldz, a.zstride, (bf16_t*)a.v, a.ldv, a.n_rows, a.J, a.D, p.per_slice, n_mb, n_nb, total);
@@ -511,13 +505,7 @@ hipError_t launch_scores_bf16(const FwdArgs& a, const Bf16TilePlan& p, hipStream
 template <int BM, int BN, int WGM, int WGN, bool PLANES, bool NARROW>
 static hipError_t launch_update(const ReconArgs& a, const Bf16TilePlan& p, hipStream_t s) {
     constexpr size_t lds_bytes = 2 * (size_t)kBfUpdateChunk * 2 * (BM + BN);
-    static std::atomic<bool> raised{false};
-    if (lds_bytes > 64 * 1024 && !raised) {
-        hipError_t e = hipFuncSetAttribute((const void*)update_bf16_kernel<BM, BN, WGM, WGN, PLANES, NARROW>,
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
-        if (e != hipSuccess) return e;
-        raised = true;
-    }
+    static_assert(lds_bytes <= 64 * 1024, "what a launch may ask for without hipFuncSetAttribute");
     const int n_jb = (a.J + BM - 1) / BM, n_db = (a.D + BN - 1) / BN, tiles = n_jb * n_db;
     const uint32_t inv_b = a.use_mask ? (uint32_t)(((1ull << 32) + a.B - 1) / a.B) : 0;
     SFB_LAUNCH((update_bf16_kernel<BM, BN, WGM, WGN, PLANES, NARROW>), dim3(tiles * p.slices), dim3(WGM * WGN * 64), lds_bytes, s,
