@@ -7,7 +7,8 @@
 // loaded and stored as data that is not used again (nontemporal: 10.3 us per call against 11.2 without).
 // W's addresses are a scalar base an entry and one lane offset: formed per lane they were a third of the vector instructions (1000 x
 // 4096, 64 pairs 10.7 -> 10.1 us; 2000 x 8192: 35.9 -> 32.5).
-// 1000 x 4096: 14.9 -> 7.4 us with 8 pairs, 12.0 -> 10.1 with 64; 2000 x 8192: 61 -> 25 and 45 -> 32.5.
+// Against the kernels that stage tiles, 1000 x 4096: 14.9 -> 7.4 us with 8 pairs, 12.0 -> 10.1 with 64; 2000 x 8192: 61 -> 25 and 45 -> 32.5 (one
+// W over and over; in a replayed chain over eight 7.2, 9.2, 25.3 and 31.0).
 // Larger tiles (128 x 64, 128 x 128) halve the copies into LDS and were 3 % slower: fewer workgroups to overlap.
 #include "sfb_kernels.h"
 #include "sfb_split.h"
@@ -341,19 +342,23 @@ static hipError_t launch_thin(const ReconArgs& a, hipStream_t s) {
     return launch_form<ThinFp32<STAGES, false, false>>(a, 64, s);
 }
 
-// Split products: 17 to 64 pairs on a W large enough for its products to show.  Where the fp32 instruction's copies into LDS go word by
-// word (unaligned rows, masks) that is from 256 tiles of 64 x 64 on (601 x 2000, 24 pairs: 5.1 us against 5.5, 64: 5.5 and 6.7; 1001 x 4099, 61:
-// 12.2 and 15.2; 401 x 2000, 40: 5.5 and 5.1); elsewhere from 512 with more than 48 pairs (1000 x 4096, 64: 9.6 us against 9.5 to 10.6, by
-// where W lies; 1000 x 2048: 5.8 and 5.4) and from 1536 with fewer (4000 x 2000, 32: 14.8 and 15.7; 2000 x 8192: 22.6 and 25.9; 1000 x
-// 4096, 48: 9.7 and 8.5).
+// Split products: 17 to 64 pairs on a W large enough for its products to show (instruction -> split below, us; "cold": eight W in turn,
+// "hot": seven updates of each in a row, W mostly in the caches).
+// Where the instruction's copies into LDS go word by word (unaligned rows, masks): from 256 tiles of 64 x 64 on (224, 401 x 2000: 32 pairs 3.9 -> 4.5, 64:
+// 4.6 -> 5.1; 320, 601 x 2001: 6.2 -> 5.2 and 7.2 -> 5.9; 1001 x 4099: 13.3 -> 9.5 and 15.0 -> 11.2; cold and hot alike).
+// Elsewhere with more than 48 pairs: beyond 768 tiles (64 pairs, 640 x 4096: cold 6.7 -> 8.1, hot 6.8 -> 7.3; 768 x 4096: 7.3 -> 8.3 and 7.0 ->
+// 7.6; 832 x 4096: 8.6 -> 8.4 and 8.6 -> 7.7; 1000 x 4096: 9.2 -> 8.8 and 9.3 -> 8.3; 4000 x 8192: 59.5 -> 57.5 and 58.9 -> 48.5): up to there every
+// compute unit has three of the instruction's workgroups at most and one or two of these, whose chain of loads, splits and
+// products is the longer one.  With up to 48, beyond 1536 tiles, for a W that is hot, as it is behind the score pass of a step or under several
+// workers' updates (2000 x 4096: 20 pairs 13.9 -> 12.5, 48: 14.8 -> 14.7; 4000 x 8192: 48.4 -> 41.5 and 51.2 -> 47.9; cold 13.7 -> 14.4, 14.7 -> 16.2, 48.9 -> 48.8,
+// 51.0 -> 54.1; 1200 x 4096, 32 pairs, 9.1 -> 9.3 hot).
 static bool thin_split_wins(const ReconArgs& a) {
     const int64_t tiles = (int64_t)((a.J + 63) / 64) * ((a.D + 63) / 64);
     return a.N > 16 && a.N <= 64 && a.J >= 4 && a.D >= 4 && (!a.use_mask || a.B > 1) && a.ldu < (1 << 23) && a.ldv < (1 << 23) &&
-           tiles > (!thin_wide(a) ? 256 : a.N > 48 ? 512 : 1536);
+           tiles > (!thin_wide(a) ? 256 : a.N > 48 ? 768 : 1536);
 }
 
-// Up to 64 pairs always (1000 x 4096: 7.9 us with 8 pairs, 10.6 with 64, against 14.9 and 12.0 with the kernels that stage
-// tiles; 2000 x 8192: 25 and 36 against 61 and 45; 300 x 1000: one launch, 5.6); up to 128 while W is small enough for
+// Up to 64 pairs always (against the kernels that stage tiles: the figures at the head); up to 128 while W is small enough for
 // the matrix pipe's share not to show (4000 x 700 with 128: 15.0 against 16.8; 1000 x 4096: 17.5 against 16.1).
 // Not with a mask, which looks up the worker of every pair (256 x 1024 with 128: 10.6 against 6.8 by split products; 64 x 64: 10.2, 6.4).
 bool reconstruct_thin_ok(const ReconArgs& a) {

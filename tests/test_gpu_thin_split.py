@@ -44,3 +44,21 @@ def test_update(J, D, P, B, pad, shift, dead, kind):
     flat = torch.empty(0, device=DEV).set_(around)                      # nothing but W's own entries was written
     assert int(torch.isnan(flat).sum()) == flat.numel() - J * D
     ctx.close()
+
+
+@pytest.mark.parametrize("J,D,N,blocks", [
+    (768, 4096, 64, 768), (832, 4096, 52, 13 * 32), (832, 4096, 48, 832), (1536, 4096, 48, 1536), (1600, 4096, 20, 25 * 32),       # 16-byte rows
+    (401, 2000 + 1, 64, 7 * 32), (601, 2001, 20, 10 * 16),                                                           # unaligned ones
+])
+def test_split_products_begin_where_they_are_the_faster_ones(J, D, N, blocks):
+    """64 x 64 tiles by the fp32 instruction, 64 x 128 as split products, one workgroup each."""
+    g = torch.Generator(device=DEV).manual_seed(J + N)
+    U, V, W = (torch.randn(*s, generator=g, device=DEV) for s in ((N, J), (N, D), (J, D)))
+    ctx = sfb.Sfb("mlr", J, D, 4, N // 4, device=DEV)
+    W2 = W.clone()
+    ctx.reconstruct_apply(W2, U, V, 0.25, scale=0.5)
+    ctx.sync()
+    assert ctx.last_kernel(2) == ("reconstruct_thin_kernel", blocks)
+    want = W.double() - 0.125 * (U.double().T @ V.double())
+    assert ((W2.double() - want).abs() <= 2.0 ** -22 * (0.125 * N ** 0.5 * (U.abs().T @ V.abs()).double() + W.double().abs())).all()
+    ctx.close()
