@@ -545,8 +545,11 @@ hipError_t launch_update_bf16(const ReconArgs& a, const Bf16TilePlan& p, hipStre
 // Tile and slices of D, by a cost in microseconds of the pass and the factor kernel behind it, fitted to 200 shapes (J = 20 to
 // 10000, D = 64 to 20928, N = 30 to 11000, four tiles, up to ten slice counts each, one MI355X; the choice is within 1 % (TERMS
 // = 1) and 2 % (TERMS = 3) of the best measured one on average).  A chunk costs a lone workgroup and a compute unit full of them
-// what the table says: a compute unit takes 64 bytes a clock from its caches, which a chunk's words (64 x 64: 24 KB, 128 x 128: 48
-// KB) keep busy for longer than its products do the matrix pipe; a slice's partial scores are written and read at about 2 TB/s.
+// what the table says; a slice's partial scores are written and read at about 2 TB/s.  No unit is full: counters of 1000 x 4096 with
+// 512, thousands of cycles a compute unit, scores and update: busy 28.3 and 30.6; vector cache (64 bytes a clock) 9.6 and 10.0, the
+// largest share, and waiting for misses 11.5 and 16.0; LDS 6.1 and 5.1, no conflicts; matrix pipe 4.1 and 4.1; vector unit 3.9 and
+// 6.5.  By the costs below 6.9 of the scores' 13.3 us and 6.7 of the update's 15.5 are chunks; the others are start, first loads, W's
+// trip and write-back.
 // Against the 256 x 256 tiles of sfb_bf16.hip: 192 x 1600, N = 1280: 21.8 -> 10.6 us; 1000 x 4096, 512: 25.7 -> 18.
 Bf16TilePlan plan_scores_bf16(int64_t n_rows, int64_t J, int64_t D, int terms, size_t most) {
     static const struct { int bm, bn, resident; double lone_us[2], full_us[2]; } tiles[4] = {

@@ -145,7 +145,8 @@ __global__ __launch_bounds__(kSpThreads) void csr_scores_kernel(
     //  * the descriptors of a sample's slabs end where its row does: a lane past the end reads value 0 and column 0 by
     //    hardware, with no compare and no select (the descriptor's length is a scalar).  Zero times W's column 0 is nothing
     //    unless that is not finite in one of the four rows: such a workgroup walks once more, with the compare and the select,
-    //    so that feature 0 counts for the samples that store it and for no others.
+    //    so that feature 0 counts for the samples that store it and for no others.  (2000 x 8192, 1024 samples, 2 %: 64.6 us with
+    //    compare and select on every entry, 61.7 without them, 62.3 with the look at column 0.)
     // (arrays of the first `end` entries; every row pointer is clamped to nnz)
     auto upto = [](const void* p, int end) { return __builtin_amdgcn_make_buffer_rsrc((void*)p, (short)0, (int)((uint32_t)end * 4u), 0x00020000); };
     const int wave_s = __builtin_amdgcn_readfirstlane(wave);
