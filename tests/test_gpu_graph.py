@@ -15,7 +15,10 @@ pytestmark = pytest.mark.gpu
                                        ("dml", dict(J=96, D=256, P=2, B=64)),
                                        ("l2svm", dict(J=64, D=512, P=2, B=32)),
                                        # padded factor copies, slices of the pairs over workgroups, the adding-up kernel
-                                       ("mlr_tiny", dict(J=10, D=784, P=12, B=100))])
+                                       ("mlr_tiny", dict(J=10, D=784, P=12, B=100)),
+                                       # bf16 tiles with slices of D and of the pairs; an fp32 update of two launches
+                                       ("mlr_large", dict(J=192, D=200, P=16, B=80)),
+                                       ("mlr_medium", dict(J=1001, D=4100, P=8, B=61))])
 def test_step_recorded_in_a_graph_replays_like_eager_steps(name, over):
     import paper_1511_08486_amd as sfb
     dev = "cuda:0"
