@@ -146,8 +146,9 @@ size_t workspace_need(const sfb_ctx* c) {
     return need > prox ? need : prox;
 }
 
-// The split products' plans.  apart: the caller chose them (sfb_set_plan), the smaller term products get sums of their own.
-void plan_split_scores(sfb_ctx* c, bool apart) {
+// The split products' plans.  exact: three terms an operand throughout, where the caller chose them (sfb_set_plan) or features are sparse: a sum of
+// a few products has the error of its products, and those of two terms are the rougher ones (2 % stored: 8e-8 of the norm against 4e-8).
+void plan_split_scores(sfb_ctx* c, bool exact) {
     const int64_t N = (int64_t)c->P * c->B;
     // room for the partial scores: what ragged contexts reserve for their padded factor copies anyway, or a few MiB; the
     // others the 16 MiB that sfb_step_noalloc has; or what the fp32 instruction's plan would take, where that is more
@@ -158,14 +159,14 @@ void plan_split_scores(sfb_ctx* c, bool apart) {
     }
     const size_t f32_need = (size_t)c->fwd_all.split_k * (size_t)N * (size_t)round_up4(c->J) * sizeof(float);
     if (f32_need > most) most = f32_need;
-    c->fwd_split = plan_forward_split(N, c->J, c->D, most, apart);
-    c->fwd_split_worker = plan_forward_split(c->B, c->J, c->D, (size_t)c->fwd_split.split_k * (size_t)N * (size_t)round_up4(c->J) * sizeof(float), apart);
+    c->fwd_split = plan_forward_split(N, c->J, c->D, most, exact);
+    c->fwd_split_worker = plan_forward_split(c->B, c->J, c->D, (size_t)c->fwd_split.split_k * (size_t)N * (size_t)round_up4(c->J) * sizeof(float), exact);
 }
-void plan_split_recon(sfb_ctx* c, bool apart) {
+void plan_split_recon(sfb_ctx* c, bool exact) {
     if (c->dtype != SFB_F32) return;
     for (int one = 0; one < 2; ++one)
         for (int with_ws = 0; with_ws < 2; ++with_ws)
-            c->split_plans[one][with_ws] = reconstruct_split_plan(c->J, c->D, one ? c->B : (int64_t)c->P * c->B, with_ws ? workspace_need(c) : 0, apart);
+            c->split_plans[one][with_ws] = reconstruct_split_plan(c->J, c->D, one ? c->B : (int64_t)c->P * c->B, with_ws ? workspace_need(c) : 0, exact);
 }
 
 // The tiles' slices are cut to the bytes the context asks for: to be planned again whenever those change (sfb_set_plan).
@@ -432,7 +433,7 @@ sfb_status recon_launch(sfb_ctx* c, float* W, int64_t ldw, const float* U, int64
         if (e != hipSuccess) return hip_fail(c, e);
         return SFB_OK;
     }
-    bool on_split = false, halves = false, on_lists = false, on_thin = false;
+    bool on_split = false, on_lists = false, on_thin = false;
     const bool have_ws = c->ws != nullptr && c->ws_bytes >= workspace_need(c);
     const SplitReconPlan* sp = nullptr;
     const bool whole = reconstruct_takes_dma(r, c->recon);
@@ -451,14 +452,8 @@ sfb_status recon_launch(sfb_ctx* c, float* W, int64_t ldw, const float* U, int64
             const size_t planes = sp->slices > 1 ? (size_t)sp->slices : sp->main_rows + sp->main_cols > 0 && sp->rest_slices > 1 ? (size_t)sp->rest_slices : 0;
             const size_t rows = (size_t)(c->J - sp->main_rows), cols = (size_t)(c->D - sp->main_cols);
             if (planes * rows * cols * sizeof(float) > workspace_need(c)) sp = &c->split_plans[n_rows > 0][0];
-            // The kernel these products stand in for adds its sums in four parts where J is 600 or 1160, say, and is the more
-            // accurate one unless they are cut in two: 600 x 4096 with 1024 pairs, of the norm, 2.9e-7 (mixed signs) and
-            // 1.3e-7 (all positive) against 3.4e-7 and 1.9e-7 in one piece (39.6 us), 2.4e-7 and 1.1e-7 in two (42.7; that
-            // kernel 51)
-            halves = c->split_recon < 0 && sp->slices == 1 && r.N > 128 && reconstruct_plan_cuts_pairs(whole ? c->recon : c->recon_padded);
-            const double split_us = sp->us + (halves ? 3.2 : 0.0);
-            on_split = c->split_recon == 1 || split_us < us;
-            if (on_split) us = split_us;
+            on_split = c->split_recon == 1 || sp->us < us;
+            if (on_split) us = sp->us;
         }
         on_lists = same_step && c->lists != nullptr && c->split_recon < 0 &&
                    sparse_update_us(r.N, c->J, c->D, c->lists_stored) < us;
@@ -473,7 +468,7 @@ sfb_status recon_launch(sfb_ctx* c, float* W, int64_t ldw, const float* U, int64
         e = launch_sparse_update(r, c->lists_stored, c->lists, c->stream);
     } else if (on_split) {
         r.partial = have_ws ? (float*)c->ws : nullptr;                   // (plans without a workspace have no slices)
-        e = launch_reconstruct_split(r, *sp, halves, c->stream);
+        e = launch_reconstruct_split(r, *sp, c->stream);
     } else {
         // calls that would end in the register-staged kernel first try a copy of the factors that the LDS-DMA
         // kernels accept: padded ones for ragged shapes, U with a dead worker's rows zeroed for a masked call
@@ -536,7 +531,7 @@ sfb_status sfb_create(sfb_ctx** out, sfb_model m, int64_t J, int64_t D, int32_t 
                             !((J % 4) == 0 && J >= 4 && (D % 128) == 0 && (N % 32) == 0 && N >= 32);
         c->recon_padded = plan_reconstruct_padded(J, D, N, -1);
     }
-    plan_split_scores(c, false);
+    plan_split_scores(c, m == SFB_L2SVM);
     c->fused_ok = input_dtype == SFB_BF16 && m == SFB_MLR && fused_shape_ok(J, D, (int64_t)P * B);
     c->use_fused = true;
     c->fused = c->fused_ok ? plan_fused(J, D, (int64_t)P * B) : FusedPlan{};
@@ -546,7 +541,7 @@ sfb_status sfb_create(sfb_ctx** out, sfb_model m, int64_t J, int64_t D, int32_t 
         const size_t planes = few_workspace((int64_t)P * B, J, D);
         c->few = planes <= SFB_NOALLOC_SCRATCH_BYTES || planes <= workspace_need(c);
     }
-    plan_split_recon(c, false);
+    plan_split_recon(c, m == SFB_L2SVM);
     c->tile_bf16_scores = c->tile_bf16_update = true;
     plan_bf16_tiles(c);
     c->ws = nullptr; c->ws_bytes = 0; c->lists = nullptr; c->lists_stored = 0; c->last_hip = 0; c->timing = false; c->sparse_forward = true; c->sparse_always = false;

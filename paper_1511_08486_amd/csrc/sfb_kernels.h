@@ -44,7 +44,7 @@ struct FwdPlan {
     int k_slice;     // columns of D per slice (multiple of the K chunk)
     int grid;        // workgroups
     bool dma;        // stage tiles by LDS-DMA where the shape allows
-    bool apart;      // split products: the smaller term products in sums of their own
+    bool exact;      // split products: three bf16 terms an operand throughout
 };
 
 // Chooses tile and split for Z[n_rows][J] = A W^T with contraction length D.
@@ -69,7 +69,7 @@ struct FwdArgs {
 hipError_t launch_forward(const FwdArgs& a, const FwdPlan& p, hipStream_t s);
 // fp32 scores on the bf16 matrix cores, every operand split exactly into three bf16 terms (sfb_forward_split.hip)
 bool forward_split_ok(const FwdArgs& a);
-FwdPlan plan_forward_split(int64_t n_rows, int64_t J, int64_t D, size_t most, bool apart);
+FwdPlan plan_forward_split(int64_t n_rows, int64_t J, int64_t D, size_t most, bool exact);
 hipError_t launch_forward_split(const FwdArgs& a, const FwdPlan& p, hipStream_t s);
 
 // Dual side of SDCA (Section 2.1): with `dual` set, the MLR factor kernel turns its
@@ -223,16 +223,14 @@ bool reconstruct_thin_ok(const ReconArgs& a);
 hipError_t launch_reconstruct_thin(const ReconArgs& a, hipStream_t s);
 struct SplitReconPlan {
     int bm, bn, slices;                // tile, slices of the pairs
-    bool apart;                        // the smaller products' sums apart
+    bool exact;                        // three bf16 terms an operand throughout
     double us;                         // estimate
     int main_rows, main_cols;          // 0, or the rows or columns that these tiles take: the others are a launch with
     int rest_bm, rest_bn, rest_slices; //   these
+    bool rest_exact;
 };
-SplitReconPlan reconstruct_split_plan(int64_t J, int64_t D, int64_t N, size_t room, bool apart);   // room: bytes for planes of sums
-// halves: calls without slices let the running sums start anew half way through the pairs
-hipError_t launch_reconstruct_split(const ReconArgs& a, const SplitReconPlan& p, bool halves, hipStream_t s);
-// true where the fp32 instruction's plan is the kernel that cuts every contraction in four (variant 11)
-bool reconstruct_plan_cuts_pairs(const ReconPlan& p);
+SplitReconPlan reconstruct_split_plan(int64_t J, int64_t D, int64_t N, size_t room, bool exact);   // room: bytes for planes of sums
+hipError_t launch_reconstruct_split(const ReconArgs& a, const SplitReconPlan& p, hipStream_t s);
 
 // Reconstruction from the stored entries of sparse features (sfb_sparse_update.hip): column lists made from the dense
 // rows V, then W += alpha U^T V over the entries only.  workspace: sparse_update_workspace(D, stored) bytes, 256-byte

@@ -558,7 +558,6 @@ constexpr int kSmallVariant = 9, kKsplitVariant = 11, kPairVariant = 12;
 constexpr int kNumReconVariants = sizeof(kReconVariants) / sizeof(kReconVariants[0]);
 
 int num_reconstruct_variants() { return kNumReconVariants; }
-bool reconstruct_plan_cuts_pairs(const ReconPlan& p) { return p.variant == kKsplitVariant; }
 
 ReconPlan plan_reconstruct(int64_t J, int64_t D, int64_t N) {
     // largest tile that still gives every compute unit a workgroup; the smallest otherwise.

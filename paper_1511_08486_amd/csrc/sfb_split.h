@@ -1,22 +1,30 @@
-// fp32 contractions on the bf16 matrix cores at fp32 accuracy: what the score pass (sfb_forward_split.hip) and the
+// fp32 contractions on the 16-bit matrix cores at fp32 accuracy: what the score pass (sfb_forward_split.hip) and the
 // reconstruction (sfb_reconstruct_split.hip) share.
 //
-// gfx950 multiplies bf16 sixteen times faster than fp32 on its matrix cores.  Every fp32 operand is split EXACTLY into
-// three bf16 terms, x = h + m + l (h = bf16(x), m = bf16(x - h), l = bf16(x - h - m): 3 x 8 significand bits cover
-// fp32's 24, and both differences are exact in fp32; below 2^-109 l runs out of bf16's exponents: sums of operands of 2^-118
-// are off by 3e-7, of 2^-120 by 1e-6, of 2^-125 by 3e-5, where the fp32 instruction keeps 1e-7), and a product a * b is taken as the six term products whose
-// weight is at least 2^-16 of the leading one:
-//     a_h b_h  +  (a_h b_m + a_m b_h)  +  (a_h b_l + a_l b_h + a_m b_m).
-// Each is exact in the fp32 accumulator's input (8 x 8 bits).  What is left out (a_m b_l + a_l b_m + a_l b_l) is below
-// 2^-24 of |a b| and unbiased, the size of ONE fp32 rounding of one product; a matrix instruction adds 16 products
-// per rounding where the fp32 one adds two, so a sum of K products is rounded 6 K / 16 times instead of K / 2 times.
+// gfx950 multiplies 16-bit operands sixteen times faster than fp32 on its matrix cores.  Every fp32 operand is split into terms of 16 bits
+// and a product is taken as its leading term products, each exact in the fp32 accumulator's input:
+//   Three bf16 terms, x = h + m + l (h = bf16(x), m = bf16(x - h), l = bf16(x - h - m)): EXACT, 3 x 8 significand bits cover
+//     fp32's 24, and both differences are exact in fp32 (below 2^-109 l runs out of bf16's exponents: sums of operands of 2^-118
+//     are off by 3e-7, of 2^-120 by 1e-6, of 2^-125 by 3e-5, where the fp32 instruction keeps 1e-7).  Six products, those whose
+//     weight is at least 2^-16 of the leading one; what is left out is below 2^-24 of |a b| and unbiased.
+//   Two fp16 terms of the scaled value, s x = h + l (h = fp16(s x), l = fp16(s x - h)): 22 significand bits and a sign, three quarters of all
+//     fp32 values exactly, the others 2^-24 off.  Three products; left out: a_l b_l, below 2^-22 and unbiased.  Half the matrix instructions and
+//     two thirds of the LDS traffic.  fp16 has few exponents, so a workgroup takes one power of two s per operand, from the largest value of
+//     its first 64 k (scaled to 2^9 .. 2^10), and looks at every group of four values that it splits: none beyond 2^15 scaled, and none whose
+//     largest is below 2^-10 but not zero.  Above 2^-2 scaled (2^-12 of the largest) a value keeps its 22 bits, below it is at most 2^-25 scaled
+//     off (2^-35 of the largest).  From the first chunk with a group outside on, the rest of the sum is taken in three terms (1000 x 4096 with 512
+//     samples: 25 us, 31 with operands over many magnitudes, which is what three terms take throughout).
+// Sums of 256 products and more are closer to fp64 with two terms than with the three terms in one running sum that they replace; of the norm,
+// operands of mixed signs (then -> two terms here): scores 1000 x 4096, 512 samples 2.5e-7 -> 1.8e-7, update 2.4e-7 -> 1.7e-7;
+// 600 x 4096 with 1024: 2.9e-7 -> 1.9e-7 and 2.4e-7 -> 1.7e-7.  Three terms here: 1.4e-7 and 1.3e-7 (1000 x 4096).  Either way the smaller
+// products have sums of their own, so that the leading ones' running sum is rounded once for every sixteen k.
 //
-// A workgroup is eight wavefronts, two per SIMD: four take k 0..15 of every chunk of 32 k, four k 16..31, each group
-// as 2 x 2 over the tile.  Everything a chunk needs is spread over the chunks before it, so that a wavefront never
-// stops between its matrix instructions: while it multiplies chunk c from registers, it reads its fragments of chunk
-// c + 1 from LDS, splits its share of chunk c + 2 into the other LDS buffer (the vector instructions go into the
-// shadow of the matrix instructions, about four each: measured free up to four, 5 % at six), and requests its share
-// of chunk c + 4 (c + 6 in the small tiles, which have registers left and are the ones that wait for memory).  One barrier per chunk, two LDS buffers of three planes [row][32 k] (rows of the A tile, then B).
+// A workgroup has two kinds of wavefronts.  Splitting ones (eight, two a SIMD) request raw words three chunks of 32 k ahead, through
+// descriptors whose base moves by scalar instructions, split them and park the terms in LDS; multiplying ones (one or two a SIMD) read
+// fragments and do nothing but matrix instructions, so neither kind stands in the other's instruction stream.  One barrier a chunk; two terms
+// have three LDS buffers (a fragment is read one phase of products before its use, across the barrier too), three terms two.
+// 128 x 128 tiles, cycles a chunk: 1600 (2300 where every wavefront did both in turns, with three terms); matrix instructions alone 770,
+// 966 with the barrier, splits alone 1027, LDS reads, writes and loads without either 1500.
 #pragma once
 #include <type_traits>
 
@@ -25,11 +33,16 @@
 namespace sfb {
 
 typedef __bf16 sp_bf16x8 __attribute__((ext_vector_type(8)));
+typedef _Float16 sp_f16x8 __attribute__((ext_vector_type(8)));
+typedef _Float16 sp_f16x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t sp_u32x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) uint32_t sp_lds_u32;             // (a flat load would wait for every load on its way)
 typedef float sp_f32x4u __attribute__((ext_vector_type(4), aligned(4)));   // a 16-byte access at any 4-byte address
 
 constexpr int kSpChunk = 32;       // k per chunk
-constexpr int kSplitThreads = 512;
+constexpr int kSpTopExp = 9;       // two terms: the first chunks' largest value is scaled to 2^9 .. 2^10
+constexpr int kSpBlankExp = 4;     // the scale's exponent where they are all zero
+constexpr int kSpLeastExp = -10;   // the largest of a group of four stays above 2^-10 scaled (or is zero)
 
 // every wavefront of the workgroup; this wavefront's LDS writes are visible and its LDS reads done
 __device__ __forceinline__ void split_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
@@ -37,6 +50,17 @@ __device__ __forceinline__ void split_barrier() { asm volatile("s_waitcnt lgkmcn
 __device__ __forceinline__ f32x16 split_mfma(sp_u32x4 a, sp_u32x4 b, f32x16 c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(sp_bf16x8, a), __builtin_bit_cast(sp_bf16x8, b), c, 0, 0, 0);
 }
+
+__device__ __forceinline__ f32x4 split_mfma16_f16(sp_u32x4 a, sp_u32x4 b, f32x4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(sp_f16x8, a), __builtin_bit_cast(sp_f16x8, b), c, 0, 0, 0);
+}
+
+__device__ __forceinline__ f32x4 split_mfma16(sp_u32x4 a, sp_u32x4 b, f32x4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(sp_bf16x8, a), __builtin_bit_cast(sp_bf16x8, b), c, 0, 0, 0);
+}
+
+// four k: one of this lane's quarter each
+__device__ __forceinline__ f32x4 split_mfma16_f32(float a, float b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
 
 __device__ __forceinline__ f32x16 split_mfma_f32(float a, float b, f32x16 c) { return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0); }
 
@@ -49,8 +73,7 @@ __device__ __forceinline__ void split_for(F f) {
 }
 
 // The exact split of two pairs of fp32 values (a0 a1, b0 b1) in four parts of four to six vector instructions, the two
-// pairs side by side so that neighbours do not depend on each other: a wavefront alone on its SIMD then needs no more
-// than a matrix instruction's 32 cycles for a part (one pair at a time: about 45, every instruction waiting for the last)
+// pairs side by side so that neighbours do not depend on each other (an instruction that waits for the last takes eight cycles, not four)
 struct SplitQuad {
     float a0, a1, b0, b1, ta, tb, ua, ub;
     uint32_t ha, hb, ma, mb, la, lb;
@@ -77,181 +100,411 @@ struct SplitQuad {
     }
 };
 
-// The multiplying side.  Tile (WM MT x 32) x (WN NT x 32), four wavefronts as WM x WN, each MT x NT blocks of 32 x 32.
-// PITCH: bytes from one LDS row to the next; SWZ: 16-byte item c of row r sits at c ^ f(r) instead of c.
-// APART: the five smaller term products have sums of their own, so that the leading ones' running sum is rounded once for
-// every sixteen k instead of six times (error of a sum of 4096 products 1.4e-7 instead of 2.5e-7, of 512 1.3e-7 instead of
-// 2.4e-7; the fp32 instruction 5.8e-7 and 2.9e-7): for callers who chose these products for their accuracy (sfb_set_plan).
-// No time of its own, but 64 x 64 blocks of a wavefront have no registers left for it.
-template <int MT, int NT, int PITCH, bool SWZ, bool APART, int WM = 2>
+// Two fp16 terms of two scaled values each, packed: h = fp16(s x), l = fp16(s x - h); s is a power of two, s x - h is exact.  Six
+// vector instructions of four cycles (v_fma_mixlo_f16, which gives either term in one, takes twice as long: four of those were 1.4 times it).
+struct SplitPair {
+    uint32_t h, l;
+    __device__ __forceinline__ SplitPair(float x0, float x1, float s) {
+        float r0, r1;
+        asm("v_cvt_pk_f16_f32 %0, %1, %2" : "=v"(h) : "v"(x0 * s), "v"(x1 * s));
+        asm("v_fma_mix_f32 %0, %1, %2, -%3 op_sel_hi:[0,0,1]" : "=v"(r0) : "v"(x0), "s"(s), "v"(h));
+        asm("v_fma_mix_f32 %0, %1, %2, -%3 op_sel:[0,0,1] op_sel_hi:[0,0,1]" : "=v"(r1) : "v"(x1), "s"(s), "v"(h));
+        asm("v_cvt_pk_f16_f32 %0, %1, %2" : "=v"(l) : "v"(r0), "v"(r1));
+    }
+};
+// largest magnitude of four
+__device__ __forceinline__ float split_most4(f32x4 x) {
+    float m;
+    asm("v_max3_f32 %0, |%1|, |%2|, |%3|" : "=v"(m) : "v"(x[0]), "v"(x[1]), "v"(x[2]));
+    asm("v_max_f32 %0, |%1|, %0" : "+v"(m) : "v"(x[3]));
+    return m;
+}
+
+// Scale of one operand and the bounds that its values keep (magnitudes as their bit patterns)
+struct SplitScale {
+    float s;
+    int e;                         // s = 2^e
+    uint32_t most, least_m1;       // largest allowed magnitude; smallest one of a group that is not all zero, minus one
+    // m: largest magnitude of the first chunks.  false: no such scale, the three-term products take the tile
+    __device__ __forceinline__ bool set(uint32_t m) {
+        const int x = (int)(m >> 23);
+        e = m == 0 ? kSpBlankExp : kSpTopExp + 127 - x;
+        s = __uint_as_float((uint32_t)(127 + e) << 23);
+        most = (uint32_t)min(127 + 15 - e, 254) << 23;
+        least_m1 = ((uint32_t)(127 + kSpLeastExp - e) << 23) - 1u;
+        return m == 0 || (x >= 24 && x < 255);
+    }
+};
+
+// largest of sixteen lanes, in each of them
+__device__ __forceinline__ uint32_t split_max16(uint32_t x) {
+    auto step = [](uint32_t v, auto ctrl) { return max(v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, decltype(ctrl)::value, 0xf, 0xf, true)); };
+    x = step(x, std::integral_constant<int, 0xb1>{});                    // quad_perm 1,0,3,2
+    x = step(x, std::integral_constant<int, 0x4e>{});                    // quad_perm 2,3,0,1
+    x = step(x, std::integral_constant<int, 0x141>{});                   // row_half_mirror
+    return step(x, std::integral_constant<int, 0x140>{});                // row_mirror
+}
+
+// One workgroup's contraction: a tile of BM x BN by WM x WN multiplying wavefronts, each MB x NB blocks of 16 x 16, and SPLITTERS
+// splitting ones.  An LDS row is 32 k of one row of the tile (BM of the A operand, then BN of B), 64 bytes a plane; 16-byte item c of row r
+// sits at c ^ swz(r).
+// EXACT: three-term products throughout, for callers who chose them (sfb_set_plan).
+template <int BM_, int BN_, int WM_, int WN_, int SPLITTERS, bool EXACT>
 struct SplitTile {
-    static constexpr int WN = 4 / WM, BM = 32 * WM * MT, BN = 32 * WN * NT, ROWS = BM + BN;
-    static constexpr int PLANE = ROWS * PITCH, BYTES = 3 * PLANE;      // one group's buffer
-    static constexpr int XCHG = 8 * MT * NT * 8 * 64 * 4;               // exchange of partial sums at the end
-    static constexpr int LDS = 2 * BYTES > XCHG ? 2 * BYTES : XCHG;
+    static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, MB = BM / (16 * WM), NB = BN / (16 * WN), ROWS = BM + BN;
+    static constexpr int MULTIPLIERS = WM * WN, THREADS = 64 * (MULTIPLIERS + SPLITTERS), WAVES = THREADS / 256;   // wavefronts a SIMD
+    static constexpr int PLANE = ROWS * 64;
+    static constexpr int CTL = 6 * PLANE;                               // three buffers of two planes or two of three; control words
+    static constexpr int LDS = CTL + 32;
+    static_assert(LDS <= 160 * 1024, "LDS");
 
     // Among eight consecutive rows any one item falls into eight different 16-byte bank groups of 128 bytes, among
     // sixteen into sixteen of 256; of four consecutive rows (from a multiple of four) half a row each, too.
-    static __device__ __forceinline__ int swz(int r) { return SWZ ? (((r >> 2) & 1) | ((((r >> 1) ^ (r >> 3)) & 1) << 1)) : 0; }
+    static __device__ __forceinline__ int swz(int r) { return ((r >> 2) & 1) | ((((r >> 1) ^ (r >> 3)) & 1) << 1); }
 
-    struct Frag { sp_u32x4 a[3][MT], b[3][NT]; };
-    static_assert(!APART || MT * NT <= 2, "registers");
-    f32x16 acc[MT][NT], rest[APART ? MT : 1][APART ? NT : 1];
+    // Control words: [0] chunks from this number on are not taken in two terms; [4 ..] what the splitting wavefronts saw in the first
+    // two chunks: of each operand the largest magnitude, and the smallest largest of a group that is not all zero, minus one (complement).
+    static __device__ __forceinline__ uint32_t stop_word(unsigned char* lds) { return *(volatile sp_lds_u32*)(lds + CTL); }
+    static __device__ __forceinline__ bool scales(const unsigned char* lds, SplitScale (&sc)[2]) {
+        const uint4 all = *reinterpret_cast<const uint4*>(lds + CTL + 16);
+        auto uniform = [](uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); };
+        const bool a = sc[0].set(uniform(all.x)), b = sc[1].set(uniform(all.z));
+        return a && b && ~uniform(all.y) >= sc[0].least_m1 && ~uniform(all.w) >= sc[1].least_m1;
+    }
+
+    // ---- the multiplying wavefronts ----
+    static constexpr bool REST = MB * NB <= 8;                          // the smaller products have sums of their own (registers)
+    // Two terms: leading products of even and odd chunks apart where there are registers for it (all-positive operands, 600 x 4096, 1024 pairs:
+    // 1.8e-7 of the norm in one sum, 0.9e-7 in two)
+    static constexpr int SUMS = ROWS > 128 && ROWS < 256 && !EXACT ? 2 : 1;
+    f32x4 acc[MB][NB], rest[REST ? MB : 1][REST ? NB : 1], odd[SUMS == 2 ? MB : 1][SUMS == 2 ? NB : 1];
     int a_base, b_base;            // byte offset of this lane's item in the A and the B part
 
     __device__ __forceinline__ void init(int wave, int lane) {
-        const int wm = (wave & 3) / WN, wn = wave % WN, l32 = lane & 31, half = lane >> 5;
-        // every row this lane reads is l32 modulo 32
-        const int item = 16 * ((2 * (wave >> 2) + half) ^ swz(l32));
-        a_base = (wm * 32 * MT + l32) * PITCH + item;
-        b_base = (BM + wn * 32 * NT + l32) * PITCH + item;
+        const int wm = wave / WN, wn = wave % WN, l16 = lane & 15;
+        const int item = 16 * ((lane >> 4) ^ swz(l16));                  // every row this lane reads is l16 modulo 16
+        a_base = (wm * 16 * MB + l16) * 64 + item;
+        b_base = (BM + wn * 16 * NB + l16) * 64 + item;
 #pragma unroll
-        for (int i = 0; i < MT; ++i)
+        for (int i = 0; i < MB; ++i)
 #pragma unroll
-            for (int j = 0; j < NT; ++j)
-#pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    acc[i][j][e] = 0.f;
-                    if constexpr (APART) rest[i][j][e] = 0.f;
-                }
+            for (int j = 0; j < NB; ++j) {
+                acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+                if constexpr (REST) rest[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+                if constexpr (SUMS == 2) odd[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+            }
     }
-    // fragment read Q of the 3 (MT + NT): plane by plane, A blocks then B blocks
-    static constexpr int READS = 3 * (MT + NT), MFMAS = 6 * MT * NT;
-    template <int Q>
-    __device__ __forceinline__ void read(Frag& f, const unsigned char* buf) {
-        constexpr int P = Q / (MT + NT), B = Q % (MT + NT);
-        if constexpr (B < MT) f.a[P][B] = *reinterpret_cast<const sp_u32x4*>(buf + a_base + P * PLANE + B * 32 * PITCH);
-        else f.b[P][B - MT] = *reinterpret_cast<const sp_u32x4*>(buf + b_base + P * PLANE + (B - MT) * 32 * PITCH);
+    struct Frags { sp_u32x4 a[MB], b[NB]; };
+    __device__ __forceinline__ sp_u32x4 item_a(const unsigned char* buf, int plane, int i) const {
+        return *reinterpret_cast<const sp_u32x4*>(buf + a_base + plane * PLANE + i * 16 * 64);
     }
-    // matrix instruction Q: the six term products, smallest first; the blocks innermost, so that none waits for the one before
-    template <int Q>
-    __device__ __forceinline__ void mma(const Frag& f) {
-        constexpr int PA[6] = {2, 0, 1, 1, 0, 0}, PB[6] = {0, 2, 1, 0, 1, 0};
-        constexpr int T = Q / (MT * NT), I = Q / NT % MT, J = Q % NT;
-        if constexpr (APART && T < 5) rest[I][J] = split_mfma(f.a[PA[T]][I], f.b[PB[T]][J], rest[I][J]);
-        else acc[I][J] = split_mfma(f.a[PA[T]][I], f.b[PB[T]][J], acc[I][J]);
+    __device__ __forceinline__ sp_u32x4 item_b(const unsigned char* buf, int plane, int j) const {
+        return *reinterpret_cast<const sp_u32x4*>(buf + b_base + plane * PLANE + j * 16 * 64);
     }
-    // fetch(raw, c): requests this lane's raw words of chunk c (c may be past the end: anything valid).
-    // prep(raw, c):  what has to happen to them before they are split, branches included.
-    // park(part, raw, state, buf): part 0 .. PARTS - 1 of splitting them into an LDS buffer.
-    // DEPTH (2 or 4): chunks whose raw words are in flight.
-    template <class Raw, class State, int PARTS, bool BEHIND_FIRST, int DEPTH, class Fetch, class Prep, class Park>
-    __device__ __forceinline__ void run(int n_chunks, unsigned char* lds, Fetch fetch, Prep prep, Park park) {
-        unsigned char* const buf0 = lds;
-        unsigned char* const buf1 = lds + BYTES;
-        static_assert(DEPTH == 2 || DEPTH == 4, "raw sets");
-        Raw r[DEPTH];
-        State st;
-        Frag f0, f1;
-#pragma unroll
-        for (int d = 0; d < DEPTH; ++d) fetch(r[d], d);
-        prep(r[0], 0);
-        split_for<0, PARTS>([&](auto p) { park(p, r[0], st, buf0); });
-        fetch(r[0], DEPTH);
-        split_barrier();
-        split_for<0, READS>([&](auto q) { read<decltype(q)::value>(f0, buf0); });
-        prep(r[1], 1);
-        split_for<0, PARTS>([&](auto p) { park(p, r[1], st, buf1); });
-        fetch(r[1], DEPTH + 1);
-        auto step = [&](int c, Frag& now, Frag& next, const unsigned char* from, Raw& raw, unsigned char* to) {
-            prep(raw, c + 2);
-            // Slot q: one matrix instruction, then its share of the reads and of the parts.  The barrier (everybody has
-            // parked chunk c + 1 and read chunk c) stands LEAD matrix instructions into the step, the LDS work after it.
-            constexpr int LEAD = MFMAS / 6, R_SLOTS = MFMAS / 2, P_SLOTS = MFMAS - LEAD;
-            split_for<0, MFMAS>([&](auto qc) {
-                constexpr int q = decltype(qc)::value, w = q - LEAD;
-                __builtin_amdgcn_sched_barrier(0);
-                // the wavefront that is behind goes first: otherwise one of the two on a SIMD runs ahead to the barrier and
-                // leaves the other alone on the matrix pipe
-                if constexpr (BEHIND_FIRST && q % (MFMAS / 4) == 0) __builtin_amdgcn_s_setprio(3 - q / (MFMAS / 4));
-                mma<q>(now);
-                __builtin_amdgcn_sched_barrier(0);
-                if constexpr (w == -1) split_barrier();
-                if constexpr (w >= 0) {
-                    constexpr int R0 = w * READS / R_SLOTS, R1 = (w + 1) * READS / R_SLOTS;
-                    split_for<(R0 < READS ? R0 : READS), (R1 < READS ? R1 : READS)>([&](auto r) { read<decltype(r)::value>(next, from); });
-                    split_for<w * PARTS / P_SLOTS, (w + 1) * PARTS / P_SLOTS>([&](auto p) { park(p, raw, st, to); });
-                }
-            });
+    // All blocks' products of one plane of A and one of B, with COUNT reads spread over the first of them (two a matrix instruction at most
+    // in small tiles, every other instruction in large ones).
+    template <int T, bool LEADING, int COUNT, bool ODD = false, class Read>
+    __device__ __forceinline__ void phase(const sp_u32x4 (&a)[MB], const sp_u32x4 (&b)[NB], Read read) {
+        split_for<0, MB * NB>([&](auto qc) {
+            constexpr int q = decltype(qc)::value, i = q / NB, j = q % NB;
             __builtin_amdgcn_sched_barrier(0);
-            fetch(raw, c + 2 + DEPTH);
+            f32x4& to = REST && !LEADING ? rest[REST ? i : 0][REST ? j : 0] : ODD ? odd[SUMS == 2 ? i : 0][SUMS == 2 ? j : 0] : acc[i][j];
+            if constexpr (T == 2) to = split_mfma16_f16(a[i], b[j], to);
+            else to = split_mfma16(a[i], b[j], to);
+            __builtin_amdgcn_sched_barrier(0);
+            constexpr int OVER = COUNT > 0 ? (MB * NB > COUNT ? COUNT : MB * NB) : 1;
+            if constexpr (q < OVER) split_for<q * COUNT / OVER, (q + 1) * COUNT / OVER>(read);
+        });
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    // Two terms (planes h, l), chunks 0 .. n - 1; returns the first that was not taken.  A fragment is read into the registers that it takes
+    // over one phase of products ahead of its use.
+    __device__ __forceinline__ int multiply2(int n, unsigned char* lds) {
+        constexpr int BUF = 2 * PLANE;
+        sp_u32x4 ah[MB], al[MB], bh[NB], bl[NB];
+        int at = 0, c = 0;
+#pragma unroll
+        for (int i = 0; i < MB; ++i) ah[i] = item_a(lds, 0, i);
+#pragma unroll
+        for (int j = 0; j < NB; ++j) bl[j] = item_b(lds, 1, j);
+        auto step = [&](auto is_odd) {
+            const unsigned char* const now = lds + at;
+            at = at == 2 * BUF ? 0 : at + BUF;
+            const unsigned char* const next = lds + at;
+            const uint32_t stop = stop_word(lds);
+            phase<2, false, NB + MB>(ah, bl, [&](auto rc) {
+                constexpr int r = decltype(rc)::value;
+                if constexpr (r < NB) bh[r] = item_b(now, 0, r);
+                else al[r - NB] = item_a(now, 1, r - NB);
+            });
+            phase<2, true, NB, decltype(is_odd)::value>(ah, bh, [&](auto rc) { bl[decltype(rc)::value] = item_b(next, 1, decltype(rc)::value); });
+            phase<2, false, MB>(al, bh, [&](auto rc) { ah[decltype(rc)::value] = item_a(next, 0, decltype(rc)::value); });
+            asm volatile("s_barrier" ::: "memory");                      // (its reads of the buffer that is written next are used up)
+            ++c;
+            return c < n && (uint32_t)__builtin_amdgcn_readfirstlane((int)stop) > (uint32_t)c;
         };
-        // (left in the middle, so that every path into a step has the other raw sets' loads behind it)
-        for (int c = 0;;) {
-            step(c, f0, f1, buf1, r[2 % DEPTH], buf0);
-            if (++c >= n_chunks) break;
-            step(c, f1, f0, buf0, r[3 % DEPTH], buf1);
-            if (++c >= n_chunks) break;
-            if constexpr (DEPTH == 4) {
-                step(c, f0, f1, buf1, r[0], buf0);
-                if (++c >= n_chunks) break;
-                step(c, f1, f0, buf0, r[1], buf1);
-                if (++c >= n_chunks) break;
+        while (step(std::false_type{}))
+            if (SUMS == 2 && !step(std::bool_constant<SUMS == 2>{})) break;
+        return c;
+    }
+    // Three terms (planes h, m, l), chunks c0 .. n - 1.
+    __device__ __forceinline__ void multiply3(int c0, int n, unsigned char* lds) {
+        constexpr int BUF = 3 * PLANE;
+        for (int c = c0, at = 0; c < n; ++c, at = BUF - at) {
+            const unsigned char* const now = lds + at;
+            sp_u32x4 a0[MB], a1[MB], bh[NB], bm[NB], bl[NB];
+#pragma unroll
+            for (int i = 0; i < MB; ++i) a0[i] = item_a(now, 0, i);
+#pragma unroll
+            for (int j = 0; j < NB; ++j) {
+                bl[j] = item_b(now, 2, j);
+                bm[j] = item_b(now, 1, j);
+            }
+            phase<3, false, NB>(a0, bl, [&](auto rc) { bh[decltype(rc)::value] = item_b(now, 0, decltype(rc)::value); });
+            phase<3, false, MB>(a0, bm, [&](auto rc) { a1[decltype(rc)::value] = item_a(now, 1, decltype(rc)::value); });
+            phase<3, true, 0>(a0, bh, [](auto) {});
+            phase<3, false, MB>(a1, bm, [&](auto rc) { a0[decltype(rc)::value] = item_a(now, 2, decltype(rc)::value); });
+            phase<3, false, 0>(a1, bh, [](auto) {});
+            phase<3, false, 0>(a0, bh, [](auto) {});
+            asm volatile("s_barrier" ::: "memory");
+        }
+    }
+    __device__ __forceinline__ void multiply(int n, unsigned char* lds) {
+        int done = 0;
+        auto merge = [&](int e) {
+#pragma unroll
+            for (int i = 0; i < MB; ++i)
+#pragma unroll
+                for (int j = 0; j < NB; ++j)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        if constexpr (SUMS == 2) {
+                            acc[i][j][q] += odd[i][j][q];
+                            odd[i][j][q] = 0.f;
+                        }
+                        if constexpr (REST) {
+                            acc[i][j][q] += rest[i][j][q];
+                            rest[i][j][q] = 0.f;
+                        }
+                        acc[i][j][q] = __builtin_amdgcn_ldexpf(acc[i][j][q], e);
+                    }
+        };
+        if constexpr (!EXACT) {
+            if (threadIdx.x < 8) *(volatile sp_lds_u32*)(lds + CTL + 4 * threadIdx.x) = threadIdx.x == 0 ? 0xffffffffu : 0u;   // wavefront 0
+            split_barrier();
+            split_barrier();
+            SplitScale sc[2];
+            const bool fits = scales(lds, sc);
+            split_barrier();
+            if (fits) {
+                done = multiply2(n, lds);
+                merge(-(sc[0].e + sc[1].e));
+            }
+            if (done >= n) return;
+        }
+        split_barrier();
+        multiply3(done, n, lds);
+        merge(0);
+    }
+
+    // ---- the splitting wavefronts ----
+    // ITEMS groups of four values a lane and chunk, in slots of the same operand: where(c, first) says where chunk c is (c may be past the end:
+    // then there is nothing to move; first: compile time, chunk 0 may be only there), load(raw, place, u, first) requests unit u of its raw
+    // words (as many units as pairs of groups), prep(raw, c, first) does what has to happen to them before they are split, take(raw, i) is
+    // group i, put(buf, plane, i, words) parks four terms of it.  DEPTH: chunks whose raw words are in flight.
+    // A unit is requested as soon as its words are used up, one behind every pair of groups (LAG pairs later): in one burst behind a chunk the
+    // requests of four wavefronts took 900 cycles to be accepted, and nothing was split meanwhile.
+    // Slot slot(i): operand second[slot], parked only where on[slot] (both uniform).
+    template <int T, class Raw, int ITEMS, int SLOTS, int DEPTH, int LAG, class Slot, class Where, class Load, class Prep, class Take, class Put>
+    static __device__ __forceinline__ int split_in(int c0, int n, unsigned char* lds, const bool (&second)[SLOTS], const bool (&on)[SLOTS],
+                                            Slot slot, Where where, Load load, Prep prep, Take take, Put put) {
+        constexpr int LEAD = T == 2 ? 2 : 1, BUF = T * PLANE, UNITS = (ITEMS + 1) / 2;
+        static_assert(DEPTH >= 2, "raw sets");
+        Raw r[DEPTH];
+        float s[SLOTS];
+        uint32_t most[SLOTS], least[SLOTS];
+        auto park = [&](const Raw& raw, int c, int at, auto after) {
+            uint32_t mx[SLOTS], mn[SLOTS];
+#pragma unroll
+            for (int q = 0; q < SLOTS; ++q) { mx[q] = 0u; mn[q] = 0xffffffffu; }
+            split_for<0, UNITS>([&](auto uc) {
+                split_for<2 * decltype(uc)::value, (2 * decltype(uc)::value + 2 < ITEMS ? 2 * decltype(uc)::value + 2 : ITEMS)>([&](auto ic) {
+                    constexpr int q = decltype(slot(ic))::value;
+                    const f32x4 x = take(raw, ic);
+                    constexpr std::integral_constant<int, 0> p0{};
+                    constexpr std::integral_constant<int, 1> p1{};
+                    constexpr std::integral_constant<int, 2> p2{};
+                    if constexpr (T == 2) {
+                        const SplitPair a(x[0], x[1], s[q]), b(x[2], x[3], s[q]);
+                        const uint32_t m = __float_as_uint(split_most4(x));
+                        mx[q] = max(mx[q], m);
+                        mn[q] = min(mn[q], m - 1u);
+                        if (on[q]) {
+                            put(lds + at, p0, ic, make_uint2(a.h, b.h));
+                            put(lds + at, p1, ic, make_uint2(a.l, b.l));
+                        }
+                    } else {
+                        SplitQuad quad;
+                        split_for<0, 4>([&](auto p) { quad.template part<decltype(p)::value>(x[0], x[1], x[2], x[3]); });
+                        if (on[q]) {
+                            put(lds + at, p0, ic, make_uint2(quad.ha, quad.hb));
+                            put(lds + at, p1, ic, make_uint2(quad.ma, quad.mb));
+                            put(lds + at, p2, ic, make_uint2(quad.la, quad.lb));
+                        }
+                    }
+                });
+                __builtin_amdgcn_sched_barrier(6);                       // (vector and scalar instructions may pass)
+                after(uc);
+                __builtin_amdgcn_sched_barrier(6);
+            });
+            if constexpr (T == 2) {
+                bool bad = false;
+#pragma unroll
+                for (int q = 0; q < SLOTS; ++q) bad |= on[q] && (mx[q] > most[q] || mn[q] < least[q]);
+                if (bad) __hip_atomic_fetch_min(reinterpret_cast<uint32_t*>(lds + CTL), (uint32_t)c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            }
+        };
+        constexpr std::false_type later{};
+        auto fetch = [&](Raw& raw, int c, auto first, auto units) {     // the first so many units
+            const auto place = where(c, first);
+            split_for<0, decltype(units)::value>([&](auto u) { load(raw, place, u, first); });
+        };
+        constexpr std::integral_constant<int, UNITS> all{};
+        constexpr std::integral_constant<int, UNITS - LAG> early{};
+        static_assert(LAG <= UNITS, "units");
+        auto nothing = [](auto) {};
+        fetch(r[0], c0, std::true_type{}, all);
+        fetch(r[1], c0 + 1, later, all);
+        if constexpr (T == 2) {
+            split_barrier();                                             // the control words are clear
+            prep(r[0], c0, std::true_type{});
+            prep(r[1], c0 + 1, later);
+            uint32_t words[4] = {0u, 0u, 0u, 0u};                        // (smallest as the largest complement)
+            split_for<0, ITEMS>([&](auto ic) {
+                constexpr int q = decltype(slot(ic))::value;
+                const uint32_t x = __float_as_uint(split_most4(take(r[0], ic))), y = __float_as_uint(split_most4(take(r[1], ic)));
+                const uint32_t m = on[q] ? max(x, y) : 0u, l = on[q] ? max(~(x - 1u), ~(y - 1u)) : 0u;
+                words[0] = max(words[0], second[q] ? 0u : m);
+                words[1] = max(words[1], second[q] ? 0u : l);
+                words[2] = max(words[2], second[q] ? m : 0u);
+                words[3] = max(words[3], second[q] ? l : 0u);
+            });
+#pragma unroll
+            for (int i = 0; i < 4; ++i) words[i] = split_max16(words[i]);
+            const int i = threadIdx.x & 15;                              // lanes 0 .. 3 of every sixteen: a word each
+            const uint32_t word = i == 0 ? words[0] : i == 1 ? words[1] : i == 2 ? words[2] : words[3];
+            // (as an atomic of the language it becomes a loop over the lanes: four of them took 1000 cycles)
+            if (i < 4) asm volatile("ds_max_u32 %0, %1" ::"v"((uint32_t)(uintptr_t)(sp_lds_u32*)(lds + CTL + 16) + 4u * i), "v"(word) : "memory");
+            split_barrier();
+            SplitScale sc[2];
+            if (!scales(lds, sc)) {
+                split_barrier();
+                return c0;
+            }
+#pragma unroll
+            for (int q = 0; q < SLOTS; ++q) {
+                s[q] = second[q] ? sc[1].s : sc[0].s;
+                most[q] = second[q] ? sc[1].most : sc[0].most;
+                least[q] = second[q] ? sc[1].least_m1 : sc[0].least_m1;
             }
         }
-    }
-    // Adds the sums of the two halves of every chunk.  Afterwards sum[i][j][t] holds entry e = 8 g + t of block (i, j),
-    // g = wave / 4: this wavefront finishes half of the entries of its blocks, its partner in the other group the other
-    // half.  (k 0..15) + (k 16..31): one fixed order.
-    __device__ __forceinline__ void exchange(int wave, int lane, unsigned char* lds, float (&sum)[MT][NT][8]) {
-        if constexpr (APART) {
-#pragma unroll
-            for (int i = 0; i < MT; ++i)
-#pragma unroll
-                for (int j = 0; j < NT; ++j)
-#pragma unroll
-                    for (int e = 0; e < 16; ++e) acc[i][j][e] += rest[i][j][e];
+        static_assert(DEPTH == 3, "raw sets");
+        if constexpr (T == 2) {
+            // (the third set's words are requested behind the first's, not before: the first's are not held up)
+            const auto third = where(c0 + 2, later), fourth = where(c0 + 3, later);
+            park(r[0], c0, 0, [&](auto uc) { load(r[2], third, uc, later); });
+            park(r[1], c0 + 1, BUF, [&](auto uc) { load(r[0], fourth, uc, later); });
+            fetch(r[1], c0 + 4, later, early);
+        } else {
+            fetch(r[2], c0 + 2, later, all);
+            prep(r[0], c0, std::true_type{});
+            park(r[0], c0, 0, nothing);
+            fetch(r[0], c0 + 3, later, early);
         }
-        const int g = wave >> 2;
-        split_barrier();                                 // everybody is done with the buffers
-        float* x = reinterpret_cast<float*>(lds);
-#pragma unroll
-        for (int i = 0; i < MT; ++i)
-#pragma unroll
-            for (int j = 0; j < NT; ++j)
-#pragma unroll
-                for (int t = 0; t < 8; ++t)
-                    x[((wave * MT * NT + i * NT + j) * 8 + t) * 64 + lane] = g == 0 ? acc[i][j][8 + t] : acc[i][j][t];
         split_barrier();
-        const int partner = wave ^ 4;
-#pragma unroll
-        for (int i = 0; i < MT; ++i)
-#pragma unroll
-            for (int j = 0; j < NT; ++j)
-#pragma unroll
-                for (int t = 0; t < 8; ++t) {
-                    const float other = x[((partner * MT * NT + i * NT + j) * 8 + t) * 64 + lane];
-                    sum[i][j][t] = g == 0 ? acc[i][j][t] + other : other + acc[i][j][8 + t];
-                }
+        int at = (T == 2 ? 2 : 1) * BUF;
+        bool go = true;
+        int c = c0;
+        auto step = [&](Raw& before, Raw& raw) {
+            uint32_t stop = 0xffffffffu;
+            if constexpr (T == 2) stop = stop_word(lds);
+            prep(raw, c + LEAD, later);
+            const auto last = where(c + LEAD + DEPTH - 1, later), next = where(c + LEAD + DEPTH, later);
+            park(raw, c + LEAD, at, [&](auto uc) {
+                constexpr int u = decltype(uc)::value;
+                if constexpr (u < LAG) load(before, last, std::integral_constant<int, UNITS - LAG + u>{}, later);
+                else load(raw, next, std::integral_constant<int, u - LAG>{}, later);
+            });
+            at = at == (T == 2 ? 2 : 1) * BUF ? 0 : at + BUF;
+            split_barrier();
+            ++c;
+            go = c < n && !(T == 2 && (uint32_t)__builtin_amdgcn_readfirstlane((int)stop) <= (uint32_t)c);
+        };
+        // (left in the middle, so that every path into a step has the other raw sets' loads behind it)
+        for (;;) {
+            step(r[(LEAD - 1) % DEPTH], r[(LEAD) % DEPTH]);
+            if (!go) break;
+            step(r[(LEAD + 1 - 1) % DEPTH], r[(LEAD + 1) % DEPTH]);
+            if (!go) break;
+            step(r[(LEAD + 1) % DEPTH], r[(LEAD + 2) % DEPTH]);
+            if (!go) break;
+        }
+        return c;
     }
+    template <class Raw, int ITEMS, int SLOTS, int DEPTH, int LAG, class Slot, class Where, class Load, class Prep, class Take, class Put>
+    static __device__ __forceinline__ void split(int n, unsigned char* lds, const bool (&second)[SLOTS], const bool (&on)[SLOTS], Slot slot,
+                                          Where where, Load load, Prep prep, Take take, Put put) {
+        int done = 0;
+        if constexpr (!EXACT) done = split_in<2, Raw, ITEMS, SLOTS, DEPTH, LAG>(0, n, lds, second, on, slot, where, load, prep, take, put);
+        if (done < n) split_in<3, Raw, ITEMS, SLOTS, DEPTH, LAG>(done, n, lds, second, on, slot, where, load, prep, take, put);
+    }
+
     // An infinity (or a finite value beyond bf16's largest, 3.39e38: it rounds to one) leaves NaN in its second term, and six
     // term products may overflow where their sum does not.  All of that ends in a sum that is not finite, so such sums, and
     // no others, are replaced by form(i, j): block (i, j) of this wavefront by the fp32 instruction from the operands as they
-    // are (a wavefront and its partner both form the whole block).  1000 x 4096, 512 samples: scores 34 us, 71 with one class
-    // at minus infinity, 140 with half of them; update 31 us, 111 with one infinite feature (a lane summing each such entry by
-    // itself: 740, 3770 and 2470).
+    // are (never a lane summing such an entry by itself: with half of the classes at minus infinity that took a hundred times the time).
     template <class Form>
-    __device__ __forceinline__ void mend(int wave, float (&sum)[MT][NT][8], Form form) {
-        const int g = wave >> 2;
+    __device__ __forceinline__ void mend(Form form) {
+        float zero[4] = {0.f, 0.f, 0.f, 0.f};                            // stays so unless an entry is not finite
 #pragma unroll
-        for (int i = 0; i < MT; ++i)
+        for (int i = 0; i < MB; ++i)
 #pragma unroll
-            for (int j = 0; j < NT; ++j) {
-                bool finite = true;
+            for (int j = 0; j < NB; ++j)
 #pragma unroll
-                for (int t = 0; t < 8; ++t) finite &= __builtin_isfinite(sum[i][j][t]);
-                if (__all(finite)) continue;
-                const f32x16 x = form(i, j);
+                for (int e = 0; e < 4; ++e) zero[e] = __builtin_fmaf(acc[i][j][e], 0.f, zero[e]);
+        if (__all((zero[0] + zero[1]) + (zero[2] + zero[3]) == 0.f)) return;
 #pragma unroll
-                for (int t = 0; t < 8; ++t)
-                    if (!__builtin_isfinite(sum[i][j][t])) sum[i][j][t] = g == 0 ? x[t] : x[8 + t];
+        for (int i = 0; i < MB; ++i)
+#pragma unroll
+            for (int j = 0; j < NB; ++j) {
+                const f32x4 x = form(i, j);
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (!__builtin_isfinite(acc[i][j][e])) acc[i][j][e] = x[e];
             }
     }
-    // row of entry 8 g + t inside its block (the column is lane % 32)
-    static __device__ __forceinline__ int entry_row(int g, int t, int lane) {
-        const int e = 8 * g + t;
-        return 8 * (e / 4) + 4 * (lane >> 5) + (e % 4);
-    }
 };
+
+// Entry e of a lane's block is its row 4 (lane / 16) + e and column lane % 16.  Which row of a matrix LDS row r holds: with split_row64 (16) four
+// (two) neighbouring blocks of a lane are neighbouring rows (columns of the result: one access); with split_row32 a lane's
+// rows are uniform ones plus its own 16 ((lane / 16) % 2) + lane / 32, and BM needs to be a multiple of 32 only.
+__device__ __forceinline__ int split_row64(int r) { return (r & ~63) + 4 * (r & 15) + ((r >> 4) & 3); }
+__device__ __forceinline__ int split_row32(int r) { return (r & ~31) + 4 * (r & 7) + ((r >> 3) & 3); }
+__device__ __forceinline__ int split_row16(int r) { return (r & ~31) + 2 * (r & 15) + ((r >> 4) & 1); }
+
+// Descriptor of raw words from p on: `bytes` of them, none where they are not wanted (such loads return zero and move nothing)
+// (p and bytes are uniform; said so, or the compiler puts a loop over the lanes' descriptors around every load)
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t split_words(const void* p, uint32_t bytes) {
+    const uint64_t at = (uint64_t)p;
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)at), hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(at >> 32));
+    return __builtin_amdgcn_make_buffer_rsrc((void*)((uint64_t)hi << 32 | lo), (short)0, __builtin_amdgcn_readfirstlane((int)bytes), 0x00020000);
+}
+typedef float sp_f32x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ sp_f32x2 split_load2(__amdgpu_buffer_rsrc_t words, uint32_t offset) {
+    return __builtin_bit_cast(sp_f32x2, __builtin_amdgcn_raw_buffer_load_b64(words, (int)offset, 0, 0));
+}
+__device__ __forceinline__ f32x4 split_load4(__amdgpu_buffer_rsrc_t words, uint32_t offset) {
+    return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(words, (int)offset, 0, 0));
+}
 
 }  // namespace sfb

@@ -1,0 +1,65 @@
+"""Split products of two terms: operands whose magnitudes make a workgroup change to three terms at some chunk, or do not."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+def _spread(kind, x):
+    """x (rows, k) of one scale -> the same with other magnitudes along the contraction."""
+    k = x.shape[1]
+    if kind == "grows":                     # beyond what the first columns' scale holds, from a middle chunk on
+        x[:, (2 * k) // 3:] *= 1e4
+    elif kind == "grows at the end":
+        x[:, k - 3:] *= 1e6
+    elif kind == "zeros first":
+        x[:, :100] = 0
+    elif kind == "blank but the end":
+        x[:, :k - 2] = 0
+    elif kind == "magnitudes":
+        x *= torch.exp(8 * torch.randn(x.shape, generator=torch.Generator(device=x.device).manual_seed(k), device=x.device))
+    elif kind == "small rows":              # far below the largest value, close to it, and none at all
+        x[1::7] *= 1e-9
+        x[2::7] *= 1e-3
+        x[3::7] = 0
+    elif kind == "large":
+        x *= 1e16                           # (twice a sum of 4096 products stays a number)
+    elif kind == "small":
+        x *= 1e-18
+    return x
+
+
+@pytest.mark.parametrize("J,D,P,B", [
+    (1000, 4096, 4, 128),                   # 128 x 128 scores, 128 x 128 update
+    (600, 4109, 6, 171),                    # ragged D, rows and pairs; 96 x 128 update
+    (130, 1503, 4, 63),                     # 64 x 64
+    (70, 2001, 10, 321),                    # slices of the pairs
+    (2049, 517, 2, 150),
+])
+@pytest.mark.parametrize("kind", ["one scale", "grows", "grows at the end", "zeros first", "blank but the end", "magnitudes", "small rows", "large", "small"])
+@pytest.mark.parametrize("both", [False, True])
+def test_scores_and_updates_over_many_magnitudes(J, D, P, B, kind, both):
+    """Entry by entry: sums of K products rounded six times at most for every sixteen, and eight roundings' worth for the terms that are left
+    out, 2^-24 (6 K / 16 + 8) sum |a b|; slices of K add theirs within that."""
+    import paper_1511_08486_amd as sfb
+    dev, N, g = "cuda:0", P * B, torch.Generator(device="cuda:0").manual_seed(J + D)
+    randn = lambda *s: torch.randn(s, generator=g, device=dev)  # noqa: E731
+    A, A2, W = _spread(kind, randn(N, D)), torch.zeros((N, D), device=dev), randn(J, D)
+    if both:
+        W = _spread(kind, W)
+    y, U, V = torch.ones(N, dtype=torch.int32, device=dev), torch.zeros((N, J), device=dev), torch.full((N, D), float("nan"), device=dev)
+    ctx = sfb.Sfb("dml", J, D, P, B, device=dev)
+    ctx.compute_factors(W, sfb.SfbBatch(a=A, a2=A2), y, U, V)   # similar pairs: u = 2 z
+    ctx.sync()
+    assert torch.equal(V, A)
+    room = 2.0 ** -24 * (6 * D / 16 + 8) * (A.double().abs() @ W.double().abs().T) + 1e-44
+    assert ((0.5 * U.double() - A.double() @ W.double().T).abs() <= room).all()
+
+    Ut, Vt, W1 = _spread(kind, randn(J, N)), randn(D, N), torch.zeros((J, D), device=dev)
+    if both:
+        Vt = _spread(kind, Vt)
+    ctx.reconstruct_apply(W1, Ut.T.contiguous(), Vt.T.contiguous(), -1.0, scale=1.0)
+    ctx.sync()
+    ctx.close()
+    room = 2.0 ** -24 * (6 * N / 16 + 8) * (Ut.double().abs() @ Vt.double().abs().T) + 1e-44
+    assert ((W1.double() - Ut.double() @ Vt.double().T).abs() <= room).all()
