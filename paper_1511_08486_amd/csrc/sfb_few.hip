@@ -2,8 +2,8 @@
 //
 // A small W leaves the separate kernels nothing to do but move the batch: scores read A and write V, the update reads V
 // again (ragged rows through a padded copy of it: twice more), and each is a launch of its own.  Here a workgroup keeps
-// its samples' feature rows in LDS from the first byte to the last use: load (and store V on the way), scores, factor u,
-// and its share of U^T V.
+// its samples' feature rows in LDS from the first byte to the last use: load (and store V on the way, or, of a large batch,
+// during the products), scores, factor u, and its share of U^T V.
 //   scores   v_mfma_f32_16x16x4_f32: 16 samples x 16 classes; lane l reads four consecutive columns of row l % 16 with
 //            one 16-byte LDS read (rows Dp + 4 floats apart, Dp the columns in whole sixteens: conflict-free) and feeds
 //            four instructions (the contraction index is a dummy); the wavefronts cut D into slices, whose sums meet
@@ -48,8 +48,40 @@ __device__ __forceinline__ void few_store4(float* __restrict__ row, int col, int
 }
 __device__ __forceinline__ void few_store4(bf16_t* __restrict__ row, int col, int cols, f32x4 v) { store4(row, col, cols, v); }
 
+// The four entries without a branch around the load, so that waiting for one load is not waiting for all of them:
+// few_peek4 reads the row's last four where the end is near (rows hold four columns or more), few_settle4 moves them.
+__device__ __forceinline__ f32x4 few_peek4(const float* __restrict__ row, int col, int cols) {
+    return *reinterpret_cast<const few_f32x4u*>(row + min(col, cols - 4));
+}
+__device__ __forceinline__ f32x4 few_settle4(f32x4 x, int col, int cols) {
+    const int past = col - (cols - 4);                                     // 4 and more: nothing of the row is left
+    if (past > 0)
+        x = f32x4{past == 1 ? x[1] : past == 2 ? x[2] : past == 3 ? x[3] : 0.f, past == 1 ? x[2] : past == 2 ? x[3] : 0.f,
+                  past == 1 ? x[3] : 0.f, 0.f};
+    return x;
+}
+// to memory past the caches
+__device__ __forceinline__ void few_store4_past(float* __restrict__ row, int col, int cols, f32x4 v) {
+    if (col + 4 <= cols)
+        __builtin_nontemporal_store(v, reinterpret_cast<few_f32x4u*>(row + col));
+    else
+        few_store4(row, col, cols, v);
+}
+
+// a thread's items of four columns: row r, columns 4 c .. 4 c + 3
+struct FewItem {
+    int r, c;
+    __device__ __forceinline__ FewItem(int i, int items) : r(i / items), c(i - i / items * items) {}
+    __device__ __forceinline__ void step(const FewItem& by, int items) {
+        r += by.r, c += by.c;
+        if (c >= items) c -= items, ++r;
+    }
+};
+
 // NJ: class blocks of 16.  UPDATE: 0 factors only, 1 sums into plane blockIdx.x of `planes`, 2 straight into W (one workgroup).
-template <typename TIn, bool DIFF, int NJ, int UPDATE>
+// LATE: V leaves from LDS, a piece at a time between the matrix instructions, instead of between the loads (see few_late).
+// Between the loads every wait for a load was one for the stores before it as well.
+template <typename TIn, bool DIFF, int NJ, int UPDATE, bool LATE>
 __global__ __launch_bounds__(kFewThreads) void few_step_kernel(FewArgs a, int rows_per_wg, int Dp, int k_slices, int groups) {
     constexpr int JP = 16 * NJ;
     extern __shared__ __attribute__((aligned(16))) float few_lds[];      // feature rows, then slices of scores; u overlays those
@@ -62,8 +94,43 @@ __global__ __launch_bounds__(kFewThreads) void few_step_kernel(FewArgs a, int ro
     const int row_blocks = (rows + 15) / 16, zrows = (rows_per_wg + 15) / 16 * 16;
 
     // features -> LDS (zeros up to Dp columns), and on to V
-    {
-        const int items = Dp / 4, total = rows * items;
+    const int items = Dp / 4;
+    const FewItem first(tid, items), stride(kFewThreads, items);
+    FewItem out = first;                                                   // what this thread stores of V next
+    auto store_late = [&]() {
+        if constexpr (LATE) {
+            if (out.r < rows) {
+                few_store4_past((float*)a.v + (row0 + out.r) * (int64_t)a.ldv, 4 * out.c, a.D,
+                                *reinterpret_cast<const f32x4*>(&feat[out.r * pitch + 4 * out.c]));
+                out.step(stride, items);
+            }
+        }
+    };
+    if constexpr (LATE) {
+        constexpr int BATCH = DIFF ? 5 : 10;
+        const float* A = (const float*)a.a + (int64_t)row0 * a.lda;
+        const float* A2 = DIFF ? (const float*)a.a2 + (int64_t)row0 * a.lda : nullptr;
+        for (FewItem at = first, to = first; to.r < rows;) {
+            f32x4 x[BATCH], x2[DIFF ? BATCH : 1];
+#pragma unroll
+            for (int q = 0; q < BATCH; ++q) {
+                if (at.r < rows) {
+                    x[q] = few_peek4(A + (int64_t)at.r * a.lda, 4 * at.c, a.D);
+                    if (DIFF) x2[q] = few_peek4(A2 + (int64_t)at.r * a.lda, 4 * at.c, a.D);
+                }
+                at.step(stride, items);
+            }
+#pragma unroll
+            for (int q = 0; q < BATCH; ++q) {
+                if (to.r < rows) {
+                    if (DIFF) x[q] -= x2[q];
+                    *reinterpret_cast<f32x4*>(&feat[to.r * pitch + 4 * to.c]) = few_settle4(x[q], 4 * to.c, a.D);
+                }
+                to.step(stride, items);
+            }
+        }
+    } else {
+        const int total = rows * items;
         const TIn* A = (const TIn*)a.a + (int64_t)row0 * a.lda;
         const TIn* A2 = DIFF ? (const TIn*)a.a2 + (int64_t)row0 * a.lda : nullptr;
         TIn* V = (TIn*)a.v + (int64_t)row0 * a.ldv;
@@ -88,6 +155,9 @@ __global__ __launch_bounds__(kFewThreads) void few_step_kernel(FewArgs a, int ro
         }
     }
     __syncthreads();
+
+    // (asked for before the late stores: a wait for a load waits for the stores before it as well)
+    const int label0 = LATE ? a.y[row0 + min(tid / JP, rows - 1)] : 0;
 
     // scores: wavefront = (row block, slice of D)
     for (int job = wave; job < row_blocks * k_slices; job += kFewWaves) {
@@ -120,6 +190,7 @@ __global__ __launch_bounds__(kFewThreads) void few_step_kernel(FewArgs a, int ro
 #pragma unroll
                 for (int j = 0; j < NJ; ++j)
                     if (s + p + AHEAD < s1) w[p][j] = few_load4(wr[j], 16 * (s + p + AHEAD) + 4 * quad, a.D);
+                if ((p & 1) != 0) store_late();
             }
         }
         // lane: class 16 j + l16 of samples 16 rb + 4 quad + e
@@ -127,6 +198,9 @@ __global__ __launch_bounds__(kFewThreads) void few_step_kernel(FewArgs a, int ro
         for (int j = 0; j < NJ; ++j)
 #pragma unroll
             for (int e = 0; e < 4; ++e) zp[(ks * zrows + rb * 16 + 4 * quad + e) * JP + 16 * j + l16] = acc[j][e];
+    }
+    if (UPDATE == 0 || a.use_mask) {                                       // (the rows of dead workers are cleared below)
+        while (LATE && out.r < rows) store_late();
     }
     __syncthreads();
 
@@ -140,7 +214,7 @@ __global__ __launch_bounds__(kFewThreads) void few_step_kernel(FewArgs a, int ro
         const int rr = live ? r : rows - 1;
         float z = 0.f;
         for (int ks = 0; ks < k_slices; ++ks) z += zp[(ks * zrows + rr) * JP + jl];
-        const int label = a.y[row0 + rr];
+        const int label = LATE && r0 == 0 ? label0 : a.y[row0 + rr];
         auto sum = [](float v) {
 #pragma unroll
             for (int o = JP / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
@@ -197,6 +271,7 @@ __global__ __launch_bounds__(kFewThreads) void few_step_kernel(FewArgs a, int ro
         }
         const int col = min(dc, Dp - 4);
         for (int n = 0; n < row_blocks * 4; ++n) {                        // samples 4 n + quad
+            store_late();
             f32x4 v = *reinterpret_cast<const f32x4*>(feat + min(4 * n + quad, rows - 1) * pitch + col);
             if (4 * n + 3 >= rows && 4 * n + quad >= rows) v = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -220,6 +295,7 @@ __global__ __launch_bounds__(kFewThreads) void few_step_kernel(FewArgs a, int ro
                 }
             }
     }
+    while (LATE && out.r < rows) store_late();
 }
 
 // W += alpha * (the planes' sums in plane order): four columns of a row to sixteen threads, each of which adds a
@@ -297,30 +373,45 @@ size_t few_workspace(int64_t N, int64_t J, int64_t D) {
     return n > 1 ? (size_t)n * J * few_dp(D) * sizeof(float) : 0;
 }
 
-template <typename TIn, bool DIFF, int NJ, int UPDATE>
+// Late stores are for batches that, with their V, are more than the L2s hold: the loads come first at the rate of memory,
+// and the stores, which take as long again, run under the products; past the caches, so that the kernel's end has nothing
+// to write back.  fp32, ten classes x 784 columns: 12000 samples 24.0 -> 21.3 us, 10600 23.8 -> 20.8, 8000 17.9 -> 17.1, 6000
+// 16.6 -> 16.3; pairs 28.2 -> 24.7, 27.7 -> 23.5, 20.9 -> 18.1, 18.3 -> 15.9.  Smaller batches have a piece or two to a thread
+// and lose (256 columns x 512 samples 6.6 -> 7.7), bf16 rows too (12000 samples 23.4 -> 24.7).  With two class blocks and
+// hundreds of rows to a workgroup the products bound the kernel (twenty classes, 246 rows of 128 columns: 63.5 -> 66.6; 129 rows
+// of 256: 32.5 -> 30.7).
+static bool few_late(const FewArgs& a, int rows) {
+    return !a.bf16 && (int64_t)a.n_rows * a.D * 4 >= (int64_t)22 << 20 && (a.J <= 16 || rows <= 192);
+}
+
+template <typename TIn, bool DIFF, int NJ, int UPDATE, bool LATE>
 static hipError_t launch_few_t(const FewArgs& a, int rows, int k_slices, size_t lds, hipStream_t s) {
     static std::atomic<bool> raised{false};
     if (lds > 64 * 1024 && !raised) {
-        hipError_t e = hipFuncSetAttribute((const void*)few_step_kernel<TIn, DIFF, NJ, UPDATE>,
+        hipError_t e = hipFuncSetAttribute((const void*)few_step_kernel<TIn, DIFF, NJ, UPDATE, LATE>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
         if (e != hipSuccess) return e;
         raised = true;
     }
-    SFB_LAUNCH((few_step_kernel<TIn, DIFF, NJ, UPDATE>), dim3((a.n_rows + rows - 1) / rows), dim3(kFewThreads), lds, s, a, rows,
+    SFB_LAUNCH((few_step_kernel<TIn, DIFF, NJ, UPDATE, LATE>), dim3((a.n_rows + rows - 1) / rows), dim3(kFewThreads), lds, s, a, rows,
                few_dp(a.D), k_slices, (a.D + 63) / 64);
     return hipGetLastError();
 }
 
-template <typename TIn, bool DIFF>
+template <typename TIn, bool DIFF, int NJ>
 static hipError_t launch_few_u(const FewArgs& a, int rows, int ks, size_t lds, int update, hipStream_t s) {
-    if (a.J <= 16) {
-        if (update == 0) return launch_few_t<TIn, DIFF, 1, 0>(a, rows, ks, lds, s);
-        if (update == 1) return launch_few_t<TIn, DIFF, 1, 1>(a, rows, ks, lds, s);
-        return launch_few_t<TIn, DIFF, 1, 2>(a, rows, ks, lds, s);
+    if constexpr (sizeof(TIn) == 4) {
+        if (few_late(a, rows)) return update == 0 ? launch_few_t<TIn, DIFF, NJ, 0, true>(a, rows, ks, lds, s)
+                                            : launch_few_t<TIn, DIFF, NJ, 1, true>(a, rows, ks, lds, s);
     }
-    if (update == 0) return launch_few_t<TIn, DIFF, 2, 0>(a, rows, ks, lds, s);
-    if (update == 1) return launch_few_t<TIn, DIFF, 2, 1>(a, rows, ks, lds, s);
-    return launch_few_t<TIn, DIFF, 2, 2>(a, rows, ks, lds, s);
+    if (update == 0) return launch_few_t<TIn, DIFF, NJ, 0, false>(a, rows, ks, lds, s);
+    if (update == 1) return launch_few_t<TIn, DIFF, NJ, 1, false>(a, rows, ks, lds, s);
+    return launch_few_t<TIn, DIFF, NJ, 2, false>(a, rows, ks, lds, s);
+}
+
+template <typename TIn, bool DIFF>
+static hipError_t launch_few_j(const FewArgs& a, int rows, int ks, size_t lds, int update, hipStream_t s) {
+    return a.J <= 16 ? launch_few_u<TIn, DIFF, 1>(a, rows, ks, lds, update, s) : launch_few_u<TIn, DIFF, 2>(a, rows, ks, lds, update, s);
 }
 
 hipError_t launch_few(const FewArgs& a, bool update, hipStream_t s) {
@@ -329,9 +420,9 @@ hipError_t launch_few(const FewArgs& a, bool update, hipStream_t s) {
     const int rows = few_rows(a.n_rows, a.J, a.D, &ks, &lds);
     if (rows <= 0) return hipErrorInvalidValue;
     const int n = (a.n_rows + rows - 1) / rows, mode = !update ? 0 : n == 1 ? 2 : 1;
-    hipError_t e = a.bf16 ? launch_few_u<bf16_t, false>(a, rows, ks, lds, mode, s)
-                   : a.diff ? launch_few_u<float, true>(a, rows, ks, lds, mode, s)
-                            : launch_few_u<float, false>(a, rows, ks, lds, mode, s);
+    hipError_t e = a.bf16 ? launch_few_j<bf16_t, false>(a, rows, ks, lds, mode, s)
+                   : a.diff ? launch_few_j<float, true>(a, rows, ks, lds, mode, s)
+                            : launch_few_j<float, false>(a, rows, ks, lds, mode, s);
     if (e != hipSuccess || mode != 1) return e;
     hipLaunchKernelGGL(few_apply_kernel, dim3((a.J * (few_dp(a.D) / 4) + 15) / 16), dim3(kFewApplyThreads), 0, s, a.w, a.ldw, a.planes,
                        n, a.J, a.D, few_dp(a.D), a.alpha, a.prox_kind, a.prox_a);
