@@ -351,7 +351,8 @@ SFB_API sfb_status sfb_last_kernel(const sfb_ctx *ctx, int32_t which, char *name
  * into three bf16 terms (exactly from 2^-109 up, where the third term is a bf16 number; 1e-6 of a sum at operands of
  * 2^-120) and every product taken as its six leading term products, the smaller five in sums of their own (error
  * at the level of one fp32 rounding; D >= 4 and leading dimensions within 32-bit offsets, else ignored),
- * a new fp32 context forms them so unless the product is small, all six in one sum; bit 3 = the same for the fp32 reconstruction, which a new
+ * a new fp32 context takes two scaled fp16 terms and three products instead, or, in short sums and from the first values on whose
+ * magnitudes the scale does not hold, these, and the fp32 instruction where the product is small; bit 3 = the same for the fp32 reconstruction, which a new
  * context takes where a fitted cost comparison expects it to be the fastest kernel; bit 4 = sfb_step_pipelined always runs its two separate passes;
  * bit 6 = L2SVM steps update W from lists of the stored entries wherever those fit (neither 3 nor 6: never); < 0 = keep.  A value <= 0 (variant < 0) keeps the current choice.
  * Any choice ends what a context does by itself with the kernels it is about, for good (a new context has it again): the

@@ -66,9 +66,9 @@ struct sfb_ctx {
     Bf16TilePlan tile_scores[2][2];   // bf16 contexts: scores in tiles, all rows or one worker's, W rounded or exact
     Bf16TilePlan tile_update[2];   // bf16 contexts: update in tiles, all pairs or one worker's
     bool tile_bf16_scores, tile_bf16_update;   // take them (a score tile or an update of the caller's choice is about the 256-row kernels)
-    FwdPlan fwd_split, fwd_split_worker;   // the same on the bf16 matrix cores, fp32 operands split exactly into bf16 terms
+    FwdPlan fwd_split, fwd_split_worker;   // the same on the 16-bit matrix cores, fp32 operands split into terms
     bool split_scores;             // use them where the shape allows
-    int split_recon;               // reconstruction with split-bf16 products: 1 where the shape allows, 0 never, -1 where it is the cheaper one
+    int split_recon;               // reconstruction with split products: 1 where the shape allows, 0 never, -1 where it is the cheaper one
     SplitReconPlan split_plans[2][2];      // its tile and slices: all pairs or one worker's, without or with a workspace
     ReconPlan recon;
     ReconPlan recon_padded;        // the plan of the padded shape (ragged fp32 contexts: see padded_factors)

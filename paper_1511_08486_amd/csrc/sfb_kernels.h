@@ -67,7 +67,7 @@ struct FwdArgs {
     bool bf16, diff;
 };
 hipError_t launch_forward(const FwdArgs& a, const FwdPlan& p, hipStream_t s);
-// fp32 scores on the bf16 matrix cores, every operand split exactly into three bf16 terms (sfb_forward_split.hip)
+// fp32 scores on the 16-bit matrix cores, every operand split into two fp16 or three bf16 terms (sfb_forward_split.hip)
 bool forward_split_ok(const FwdArgs& a);
 FwdPlan plan_forward_split(int64_t n_rows, int64_t J, int64_t D, size_t most, bool exact);
 hipError_t launch_forward_split(const FwdArgs& a, const FwdPlan& p, hipStream_t s);
@@ -215,7 +215,7 @@ hipError_t launch_reconstruct_ksplit(const ReconArgs& a, hipStream_t s);
 // 128 x 128 tiles with eight wavefronts in two groups that take the stages in turn (sfb_reconstruct_pair.hip)
 bool reconstruct_pair_ok(const ReconArgs& a);
 hipError_t launch_reconstruct_pair(const ReconArgs& a, hipStream_t s);
-// fp32 reconstruction on the bf16 matrix cores, every operand split exactly into three bf16 terms
+// fp32 reconstruction on the 16-bit matrix cores, every operand split into two fp16 or three bf16 terms
 // (sfb_reconstruct_split.hip); takes ragged, misaligned and masked factors as they are
 bool reconstruct_split_ok(const ReconArgs& a);
 // few factor pairs, bound by W's trip through memory (sfb_reconstruct_thin.hip); any shape and alignment
