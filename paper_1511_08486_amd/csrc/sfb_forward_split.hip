@@ -145,26 +145,25 @@ __global__ __launch_bounds__((ScoreTile<BM, BN, EXACT>::THREADS), BM + BN == 256
         }
         return x;
     });
-    // The blocks of a lane are that many neighbouring classes.  A scalar address a row and one lane offset (host: 13
-    // rows of Z below 2^32 bytes); rows and columns beyond the matrix one by one.
+    // The blocks of a lane are that many neighbouring classes: one access a row.  (Rows of Z are as long as there are classes: twelve of
+    // them pass 2^32 bytes from 89 million on, so a lane's rows are 64-bit offsets.)  Rows and columns beyond the matrix one by one.
     constexpr int WIDE = Tile::NB;
     typedef float f32_wide __attribute__((ext_vector_type(WIDE), aligned(4)));
-    const int first_col = wn * 16 * WIDE, lane_col = WIDE * l16;
-    float* const zout = Z + (int64_t)ks * zstride + (int64_t)m0 * ldz + (n0 + first_col);
-    const uint32_t z_lane = (uint32_t)(4 * quarter) * (uint32_t)ldz * 4u + (uint32_t)lane_col * 4u;
+    const int lane_row = m0 + wm * Tile::MB * 16 + 4 * quarter, col = n0 + wn * 16 * WIDE + WIDE * l16;
+    float* const zout = Z + (int64_t)ks * zstride + (int64_t)lane_row * ldz + col;
     auto store = [&](auto all) {
 #pragma unroll
         for (int i = 0; i < Tile::MB; ++i)
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const int row = (wm * Tile::MB + i) * 16 + e, col = n0 + first_col + lane_col;
-                float* const at = reinterpret_cast<float*>(reinterpret_cast<char*>(zout + (int64_t)row * ldz) + z_lane);
+                const int row = i * 16 + e;
+                float* const at = zout + (int64_t)row * ldz;
                 f32_wide x;
 #pragma unroll
                 for (int j = 0; j < WIDE; ++j) x[j] = t.acc[i][j][e];
                 if (decltype(all)::value) {
                     *reinterpret_cast<f32_wide*>(at) = x;
-                } else if (m0 + row + 4 * quarter < M) {
+                } else if (lane_row + row < M) {
 #pragma unroll
                     for (int j = 0; j < WIDE; ++j)
                         if (col + j < N) at[j] = x[j];
@@ -177,7 +176,7 @@ __global__ __launch_bounds__((ScoreTile<BM, BN, EXACT>::THREADS), BM + BN == 256
 
 bool forward_split_ok(const FwdArgs& a) {
     // lane offsets (up to 128 rows of 4-byte words) stay below 2^32
-    return !a.bf16 && a.D >= 4 && a.lda < (1 << 22) && a.ldw < (1 << 22) && a.ldz < (1 << 27);
+    return !a.bf16 && a.D >= 4 && a.lda < (1 << 22) && a.ldw < (1 << 22);
 }
 
 template <int BM, int BN, bool DIFF, bool EXACT>

@@ -429,3 +429,21 @@ def test_updates_whose_last_tiles_are_a_launch_of_their_own(J, D, P, B, grid, ma
     assert ((got - want)[ok].abs() <= room[ok]).all()
     assert torch.isnan(W[:, D:]).all()
     ctx.close()
+
+
+def test_rows_of_scores_whose_offsets_pass_32_bits():
+    """Twelve rows of 90 million classes are more than 2^32 bytes: every row of a block of sixteen, entry by entry, is its own product
+    (four columns: four products of 2^-24 each and three sums)."""
+    import paper_1511_08486_amd as sfb
+    dev, J, D, N = "cuda:0", 89_500_003, 4, 16
+    g = torch.Generator(device=dev).manual_seed(1)
+    W, A = torch.randn((J, D), generator=g, device=dev), torch.randn((N, D), generator=g, device=dev)
+    U, V = torch.full((N, J), float("nan"), device=dev), torch.empty((N, D), device=dev)
+    ctx = sfb.Sfb("dml", J, D, 1, N, device=dev)
+    ctx.compute_factors(W, sfb.SfbBatch(a=A, a2=torch.zeros_like(A)), torch.ones(N, dtype=torch.int32, device=dev), U, V)
+    ctx.sync()                                                   # similar pairs: u = 2 z
+    assert ctx.last_kernel(0)[0] == "scores_split_kernel"
+    ctx.close()
+    for j in range(0, J, 1 << 22):
+        w, u = W[j:j + (1 << 22)].double(), U[:, j:j + (1 << 22)].double()
+        assert ((0.5 * u - A.double() @ w.T).abs() <= 8 * 2.0 ** -24 * (A.double().abs() @ w.abs().T)).all()
