@@ -7,12 +7,14 @@
 //     fp32's 24, and both differences are exact in fp32 (below 2^-109 l runs out of bf16's exponents: sums of operands of 2^-118
 //     are off by 3e-7, of 2^-120 by 1e-6, of 2^-125 by 3e-5, where the fp32 instruction keeps 1e-7).  Six products, those whose
 //     weight is at least 2^-16 of the leading one; what is left out is below 2^-24 of |a b| and unbiased.
-//   Two fp16 terms of the scaled value, s x = h + l (h = fp16(s x), l = fp16(s x - h)): 22 significand bits and a sign, three quarters of all
-//     fp32 values exactly, the others 2^-24 off.  Three products; left out: a_l b_l, below 2^-22 and unbiased.  Half the matrix instructions and
-//     two thirds of the LDS traffic.  fp16 has few exponents, so a workgroup takes one power of two s per operand, from the largest value of
-//     its first 64 k (scaled to 2^9 .. 2^10), and looks at every group of four values that it splits: none beyond 2^15 scaled, and none whose
-//     largest is below 2^-10 but not zero.  Above 2^-2 scaled (2^-12 of the largest) a value keeps its 22 bits, below it is at most 2^-25 scaled
-//     off (2^-35 of the largest).  From the first chunk with a group outside on, the rest of the sum is taken in three terms (1000 x 4096 with 512
+//   Two fp16 terms of the scaled value, s x = h + l / 2048 (h = fp16(s x), l = fp16(2048 (s x - h))): 22 significand bits and a sign, three
+//     quarters of all fp32 values exactly, the others 2^-24 off.  Three products; left out: a_l b_l, below 2^-22 and unbiased.  Half the matrix
+//     instructions and two thirds of the LDS traffic.  fp16 has few exponents, so a workgroup takes one power of two s per operand, from the
+//     largest value of its first 64 k (scaled to 2^9 .. 2^10).  l is kept 2048 times as large, in sums of its own, and so has the exponents of h:
+//     every value above 2^-12 scaled (2^-21 of that largest one) keeps its 22 bits, below it is at most 2^-36 scaled off.  (With l as it is, values lost
+//     bits from 2^-2 scaled on: samples or classes 2^-15 of their neighbours were 1e-6 of their own norm off, now 2e-7 at any factor.)  Every
+//     group of four values is looked at: none beyond 2^15 scaled, and none whose largest is below 2^-12 but not zero, so that a value is at most 2^-24
+//     of its group's largest off.  From the first chunk with a group outside on, the rest of the sum is taken in three terms (1000 x 4096 with 512
 //     samples: 25 us, 31 with operands over many magnitudes, which is what three terms take throughout).
 // Sums of 256 products and more are closer to fp64 with two terms than with the three terms in one running sum that they replace; of the norm,
 // operands of mixed signs (then -> two terms here): scores 1000 x 4096, 512 samples 2.5e-7 -> 1.8e-7, update 2.4e-7 -> 1.7e-7;
@@ -42,7 +44,8 @@ typedef float sp_f32x4u __attribute__((ext_vector_type(4), aligned(4)));   // a 
 constexpr int kSpChunk = 32;       // k per chunk
 constexpr int kSpTopExp = 9;       // two terms: the first chunks' largest value is scaled to 2^9 .. 2^10
 constexpr int kSpBlankExp = 4;     // the scale's exponent where they are all zero
-constexpr int kSpLeastExp = -10;   // the largest of a group of four stays above 2^-10 scaled (or is zero)
+constexpr int kSpLeastExp = -12;   // the largest of a group of four stays above 2^-12 scaled (or is zero)
+constexpr int kSpLowExp = 11;      // the second term is kept 2^11 times as large
 
 // every wavefront of the workgroup; this wavefront's LDS writes are visible and its LDS reads done
 __device__ __forceinline__ void split_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
@@ -100,15 +103,16 @@ struct SplitQuad {
     }
 };
 
-// Two fp16 terms of two scaled values each, packed: h = fp16(s x), l = fp16(s x - h); s is a power of two, s x - h is exact.  Six
-// vector instructions of four cycles (v_fma_mixlo_f16, which gives either term in one, takes twice as long: four of those were 1.4 times it).
+// Two fp16 terms of two scaled values each, packed: h = fp16(s x), l = fp16(2^11 (s x - h)); s is a power of two, the difference is exact.
+// s_low = 2^11 s.  Eight vector instructions of four cycles (v_fma_mixlo_f16, which gives either term in one, takes twice as long).
 struct SplitPair {
     uint32_t h, l;
-    __device__ __forceinline__ SplitPair(float x0, float x1, float s) {
+    __device__ __forceinline__ SplitPair(float x0, float x1, float s, float s_low) {
+        const float minus = -(float)(1 << kSpLowExp);
         float r0, r1;
         asm("v_cvt_pk_f16_f32 %0, %1, %2" : "=v"(h) : "v"(x0 * s), "v"(x1 * s));
-        asm("v_fma_mix_f32 %0, %1, %2, -%3 op_sel_hi:[0,0,1]" : "=v"(r0) : "v"(x0), "s"(s), "v"(h));
-        asm("v_fma_mix_f32 %0, %1, %2, -%3 op_sel:[0,0,1] op_sel_hi:[0,0,1]" : "=v"(r1) : "v"(x1), "s"(s), "v"(h));
+        asm("v_fma_mix_f32 %0, %1, %2, %3 op_sel_hi:[1,0,0]" : "=v"(r0) : "v"(h), "s"(minus), "v"(x0 * s_low));
+        asm("v_fma_mix_f32 %0, %1, %2, %3 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(r1) : "v"(h), "s"(minus), "v"(x1 * s_low));
         asm("v_cvt_pk_f16_f32 %0, %1, %2" : "=v"(l) : "v"(r0), "v"(r1));
     }
 };
@@ -122,14 +126,15 @@ __device__ __forceinline__ float split_most4(f32x4 x) {
 
 // Scale of one operand and the bounds that its values keep (magnitudes as their bit patterns)
 struct SplitScale {
-    float s;
-    int e;                         // s = 2^e
+    float s, s_low;
+    int e;                         // s = 2^e, s_low = 2^(e + 11)
     uint32_t most, least_m1;       // largest allowed magnitude; smallest one of a group that is not all zero, minus one
     // m: largest magnitude of the first chunks.  false: no such scale, the three-term products take the tile
     __device__ __forceinline__ bool set(uint32_t m) {
         const int x = (int)(m >> 23);
         e = m == 0 ? kSpBlankExp : kSpTopExp + 127 - x;
         s = __uint_as_float((uint32_t)(127 + e) << 23);
+        s_low = __uint_as_float((uint32_t)(127 + e + kSpLowExp) << 23);
         most = (uint32_t)min(127 + 15 - e, 254) << 23;
         least_m1 = ((uint32_t)(127 + kSpLeastExp - e) << 23) - 1u;
         return m == 0 || (x >= 24 && x < 255);
@@ -174,6 +179,7 @@ struct SplitTile {
 
     // ---- the multiplying wavefronts ----
     static constexpr bool REST = MB * NB <= 8;                          // the smaller products have sums of their own (registers)
+    static_assert(REST || EXACT, "two terms: the smaller products are on another scale");
     // Two terms: leading products of even and odd chunks apart where there are registers for it (all-positive operands, 600 x 4096, 1024 pairs:
     // 1.8e-7 of the norm in one sum, 0.9e-7 in two)
     static constexpr int SUMS = ROWS > 128 && ROWS < 256 && !EXACT ? 2 : 1;
@@ -271,7 +277,7 @@ struct SplitTile {
     }
     __device__ __forceinline__ void multiply(int n, unsigned char* lds) {
         int done = 0;
-        auto merge = [&](int e) {
+        auto merge = [&](int e, float rest_scale) {
 #pragma unroll
             for (int i = 0; i < MB; ++i)
 #pragma unroll
@@ -283,7 +289,7 @@ struct SplitTile {
                             odd[i][j][q] = 0.f;
                         }
                         if constexpr (REST) {
-                            acc[i][j][q] += rest[i][j][q];
+                            acc[i][j][q] = __builtin_fmaf(rest[i][j][q], rest_scale, acc[i][j][q]);
                             rest[i][j][q] = 0.f;
                         }
                         acc[i][j][q] = __builtin_amdgcn_ldexpf(acc[i][j][q], e);
@@ -298,13 +304,13 @@ struct SplitTile {
             split_barrier();
             if (fits) {
                 done = multiply2(n, lds);
-                merge(-(sc[0].e + sc[1].e));
+                merge(-(sc[0].e + sc[1].e), 1.0f / (1 << kSpLowExp));
             }
             if (done >= n) return;
         }
         split_barrier();
         multiply3(done, n, lds);
-        merge(0);
+        merge(0, 1.f);
     }
 
     // ---- the splitting wavefronts ----
@@ -321,7 +327,7 @@ struct SplitTile {
         constexpr int LEAD = T == 2 ? 2 : 1, BUF = T * PLANE, UNITS = (ITEMS + 1) / 2;
         static_assert(DEPTH >= 2, "raw sets");
         Raw r[DEPTH];
-        float s[SLOTS];
+        float s[SLOTS], s_low[SLOTS];
         uint32_t most[SLOTS], least[SLOTS];
         auto park = [&](const Raw& raw, int c, int at, auto after) {
             uint32_t mx[SLOTS], mn[SLOTS];
@@ -335,7 +341,7 @@ struct SplitTile {
                     constexpr std::integral_constant<int, 1> p1{};
                     constexpr std::integral_constant<int, 2> p2{};
                     if constexpr (T == 2) {
-                        const SplitPair a(x[0], x[1], s[q]), b(x[2], x[3], s[q]);
+                        const SplitPair a(x[0], x[1], s[q], s_low[q]), b(x[2], x[3], s[q], s_low[q]);
                         const uint32_t m = __float_as_uint(split_most4(x));
                         mx[q] = max(mx[q], m);
                         mn[q] = min(mn[q], m - 1u);
@@ -404,6 +410,7 @@ struct SplitTile {
 #pragma unroll
             for (int q = 0; q < SLOTS; ++q) {
                 s[q] = second[q] ? sc[1].s : sc[0].s;
+                s_low[q] = second[q] ? sc[1].s_low : sc[0].s_low;
                 most[q] = second[q] ? sc[1].most : sc[0].most;
                 least[q] = second[q] ? sc[1].least_m1 : sc[0].least_m1;
             }

@@ -22,11 +22,23 @@ def _spread(kind, x):
         x[1::7] *= 1e-9
         x[2::7] *= 1e-3
         x[3::7] = 0
+    elif kind == "rows in between":         # down to 2^-19 of the largest value, entries of even magnitude
+        x.copy_(x.sign() * (1 + 0.5 * x.abs().clamp(max=1)))
+        x *= 2.0 ** -(torch.arange(x.shape[0], device=x.device) % 20).float()[:, None]
     elif kind == "large":
         x *= 1e16                           # (twice a sum of 4096 products stays a number)
     elif kind == "small":
         x *= 1e-18
     return x
+
+
+def _assert_rows_and_columns(got, a, b):
+    """got = a b^T, every row and column within 2^-24 (4 + sqrt(k) / 4) of the norm of its products: 4 for the terms of both operands and what
+    is left out of their products, and the running sum of an instruction that adds four products, k / 4 roundings of random sign (1.2e-6
+    at 4096; the kernels are at 2e-7; without second terms products alone are 3e-4 off)."""
+    e, products = got - a @ b.T, (a * a) @ (b * b).T
+    for dim in (0, 1):
+        assert (e.norm(dim=dim) <= 2.0 ** -24 * (4 + a.shape[1] ** 0.5 / 4) * products.sum(dim=dim).sqrt() + 1e-42).all()
 
 
 @pytest.mark.parametrize("J,D,P,B", [
@@ -36,11 +48,11 @@ def _spread(kind, x):
     (70, 2001, 10, 321),                    # slices of the pairs
     (2049, 517, 2, 150),
 ])
-@pytest.mark.parametrize("kind", ["one scale", "grows", "grows at the end", "zeros first", "blank but the end", "magnitudes", "small rows", "large", "small"])
+@pytest.mark.parametrize("kind", ["grows", "grows at the end", "zeros first", "blank but the end", "magnitudes", "small rows", "rows in between", "large", "small"])
 @pytest.mark.parametrize("both", [False, True])
 def test_scores_and_updates_over_many_magnitudes(J, D, P, B, kind, both):
-    """Entry by entry: sums of K products rounded six times at most for every sixteen, and eight roundings' worth for the terms that are left
-    out, 2^-24 (6 K / 16 + 8) sum |a b|; slices of K add theirs within that."""
+    """Row by row and column by column, and entry by entry: sums of K products rounded six times at most for every sixteen, and eight roundings'
+    worth for the terms that are left out, 2^-24 (6 K / 16 + 8) sum |a b|; slices of K add theirs within that."""
     import paper_1511_08486_amd as sfb
     dev, N, g = "cuda:0", P * B, torch.Generator(device="cuda:0").manual_seed(J + D)
     randn = lambda *s: torch.randn(s, generator=g, device=dev)  # noqa: E731
@@ -52,6 +64,7 @@ def test_scores_and_updates_over_many_magnitudes(J, D, P, B, kind, both):
     ctx.compute_factors(W, sfb.SfbBatch(a=A, a2=A2), y, U, V)   # similar pairs: u = 2 z
     ctx.sync()
     assert torch.equal(V, A)
+    _assert_rows_and_columns(0.5 * U.double(), A.double(), W.double())
     room = 2.0 ** -24 * (6 * D / 16 + 8) * (A.double().abs() @ W.double().abs().T) + 1e-44
     assert ((0.5 * U.double() - A.double() @ W.double().T).abs() <= room).all()
 
@@ -61,5 +74,6 @@ def test_scores_and_updates_over_many_magnitudes(J, D, P, B, kind, both):
     ctx.reconstruct_apply(W1, Ut.T.contiguous(), Vt.T.contiguous(), -1.0, scale=1.0)
     ctx.sync()
     ctx.close()
+    _assert_rows_and_columns(W1.double(), Ut.double(), Vt.double())
     room = 2.0 ** -24 * (6 * N / 16 + 8) * (Ut.double().abs() @ Vt.double().abs().T) + 1e-44
     assert ((W1.double() - Ut.double() @ Vt.double().T).abs() <= room).all()
