@@ -58,7 +58,7 @@ __global__ __launch_bounds__((ScoreTile<BM, BN, EXACT>::THREADS), BM + BN == 256
         auto where = [&](int c, auto first) {
             const bool partial = decltype(first)::value && ragged && c == 0;
             const int k = partial ? 0 : k_begin + (c - (ragged ? 1 : 0)) * kSpChunk;
-            const uint32_t bytes = c < n_chunks ? 0xffffffffu : 0u;
+            const uint32_t bytes = split_while(c, n_chunks);
             return Place{split_words(A + (int64_t)m0 * lda + k, bytes), split_words(DIFF ? A2 + (int64_t)m0 * lda + k : nullptr, bytes),
                          split_words(W + (int64_t)n0 * ldw + k, bytes), partial ? last_off : 0u};
         };
@@ -109,7 +109,7 @@ __global__ __launch_bounds__((ScoreTile<BM, BN, EXACT>::THREADS), BM + BN == 256
             *reinterpret_cast<uint2*>(buf + lds_item + decltype(plane)::value * Tile::PLANE + decltype(ic)::value * STEP * 64) = words;
         };
         const bool second[2] = {false, true}, on[2] = {true, true};
-        Tile::template split<Raw, IT, 2, 3, 0>(n_chunks, ss_lds, second, on,
+        Tile::template split<Raw, IT, 2, 0>(n_chunks, ss_lds, second, on,
                                                [](auto ic) { return std::integral_constant<int, (decltype(ic)::value >= A_IT)>{}; }, where, load, prep,
                                                take, put);
         return;

@@ -80,7 +80,7 @@ __global__ __launch_bounds__((ReconTile<BM, BN, SPLITTERS, EXACT>::THREADS), BM 
         struct Raw { f32_cb x[4]; };
         auto where = [&](int c, auto) {
             const uint32_t gone = (uint32_t)c * (32u * pitch);
-            return split_words(src + gone, c < n_chunks && on[0] ? bytes - gone : 0u);
+            return split_words(src + gone, on[0] ? (bytes - gone) & split_while(c, n_chunks) : 0u);
         };
         auto load = [&](Raw& raw, const __amdgpu_buffer_rsrc_t& words, auto uc, auto) {
             if constexpr (CB == 4) {
@@ -120,7 +120,7 @@ __global__ __launch_bounds__((ReconTile<BM, BN, SPLITTERS, EXACT>::THREADS), BM 
         auto put = [&](unsigned char* buf, auto plane, auto ic, uint2 words) {
             *reinterpret_cast<uint2*>(buf + lds_at[decltype(ic)::value] + decltype(plane)::value * Tile::PLANE) = words;
         };
-        Tile::template split<Raw, CB, 1, 3, (CB == 4 ? 2 : 0)>(n_chunks, rs_lds, is_v, on, [](auto) { return std::integral_constant<int, 0>{}; }, where, load,
+        Tile::template split<Raw, CB, 1, (CB == 4 ? 2 : 0)>(n_chunks, rs_lds, is_v, on, [](auto) { return std::integral_constant<int, 0>{}; }, where, load,
                                               prep, take, put);
         return;
     }

@@ -177,6 +177,8 @@ struct SplitTile {
         return a && b && ~uniform(all.y) >= sc[0].least_m1 && ~uniform(all.w) >= sc[1].least_m1;
     }
 
+    static __device__ __forceinline__ int threes(int n) { return n > 0 ? n / 3 * 3 : 0; }   // of n, in whole threes
+
     // ---- the multiplying wavefronts ----
     static constexpr bool REST = MB * NB <= 8;                          // the smaller products have sums of their own (registers)
     static_assert(REST || EXACT, "two terms: the smaller products are on another scale");
@@ -251,27 +253,29 @@ struct SplitTile {
         };
         while (step(std::false_type{}))
             if (SUMS == 2 && !step(std::bool_constant<SUMS == 2>{})) break;
+        // (the splitting wavefronts see it behind three steps, or at the end)
+        const int whole = threes(n - 2);
+        for (int b = c; b < n && (b > whole || b % 3 != 0); ++b) asm volatile("s_barrier" ::: "memory");
         return c;
     }
-    // Three terms (planes h, m, l), chunks c0 .. n - 1.
+    // Three terms (planes h, m, l), chunks c0 .. n - 1.  The first products wait for two planes' fragments only, every other plane is read over
+    // the products before its use, into the registers that are free by then.
     __device__ __forceinline__ void multiply3(int c0, int n, unsigned char* lds) {
         constexpr int BUF = 3 * PLANE;
         for (int c = c0, at = 0; c < n; ++c, at = BUF - at) {
             const unsigned char* const now = lds + at;
-            sp_u32x4 a0[MB], a1[MB], bh[NB], bm[NB], bl[NB];
-#pragma unroll
-            for (int i = 0; i < MB; ++i) a0[i] = item_a(now, 0, i);
-#pragma unroll
-            for (int j = 0; j < NB; ++j) {
-                bl[j] = item_b(now, 2, j);
-                bm[j] = item_b(now, 1, j);
-            }
-            phase<3, false, NB>(a0, bl, [&](auto rc) { bh[decltype(rc)::value] = item_b(now, 0, decltype(rc)::value); });
-            phase<3, false, MB>(a0, bm, [&](auto rc) { a1[decltype(rc)::value] = item_a(now, 1, decltype(rc)::value); });
-            phase<3, true, 0>(a0, bh, [](auto) {});
-            phase<3, false, MB>(a1, bm, [&](auto rc) { a0[decltype(rc)::value] = item_a(now, 2, decltype(rc)::value); });
+            sp_u32x4 ah[MB], a1[MB], bh[NB], b1[NB];
+            split_for<0, (MB > NB ? MB : NB)>([&](auto rc) {
+                constexpr int r = decltype(rc)::value;
+                if constexpr (r < MB) ah[r] = item_a(now, 0, r);
+                if constexpr (r < NB) bh[r] = item_b(now, 0, r);
+            });
+            phase<3, true, NB>(ah, bh, [&](auto rc) { b1[decltype(rc)::value] = item_b(now, 1, decltype(rc)::value); });
+            phase<3, false, MB>(ah, b1, [&](auto rc) { a1[decltype(rc)::value] = item_a(now, 1, decltype(rc)::value); });
+            phase<3, false, 0>(a1, b1, [](auto) {});
+            phase<3, false, NB>(a1, bh, [&](auto rc) { b1[decltype(rc)::value] = item_b(now, 2, decltype(rc)::value); });
+            phase<3, false, MB>(ah, b1, [&](auto rc) { a1[decltype(rc)::value] = item_a(now, 2, decltype(rc)::value); });
             phase<3, false, 0>(a1, bh, [](auto) {});
-            phase<3, false, 0>(a0, bh, [](auto) {});
             asm volatile("s_barrier" ::: "memory");
         }
     }
@@ -300,9 +304,8 @@ struct SplitTile {
             split_barrier();
             split_barrier();
             SplitScale sc[2];
-            const bool fits = scales(lds, sc);
-            split_barrier();
-            if (fits) {
+            if (scales(lds, sc)) {
+                split_barrier();
                 done = multiply2(n, lds);
                 merge(-(sc[0].e + sc[1].e), 1.0f / (1 << kSpLowExp));
             }
@@ -317,18 +320,27 @@ struct SplitTile {
     // ITEMS groups of four values a lane and chunk, in slots of the same operand: where(c, first) says where chunk c is (c may be past the end:
     // then there is nothing to move; first: compile time, chunk 0 may be only there), load(raw, place, u, first) requests unit u of its raw
     // words (as many units as pairs of groups), prep(raw, c, first) does what has to happen to them before they are split, take(raw, i) is
-    // group i, put(buf, plane, i, words) parks four terms of it.  DEPTH: chunks whose raw words are in flight.
+    // group i, put(buf, plane, i, words) parks four terms of it.  Raw words of three chunks are in flight.
     // A unit is requested as soon as its words are used up, one behind every pair of groups (LAG pairs later): in one burst behind a chunk the
     // requests of four wavefronts took 900 cycles to be accepted, and nothing was split meanwhile.
     // Slot slot(i): operand second[slot], parked only where on[slot] (both uniform).
-    template <int T, class Raw, int ITEMS, int SLOTS, int DEPTH, int LAG, class Slot, class Where, class Load, class Prep, class Take, class Put>
-    static __device__ __forceinline__ int split_in(int c0, int n, unsigned char* lds, const bool (&second)[SLOTS], const bool (&on)[SLOTS],
-                                            Slot slot, Where where, Load load, Prep prep, Take take, Put put) {
+    // split_in: chunks c0 .. n - 1 in T terms; r[0] holds the raw words of chunk c0.  ready (two terms: always): prepared (and r[1] those of the next).
+    template <int T, class Raw, int ITEMS, int SLOTS, int LAG, class Slot, class Where, class Load, class Prep, class Take, class Put>
+    static __device__ __forceinline__ int split_in(int c0, int n, unsigned char* lds, Raw (&r)[3], bool ready, const SplitScale (&sc)[2],
+                                            const bool (&second)[SLOTS], const bool (&on)[SLOTS], Slot slot, Where where, Load load, Prep prep,
+                                            Take take, Put put) {
         constexpr int LEAD = T == 2 ? 2 : 1, BUF = T * PLANE, UNITS = (ITEMS + 1) / 2;
-        static_assert(DEPTH >= 2, "raw sets");
-        Raw r[DEPTH];
         float s[SLOTS], s_low[SLOTS];
         uint32_t most[SLOTS], least[SLOTS];
+        if constexpr (T == 2) {
+#pragma unroll
+            for (int q = 0; q < SLOTS; ++q) {
+                s[q] = second[q] ? sc[1].s : sc[0].s;
+                s_low[q] = second[q] ? sc[1].s_low : sc[0].s_low;
+                most[q] = second[q] ? sc[1].most : sc[0].most;
+                least[q] = second[q] ? sc[1].least_m1 : sc[0].least_m1;
+            }
+        }
         auto park = [&](const Raw& raw, int c, int at, auto after) {
             uint32_t mx[SLOTS], mn[SLOTS];
 #pragma unroll
@@ -371,20 +383,78 @@ struct SplitTile {
             }
         };
         constexpr std::false_type later{};
-        auto fetch = [&](Raw& raw, int c, auto first, auto units) {     // the first so many units
-            const auto place = where(c, first);
-            split_for<0, decltype(units)::value>([&](auto u) { load(raw, place, u, first); });
+        auto fetch = [&](Raw& raw, int c, auto units) {                  // the first so many units
+            const auto place = where(c, later);
+            split_for<0, decltype(units)::value>([&](auto u) { load(raw, place, u, later); });
         };
         constexpr std::integral_constant<int, UNITS> all{};
         constexpr std::integral_constant<int, UNITS - LAG> early{};
         static_assert(LAG <= UNITS, "units");
-        auto nothing = [](auto) {};
-        fetch(r[0], c0, std::true_type{}, all);
-        fetch(r[1], c0 + 1, later, all);
+        int at = LEAD * BUF;
         if constexpr (T == 2) {
+            // (the third set's words are requested behind the first's, not before: the first's are not held up)
+            const auto third = where(c0 + 2, later), fourth = where(c0 + 3, later);
+            park(r[0], c0, 0, [&](auto uc) { load(r[2], third, uc, later); });
+            park(r[1], c0 + 1, BUF, [&](auto uc) { load(r[0], fourth, uc, later); });
+            fetch(r[1], c0 + 4, early);
+        } else {
+            fetch(r[1], c0 + 1, all);
+            fetch(r[2], c0 + 2, all);
+            if (!ready) prep(r[0], c0, std::true_type{});
+            park(r[0], c0, 0, [](auto) {});
+            fetch(r[0], c0 + 3, early);
+        }
+        split_barrier();
+        int c = c0;
+        auto step = [&](Raw& raw, auto after) {
+            prep(raw, c + LEAD, later);
+            park(raw, c + LEAD, at, after);
+            at = at == (T == 2 ? 2 : 1) * BUF ? 0 : at + BUF;
+            split_barrier();
+            ++c;
+        };
+        auto full_step = [&](Raw& before, Raw& raw) {
+            const auto last = where(c + LEAD + 2, later), next = where(c + LEAD + 3, later);
+            step(raw, [&](auto uc) {
+                constexpr int u = decltype(uc)::value;
+                if constexpr (u < LAG) load(before, last, std::integral_constant<int, UNITS - LAG + u>{}, later);
+                else load(raw, next, std::integral_constant<int, u - LAG>{}, later);
+            });
+        };
+        // Whole rounds of the three raw sets, then what is left of them.  The loop is left behind three steps only: an exit between
+        // steps meets the loop's own back edge in the generated code, where the wait for a raw set is then one for whatever
+        // any of the paths has on its way (the first of three steps waited for every load).
+        const int whole = c0 + threes(n - c0 - LEAD);
+        uint32_t stop = 0xffffffffu;
+        while (c < whole && stop > (uint32_t)c) {
+            full_step(r[LEAD - 1], r[LEAD]);
+            full_step(r[LEAD], r[(LEAD + 1) % 3]);
+            full_step(r[(LEAD + 1) % 3], r[LEAD - 1]);
+            if (T == 2) stop = (uint32_t)__builtin_amdgcn_readfirstlane((int)stop_word(lds));
+        }
+        if (stop <= (uint32_t)c) return (int)stop;
+        if (c + LEAD < n) step(r[LEAD], [](auto) {});
+        if (c + LEAD < n) step(r[(LEAD + 1) % 3], [](auto) {});
+        for (; c < n; ++c) split_barrier();
+        return T == 2 ? (int)min((uint32_t)n, (uint32_t)__builtin_amdgcn_readfirstlane((int)stop_word(lds))) : n;
+    }
+    template <class Raw, int ITEMS, int SLOTS, int LAG, class Slot, class Where, class Load, class Prep, class Take, class Put>
+    static __device__ __forceinline__ void split(int n, unsigned char* lds, const bool (&second)[SLOTS], const bool (&on)[SLOTS], Slot slot,
+                                          Where where, Load load, Prep prep, Take take, Put put) {
+        Raw r[3];
+        SplitScale sc[2];
+        auto fetch = [&](Raw& raw, int c, auto first) {
+            const auto place = where(c, first);
+            split_for<0, (ITEMS + 1) / 2>([&](auto u) { load(raw, place, u, first); });
+        };
+        int done = 0;
+        bool ready = false;
+        fetch(r[0], 0, std::true_type{});
+        if constexpr (!EXACT) {
+            fetch(r[1], 1, std::false_type{});
             split_barrier();                                             // the control words are clear
-            prep(r[0], c0, std::true_type{});
-            prep(r[1], c0 + 1, later);
+            prep(r[0], 0, std::true_type{});
+            prep(r[1], 1, std::false_type{});
             uint32_t words[4] = {0u, 0u, 0u, 0u};                        // (smallest as the largest complement)
             split_for<0, ITEMS>([&](auto ic) {
                 constexpr int q = decltype(slot(ic))::value;
@@ -402,68 +472,14 @@ struct SplitTile {
             // (as an atomic of the language it becomes a loop over the lanes: four of them took 1000 cycles)
             if (i < 4) asm volatile("ds_max_u32 %0, %1" ::"v"((uint32_t)(uintptr_t)(sp_lds_u32*)(lds + CTL + 16) + 4u * i), "v"(word) : "memory");
             split_barrier();
-            SplitScale sc[2];
-            if (!scales(lds, sc)) {
-                split_barrier();
-                return c0;
-            }
-#pragma unroll
-            for (int q = 0; q < SLOTS; ++q) {
-                s[q] = second[q] ? sc[1].s : sc[0].s;
-                s_low[q] = second[q] ? sc[1].s_low : sc[0].s_low;
-                most[q] = second[q] ? sc[1].most : sc[0].most;
-                least[q] = second[q] ? sc[1].least_m1 : sc[0].least_m1;
+            ready = !scales(lds, sc);                                    // (then three terms begin with the words that are there)
+            if (!ready) {
+                done = split_in<2, Raw, ITEMS, SLOTS, LAG>(0, n, lds, r, true, sc, second, on, slot, where, load, prep, take, put);
+                if (done >= n) return;
+                fetch(r[0], done, std::true_type{});
             }
         }
-        static_assert(DEPTH == 3, "raw sets");
-        if constexpr (T == 2) {
-            // (the third set's words are requested behind the first's, not before: the first's are not held up)
-            const auto third = where(c0 + 2, later), fourth = where(c0 + 3, later);
-            park(r[0], c0, 0, [&](auto uc) { load(r[2], third, uc, later); });
-            park(r[1], c0 + 1, BUF, [&](auto uc) { load(r[0], fourth, uc, later); });
-            fetch(r[1], c0 + 4, later, early);
-        } else {
-            fetch(r[2], c0 + 2, later, all);
-            prep(r[0], c0, std::true_type{});
-            park(r[0], c0, 0, nothing);
-            fetch(r[0], c0 + 3, later, early);
-        }
-        split_barrier();
-        int at = (T == 2 ? 2 : 1) * BUF;
-        bool go = true;
-        int c = c0;
-        auto step = [&](Raw& before, Raw& raw) {
-            uint32_t stop = 0xffffffffu;
-            if constexpr (T == 2) stop = stop_word(lds);
-            prep(raw, c + LEAD, later);
-            const auto last = where(c + LEAD + DEPTH - 1, later), next = where(c + LEAD + DEPTH, later);
-            park(raw, c + LEAD, at, [&](auto uc) {
-                constexpr int u = decltype(uc)::value;
-                if constexpr (u < LAG) load(before, last, std::integral_constant<int, UNITS - LAG + u>{}, later);
-                else load(raw, next, std::integral_constant<int, u - LAG>{}, later);
-            });
-            at = at == (T == 2 ? 2 : 1) * BUF ? 0 : at + BUF;
-            split_barrier();
-            ++c;
-            go = c < n && !(T == 2 && (uint32_t)__builtin_amdgcn_readfirstlane((int)stop) <= (uint32_t)c);
-        };
-        // (left in the middle, so that every path into a step has the other raw sets' loads behind it)
-        for (;;) {
-            step(r[(LEAD - 1) % DEPTH], r[(LEAD) % DEPTH]);
-            if (!go) break;
-            step(r[(LEAD + 1 - 1) % DEPTH], r[(LEAD + 1) % DEPTH]);
-            if (!go) break;
-            step(r[(LEAD + 1) % DEPTH], r[(LEAD + 2) % DEPTH]);
-            if (!go) break;
-        }
-        return c;
-    }
-    template <class Raw, int ITEMS, int SLOTS, int DEPTH, int LAG, class Slot, class Where, class Load, class Prep, class Take, class Put>
-    static __device__ __forceinline__ void split(int n, unsigned char* lds, const bool (&second)[SLOTS], const bool (&on)[SLOTS], Slot slot,
-                                          Where where, Load load, Prep prep, Take take, Put put) {
-        int done = 0;
-        if constexpr (!EXACT) done = split_in<2, Raw, ITEMS, SLOTS, DEPTH, LAG>(0, n, lds, second, on, slot, where, load, prep, take, put);
-        if (done < n) split_in<3, Raw, ITEMS, SLOTS, DEPTH, LAG>(done, n, lds, second, on, slot, where, load, prep, take, put);
+        split_in<3, Raw, ITEMS, SLOTS, LAG>(done, n, lds, r, ready, sc, second, on, slot, where, load, prep, take, put);
     }
 
     // An infinity (or a finite value beyond bf16's largest, 3.39e38: it rounds to one) leaves NaN in its second term, and six
@@ -498,6 +514,14 @@ struct SplitTile {
 __device__ __forceinline__ int split_row64(int r) { return (r & ~63) + 4 * (r & 15) + ((r >> 4) & 3); }
 __device__ __forceinline__ int split_row32(int r) { return (r & ~31) + 4 * (r & 7) + ((r >> 3) & 3); }
 __device__ __forceinline__ int split_row16(int r) { return (r & ~31) + 2 * (r & 15) + ((r >> 4) & 1); }
+
+// All bits while c < n, none from there on.  (Left to the compiler as a choice between two constants, it ended in a vector register, and
+// every load that takes its descriptor's size from it in a loop over the lanes.)
+__device__ __forceinline__ uint32_t split_while(int c, int n) {
+    int all;
+    asm("s_sub_i32 %0, %1, %2\n\ts_ashr_i32 %0, %0, 31" : "=&s"(all) : "s"(c), "s"(n) : "scc");
+    return (uint32_t)all;
+}
 
 // Descriptor of raw words from p on: `bytes` of them, none where they are not wanted (such loads return zero and move nothing)
 // (p and bytes are uniform; said so, or the compiler puts a loop over the lanes' descriptors around every load)

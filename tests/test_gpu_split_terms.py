@@ -77,3 +77,30 @@ def test_scores_and_updates_over_many_magnitudes(J, D, P, B, kind, both):
     _assert_rows_and_columns(W1.double(), Ut.double(), Vt.double())
     room = 2.0 ** -24 * (6 * N / 16 + 8) * (Ut.double().abs() @ Vt.double().abs().T) + 1e-44
     assert ((W1.double() - Ut.double() @ Vt.double().T).abs() <= room).all()
+
+
+@pytest.mark.parametrize("k", [32 * 12, 32 * 13 + 5, 32 * 14, 32 * 17 + 31])
+def test_the_split_changes_at_any_chunk(k):
+    """Walks of every remainder of three chunks, left by one operand's values at each chunk in turn."""
+    import paper_1511_08486_amd as sfb
+    dev, J, D, N, g = "cuda:0", 1000, 4096, 2048, torch.Generator(device="cuda:0").manual_seed(k)
+    randn = lambda *s: torch.randn(s, generator=g, device=dev)  # noqa: E731
+    u, v, w, a = randn(k, J), randn(k, D), randn(J, k), randn(N, k)
+    update, scores = sfb.Sfb("dml", J, D, 1, k, device=dev), sfb.Sfb("dml", J, k, 1, N, device=dev)
+    W1, U, V, y = torch.empty((J, D), device=dev), torch.empty((N, J), device=dev), torch.empty((N, k), device=dev), torch.ones(N, dtype=torch.int32, device=dev)
+    for c in range(2, k // 32 + 1):
+        for grown, still in ((u, v), (v, u)):
+            x = grown.clone()
+            x[32 * c:] *= 1e4
+            U1, V1 = (x, still) if grown is u else (still, x)
+            update.reconstruct_apply(W1.zero_(), U1, V1, -1.0, scale=1.0)
+            update.sync()
+            _assert_rows_and_columns(W1.double(), U1.double().T, V1.double().T)
+        x = a.clone()
+        x[:, 32 * c:] *= 1e4
+        scores.compute_factors(w, sfb.SfbBatch(a=x, a2=torch.zeros_like(x)), y, U, V.fill_(float("nan")))
+        scores.sync()
+        assert torch.equal(V, x)
+        _assert_rows_and_columns(0.5 * U.double(), x.double(), w.double())
+    update.close()
+    scores.close()
