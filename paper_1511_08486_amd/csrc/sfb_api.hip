@@ -148,7 +148,11 @@ size_t workspace_need(const sfb_ctx* c) {
 
 // The split products' plans.  exact: three terms an operand throughout, where the caller chose them (sfb_set_plan) or features are sparse: a sum of
 // a few products has the error of its products, and those of two terms are the rougher ones (2 % stored: 8e-8 of the norm against 4e-8).
-void plan_split_scores(sfb_ctx* c, bool exact) {
+// chosen: ... and sums in two halves however short, which has half the error of a long one (by default only walks of 48 chunks and more, where
+// it is below the fp32 instruction's and costs nothing that shows: positive operands, 4096 of them, 3.0e-7 of the norm in one sum, 1.5e-7 in two).
+constexpr int kSplitHalves = 48, kSplitHalvesChosen = 4;
+void plan_split_scores(sfb_ctx* c, bool exact, bool chosen) {
+    const int halves = chosen ? kSplitHalvesChosen : kSplitHalves;
     const int64_t N = (int64_t)c->P * c->B;
     // room for the partial scores: what ragged contexts reserve for their padded factor copies anyway, or a few MiB; the
     // others the 16 MiB that sfb_step_noalloc has; or what the fp32 instruction's plan would take, where that is more
@@ -159,14 +163,15 @@ void plan_split_scores(sfb_ctx* c, bool exact) {
     }
     const size_t f32_need = (size_t)c->fwd_all.split_k * (size_t)N * (size_t)round_up4(c->J) * sizeof(float);
     if (f32_need > most) most = f32_need;
-    c->fwd_split = plan_forward_split(N, c->J, c->D, most, exact);
-    c->fwd_split_worker = plan_forward_split(c->B, c->J, c->D, (size_t)c->fwd_split.split_k * (size_t)N * (size_t)round_up4(c->J) * sizeof(float), exact);
+    c->fwd_split = plan_forward_split(N, c->J, c->D, most, exact, halves);
+    c->fwd_split_worker = plan_forward_split(c->B, c->J, c->D, (size_t)c->fwd_split.split_k * (size_t)N * (size_t)round_up4(c->J) * sizeof(float), exact, halves);
 }
-void plan_split_recon(sfb_ctx* c, bool exact) {
+void plan_split_recon(sfb_ctx* c, bool exact, bool chosen) {
     if (c->dtype != SFB_F32) return;
     for (int one = 0; one < 2; ++one)
         for (int with_ws = 0; with_ws < 2; ++with_ws)
-            c->split_plans[one][with_ws] = reconstruct_split_plan(c->J, c->D, one ? c->B : (int64_t)c->P * c->B, with_ws ? workspace_need(c) : 0, exact);
+            c->split_plans[one][with_ws] = reconstruct_split_plan(c->J, c->D, one ? c->B : (int64_t)c->P * c->B, with_ws ? workspace_need(c) : 0, exact,
+                                                                  chosen ? kSplitHalvesChosen : kSplitHalves);
 }
 
 // The tiles' slices are cut to the bytes the context asks for: to be planned again whenever those change (sfb_set_plan).
@@ -531,7 +536,7 @@ sfb_status sfb_create(sfb_ctx** out, sfb_model m, int64_t J, int64_t D, int32_t 
                             !((J % 4) == 0 && J >= 4 && (D % 128) == 0 && (N % 32) == 0 && N >= 32);
         c->recon_padded = plan_reconstruct_padded(J, D, N, -1);
     }
-    plan_split_scores(c, m == SFB_L2SVM);
+    plan_split_scores(c, m == SFB_L2SVM, false);
     c->fused_ok = input_dtype == SFB_BF16 && m == SFB_MLR && fused_shape_ok(J, D, (int64_t)P * B);
     c->use_fused = true;
     c->fused = c->fused_ok ? plan_fused(J, D, (int64_t)P * B) : FusedPlan{};
@@ -541,7 +546,7 @@ sfb_status sfb_create(sfb_ctx** out, sfb_model m, int64_t J, int64_t D, int32_t 
         const size_t planes = few_workspace((int64_t)P * B, J, D);
         c->few = planes <= SFB_NOALLOC_SCRATCH_BYTES || planes <= workspace_need(c);
     }
-    plan_split_recon(c, m == SFB_L2SVM);
+    plan_split_recon(c, m == SFB_L2SVM, false);
     c->tile_bf16_scores = c->tile_bf16_update = true;
     plan_bf16_tiles(c);
     c->ws = nullptr; c->ws_bytes = 0; c->lists = nullptr; c->lists_stored = 0; c->last_hip = 0; c->timing = false; c->sparse_forward = true; c->sparse_always = false;
@@ -912,7 +917,7 @@ sfb_status sfb_set_plan(sfb_ctx* c, int32_t fwd_bm, int32_t fwd_bn, int32_t fwd_
     if (fwd_dma >= 0) c->lists_always = (fwd_dma & 64) != 0;    // bit 6 set: L2SVM steps update from the column lists wherever they fit
     if (fwd_dma >= 0) c->use_fused = (fwd_dma & 16) == 0;       // bit 4 set: sfb_step_pipelined runs two separate passes
     finish_forward_plan(&p, (int64_t)c->P * c->B, c->J, c->D);
-    if (fwd_dma >= 0 && c->split_scores) plan_split_scores(c, true);
+    if (fwd_dma >= 0 && c->split_scores) plan_split_scores(c, true, true);
     c->fwd_all = p;
     if (fwd_bm > 0 || fwd_bn > 0 || fwd_split_k > 0) c->tile_bf16_scores = false;
     if (recon_variant >= 0) {
@@ -920,7 +925,7 @@ sfb_status sfb_set_plan(sfb_ctx* c, int32_t fwd_bm, int32_t fwd_bn, int32_t fwd_
         c->recon = plan_reconstruct_variant(c->J, c->D, recon_variant);
         c->recon_padded = plan_reconstruct_padded(c->J, c->D, (int64_t)c->P * c->B, recon_variant);
     }
-    if (fwd_dma >= 0 && c->split_recon == 1) plan_split_recon(c, true);
+    if (fwd_dma >= 0 && c->split_recon == 1) plan_split_recon(c, true, true);
     plan_bf16_tiles(c);                                          // (the choice may have changed the workspace, either way)
     return SFB_OK;
 }

@@ -22,7 +22,7 @@ template <int BM, int BN, bool DIFF, bool EXACT>
 __global__ __launch_bounds__((ScoreTile<BM, BN, EXACT>::THREADS), BM + BN == 256 ? 4 : BM + BN == 192 || DIFF ? 3 : 6) void scores_split_kernel(
     const float* __restrict__ A, const float* __restrict__ A2, int64_t lda, const float* __restrict__ W, int64_t ldw,
     float* __restrict__ Z, int64_t ldz, int64_t zstride, float* __restrict__ Vout, int64_t ldv, int M, int N, int K,
-    int k_slice, int n_mb, int n_nb, int total) {
+    int k_slice, int halves, int n_mb, int n_nb, int total) {
     using Tile = ScoreTile<BM, BN, EXACT>;
     constexpr int STEP = 64;                                             // rows that the splitting lanes take at a time, eight lanes a row
     constexpr int A_IT = BM / STEP, IT = (BM + BN) / STEP;               // 16-byte items per splitting lane and chunk: of A, of A and W
@@ -117,7 +117,7 @@ __global__ __launch_bounds__((ScoreTile<BM, BN, EXACT>::THREADS), BM + BN == 256
 
     Tile t;
     t.init(wave, lane);
-    t.multiply(n_chunks, ss_lds);
+    t.multiply(n_chunks, halves, ss_lds);
     const int wm = wave / Tile::WN, wn = wave % Tile::WN, l16 = lane & 15, quarter = lane >> 4;
     t.mend([&](int i, int j) {
         const int64_t row = min(m0 + (wm * Tile::MB + i) * 16 + l16, M - 1), col = min(n0 + ss_row<Tile::NB>((wn * Tile::NB + j) * 16 + l16), N - 1);
@@ -194,7 +194,7 @@ static hipError_t launch_split(const FwdArgs& a, const FwdPlan& p, hipStream_t s
     const int total = n_mb * n_nb * p.split_k;
     SFB_LAUNCH((scores_split_kernel<BM, BN, DIFF, EXACT>), dim3(total), dim3(Tile::THREADS), lds_bytes, s, (const float*)a.a,
                (const float*)a.a2, a.lda, a.w, a.ldw, a.zp, a.ldz, a.zstride, (float*)a.v, a.ldv, a.n_rows, a.J, a.D,
-               p.k_slice, n_mb, n_nb, total);
+               p.k_slice, p.halves, n_mb, n_nb, total);
     return hipGetLastError();
 }
 
@@ -219,13 +219,14 @@ static hipError_t launch_split_tile(const FwdArgs& a, const FwdPlan& p, hipStrea
 // Two terms first look at their operands, 1 to 2 us longer to start, and win from 4 (large tiles) to 16 chunks a workgroup on: 1000 x 4096, 512
 // samples (16 chunks) 25.6 against 30.3 us, 333 x 1001 with 228 (4) 8.3 against 7.6.  Below eight chunks (256 columns) they are also the less exact ones:
 // products are 7e-8 of the norm off, 8 chunks' running sums 1e-7.
-// `most` bounds the bytes of partial scores (the caller's room for them); one slice is always allowed.  exact: three terms.
-FwdPlan plan_forward_split(int64_t n_rows, int64_t J, int64_t D, size_t most, bool exact) {
+// `most` bounds the bytes of partial scores (the caller's room for them); one slice is always allowed.  exact: three terms; halves: see FwdPlan.
+FwdPlan plan_forward_split(int64_t n_rows, int64_t J, int64_t D, size_t most, bool exact, int halves) {
     static const struct { int bm, bn, resident, terms; double start_us, chunk_us, lone_us; } tiles[8] = {
         {128, 128, 1, 2, 8.5, 0.74, 0.74}, {64, 128, 1, 2, 7.4, 0.58, 0.58}, {128, 64, 1, 2, 7.4, 0.58, 0.58}, {64, 64, 2, 2, 7.2, 0.36, 0.40},
         {128, 128, 1, 3, 7.5, 1.08, 1.08}, {64, 128, 1, 3, 5.9, 0.78, 0.78}, {128, 64, 1, 3, 5.9, 0.78, 0.78}, {64, 64, 2, 3, 5.4, 0.47, 0.48}};
     FwdPlan p{};
     p.dma = false;
+    p.halves = halves;
     double best = 1e300;
     const int64_t chunks = (D + kSpChunk - 1) / kSpChunk;
     const double plane = (double)n_rows * (double)((J + 3) / 4 * 4) * 4.0;

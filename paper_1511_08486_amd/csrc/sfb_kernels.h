@@ -45,6 +45,7 @@ struct FwdPlan {
     int grid;        // workgroups
     bool dma;        // stage tiles by LDS-DMA where the shape allows
     bool exact;      // split products: three bf16 terms an operand throughout
+    int halves;      //   walks of so many chunks of 32 and more are summed in two halves
 };
 
 // Chooses tile and split for Z[n_rows][J] = A W^T with contraction length D.
@@ -69,7 +70,7 @@ struct FwdArgs {
 hipError_t launch_forward(const FwdArgs& a, const FwdPlan& p, hipStream_t s);
 // fp32 scores on the 16-bit matrix cores, every operand split into two fp16 or three bf16 terms (sfb_forward_split.hip)
 bool forward_split_ok(const FwdArgs& a);
-FwdPlan plan_forward_split(int64_t n_rows, int64_t J, int64_t D, size_t most, bool exact);
+FwdPlan plan_forward_split(int64_t n_rows, int64_t J, int64_t D, size_t most, bool exact, int halves);
 hipError_t launch_forward_split(const FwdArgs& a, const FwdPlan& p, hipStream_t s);
 
 // Dual side of SDCA (Section 2.1): with `dual` set, the MLR factor kernel turns its
@@ -228,8 +229,9 @@ struct SplitReconPlan {
     int main_rows, main_cols;          // 0, or the rows or columns that these tiles take: the others are a launch with
     int rest_bm, rest_bn, rest_slices; //   these
     bool rest_exact;
+    int halves;                        // as in FwdPlan
 };
-SplitReconPlan reconstruct_split_plan(int64_t J, int64_t D, int64_t N, size_t room, bool exact);   // room: bytes for planes of sums
+SplitReconPlan reconstruct_split_plan(int64_t J, int64_t D, int64_t N, size_t room, bool exact, int halves);   // room: bytes for planes of sums
 hipError_t launch_reconstruct_split(const ReconArgs& a, const SplitReconPlan& p, hipStream_t s);
 
 // Reconstruction from the stored entries of sparse features (sfb_sparse_update.hip): column lists made from the dense

@@ -31,7 +31,7 @@ __device__ __forceinline__ int rs_v(int r) { return CB == 2 ? split_row16(r) : s
 template <int BM, int BN, int SPLITTERS, bool PLANES, bool EXACT>
 __global__ __launch_bounds__((ReconTile<BM, BN, SPLITTERS, EXACT>::THREADS), BM + BN == 128 ? (SPLITTERS == 8 ? 6 : 4) : BM + BN == 192 ? 3 : 4) void reconstruct_split_kernel(
     float* __restrict__ W, int64_t ldw, const float* __restrict__ U, int64_t ldu, const float* __restrict__ V,
-    int64_t ldv, int J, int D, int N, float alpha, int n_jb, int tiles, int total, int k_chunks, int prox_kind, float prox_a,
+    int64_t ldv, int J, int D, int N, float alpha, int n_jb, int tiles, int total, int k_chunks, int halves, int prox_kind, float prox_a,
     uint64_t live_mask, uint32_t inv_b) {
     using Tile = ReconTile<BM, BN, SPLITTERS, EXACT>;
     constexpr int CB = BM + BN == 128 && SPLITTERS == 8 ? 2 : 4;         // columns of a splitting lane's block
@@ -127,7 +127,7 @@ __global__ __launch_bounds__((ReconTile<BM, BN, SPLITTERS, EXACT>::THREADS), BM 
 
     Tile t;
     t.init(wave, lane);
-    t.multiply(n_chunks, rs_lds);
+    t.multiply(n_chunks, halves, rs_lds);
 
     // The entries of W this wavefront finishes: four (two) neighbouring columns a row.  A scalar address a row and one lane offset (host: 50
     // rows of W below 2^32 bytes) where the tile is whole.
@@ -213,7 +213,7 @@ bool reconstruct_split_ok(const ReconArgs& a) {
 }
 
 template <int BM, int BN, int SPLITTERS, bool PLANES, bool EXACT>
-static hipError_t launch_split(const ReconArgs& a, int slices, hipStream_t s) {
+static hipError_t launch_split(const ReconArgs& a, int slices, int halves, hipStream_t s) {
     using Tile = ReconTile<BM, BN, SPLITTERS, EXACT>;
     constexpr size_t lds_bytes = Tile::LDS;
     static std::atomic<bool> raised{false};
@@ -229,7 +229,7 @@ static hipError_t launch_split(const ReconArgs& a, int slices, hipStream_t s) {
     const uint32_t inv_b = a.use_mask ? (uint32_t)(((1ull << 32) + a.B - 1) / a.B) : 0;
     SFB_LAUNCH((reconstruct_split_kernel<BM, BN, SPLITTERS, PLANES, EXACT>), dim3(tiles * slices), dim3(Tile::THREADS), lds_bytes, s,
                PLANES ? a.partial : a.w, PLANES ? (int64_t)a.D : a.ldw, a.u, a.ldu, (const float*)a.v, a.ldv, a.J, a.D, a.N,
-               a.alpha, n_jb, tiles, tiles * slices, k_chunks, a.prox_kind, a.prox_a, a.live_mask, inv_b);
+               a.alpha, n_jb, tiles, tiles * slices, k_chunks, halves, a.prox_kind, a.prox_a, a.live_mask, inv_b);
     return hipGetLastError();
 }
 
@@ -254,7 +254,7 @@ static SplitReconPlan plan_part(int64_t J, int64_t D, int64_t N, size_t room, bo
     // (walks of more than 32 chunks: a second round that is not full takes up to a tenth less than its estimate, 1412 x 4395 with 1256 pairs
     // 79.7 us in one launch and 86.9 in two; up to there two launches go by the estimate, 1001 x 4100 with 488: 38.7 and 35.3)
     const double margin = chunks > 32 ? 0.97 : 1.0;
-    SplitReconPlan best{0, 0, 1, true, 1e300, 0, 0, 0, 0, 1, true};
+    SplitReconPlan best{0, 0, 1, true, 1e300, 0, 0, 0, 0, 1, true, 0};
     for (const auto& t : tiles) {
         if (exact && t.terms == 2) continue;
         if (t.bm == 96 && chunks < 16) continue;
@@ -273,43 +273,47 @@ static SplitReconPlan plan_part(int64_t J, int64_t D, int64_t N, size_t room, bo
             if ((chunks + per - 1) / per != s) continue;                          // the same cut as a smaller count, or an empty slice
             if ((t.bm == 96 && per > 64) || (!ex && per < 4)) continue;
             const double us = cost(J, D, s, per);
-            if (us < best.us) best = SplitReconPlan{t.bm, t.bn, (int)s, ex, us, 0, 0, 0, 0, 1, true};
+            if (us < best.us) best = SplitReconPlan{t.bm, t.bn, (int)s, ex, us, 0, 0, 0, 0, 1, true, 0};
         }
         if (!alone || t.resident != 1 || (t.bm == 96 && chunks > 64) || (!ex && chunks < 4)) continue;
         const int64_t rows = (J - 4) / t.bm * t.bm, cols = (D - 4) / t.bn * t.bn; // (a launch takes four rows and columns and more)
         if (cols > 0 && (((J + t.bm - 1) / t.bm) * (cols / t.bn) + 255) / 256 < (n + 255) / 256) {
             const SplitReconPlan rest = plan_part(J, D - cols, N, room, exact, false);
             const double us = cost(J, cols, 1, chunks) + rest.us;
-            if (us < margin * best.us) best = SplitReconPlan{t.bm, t.bn, 1, ex, us, 0, (int)cols, rest.bm, rest.bn, rest.slices, rest.exact};
+            if (us < margin * best.us) best = SplitReconPlan{t.bm, t.bn, 1, ex, us, 0, (int)cols, rest.bm, rest.bn, rest.slices, rest.exact, 0};
         }
         if (rows > 0 && ((rows / t.bm) * ((D + t.bn - 1) / t.bn) + 255) / 256 < (n + 255) / 256) {
             const SplitReconPlan rest = plan_part(J - rows, D, N, room, exact, false);
             const double us = cost(rows, D, 1, chunks) + rest.us;
-            if (us < margin * best.us) best = SplitReconPlan{t.bm, t.bn, 1, ex, us, (int)rows, 0, rest.bm, rest.bn, rest.slices, rest.exact};
+            if (us < margin * best.us) best = SplitReconPlan{t.bm, t.bn, 1, ex, us, (int)rows, 0, rest.bm, rest.bn, rest.slices, rest.exact, 0};
         }
     }
     return best;
 }
 // Where the last row or column of tiles is what begins another round of 256, it is a second, smaller launch with a plan of its
 // own (1001 x 4100, 488 pairs: 256 tiles of 128 x 128 and four columns, 42.7 -> 39.3 us; 1001 x 4129, 1000: 88.6 -> 59.7).
-SplitReconPlan reconstruct_split_plan(int64_t J, int64_t D, int64_t N, size_t room, bool exact) { return plan_part(J, D, N, room, exact, true); }
+SplitReconPlan reconstruct_split_plan(int64_t J, int64_t D, int64_t N, size_t room, bool exact, int halves) {
+    SplitReconPlan p = plan_part(J, D, N, room, exact, true);
+    p.halves = halves;
+    return p;
+}
 
 template <int BM, int BN, int SPLITTERS, bool EXACT>
-static hipError_t launch_tile(const ReconArgs& a, int slices, hipStream_t s) {
-    if (slices == 1) return launch_split<BM, BN, SPLITTERS, false, EXACT>(a, 1, s);
-    const hipError_t e = launch_split<BM, BN, SPLITTERS, true, EXACT>(a, slices, s);
+static hipError_t launch_tile(const ReconArgs& a, int slices, int halves, hipStream_t s) {
+    if (slices == 1) return launch_split<BM, BN, SPLITTERS, false, EXACT>(a, 1, halves, s);
+    const hipError_t e = launch_split<BM, BN, SPLITTERS, true, EXACT>(a, slices, halves, s);
     return e != hipSuccess ? e : launch_apply_partials(a, slices, a.D, s);
 }
 
-static hipError_t launch_part(const ReconArgs& a, int bm, int bn, int slices, bool exact, hipStream_t s) {
+static hipError_t launch_part(const ReconArgs& a, int bm, int bn, int slices, bool exact, int halves, hipStream_t s) {
     if (slices < 1 || (slices > 1 && a.partial == nullptr)) return hipErrorInvalidValue;
     auto with = [&](auto ex) {
         constexpr bool X = decltype(ex)::value;
-        if (bm == 128 && bn == 128) return launch_tile<128, 128, 8, X>(a, slices, s);
-        if (bm == 96 && bn == 128) return launch_tile<96, 128, 8, X>(a, slices, s);
-        if (bm == 64 && bn == 128) return launch_tile<64, 128, 8, X>(a, slices, s);
+        if (bm == 128 && bn == 128) return launch_tile<128, 128, 8, X>(a, slices, halves, s);
+        if (bm == 96 && bn == 128) return launch_tile<96, 128, 8, X>(a, slices, halves, s);
+        if (bm == 64 && bn == 128) return launch_tile<64, 128, 8, X>(a, slices, halves, s);
         const int64_t small = (int64_t)((a.J + 63) / 64) * ((a.D + 63) / 64) * slices;
-        if (bm == 64 && bn == 64) return small <= 256 ? launch_tile<64, 64, 8, X>(a, slices, s) : launch_tile<64, 64, 4, X>(a, slices, s);
+        if (bm == 64 && bn == 64) return small <= 256 ? launch_tile<64, 64, 8, X>(a, slices, halves, s) : launch_tile<64, 64, 4, X>(a, slices, halves, s);
         return hipErrorInvalidValue;
     };
     return exact ? with(std::true_type{}) : with(std::false_type{});
@@ -317,11 +321,11 @@ static hipError_t launch_part(const ReconArgs& a, int bm, int bn, int slices, bo
 
 // plan.slices > 1 (or rest_slices): a.partial holds that many planes of J x D (of the rest's rows and columns) floats
 hipError_t launch_reconstruct_split(const ReconArgs& a, const SplitReconPlan& p, hipStream_t s) {
-    if (p.main_rows == 0 && p.main_cols == 0) return launch_part(a, p.bm, p.bn, p.slices, p.exact, s);
+    if (p.main_rows == 0 && p.main_cols == 0) return launch_part(a, p.bm, p.bn, p.slices, p.exact, p.halves, s);
     ReconArgs b = a;
     if (p.main_rows > 0) b.J = p.main_rows;
     else b.D = p.main_cols;
-    const hipError_t e = launch_part(b, p.bm, p.bn, p.slices, p.exact, s);
+    const hipError_t e = launch_part(b, p.bm, p.bn, p.slices, p.exact, p.halves, s);
     if (e != hipSuccess) return e;
     const LaunchEvents main = launch_events();                           // the launch that is reported as the family's
     b = a;
@@ -330,7 +334,7 @@ hipError_t launch_reconstruct_split(const ReconArgs& a, const SplitReconPlan& p,
     b.v = (const float*)a.v + p.main_cols;
     b.J -= p.main_rows;
     b.D -= p.main_cols;
-    const hipError_t e2 = launch_part(b, p.rest_bm, p.rest_bn, p.rest_slices, p.rest_exact, s);
+    const hipError_t e2 = launch_part(b, p.rest_bm, p.rest_bn, p.rest_slices, p.rest_exact, p.halves, s);
     launch_events().name = main.name;
     launch_events().blocks = main.blocks;
     return e2;

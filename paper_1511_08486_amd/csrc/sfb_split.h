@@ -159,8 +159,8 @@ struct SplitTile {
     static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, MB = BM / (16 * WM), NB = BN / (16 * WN), ROWS = BM + BN;
     static constexpr int MULTIPLIERS = WM * WN, THREADS = 64 * (MULTIPLIERS + SPLITTERS), WAVES = THREADS / 256;   // wavefronts a SIMD
     static constexpr int PLANE = ROWS * 64;
-    static constexpr int CTL = 6 * PLANE;                               // three buffers of two planes or two of three; control words
-    static constexpr int LDS = CTL + 32;
+    static constexpr int CTL = 6 * PLANE;                               // three buffers of two planes or two of three; control words; first halves
+    static constexpr int HALF = CTL + 32, LDS = HALF + 64 * MULTIPLIERS * 4 * (4 * MB * NB - 1);
     static_assert(LDS <= 160 * 1024, "LDS");
 
     // Among eight consecutive rows any one item falls into eight different 16-byte bank groups of 128 bytes, among
@@ -186,6 +186,8 @@ struct SplitTile {
     // 1.8e-7 of the norm in one sum, 0.9e-7 in two)
     static constexpr int SUMS = ROWS > 128 && ROWS < 256 && !EXACT ? 2 : 1;
     f32x4 acc[MB][NB], rest[REST ? MB : 1][REST ? NB : 1], odd[SUMS == 2 ? MB : 1][SUMS == 2 ? NB : 1];
+    float kept;                    // of the first half's sums: the one that LDS has no room for (128 x 128: 160 KB but 2016 bytes)
+    bool halved;                   // the others are there (uniform)
     int a_base, b_base;            // byte offset of this lane's item in the A and the B part
 
     __device__ __forceinline__ void init(int wave, int lane) {
@@ -193,6 +195,7 @@ struct SplitTile {
         const int item = 16 * ((lane >> 4) ^ swz(l16));                  // every row this lane reads is l16 modulo 16
         a_base = (wm * 16 * MB + l16) * 64 + item;
         b_base = (BM + wn * 16 * NB + l16) * 64 + item;
+        halved = false;
 #pragma unroll
         for (int i = 0; i < MB; ++i)
 #pragma unroll
@@ -202,7 +205,39 @@ struct SplitTile {
                 if constexpr (SUMS == 2) odd[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
             }
     }
-    struct Frags { sp_u32x4 a[MB], b[NB]; };
+    // The leading sums so far wait in LDS (a lane's own words), new ones start at zero: half as many roundings of sums half as large
+    __device__ __forceinline__ void set_aside(unsigned char* lds) {
+        split_for<0, MB * NB>([&](auto qc) {
+            constexpr int q = decltype(qc)::value;
+            f32x4& sum = acc[q / NB][q % NB];
+            if constexpr (q + 1 < MB * NB) {
+                *reinterpret_cast<f32x4*>(lds + HALF + (q * 64 * MULTIPLIERS + (int)threadIdx.x) * 16) = sum;
+            } else {
+#pragma unroll
+                for (int e = 0; e < 3; ++e)
+                    *reinterpret_cast<float*>(lds + HALF + q * 64 * MULTIPLIERS * 16 + (e * 64 * MULTIPLIERS + (int)threadIdx.x) * 4) = sum[e];
+                kept = sum[3];
+            }
+            sum = f32x4{0.f, 0.f, 0.f, 0.f};
+        });
+        halved = true;
+    }
+    __device__ __forceinline__ void add_halves(const unsigned char* lds) {
+        if (!halved) return;
+        split_for<0, MB * NB>([&](auto qc) {
+            constexpr int q = decltype(qc)::value;
+            f32x4& sum = acc[q / NB][q % NB];
+            if constexpr (q + 1 < MB * NB) {
+                sum += *reinterpret_cast<const f32x4*>(lds + HALF + (q * 64 * MULTIPLIERS + (int)threadIdx.x) * 16);
+            } else {
+#pragma unroll
+                for (int e = 0; e < 3; ++e)
+                    sum[e] += *reinterpret_cast<const float*>(lds + HALF + q * 64 * MULTIPLIERS * 16 + (e * 64 * MULTIPLIERS + (int)threadIdx.x) * 4);
+                sum[3] += kept;
+            }
+        });
+        halved = false;
+    }
     __device__ __forceinline__ sp_u32x4 item_a(const unsigned char* buf, int plane, int i) const {
         return *reinterpret_cast<const sp_u32x4*>(buf + a_base + plane * PLANE + i * 16 * 64);
     }
@@ -227,7 +262,7 @@ struct SplitTile {
     }
     // Two terms (planes h, l), chunks 0 .. n - 1; returns the first that was not taken.  A fragment is read into the registers that it takes
     // over one phase of products ahead of its use.
-    __device__ __forceinline__ int multiply2(int n, unsigned char* lds) {
+    __device__ __forceinline__ int multiply2(int n, int half, unsigned char* lds) {
         constexpr int BUF = 2 * PLANE;
         sp_u32x4 ah[MB], al[MB], bh[NB], bl[NB];
         int at = 0, c = 0;
@@ -249,6 +284,7 @@ struct SplitTile {
             phase<2, false, MB>(al, bh, [&](auto rc) { ah[decltype(rc)::value] = item_a(next, 0, decltype(rc)::value); });
             asm volatile("s_barrier" ::: "memory");                      // (its reads of the buffer that is written next are used up)
             ++c;
+            if (SUMS == 1 && c == half) set_aside(lds);
             return c < n && (uint32_t)__builtin_amdgcn_readfirstlane((int)stop) > (uint32_t)c;
         };
         while (step(std::false_type{}))
@@ -260,10 +296,11 @@ struct SplitTile {
     }
     // Three terms (planes h, m, l), chunks c0 .. n - 1.  The first products wait for two planes' fragments only, every other plane is read over
     // the products before its use, into the registers that are free by then.
-    __device__ __forceinline__ void multiply3(int c0, int n, unsigned char* lds) {
+    __device__ __forceinline__ void multiply3(int c0, int n, int half, unsigned char* lds) {
         constexpr int BUF = 3 * PLANE;
         for (int c = c0, at = 0; c < n; ++c, at = BUF - at) {
             const unsigned char* const now = lds + at;
+            if (c == half) set_aside(lds);
             sp_u32x4 ah[MB], a1[MB], bh[NB], b1[NB];
             split_for<0, (MB > NB ? MB : NB)>([&](auto rc) {
                 constexpr int r = decltype(rc)::value;
@@ -279,8 +316,10 @@ struct SplitTile {
             asm volatile("s_barrier" ::: "memory");
         }
     }
-    __device__ __forceinline__ void multiply(int n, unsigned char* lds) {
+    // halves: walks of so many chunks and more are summed in two halves, the second from the middle on or from where the split changes
+    __device__ __forceinline__ void multiply(int n, int halves, unsigned char* lds) {
         int done = 0;
+        const int half = n >= halves ? n / 2 : -1;
         auto merge = [&](int e, float rest_scale) {
 #pragma unroll
             for (int i = 0; i < MB; ++i)
@@ -306,13 +345,15 @@ struct SplitTile {
             SplitScale sc[2];
             if (scales(lds, sc)) {
                 split_barrier();
-                done = multiply2(n, lds);
+                done = multiply2(n, half, lds);
+                add_halves(lds);
                 merge(-(sc[0].e + sc[1].e), 1.0f / (1 << kSpLowExp));
             }
             if (done >= n) return;
         }
         split_barrier();
-        multiply3(done, n, lds);
+        multiply3(done, n, half < 0 || done == 0 ? half : done, lds);
+        add_halves(lds);
         merge(0, 1.f);
     }
 

@@ -104,3 +104,27 @@ def test_the_split_changes_at_any_chunk(k):
         _assert_rows_and_columns(0.5 * U.double(), x.double(), w.double())
     update.close()
     scores.close()
+
+
+@pytest.mark.parametrize("chosen,positive,J,D,N,most", [
+    (False, True, 1000, 4096, 4096, 2.2e-7),      # 3.0e-7 in one running sum (n roundings of a growing sum), 1.6e-7 in two
+    (False, False, 1000, 4096, 4096, 3.5e-7),     # 4.1e-7 and 3.0e-7
+    (True, False, 1000, 4096, 512, 1.15e-7),      # 1.3e-7 and 0.94e-7, scores 1.4e-7 and 1.1e-7
+    (True, True, 1000, 4096, 4096, 2.2e-7),
+])
+def test_long_and_chosen_sums_are_added_in_two_halves(chosen, positive, J, D, N, most):
+    """Error against fp64, of the norm, half way between what one running sum and two have."""
+    import paper_1511_08486_amd as sfb
+    dev, g = "cuda:0", torch.Generator(device="cuda:0").manual_seed(1)
+    draw = lambda *s: (torch.rand if positive else torch.randn)(s, generator=g, device=dev)  # noqa: E731
+    U0, V0, A, W = draw(N, J), draw(N, D), draw(N, D), draw(J, D)
+    W1, U, V = torch.zeros((J, D), device=dev), torch.empty((N, J), device=dev), torch.empty((N, D), device=dev)
+    ctx = sfb.Sfb("dml", J, D, 4, N // 4, device=dev)
+    if chosen:
+        ctx.set_plan(fwd_dma=13)
+    ctx.reconstruct_apply(W1, U0, V0, -1.0, scale=1.0)
+    ctx.compute_factors(W, sfb.SfbBatch(a=A, a2=torch.zeros_like(A)), torch.ones(N, dtype=torch.int32, device=dev), U, V)
+    ctx.sync()
+    ctx.close()
+    for got, want in ((W1, U0.double().T @ V0.double()), (0.5 * U, A.double() @ W.double().T)):
+        assert (got.double() - want).norm() <= most * want.norm()
