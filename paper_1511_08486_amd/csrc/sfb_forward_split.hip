@@ -146,7 +146,7 @@ __global__ __launch_bounds__((ScoreTile<BM, BN, EXACT>::THREADS), BM + BN == 256
         return x;
     });
     // The blocks of a lane are that many neighbouring classes: one access a row.  (Rows of Z are as long as there are classes: twelve of
-    // them pass 2^32 bytes from 89 million on, so a lane's rows are 64-bit offsets.)  Rows and columns beyond the matrix one by one.
+    // them pass 2^32 bytes from 89 million on, so a lane's rows are 64-bit offsets.)
     constexpr int WIDE = Tile::NB;
     typedef float f32_wide __attribute__((ext_vector_type(WIDE), aligned(4)));
     const int lane_row = m0 + wm * Tile::MB * 16 + 4 * quarter, col = n0 + wn * 16 * WIDE + WIDE * l16;
@@ -163,10 +163,8 @@ __global__ __launch_bounds__((ScoreTile<BM, BN, EXACT>::THREADS), BM + BN == 256
                 for (int j = 0; j < WIDE; ++j) x[j] = t.acc[i][j][e];
                 if (decltype(all)::value) {
                     *reinterpret_cast<f32_wide*>(at) = x;
-                } else if (lane_row + row < M) {
-#pragma unroll
-                    for (int j = 0; j < WIDE; ++j)
-                        if (col + j < N) at[j] = x[j];
+                } else if (lane_row + row < M && col < N) {              // (rows of Z are whole fours: what lies past N is nobody's)
+                    *reinterpret_cast<f32_wide*>(at) = x;
                 }
             }
     };

@@ -141,27 +141,44 @@ __global__ __launch_bounds__((ReconTile<BM, BN, SPLITTERS, EXACT>::THREADS), BM 
     const int lane_col = EVERY_OTHER ? 4 * l16 + 2 * (wn & 1) : WIDE * l16;
     const int first_col = d0 + (EVERY_OTHER ? (wn >> 1) * 64 : wn * 16 * WIDE), col = first_col + lane_col;
     static_assert(Tile::NB <= 4, "columns");
-    const bool inside = j0 + BM <= J && d0 + BN <= D;
+    const bool inside = j0 + BM <= J && d0 + BN <= D, whole = col + WIDE <= D;   // of the tile, of this lane's columns
     const uint32_t w_lane = (uint32_t)lane_row * (uint32_t)ldw * 4u + (uint32_t)lane_col * 4u;
     float* const w_out = W + (PLANES ? (int64_t)slice * J * ldw : 0);
     auto w_at = [&](int i, int e) {
         float* base = w_out + (int64_t)(j0 + row_of(i, e)) * ldw + first_col;
         return reinterpret_cast<float*>(reinterpret_cast<char*>(base) + w_lane);
     };
+    // (a tile that is not: no load under a condition, which would be waited for before the next.  Rows beyond J read an earlier
+    // one, columns beyond D the row's last words: 36 x 541, 192 pairs 7.8 us, entry by entry 7.9)
     f32_wide w[Tile::MB][4];
+    const bool part = !inside && d0 + BN > D && D % WIDE != 0;               // some lane's columns end within its words (uniform)
     if constexpr (!PLANES) {
+        const int col_ok = min(col, D - WIDE);                               // host: D >= 4
+        const uint32_t col_bytes = (uint32_t)col_ok * 4u, lane_bytes = (uint32_t)lane_row * (uint32_t)ldw * 4u + col_bytes;
 #pragma unroll
         for (int i = 0; i < Tile::MB; ++i)
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                if (inside) {
-                    w[i][e] = *reinterpret_cast<const f32_wide*>(w_at(i, e));
-                } else {
-                    const float* row = W + (int64_t)min(j0 + row_of(i, e) + lane_row, J - 1) * ldw;
-#pragma unroll
-                    for (int j = 0; j < WIDE; ++j) w[i][e][j] = row[min(col + j, D - 1)];
-                }
+                const float* base = W + (int64_t)min(j0 + row_of(i, e), J - 1) * ldw;
+                const uint32_t bytes = j0 + row_of(i, e) + lane_row < J ? lane_bytes : col_bytes;
+                if (inside) w[i][e] = *reinterpret_cast<const f32_wide*>(w_at(i, e));
+                else w[i][e] = *reinterpret_cast<const f32_wide*>(reinterpret_cast<const char*>(base) + bytes);
             }
+        if (part) {
+            const int early = col - col_ok;                                  // the words come down by that many
+#pragma unroll
+            for (int i = 0; i < Tile::MB; ++i)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    f32_wide& x = w[i][e];
+                    if (early & 1) {
+#pragma unroll
+                        for (int j = 0; j + 1 < WIDE; ++j) x[j] = x[j + 1];
+                    }
+                    if constexpr (WIDE == 4)
+                        if (early & 2) x[0] = x[2], x[1] = x[3];
+                }
+        }
     }
     t.mend([&](int i, int j) {
         const float* u = U + min(j0 + rs_u<BM, CB>((wm * Tile::MB + i) * 16 + l16), J - 1);
@@ -195,9 +212,12 @@ __global__ __launch_bounds__((ReconTile<BM, BN, SPLITTERS, EXACT>::THREADS), BM 
                 if (decltype(all)::value) {
                     *reinterpret_cast<f32_wide*>(w_at(i, e)) = x;
                 } else if (j0 + row_of(i, e) + lane_row < J) {
+                    if (whole) *reinterpret_cast<f32_wide*>(w_at(i, e)) = x;
+                    if (part && !whole) {
 #pragma unroll
-                    for (int j = 0; j < WIDE; ++j)
-                        if (col + j < D) w_at(i, e)[j] = x[j];
+                        for (int j = 0; j + 1 < WIDE; ++j)
+                            if (col + j < D) w_at(i, e)[j] = x[j];
+                    }
                 }
             }
     };

@@ -128,3 +128,34 @@ def test_long_and_chosen_sums_are_added_in_two_halves(chosen, positive, J, D, N,
     ctx.close()
     for got, want in ((W1, U0.double().T @ V0.double()), (0.5 * U, A.double() @ W.double().T)):
         assert (got.double() - want).norm() <= most * want.norm()
+
+
+@pytest.mark.parametrize("J,D,N", [(1001, 4096, 512), (600, 4096, 1024), (300, 4096, 512), (130, 1536, 252), (70, 192, 160)])
+@pytest.mark.parametrize("off", [-3, -2, -1, 0, 1, 2, 3])
+def test_tiles_at_the_end_of_rows_and_columns(J, D, N, off):
+    """Rows that end within a lane's words, rows of W apart and not: every entry is its own, and nothing beyond W is written."""
+    import paper_1511_08486_amd as sfb
+    dev, g = "cuda:0", torch.Generator(device="cuda:0").manual_seed(J)
+    D, J = D + off, J + (off & 1)
+    U, V = torch.randn((N, J), generator=g, device=dev), torch.randn((N, D), generator=g, device=dev)
+    ctx = sfb.Sfb("mlr", J, D, 1, N, device=dev)
+    for pitch in (D, D + 5):
+        whole = torch.full((J + 2, pitch), 7.0, device=dev)
+        W = whole[:J, :D]
+        ctx.reconstruct_apply(W, U, V, -1.0, scale=1.0)
+        ctx.sync()
+        assert ctx.last_kernel(2)[0] == "reconstruct_split_kernel"
+        got = W.double() - 7.0
+        room = 2.0 ** -24 * (6 * N / 16 + 8) * (U.double().abs().T @ V.double().abs()) + 2.0 ** -21
+        assert ((got - U.double().T @ V.double()).abs() <= room).all()
+        whole[:J, :D] = 7.0
+        assert (whole == 7.0).all()
+    # scores of as many classes, and their row of Z's last words
+    A, y, U, V = torch.randn((200, 640), generator=g, device=dev), torch.ones(200, dtype=torch.int32, device=dev), torch.full((200, J), float("nan"), device=dev), torch.empty((200, 640), device=dev)
+    W = torch.randn((J, 640), generator=g, device=dev)
+    ctx.close()
+    ctx = sfb.Sfb("dml", J, 640, 1, 200, device=dev)
+    ctx.compute_factors(W, sfb.SfbBatch(a=A, a2=torch.zeros_like(A)), y, U, V)
+    ctx.sync()
+    ctx.close()
+    _assert_rows_and_columns(0.5 * U.double(), A.double(), W.double())
