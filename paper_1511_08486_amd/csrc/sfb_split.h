@@ -9,13 +9,14 @@
 //     weight is at least 2^-16 of the leading one; what is left out is below 2^-24 of |a b| and unbiased.
 //   Two fp16 terms of the scaled value, s x = h + l / 2048 (h = fp16(s x), l = fp16(2048 (s x - h))): 22 significand bits and a sign, three
 //     quarters of all fp32 values exactly, the others 2^-24 off.  Three products; left out: a_l b_l, below 2^-22 and unbiased.  Half the matrix
-//     instructions and two thirds of the LDS traffic.  fp16 has few exponents, so a workgroup takes one power of two s per operand, from the
-//     largest value of its first 64 k (scaled to 2^9 .. 2^10).  l is kept 2048 times as large, in sums of its own, and so has the exponents of h:
-//     every value above 2^-12 scaled (2^-21 of that largest one) keeps its 22 bits, below it is at most 2^-36 scaled off.  (With l as it is, values lost
-//     bits from 2^-2 scaled on: samples or classes 2^-15 of their neighbours were 1e-6 of their own norm off, now 2e-7 at any factor.)  Every
-//     group of four values is looked at: none beyond 2^15 scaled, and none whose largest is below 2^-12 but not zero, so that a value is at most 2^-24
-//     of its group's largest off.  From the first chunk with a group outside on, the rest of the sum is taken in three terms (1000 x 4096 with 512
-//     samples: 25 us, 31 with operands over many magnitudes, which is what three terms take throughout).
+//     instructions and two thirds of the LDS traffic.  fp16 has few exponents, so a workgroup takes one power of two s per operand, from its
+//     first 64 k.  l is kept 2048 times as large, in sums of its own, and so has the exponents of h: every value between 2^-12 and 2^15
+//     scaled keeps its 22 bits, below it is at most 2^-36 scaled off.  (With l as it is, values lost bits from 2^-2 scaled on: samples
+//     or classes 2^-15 of their neighbours were 1e-6 of their own norm off, now 2e-7 at any factor.)  Every group of four values is looked
+//     at: none beyond 2^15 scaled, and none whose largest is below 2^-12 but not zero, so that a value is at most 2^-24 of its group's largest
+//     off.  From the first chunk with a group outside on, the rest of the sum is taken in three terms.  s puts the first 64 k in the middle of that
+//     window: softmax factors of 3326 classes are 3e-4 in most blocks until a label comes, and 1 then (update with 532 pairs: with 2^6 above the
+//     first values and 2^21 below 21.1 us, with the window's middle 18.9).
 // Sums of 256 products and more are closer to fp64 with two terms than with the three terms in one running sum that they replace; of the norm,
 // operands of mixed signs (then -> two terms here): scores 1000 x 4096, 512 samples 2.5e-7 -> 1.8e-7, update 2.4e-7 -> 1.7e-7;
 // 600 x 4096 with 1024: 2.9e-7 -> 1.9e-7 and 2.4e-7 -> 1.7e-7.  Three terms here: 1.4e-7 and 1.3e-7 (1000 x 4096).  Either way the smaller
@@ -42,9 +43,10 @@ typedef __attribute__((address_space(3))) uint32_t sp_lds_u32;             // (a
 typedef float sp_f32x4u __attribute__((ext_vector_type(4), aligned(4)));   // a 16-byte access at any 4-byte address
 
 constexpr int kSpChunk = 32;       // k per chunk
-constexpr int kSpTopExp = 9;       // two terms: the first chunks' largest value is scaled to 2^9 .. 2^10
+constexpr int kSpTopExp = 14;      // two terms: values stay below 2^15 scaled,
+constexpr int kSpLeastExp = -12;   // the largest of a group of four above 2^-12 (or it is zero),
+constexpr int kSpTopExpLeast = 2;  // and the first chunks' largest is above 2^2
 constexpr int kSpBlankExp = 4;     // the scale's exponent where they are all zero
-constexpr int kSpLeastExp = -12;   // the largest of a group of four stays above 2^-12 scaled (or is zero)
 constexpr int kSpLowExp = 11;      // the second term is kept 2^11 times as large
 
 // every wavefront of the workgroup; this wavefront's LDS writes are visible and its LDS reads done
@@ -129,15 +131,16 @@ struct SplitScale {
     float s, s_low;
     int e;                         // s = 2^e, s_low = 2^(e + 11)
     uint32_t most, least_m1;       // largest allowed magnitude; smallest one of a group that is not all zero, minus one
-    // m: largest magnitude of the first chunks.  false: no such scale, the three-term products take the tile
-    __device__ __forceinline__ bool set(uint32_t m) {
-        const int x = (int)(m >> 23);
-        e = m == 0 ? kSpBlankExp : kSpTopExp + 127 - x;
+    // m: largest magnitude of the first chunks, low_m1: smallest largest of a group of them that is not all zero, minus one.  What they
+    // leave of the window lies half above them and half below.  false: no such scale, the three-term products take the tile.
+    __device__ __forceinline__ bool set(uint32_t m, uint32_t low_m1) {
+        const int x = (int)(m >> 23), span = x - (int)((low_m1 + 1u) >> 23);
+        e = m == 0 ? kSpBlankExp : max(kSpTopExp - (kSpTopExp - kSpLeastExp - span) / 2, kSpTopExpLeast) + 127 - x;
         s = __uint_as_float((uint32_t)(127 + e) << 23);
         s_low = __uint_as_float((uint32_t)(127 + e + kSpLowExp) << 23);
-        most = (uint32_t)min(127 + 15 - e, 254) << 23;
+        most = (uint32_t)min(127 + kSpTopExp + 1 - e, 254) << 23;
         least_m1 = ((uint32_t)(127 + kSpLeastExp - e) << 23) - 1u;
-        return m == 0 || (x >= 24 && x < 255);
+        return m == 0 || (x >= 28 && x < 255 && span <= kSpTopExp - kSpLeastExp);
     }
 };
 
@@ -173,8 +176,8 @@ struct SplitTile {
     static __device__ __forceinline__ bool scales(const unsigned char* lds, SplitScale (&sc)[2]) {
         const uint4 all = *reinterpret_cast<const uint4*>(lds + CTL + 16);
         auto uniform = [](uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); };
-        const bool a = sc[0].set(uniform(all.x)), b = sc[1].set(uniform(all.z));
-        return a && b && ~uniform(all.y) >= sc[0].least_m1 && ~uniform(all.w) >= sc[1].least_m1;
+        const bool a = sc[0].set(uniform(all.x), ~uniform(all.y)), b = sc[1].set(uniform(all.z), ~uniform(all.w));
+        return a && b;
     }
 
     static __device__ __forceinline__ int threes(int n) { return n > 0 ? n / 3 * 3 : 0; }   // of n, in whole threes

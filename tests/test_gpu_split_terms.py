@@ -159,3 +159,20 @@ def test_tiles_at_the_end_of_rows_and_columns(J, D, N, off):
     ctx.sync()
     ctx.close()
     _assert_rows_and_columns(0.5 * U.double(), A.double(), W.double())
+
+
+@pytest.mark.parametrize("J,D,N", [(1000, 4096, 512), (3326, 376, 532)])
+@pytest.mark.parametrize("deviation", [0.1, 3.0, 6.0])
+def test_softmax_factors(J, D, N, deviation):
+    """Factors of models that are new, half way and done: ones at the labels, which most blocks of many classes meet late, and probabilities
+    down to e^-60 elsewhere."""
+    import paper_1511_08486_amd as sfb
+    dev, g = "cuda:0", torch.Generator(device="cuda:0").manual_seed(J)
+    p = torch.softmax(deviation * torch.randn((N, J), generator=g, device=dev), 1)
+    U = p.scatter_add(1, torch.multinomial(p, 1, generator=g), torch.full((N, 1), -1.0, device=dev))
+    V, W = torch.randn((N, D), generator=g, device=dev) / D ** 0.5, torch.zeros((J, D), device=dev)
+    ctx = sfb.Sfb("mlr", J, D, 4, N // 4, device=dev)
+    ctx.reconstruct_apply(W, U, V, -1.0, scale=1.0)
+    ctx.sync()
+    ctx.close()
+    _assert_rows_and_columns(W.double(), U.double().T, V.double().T)
