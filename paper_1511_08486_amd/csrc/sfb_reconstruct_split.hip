@@ -268,12 +268,9 @@ static hipError_t launch_split(const ReconArgs& a, int slices, int halves, hipSt
 // three; 353 x 80 with 308: 9.6 and 8.1; 193 x 1473 with 476: 11.9 and 10.7; 964 x 242 with 332: the same).
 static SplitReconPlan plan_part(int64_t J, int64_t D, int64_t N, size_t room, bool exact, bool alone) {
     static const struct { int bm, bn, resident, terms; double start_us, chunk_us, lone_us, round_us; } tiles[8] = {
-        {128, 128, 1, 2, 8.0, 0.80, 0.80, 2.8}, {96, 128, 1, 2, 7.8, 0.64, 0.64, 2.5}, {64, 128, 1, 2, 7.5, 0.62, 0.62, 1.5}, {64, 64, 2, 2, 6.7, 0.36, 0.46, 0.0},
-        {128, 128, 1, 3, 7.0, 1.25, 1.25, 3.5}, {96, 128, 1, 3, 6.2, 0.95, 0.95, 3.5}, {64, 128, 1, 3, 6.8, 0.78, 0.78, 3.0}, {64, 64, 2, 3, 5.2, 0.49, 0.48, 0.0}};
+        {128, 128, 1, 2, 6.4, 0.88, 0.88, 0.4}, {96, 128, 1, 2, 6.5, 0.76, 0.76, 1.5}, {64, 128, 1, 2, 6.2, 0.68, 0.68, 1.4}, {64, 64, 2, 2, 5.4, 0.34, 0.44, 0.9},
+        {128, 128, 1, 3, 5.4, 1.02, 1.02, 1.0}, {96, 128, 1, 3, 5.4, 0.91, 0.91, 1.8}, {64, 128, 1, 3, 5.0, 0.82, 0.82, 0.9}, {64, 64, 2, 3, 4.8, 0.39, 0.46, 0.7}};
     const int64_t chunks = (N + kSpChunk - 1) / kSpChunk;
-    // (walks of more than 32 chunks: a second round that is not full takes up to a tenth less than its estimate, 1412 x 4395 with 1256 pairs
-    // 79.7 us in one launch and 86.9 in two; up to there two launches go by the estimate, 1001 x 4100 with 488: 38.7 and 35.3)
-    const double margin = chunks > 32 ? 0.97 : 1.0;
     SplitReconPlan best{0, 0, 1, true, 1e300, 0, 0, 0, 0, 1, true, 0};
     for (const auto& t : tiles) {
         if (exact && t.terms == 2) continue;
@@ -284,9 +281,9 @@ static SplitReconPlan plan_part(int64_t J, int64_t D, int64_t N, size_t room, bo
             const int64_t wgs = ((rows + t.bm - 1) / t.bm) * ((cols + t.bn - 1) / t.bn) * s;
             const double w_mb = 8e-6 * (double)rows * (double)cols, rounds = (double)((wgs + 255) / 256);
             const double deep = (double)((wgs + 256 * t.resident - 1) / (256 * t.resident));
-            const double a = t.lone_us * deep, b = t.chunk_us * rounds;
-            return t.start_us + (double)per * (a > b ? a : b) + t.round_us * (rounds - 1.0) +
-                   (s == 1 ? 0.25 * w_mb : 3.2 + 0.13 * (double)s * w_mb);        // planes written and read, W read and written
+            const double more = t.resident == 1 ? rounds - 1.0 : deep - (rounds > 1.0 ? 0.0 : 1.0);
+            return t.start_us + (double)per * (rounds > 1.0 ? t.chunk_us * rounds : t.lone_us) + t.round_us * more +
+                   (s == 1 ? 0.12 * w_mb : 1.3 + 0.27 * (double)s * w_mb);        // planes written and read, W read and written
         };
         for (int64_t s = 1; s <= 64 && (s == 1 || ((size_t)(s * J * D) * sizeof(float) <= room && chunks >= 2 * s && n * s <= 1536)); ++s) {
             const int64_t per = (chunks + s - 1) / s;
@@ -300,12 +297,12 @@ static SplitReconPlan plan_part(int64_t J, int64_t D, int64_t N, size_t room, bo
         if (cols > 0 && (((J + t.bm - 1) / t.bm) * (cols / t.bn) + 255) / 256 < (n + 255) / 256) {
             const SplitReconPlan rest = plan_part(J, D - cols, N, room, exact, false);
             const double us = cost(J, cols, 1, chunks) + rest.us;
-            if (us < margin * best.us) best = SplitReconPlan{t.bm, t.bn, 1, ex, us, 0, (int)cols, rest.bm, rest.bn, rest.slices, rest.exact, 0};
+            if (us < best.us) best = SplitReconPlan{t.bm, t.bn, 1, ex, us, 0, (int)cols, rest.bm, rest.bn, rest.slices, rest.exact, 0};
         }
         if (rows > 0 && ((rows / t.bm) * ((D + t.bn - 1) / t.bn) + 255) / 256 < (n + 255) / 256) {
             const SplitReconPlan rest = plan_part(J - rows, D, N, room, exact, false);
             const double us = cost(rows, D, 1, chunks) + rest.us;
-            if (us < margin * best.us) best = SplitReconPlan{t.bm, t.bn, 1, ex, us, (int)rows, 0, rest.bm, rest.bn, rest.slices, rest.exact, 0};
+            if (us < best.us) best = SplitReconPlan{t.bm, t.bn, 1, ex, us, (int)rows, 0, rest.bm, rest.bn, rest.slices, rest.exact, 0};
         }
     }
     return best;

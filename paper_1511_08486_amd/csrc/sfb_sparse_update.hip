@@ -266,7 +266,7 @@ double sparse_update_us(int64_t N, int64_t J, int64_t D, int64_t stored) {
     const double n_jb = (double)((J + kSuClasses - 1) / kSuClasses), splits = (double)sparse_update_splits(J, D);
     const double rounds = (double)(int64_t)((n_jb * splits + 255.0) / 256.0);
     const double walk = rounds * 1.12e-3 * (double)stored / splits, w_us = 2e-6 * (double)J * (double)D;
-    return 8.0 + 1.2e-6 * (double)N * (double)D + 7.0 + (walk > w_us ? walk : w_us);
+    return 6.0 + 1.2e-6 * (double)N * (double)D + 7.0 + (walk > w_us ? walk : w_us);
 }
 
 hipError_t launch_sparse_update(const ReconArgs& a, int64_t stored, void* workspace, hipStream_t s) {
