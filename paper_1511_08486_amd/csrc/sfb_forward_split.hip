@@ -212,7 +212,7 @@ static hipError_t launch_split_tile(const FwdArgs& a, const FwdPlan& p, hipStrea
 // Tile, slices of D and terms, by a cost in microseconds fitted to 22 shapes (J = 40 to 4000, D = 300 to 8192, N = 128 to 11200, every
 // tile in two and three terms, one MI355X).  A chunk of 32 columns costs a compute unit (two terms / three) 0.74 / 1.08 us with 256 rows
 // staged, 0.58 / 0.78 with 192 and 0.36 / 0.47 with 128 (two 64 x 64 workgroups share a unit; one alone 0.40 / 0.48), every further
-// round of 256 workgroups restarts for 1.7 us, and a slice's partial scores are written and read back at about 2.2 TB/s together, one plane after
+// round of 256 workgroups restarts for 1.7 us, and a slice's partial scores are written and read back at about 1.9 TB/s together, one plane after
 // the other: 0.1 us more each (3 classes x 3072, 976 samples: 20 slices instead of 27, 14.9 -> 13.0 us; 20 x 5504: 18.7 -> 16.7).
 // Two terms first look at their operands, 1 to 2 us longer to start, and win from 4 (large tiles) to 16 chunks a workgroup on: 1000 x 4096, 512
 // samples (16 chunks) 25.6 against 30.3 us, 333 x 1001 with 228 (4) 8.3 against 7.6.  Below eight chunks (256 columns) they are also the less exact ones:
@@ -238,7 +238,7 @@ FwdPlan plan_forward_split(int64_t n_rows, int64_t J, int64_t D, size_t most, bo
             const double rounds = (double)((n * s + 255) / 256);
             const double deep = (double)((n * s + 256 * t.resident - 1) / (256 * t.resident));
             const double a = t.lone_us * deep, b = t.chunk_us * rounds;
-            const double us = t.start_us + (double)per * (a > b ? a : b) + (t.resident == 1 ? 1.7 * (rounds - 1.0) : 0.0) + (double)s * (plane / 2.2e6 + 0.1);
+            const double us = t.start_us + (double)per * (a > b ? a : b) + (t.resident == 1 ? 1.7 * (rounds - 1.0) : 0.0) + (double)s * (plane / 1.9e6 + 0.1);
             if (us < best * (1.0 - 1e-9)) {
                 best = us;
                 p.bm = t.bm; p.bn = t.bn; p.split_k = (int)s;
