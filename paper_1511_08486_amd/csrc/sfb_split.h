@@ -37,7 +37,6 @@ namespace sfb {
 
 typedef __bf16 sp_bf16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 sp_f16x8 __attribute__((ext_vector_type(8)));
-typedef _Float16 sp_f16x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t sp_u32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) uint32_t sp_lds_u32;             // (a flat load would wait for every load on its way)
 typedef float sp_f32x4u __attribute__((ext_vector_type(4), aligned(4)));   // a 16-byte access at any 4-byte address
@@ -160,7 +159,7 @@ __device__ __forceinline__ uint32_t split_max16(uint32_t x) {
 template <int BM_, int BN_, int WM_, int WN_, int SPLITTERS, bool EXACT>
 struct SplitTile {
     static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, MB = BM / (16 * WM), NB = BN / (16 * WN), ROWS = BM + BN;
-    static constexpr int MULTIPLIERS = WM * WN, THREADS = 64 * (MULTIPLIERS + SPLITTERS), WAVES = THREADS / 256;   // wavefronts a SIMD
+    static constexpr int MULTIPLIERS = WM * WN, THREADS = 64 * (MULTIPLIERS + SPLITTERS);
     static constexpr int PLANE = ROWS * 64;
     static constexpr int CTL = 6 * PLANE;                               // three buffers of two planes or two of three; control words; first halves
     static constexpr int HALF = CTL + 32, LDS = HALF + 64 * MULTIPLIERS * 4 * (4 * MB * NB - 1);

@@ -272,7 +272,7 @@ def _split_update(J, D, P, B, V0, active=None, seed=0, chosen=True):
     (515, 2051, 4, 64, (64, 128), False, True),                 # an odd last column
     (515, 2051, 4, 64, (64, 128), False, False),
     (1001, 4093, 6, 85, (128, 128), False, False),
-    (600, 4095, 4, 100, (128, 128), False, False),              # sums that start anew half way, at six chunks of thirteen
+    (600, 4095, 4, 100, (128, 128), False, False),              # thirteen chunks: one more than whole rounds of three
     (602, 779, 3, 343, (64, 128), True, True),                  # slices of the pairs
     (602, 779, 3, 343, (64, 128), True, False),
     (65, 66, 3, 350, (64, 64), True, True),

@@ -176,3 +176,89 @@ def test_softmax_factors(J, D, N, deviation):
     ctx.sync()
     ctx.close()
     _assert_rows_and_columns(W.double(), U.double().T, V.double().T)
+
+
+# 1 + 2^-12 + 2^-23 has 24 bits: exact in three terms, one bit short in two
+_ODD = 1.0 + 2.0 ** -12 + 2.0 ** -23
+
+
+@pytest.mark.parametrize("J,D,N,blocks", [                      # update tiles and workgroups
+    (1000, 4096, 512, 8 * 32),                                  # 128 x 128
+    (517, 3618, 482, 6 * 29),                                   # 96 x 128
+    (213, 4520, 392, 4 * 36),                                   # 64 x 128
+    (1000, 1000, 1400, 256),                                    # 64 x 64, eight splitting wavefronts
+    (2908, 647, 291, 46 * 11),                                  # 64 x 64, four
+    (907, 755, 3800, None),                                     # with slices of the pairs
+    (2775, 135, 1130, None),
+    (1101, 76, 5676, None),
+    (909, 665, 1224, None),
+])
+@pytest.mark.parametrize("masked", [False, True])
+def test_update_tiles_in_two_terms(J, D, N, blocks, masked):
+    """The split that ran, by a value that tells them apart; columns of every magnitude; pairs that end two terms half way, and an infinity
+    in the last of them."""
+    import paper_1511_08486_amd as sfb
+    dev, g = "cuda:0", torch.Generator(device="cuda:0").manual_seed(J)
+    P = next(p for p in range(2, 65) if N % p == 0) if masked else 1
+    active = [p != 0 for p in range(P)] if masked else None
+    live = torch.ones(N, dtype=torch.bool, device=dev)
+    ctx, W = sfb.Sfb("mlr", J, D, P, N // P, device=dev), torch.zeros((J, D), device=dev)
+    if masked:
+        live[:N // P] = False
+
+    def update(U, V):
+        ctx.reconstruct_apply(W.zero_(), U, V, -1.0, scale=1.0, active=active)
+        ctx.sync()
+        assert ctx.last_kernel(2)[0] == "reconstruct_split_kernel" and (blocks is None or ctx.last_kernel(2)[1] == blocks)
+        return W.double()
+
+    U, V = torch.zeros((N, J), device=dev), torch.zeros((N, D), device=dev)
+    U[N - 1], V[N - 1] = _ODD, 1.0
+    got = update(U, V)
+    assert ((got - _ODD).abs() <= 2.0 ** -22).all() and (got != _ODD).all()
+    U, V = torch.randn((N, J), generator=g, device=dev), torch.randn((N, D), generator=g, device=dev)
+    U = _spread("rows in between", U.T.contiguous()).T.contiguous()
+    if masked:
+        U[~live] = float("nan")
+        V[~live] = float("inf")
+    _assert_rows_and_columns(update(U, V), U[live].double().T, V[live].double().T)
+    V[N // 2:] *= 1e7
+    _assert_rows_and_columns(update(U, V), U[live].double().T, V[live].double().T)
+    V[N - 1, D - 1] = float("inf")
+    got = update(U, V)
+    assert torch.equal(got[:, D - 1], torch.sign(U[N - 1].double()) * float("inf"))
+    _assert_rows_and_columns(got[:, :D - 1], U[live].double().T, V[live, :D - 1].double().T)
+    ctx.close()
+
+
+@pytest.mark.parametrize("J,D,N,blocks", [                      # score tiles and workgroups
+    (2698, 588, 713, 6 * 22),                                   # 128 x 128
+    (649, 651, 2779, 22 * 11),                                  # 128 x 64
+    (2783, 694, 642, 11 * 22),                                  # 64 x 128
+    (75, 2046, 3328, 52 * 2 * 2),                               # 64 x 64, with slices of the columns
+    (1000, 4096, 512, 4 * 8 * 8),
+])
+def test_score_tiles_in_two_terms(J, D, N, blocks):
+    import paper_1511_08486_amd as sfb
+    dev, g = "cuda:0", torch.Generator(device="cuda:0").manual_seed(J)
+    ctx, y = sfb.Sfb("dml", J, D, 1, N, device=dev), torch.ones(N, dtype=torch.int32, device=dev)   # similar pairs: u = 2 z
+    U, V = torch.empty((N, J), device=dev), torch.empty((N, D), device=dev)
+
+    def scores(A, W, shift=0.0):
+        ctx.compute_factors(W, sfb.SfbBatch(a=A + shift, a2=torch.full_like(A, shift)), y, U, V)
+        ctx.sync()
+        assert ctx.last_kernel(0)[0] == "scores_split_kernel" and (blocks is None or ctx.last_kernel(0)[1] == blocks)
+        return 0.5 * U.double()
+
+    A, W = torch.zeros((N, D), device=dev), torch.zeros((J, D), device=dev)
+    A[:, 0], W[:, 0] = _ODD, 1.0
+    got = scores(A, W)
+    assert ((got - _ODD).abs() <= 2.0 ** -22).all() and (got != _ODD).all()
+    A, W = torch.randn((N, D), generator=g, device=dev), torch.randn((J, D), generator=g, device=dev)
+    got = scores(A, W, 0.25)
+    _assert_rows_and_columns(got, V.double(), W.double())       # (of the differences as they are)
+    A = _spread("rows in between", A)
+    _assert_rows_and_columns(scores(A, W), A.double(), W.double())
+    W[:, D // 2:] *= 1e7
+    _assert_rows_and_columns(scores(A, W), A.double(), W.double())
+    ctx.close()
