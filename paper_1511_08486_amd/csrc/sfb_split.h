@@ -267,7 +267,8 @@ struct SplitTile {
     __device__ __forceinline__ int multiply2(int n, int half, unsigned char* lds) {
         constexpr int BUF = 2 * PLANE;
         sp_u32x4 ah[MB], al[MB], bh[NB], bl[NB];
-        int at = 0, c = 0;
+        int at = 0, c = 0, end = SUMS == 1 && half > 0 ? half : n;
+        bool go;
 #pragma unroll
         for (int i = 0; i < MB; ++i) ah[i] = item_a(lds, 0, i);
 #pragma unroll
@@ -286,11 +287,16 @@ struct SplitTile {
             phase<2, false, MB>(al, bh, [&](auto rc) { ah[decltype(rc)::value] = item_a(next, 0, decltype(rc)::value); });
             asm volatile("s_barrier" ::: "memory");                      // (its reads of the buffer that is written next are used up)
             ++c;
-            if (SUMS == 1 && c == half) set_aside(lds);
-            return c < n && (uint32_t)__builtin_amdgcn_readfirstlane((int)stop) > (uint32_t)c;
+            go = (uint32_t)__builtin_amdgcn_readfirstlane((int)stop) > (uint32_t)c;
+            return go && c < end;
         };
-        while (step(std::false_type{}))
-            if (SUMS == 2 && !step(std::bool_constant<SUMS == 2>{})) break;
+        for (;;) {
+            while (step(std::false_type{}))
+                if (SUMS == 2 && !step(std::bool_constant<SUMS == 2>{})) break;
+            if (SUMS == 2 || !go || c == n) break;
+            set_aside(lds);                                              // (c == half; not in the loop, whose registers it would take)
+            end = n;
+        }
         // (the splitting wavefronts see it behind three steps, or at the end)
         const int whole = threes(n - 2);
         for (int b = c; b < n && (b > whole || b % 3 != 0); ++b) asm volatile("s_barrier" ::: "memory");
