@@ -283,7 +283,8 @@ static SplitReconPlan plan_part(int64_t J, int64_t D, int64_t N, size_t room, bo
             const double deep = (double)((wgs + 256 * t.resident - 1) / (256 * t.resident));
             const double more = t.resident == 1 ? rounds - 1.0 : deep - (rounds > 1.0 ? 0.0 : 1.0);
             return t.start_us + (double)per * (rounds > 1.0 ? t.chunk_us * rounds : t.lone_us) + t.round_us * more +
-                   (s == 1 ? 0.12 * w_mb : 1.3 + 0.27 * (double)s * w_mb);        // planes written and read, W read and written
+                   (s == 1 ? 0.12 * w_mb                                          // W read and written
+                           : 1.3 + 0.27 * (double)s * w_mb + (cols < 3600 ? (double)cols / 1500.0 : 2.4));   // planes written and read; a later W
         };
         for (int64_t s = 1; s <= 64 && (s == 1 || ((size_t)(s * J * D) * sizeof(float) <= room && chunks >= 2 * s && n * s <= 1536)); ++s) {
             const int64_t per = (chunks + s - 1) / s;
