@@ -375,13 +375,14 @@ size_t few_workspace(int64_t N, int64_t J, int64_t D) {
 
 // Late stores are for batches that, with their V, are more than the L2s hold: the loads come first at the rate of memory,
 // and the stores, which take as long again, run under the products; past the caches, so that the kernel's end has nothing
-// to write back.  fp32, ten classes x 784 columns: 12000 samples 24.0 -> 21.3 us, 10600 23.8 -> 20.8, 8000 17.9 -> 17.1, 6000
-// 16.6 -> 16.3; pairs 28.2 -> 24.7, 27.7 -> 23.5, 20.9 -> 18.1, 18.3 -> 15.9.  Smaller batches have a piece or two to a thread
-// and lose (256 columns x 512 samples 6.6 -> 7.7), bf16 rows too (12000 samples 23.4 -> 24.7).  With two class blocks and
-// hundreds of rows to a workgroup the products bound the kernel (twenty classes, 246 rows of 128 columns: 63.5 -> 66.6; 129 rows
-// of 256: 32.5 -> 30.7).
+// to write back.  Steps of fp32, us, one batch again and again / a ring of batches of 1.2 GB: ten classes x 784 columns, 12000 samples 27.5 -> 24.6 /
+// 32.9 -> 26.4, 8000 samples 22.0 -> 20.5 / 25.7 -> 22.8; thirteen classes x 1000, 9000 samples 30.6 -> 27.9 / 36.7 -> 29.8, pairs 36.5 -> 31.6 / 44.1 -> 34.0.
+// Smaller batches have a piece or two to a thread and lose (256 columns x 512 samples 6.6 -> 7.7), bf16 rows too (12000
+// samples 23.4 -> 24.7).  Batches of more than 256 workgroups gain where they are new and lose where they are not (thirteen classes x 1664, 7208 samples
+// 71.9 -> 73.9 / 80.0 -> 78.6).  With two class blocks the products bound the kernel where a workgroup has hundreds of rows (twenty classes, 246 rows of 128 columns:
+// 63.5 -> 66.6; 129 rows of 256: 32.5 -> 30.7) or follows another (twenty-four x 1280, 9368 samples 82.0 -> 86.4 / 90.4 -> 91.3; pairs gain there too).
 static bool few_late(const FewArgs& a, int rows) {
-    return !a.bf16 && (int64_t)a.n_rows * a.D * 4 >= (int64_t)22 << 20 && (a.J <= 16 || rows <= 192);
+    return !a.bf16 && (int64_t)a.n_rows * a.D * 4 >= (int64_t)22 << 20 && (a.J <= 16 || (rows <= 192 && (a.diff || (a.n_rows + rows - 1) / rows <= 256)));
 }
 
 template <typename TIn, bool DIFF, int NJ, int UPDATE, bool LATE>
