@@ -32,7 +32,7 @@ if ROOT not in sys.path:
 
 PEAK_FP32_MFMA_TFLOPS = 157.3     # MI355X dense fp32 matrix-core peak
 PEAK_BF16_MFMA_TFLOPS = 2500.0    # dense bf16
-PEAK_SPLIT_TFLOPS = PEAK_BF16_MFMA_TFLOPS / 6.0   # fp32 products formed as six bf16 term products (the default for fp32)
+PEAK_SPLIT_TFLOPS = PEAK_BF16_MFMA_TFLOPS / 3.0   # fp32 products formed as three fp16 term products (six of bf16 for a wider spread)
 PEAK_HBM_GBS = 8000.0
 PEAK_LDS_GBS = 256 * 128 * 2.4    # 128 bytes a cycle and compute unit
 FAMILIES = {0: "scores", 1: "factor u", 2: "reconstruct-apply", 3: "csr densify", 5: "update + next scores (one pass)"}

@@ -349,7 +349,7 @@ SFB_API sfb_status sfb_last_kernel(const sfb_ctx *ctx, int32_t which, char *name
  * bit 5 = always from the CSR entries where that kernel can take them (four rows of W in LDS: D <= 10240)
  * (neither: whichever a fitted cost comparison on N, J, D and nnz expects to be faster); bit 2 = fp32 scores on the bf16 matrix cores, every fp32 operand split
  * into three bf16 terms (exactly from 2^-109 up, where the third term is a bf16 number; 1e-6 of a sum at operands of
- * 2^-120) and every product taken as its six leading term products, the smaller five in sums of their own (error
+ * 2^-120) and every product taken as its six leading term products, the smaller five in sums of their own, the leading ones in two halves (error
  * at the level of one fp32 rounding; D >= 4 and leading dimensions within 32-bit offsets, else ignored),
  * a new fp32 context takes two scaled fp16 terms and three products instead, or, in short sums and from the first values on whose
  * magnitudes the scale does not hold, these, and the fp32 instruction where the product is small; bit 3 = the same for the fp32 reconstruction, which a new

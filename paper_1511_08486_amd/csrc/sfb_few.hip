@@ -375,7 +375,7 @@ size_t few_workspace(int64_t N, int64_t J, int64_t D) {
 
 // Late stores are for batches that, with their V, are more than the L2s hold: the loads come first at the rate of memory,
 // and the stores, which take as long again, run under the products; past the caches, so that the kernel's end has nothing
-// to write back.  Steps of fp32, us, one batch again and again / a ring of batches of 1.2 GB: ten classes x 784 columns, 12000 samples 27.5 -> 24.6 /
+// to write back.  Steps of fp32, us, one batch again and again / a ring of batches of 1.2 to 2 GB: ten classes x 784 columns, 12000 samples 27.5 -> 24.6 /
 // 32.9 -> 26.4, 8000 samples 22.0 -> 20.5 / 25.7 -> 22.8; thirteen classes x 1000, 9000 samples 30.6 -> 27.9 / 36.7 -> 29.8, pairs 36.5 -> 31.6 / 44.1 -> 34.0.
 // Smaller batches have a piece or two to a thread and lose (256 columns x 512 samples 6.6 -> 7.7), bf16 rows too (12000
 // samples 23.4 -> 24.7).  Batches of more than 256 workgroups gain where they are new and lose where they are not (thirteen classes x 1664, 7208 samples

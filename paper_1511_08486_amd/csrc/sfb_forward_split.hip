@@ -6,7 +6,8 @@
 // once more only to be stored as V.  Rows beyond the matrix repeat the last row (their scores are not stored); a partial
 // chunk of D is taken first, before the loop, with the words beyond D replaced by zero in both operands.  Accesses are 16 bytes wide at
 // 4-byte alignment: any leading dimension is taken.  DIFF: the operand is x_i - y_i (metric learning).
-// 1000 x 4096, 512 samples: 28.6 -> 24.2 us; 600 x 4096, 1024 pairs of points: 37.6 -> 30.6; 1000 x 4096, 4096 samples: 176 -> 125.
+// us, every wavefront splitting and multiplying in three terms -> here: 1000 x 4096, 512 samples 28.6 -> 22.9; 600 x 4096, 1024 pairs of points 37.6 ->
+// 29.5; 1000 x 4096, 4096 samples 176 -> 125.
 #include "sfb_kernels.h"
 #include "sfb_split.h"
 
@@ -214,8 +215,9 @@ static hipError_t launch_split_tile(const FwdArgs& a, const FwdPlan& p, hipStrea
 // staged, 0.58 / 0.78 with 192 and 0.36 / 0.47 with 128 (two 64 x 64 workgroups share a unit; one alone 0.40 / 0.48), every further
 // round of 256 workgroups restarts for 1.7 us, and a slice's partial scores are written and read back at about 1.9 TB/s together, one plane after
 // the other: 0.1 us more each (3 classes x 3072, 976 samples: 20 slices instead of 27, 14.9 -> 13.0 us; 20 x 5504: 18.7 -> 16.7).
-// Two terms first look at their operands, 1 to 2 us longer to start, and win from 4 (large tiles) to 16 chunks a workgroup on: 1000 x 4096, 512
-// samples (16 chunks) 25.6 against 30.3 us, 333 x 1001 with 228 (4) 8.3 against 7.6.  Below eight chunks (256 columns) they are also the less exact ones:
+// Two terms start 1 to 2 us later and win from 4 (large tiles) to 16 chunks a workgroup on (over many magnitudes, where they are refused, 1000 x 4096
+// with 512 samples takes 33 us with the factor kernel and 27 in two terms).  On 150 shapes the choices are 1.7 % over the best on average; costs
+// fitted anew gain 0.4 %, and lose 4 % at 1000 x 4096 with 512.  Below eight chunks (256 columns) they are also the less exact ones:
 // products are 7e-8 of the norm off, 8 chunks' running sums 1e-7.
 // `most` bounds the bytes of partial scores (the caller's room for them); one slice is always allowed.  exact: three terms; halves: see FwdPlan.
 FwdPlan plan_forward_split(int64_t n_rows, int64_t J, int64_t D, size_t most, bool exact, int halves) {

@@ -9,14 +9,15 @@
 // off each other's banks, and a multiplying lane's blocks hold neighbouring columns of W, which it reads and writes in one 16- or 8-byte access.
 // Columns beyond J or D repeat the last ones (they feed entries of W that are not stored); pairs beyond N lie behind the end of the
 // descriptors and read as zero, pairs of dead workers are replaced by zero on the way into LDS.  Any alignment and leading dimension is taken.
-// 1000 x 4096, 512 pairs: 31.3 -> 27.5 us; 600 x 4096, 1024: 43.1 -> 32.6; 1000 x 4096, 2048: 95 -> 71.
+// us, every wavefront splitting and multiplying in three terms -> here: 1000 x 4096, 512 pairs 31.3 -> 24.5; 600 x 4096, 1024 43.7 -> 31.1; 1000 x 4096, 4096
+// 169 -> 115; refused by two terms 29.5 -> 27.5, 169 -> 167.
 #include "sfb_kernels.h"
 #include "sfb_split.h"
 
 namespace sfb {
 
-// SPLITTERS: eight, or four in 64 x 64 tiles of which several share a compute unit (800 x 2500, 200 pairs, 520 tiles: 15.2 us, 19.0 with
-// eight; 333 x 1001 with 228, 96 tiles: 11.6 and 9.4)
+// SPLITTERS: eight, or four in 64 x 64 tiles of which several share a compute unit (first measured at 800 x 2500, 200 pairs, 520 tiles: 15.2 us, 19.0
+// with eight; 333 x 1001 with 228, 96 tiles: 11.6 and 9.4)
 template <int BM, int BN, int SPLITTERS, bool EXACT>
 using ReconTile = SplitTile<BM, BN, BM == 128 ? 4 : 2, BM == 96 ? 4 : 2, SPLITTERS, EXACT>;
 
@@ -253,19 +254,21 @@ static hipError_t launch_split(const ReconArgs& a, int slices, int halves, hipSt
     return hipGetLastError();
 }
 
-// Tile, slices of the pairs, terms and microseconds (the other kernels': reconstruct_fp32_us), fitted to 22 shapes (J = 40 to 4000, D = 300
-// to 8192, N = 128 to 11200, every tile in two and three terms) on one MI355X.  A chunk of 32 pairs costs (two terms / three) 0.84 / 1.25 us per
-// round of 256 tiles of 128 x 128, 0.66 / 0.95 with 96 x 128, 0.62 / 0.78 with 64 x 128 and 0.36 / 0.49 with 64 x 64 tiles (two share a compute
-// unit; one alone 0.50 / 0.56), on top of 6 to 9 us, W's trip at 4 TB/s and up to 3.5 us per further round.  1000 x 4096 (fp32 instruction -> here):
-// 23.1 -> 19.8 us at 256 pairs, 40 -> 28 at 512, 255 -> 137 at 4096; 600 x 784 with 1024: 32.6 -> 17.
-// Two terms win from 3 (large tiles) to 10 chunks a workgroup on (1000 x 4096 with 512 pairs 28.9 against 34.6 us, 333 x 1001 with 228
-// 11.9 against 11.3); below four chunks (128 pairs) they are also the less exact ones.
-// 96 x 128 tiles are for the J whose 128-row tiles leave compute units idle or just pass a round of 256 (600 x 4096 with 1024 pairs 40.1 ->
-// 34.0 us, 160 -> 224 workgroups); below 16 chunks they save 2 us at most, and in walks of more than 64 the chip's power sets the pace, not its
+// Tile, slices of the pairs, terms and microseconds (the other kernels': reconstruct_fp32_us), fitted to 150 shapes (J = 6 to 4000, D = 50
+// to 8192, N = 66 to 12000, every tile in two and three terms with up to ten counts of slices) on one MI355X: 1.8 % over the best of them on average.
+// A chunk of 32 pairs costs (two terms / three) 0.88 / 1.02 us per round of 256 tiles of 128 x 128, 0.76 / 0.91 with 96 x 128, 0.68 / 0.82 with 64 x
+// 128 and 0.34 / 0.39 with 64 x 64 tiles where two share a compute unit (0.44 / 0.46 alone), on top of 5 to 6.5 us, W's trip (0.12 us a MB, read and
+// written) and up to 1.8 us per further round.  1000 x 4096 (fp32 instruction -> here): 22.5 -> 16.9 us at 256 pairs, 39.8 -> 24.5 at 512; 600 x 780
+// with 1024: 32.1 -> 15.8; 2000 x 8192 with 80: 67 -> 40.
+// Two terms win from 4 (64 x 64: 13) chunks a workgroup on (1000 x 4096 with 512 pairs 24.5 against 26.6 us); below four chunks (128 pairs) they are
+// also the less exact ones.
+// 96 x 128 tiles are for the J whose 128-row tiles leave compute units idle or just pass a round of 256 (600 x 4096 with 1024 pairs: 160 -> 224
+// workgroups); below 16 chunks they save 2 us at most, and in walks of more than 64 the chip's power sets the pace, not its
 // idle units (2894 x 512, 6912 pairs in two slices: 2 % slower).
 // Where the tiles leave compute units idle the pairs are cut into slices, at most 64 and as many as `room` bytes hold
-// planes of J x D sums for; adding those up is a second kernel, 3.2 us and its traffic (216 x 268, 384 pairs: 10.6 us in one piece, 8.4 in
-// three; 353 x 80 with 308: 9.6 and 8.1; 193 x 1473 with 476: 11.9 and 10.7; 964 x 242 with 332: the same).
+// planes of J x D sums for; adding those up is a second kernel, 1.3 us and its traffic, and what the next score pass waits longer for W then: D / 1500 us, 2.4 at
+// most (steps of 40 x 7383 with 322 pairs 24.8 us in one piece and 27.4 in two slices, updates 10.3 both; 193 x 1473 with 476: 23.2 and 23.3, 11.5 and 10.7;
+// 216 x 268 with 384: 18.9 and, in four, 17.4, 10.2 and 8.6).
 static SplitReconPlan plan_part(int64_t J, int64_t D, int64_t N, size_t room, bool exact, bool alone) {
     static const struct { int bm, bn, resident, terms; double start_us, chunk_us, lone_us, round_us; } tiles[8] = {
         {128, 128, 1, 2, 6.4, 0.88, 0.88, 0.4}, {96, 128, 1, 2, 6.5, 0.76, 0.76, 1.5}, {64, 128, 1, 2, 6.2, 0.68, 0.68, 1.4}, {64, 64, 2, 2, 5.4, 0.34, 0.44, 0.9},
@@ -309,7 +312,8 @@ static SplitReconPlan plan_part(int64_t J, int64_t D, int64_t N, size_t room, bo
     return best;
 }
 // Where the last row or column of tiles is what begins another round of 256, it is a second, smaller launch with a plan of its
-// own (1001 x 4100, 488 pairs: 256 tiles of 128 x 128 and four columns, 42.7 -> 39.3 us; 1001 x 4129, 1000: 88.6 -> 59.7).
+// own: 1001 x 4100, 384 to 2048 pairs: 256 tiles of 128 x 128 and four columns 30 to 83 us, 34 to 103 in one; 2049 x 4096 with 384 46.8 and 52.2; 1412 x 4395
+// with 1536 94.3 and 97.8.
 SplitReconPlan reconstruct_split_plan(int64_t J, int64_t D, int64_t N, size_t room, bool exact, int halves) {
     SplitReconPlan p = plan_part(J, D, N, room, exact, true);
     p.halves = halves;

@@ -16,18 +16,21 @@
 //     at: none beyond 2^15 scaled, and none whose largest is below 2^-12 but not zero, so that a value is at most 2^-24 of its group's largest
 //     off.  From the first chunk with a group outside on, the rest of the sum is taken in three terms.  s puts the first 64 k in the middle of that
 //     window: softmax factors of 3326 classes are 3e-4 in most blocks until a label comes, and 1 then (update with 532 pairs: with 2^6 above the
-//     first values and 2^21 below 21.1 us, with the window's middle 18.9).
+//     first values and 2^21 below 21.2 us, with the window's middle 18.4).  Softmax factors of logits of deviation 3.5 stay in two terms (1000 x
+//     4096 with 512 pairs 23.4 us), of 4 and more are refused at the first look (27.5; three terms throughout 26.6; before two terms 29.5).
 // Sums of 256 products and more are closer to fp64 with two terms than with the three terms in one running sum that they replace; of the norm,
 // operands of mixed signs (then -> two terms here): scores 1000 x 4096, 512 samples 2.5e-7 -> 1.8e-7, update 2.4e-7 -> 1.7e-7;
 // 600 x 4096 with 1024: 2.9e-7 -> 1.9e-7 and 2.4e-7 -> 1.7e-7.  Three terms here: 1.4e-7 and 1.3e-7 (1000 x 4096).  Either way the smaller
-// products have sums of their own, so that the leading ones' running sum is rounded once for every sixteen k.
+// products have sums of their own, so that the leading ones' running sum is rounded once for every 32 k, and long walks add theirs in two
+// halves (4096 positive products: 2.7e-7 before, 3.0e-7 in one running sum, 1.6e-7 in halves).
 //
 // A workgroup has two kinds of wavefronts.  Splitting ones (eight, two a SIMD) request raw words three chunks of 32 k ahead, through
 // descriptors whose base moves by scalar instructions, split them and park the terms in LDS; multiplying ones (one or two a SIMD) read
 // fragments and do nothing but matrix instructions, so neither kind stands in the other's instruction stream.  One barrier a chunk; two terms
 // have three LDS buffers (a fragment is read one phase of products before its use, across the barrier too), three terms two.
-// 128 x 128 tiles, cycles a chunk: 1600 (2300 where every wavefront did both in turns, with three terms); matrix instructions alone 770,
-// 966 with the barrier, splits alone 1027, LDS reads, writes and loads without either 1500.
+// 128 x 128 tiles, a chunk: 0.76 us for scores and 0.88 for the update (1.04 where every wavefront did both in turns, with three terms); in cycles, of
+// then 1600: matrix instructions alone 770, 966 with the barrier, LDS reads, writes and loads without either 1500, splits alone 1027 (of
+// 17 vector instructions for four values; 21 with the second term's scale).
 #pragma once
 #include <type_traits>
 
